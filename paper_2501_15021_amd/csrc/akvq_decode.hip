@@ -64,12 +64,13 @@ __device__ __forceinline__ void wht128_wave(float &x0, float &x1, int lane) {
   x0 = s * inv_sqrt128();
   x1 = d * inv_sqrt128();
 }
-// rotate a query row inside one wavefront (unless it arrives rotated) and leave it in LDS (the caller synchronises before other waves read it)
+// rotate a query row inside one wavefront (unless it arrives rotated): x0 = element `lane`, x1 = element `lane + 64`
 // A pre-RoPE query (cos_row != null) first takes its rotary position embedding: channel i pairs with i + 64, both held
 // by this lane; exact fp32 products, one rounding of their sum to fp32, then to binary16 (kept apart by the barrier).
-__device__ __forceinline__ void rotate_query_lds(const uint16_t *q_row, float *qf, bool q_rotated,
-                                                 const uint16_t *cos_row, const uint16_t *sin_row, int lane) {
-  float x0 = half_bits_to_float(q_row[lane]), x1 = half_bits_to_float(q_row[lane + 64]);
+__device__ __forceinline__ void rotate_query(const uint16_t *q_row, float &x0, float &x1, bool q_rotated,
+                                             const uint16_t *cos_row, const uint16_t *sin_row, int lane) {
+  x0 = half_bits_to_float(q_row[lane]);
+  x1 = half_bits_to_float(q_row[lane + 64]);
   if (cos_row != nullptr) {
     const float c = half_bits_to_float(cos_row[lane]), sn = half_bits_to_float(sin_row[lane]);
     float r0 = __fmaf_rn(x0, c, -__fmul_rn(x1, sn)), r1 = __fmaf_rn(x1, c, __fmul_rn(x0, sn));
@@ -79,6 +80,12 @@ __device__ __forceinline__ void rotate_query_lds(const uint16_t *q_row, float *q
     x1 = half_bits_to_float(float_to_half_bits_rne(r1));
   }
   if (!q_rotated) wht128_wave(x0, x1, lane);
+}
+// ... and leave it in LDS (the caller synchronises before other waves read it)
+__device__ __forceinline__ void rotate_query_lds(const uint16_t *q_row, float *qf, bool q_rotated,
+                                                 const uint16_t *cos_row, const uint16_t *sin_row, int lane) {
+  float x0, x1;
+  rotate_query(q_row, x0, x1, q_rotated, cos_row, sin_row, lane);
   qf[lane] = x0;
   qf[lane + 64] = x1;
 }
@@ -631,9 +638,11 @@ struct GqaTile {
 template <int G, bool PAIRS>
 __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   constexpr int NG = kD / G;
-  __shared__ float qf[8][kD];
-  __shared__ __attribute__((aligned(16))) uint16_t q_scaled[16][kD];  // row 2h+term, A-operand order
+  __shared__ __attribute__((aligned(16))) int q_int[8][kD];           // queries as integers, in units of their head's U
   __shared__ __attribute__((aligned(16))) uint16_t q_plain[16][kD];   // row 2h+term, natural order
+  __shared__ __attribute__((aligned(16))) uint32_t a_lds[2][6][kWave];  // the two operand images of the code stream
+  __shared__ float q_sum[8][NG];                                      // per head and group: sum of the queries
+  __shared__ uint32_t q_exp[8];                                       // biased exponent above the head's largest query
   __shared__ __attribute__((aligned(16))) uint16_t w_lds_all[kWaves][NG][16][kTokBlock];  // [group][row][slot]
   __shared__ float mrg_m[kWaves][8], mrg_l[kWaves][8];
   __shared__ float mrg_o[kWaves][8][kD];
@@ -648,10 +657,9 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   const int b = bh / a.Hkv, hkv = bh % a.Hkv;
   const int mrow = lane & 15, qd = lane >> 4;
   const ExpandK ex;
+  const ExpandF4 ex4;
   auto &w_lds = w_lds_all[wave];
 
-  for (int x = tid; x < 16 * kD; x += 64 * kWaves) { (&q_scaled[0][0])[x] = 0; (&q_plain[0][0])[x] = 0; }
-  for (int x = lane; x < NG * 16 * kTokBlock; x += 64) (&w_lds[0][0][0])[x] = 0;
   // Fused decode step: the workgroups of the split that owns the row's tile first write the new row (wavefront 3 the
   // K row, wavefront 2 the V row); the barrier below orders those stores before this workgroup's loads, which all
   // come later, and no other workgroup reads that tile.
@@ -661,56 +669,87 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t step_row[2][kD];
     append_row_wave<G>(a.step, bh, 3 - wave, lane, step_codes[3 - wave], step_row[3 - wave]);
   }
-  for (int h = wave; h < R; h += kWaves) rotate_query_lds(a.q + ((size_t)b * a.Hq + hkv * R + h) * kD, qf[h], a.q_rotated != 0,
-                     a.rope_cos ? a.rope_cos + (size_t)b * a.rope_stride : nullptr,
-                     a.rope_sin ? a.rope_sin + (size_t)b * a.rope_stride : nullptr, lane);
-  __syncthreads();
-  // sm_scale * log2(e) is folded into the staged queries (and through them into the bias and group sums), so the
-  // products already are base-2 logits
+  // Queries, one head per wavefront at a time, two channels (lane, lane + 64) per lane.  sm_scale * log2(e) is folded in,
+  // so the products already are base-2 logits.  For the 16-bit rows: two bfloat16 terms.  For the code stream: integers
+  // of up to 20 bits in units of a power of two U (|q| < 2^19 U), and their sums per group.
   const float sm2 = a.sm_scale * kLog2e;
-  for (int x = tid; x < R * kD; x += 64 * kWaves) {
-    const int h = x >> 7, e = x & 127;
-    const float v = qf[h][e] * sm2;
+  for (int h = wave; h < 8; h += kWaves) {
+    float x0 = 0.0f, x1 = 0.0f;
+    if (h < R)  // uniform
+      rotate_query(a.q + ((size_t)b * a.Hq + hkv * R + h) * kD, x0, x1, a.q_rotated != 0,
+                   a.rope_cos ? a.rope_cos + (size_t)b * a.rope_stride : nullptr,
+                   a.rope_sin ? a.rope_sin + (size_t)b * a.rope_stride : nullptr, lane);
+    x0 *= sm2;
+    x1 *= sm2;
     float hif, lof;
-    split2(v, hif, lof);
-    q_plain[2 * h][e] = (uint16_t)hi16(hif); q_plain[2 * h + 1][e] = (uint16_t)hi16(lof);
-    split2(v * pow4_neg(k_channel_exp(e)), hif, lof);
-    const int p = k_operand_pos(e);
-    q_scaled[2 * h][p] = (uint16_t)hi16(hif); q_scaled[2 * h + 1][p] = (uint16_t)hi16(lof);
+    split2(x0, hif, lof);
+    q_plain[2 * h][lane] = (uint16_t)hi16(hif); q_plain[2 * h + 1][lane] = (uint16_t)hi16(lof);
+    split2(x1, hif, lof);
+    q_plain[2 * h][lane + 64] = (uint16_t)hi16(hif); q_plain[2 * h + 1][lane + 64] = (uint16_t)hi16(lof);
+    const float mx = wave_max_dpp(fmaxf(fabsf(x0), fabsf(x1)));
+    const uint32_t e_biased = min(max(__float_as_uint(mx) >> 23, 20u), 250u);    // mx < 2^(e_biased - 126)
+    const float unit_inv = __uint_as_float((272u - e_biased) << 23);             // 1 / U = 2^19 / 2^(e_biased - 126)
+    const float n0 = rintf(x0 * unit_inv), n1 = rintf(x1 * unit_inv);
+    q_int[h][lane] = (int)n0;
+    q_int[h][lane + 64] = (int)n1;
+    const float unit = 1.0f / unit_inv;  // exact
+    if constexpr (NG == 2) {
+      const float s0 = wave_sum_dpp(n0 * unit), s1 = wave_sum_dpp(n1 * unit);
+      if (lane == 0) { q_sum[h][0] = s0; q_sum[h][1] = s1; q_exp[h] = e_biased; }
+    } else {
+      const float s0 = wave_sum_dpp(n0 * unit + n1 * unit);
+      if (lane == 0) { q_sum[h][0] = s0; q_exp[h] = e_biased; }
+    }
   }
   __syncthreads();
 
-  // this lane scores heads h0 = 2*qd and h0+1: their bias / group sums
-  const int h0 = 2 * qd;
-  float qbias[2][NG], qsum[2][NG];
+  // Row operands of the code stream: the integer of a channel is four balanced base-32 digits, |digit| <= 16, which E2M3
+  // holds exactly as digit / 8.  Image 0 holds digit 3 in row 2h and digit 2 in row 2h+1, image 1 digits 1 and 0; the
+  // products of the two images accumulate on top of each other, every row weighted by its digit's power of 32, the
+  // unit U and the factor 16 of the two operands' fractions through the scale operand, so row 2h + row 2h+1 is the
+  // dot product.  Slot v of lane (m, q) is what ExpandF4 makes of the code words: word v / 16, field 2*(v % 8) + (v / 8) % 2.
+  const uint32_t e_row = q_exp[mrow >> 1];
+  uint32_t a_scale[2];
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
-    const int h = min(h0 + hh, 7);
-    float bias_part[NG], qsum_part[NG];
+  for (int img = 0; img < 2; ++img) a_scale[img] = e_row - 14u + 5u * (uint32_t)(3 - (mrow & 1) - 2 * img);
+  if (wave < 2) {
+    const int shift = 5 * (3 - (mrow & 1) - 2 * wave);
+    f32x16 dig[2];  // even and odd slots, as the packing conversion takes them
 #pragma unroll
-    for (int g = 0; g < NG; ++g) bias_part[g] = qsum_part[g] = 0.0f;
-    // 16 lanes of the row share the work: lane mrow sums channels mrow, mrow+16, ...
+    for (int w = 0; w < 2; ++w)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int e = mrow + 16 * c;
-      const int g = (NG == 2) ? (c >> 2) : 0;
-      bias_part[g] += bf16_bits_to_f32(q_scaled[2 * h][e]) + bf16_bits_to_f32(q_scaled[2 * h + 1][e]);
-      qsum_part[g] += (h < R) ? qf[h][e] * sm2 : 0.0f;
-    }
+      for (int f8 = 0; f8 < 2; ++f8) {  // fields 8*f8 .. 8*f8 + 7 of word w: channels 64*w + 32*f8 + 8*q + (0 .. 7)
+        const i32x4 lo = *reinterpret_cast<const i32x4 *>(&q_int[mrow >> 1][64 * w + 32 * f8 + 8 * qd]);
+        const i32x4 hi = *reinterpret_cast<const i32x4 *>(&q_int[mrow >> 1][64 * w + 32 * f8 + 8 * qd + 4]);
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      qbias[hh][g] = kCodeBias * row_sum_dpp(bias_part[g]);
-      qsum[hh][g] = row_sum_dpp(qsum_part[g]);
-    }
+        for (int i = 0; i < 8; ++i) {
+          const int n = (i < 4 ? lo[i & 3] : hi[i & 3]) + 16 * (1 + 32 + 1024);  // the lower digits offset to 0 .. 31
+          const int d = shift == 15 ? n >> 15 : ((n >> shift) & 31) - 16;
+          const int slot = 16 * w + 8 * (i & 1) + 4 * f8 + (i >> 1);
+          dig[slot & 1][slot >> 1] = 0.125f * (float)d;
+        }
+      }
+    const u32x6 img = __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(dig[0], dig[1], 1.0f));
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a_lds[wave][i][lane] = img[i];
   }
+  __syncthreads();
+  // with two groups per row each group's operand has zeros in the other group's slots (half of the registers)
+  u32x6 a_k[2][NG];
+#pragma unroll
+  for (int img = 0; img < 2; ++img)
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int i = 0; i < 6; ++i) a_k[img][g][i] = (NG == 1 || i / 3 == g) ? a_lds[img][i][lane] : 0u;
 
-  bf16x8 a_k[4];
+  // this lane scores heads h0 = 2*qd and h0+1
+  const int h0 = 2 * qd;
+  float qsum[2][NG];
 #pragma unroll
-  for (int kc = 0; kc < 4; ++kc)
-    a_k[kc] = *reinterpret_cast<const bf16x8 *>(&q_scaled[mrow][(4 * kc + qd) * 8]);
-  f32x4 acc_init[NG];  // rows (head h0: hi, lo; head h0+1: hi, lo): the bias enters through the hi rows
+  for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-  for (int g = 0; g < NG; ++g) acc_init[g] = (f32x4){-qbias[0][g], 0.f, -qbias[1][g], 0.f};
+    for (int g = 0; g < NG; ++g) qsum[hh][g] = q_sum[h0 + hh][g];
 
   f32x4 acc_o[8];
 #pragma unroll
@@ -845,13 +884,12 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
     for (int tg = 0; tg < 2; ++tg) {
       f32x4 acc[NG];
+      const u32x2 c0 = ex4(cur.kc[2 * tg]), c1 = ex4(cur.kc[2 * tg + 1]);
+      const u32x4 codes = {c0[0], c0[1], c1[0], c1[1]};
 #pragma unroll
-      for (int g = 0; g < NG; ++g) acc[g] = acc_init[g];  // starts at -128*sum(q'): the expansion constant's share
-      const uint32_t w0 = cur.kc[2 * tg], w1 = cur.kc[2 * tg + 1];
-      acc[0] = mfma_bf16(a_k[0], ex.x(w0), acc[0]);
-      acc[0] = mfma_bf16(a_k[1], ex.y(w0), acc[0]);
-      acc[NG - 1] = mfma_bf16(a_k[2], ex.x(w1), acc[NG - 1]);
-      acc[NG - 1] = mfma_bf16(a_k[3], ex.y(w1), acc[NG - 1]);
+      for (int g = 0; g < NG; ++g) acc[g] = mfma_f6f4(a_k[0][g], a_scale[0], codes, (f32x4){0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+      for (int g = 0; g < NG; ++g) acc[g] = mfma_f6f4(a_k[1][g], a_scale[1], codes, acc[g]);
       // bit 15 of every meta word of a salient row is set: as a binary16 pattern the low half is then negative
       const bool off = meta_is_salient(km[tg][0]);
       ok[tg] = !off;
@@ -860,7 +898,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const Meta mk = unpack_meta(km[tg][g]);
-        // scale * (dot - 128*sum(q') - zero*sum(q)); the accumulators started at -128*sum(q')
+        // scale * (dot - zero*sum(q))
         s0 = __builtin_fmaf(mk.scale, __builtin_fmaf(-mk.zero, qsum[0][g], acc[g][0] + acc[g][1]), s0);
         s1 = __builtin_fmaf(mk.scale, __builtin_fmaf(-mk.zero, qsum[1][g], acc[g][2] + acc[g][3]), s1);
       }
@@ -1088,7 +1126,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
     }
     const size_t bhq = (size_t)b * a.Hq + hkv * R + h;
     if (a.n_split == 1) {
-      if (tid < kD) qf[h][tid] = o / l_all;  // the queries are no longer needed: their buffers carry the rows
+      if (tid < kD) reinterpret_cast<float *>(q_int[h])[tid] = o / l_all;  // the queries are no longer needed: their buffers carry the rows
       if (a.lse && tid == 0) a.lse[bhq] = (m_all + __log2f(l_all)) * kLn2;
     } else if (tid < kD) {
       float *dst = a.partial + (bhq * a.n_split + split) * kPartialStride;
@@ -1099,7 +1137,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   if (a.n_split == 1) {
     __syncthreads();
     for (int h = wave; h < R; h += kWaves)
-      unrotate_store_wave(qf[h], a.out, (size_t)b * a.Hq + hkv * R + h, a.out_rotated != 0, a.out_half != 0, lane);
+      unrotate_store_wave(reinterpret_cast<const float *>(q_int[h]), a.out, (size_t)b * a.Hq + hkv * R + h, a.out_rotated != 0, a.out_half != 0, lane);
   }
 }
 
