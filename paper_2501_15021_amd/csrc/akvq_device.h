@@ -106,7 +106,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 // OR-ing a masked pair into 0x4300'4300 yields two bfloat16 numbers 128 + 4^k * code (k = the field's
 // position inside the 7-bit mantissa: 0, 1 or 2).  The constant 128 and the factor 4^k are undone on the
 // other operand of the contraction, so expansion costs one and-or per two codes (plus two shifts per word).
-// Pairs 0..3 form the "X" operand, pairs 4..7 the "Y" operand; both carry the factors 4^{0,1,2,0}.
+// Pairs 0..3 form the "X" operand, pairs 4..7 the "Y" operand; both carry the factors 4^{0,1,2,2}.  (The fourth pair
+// could land on any of the three fields; the highest one makes the constant's share of the sums, 128 / 4^k per unit of
+// weight, smallest: what the sums lose in 32 bits to the constant shrinks by 0.6 against the lowest field.)
 // The masks and the constant are kept as opaque register values (not literals) so that the compiler selects the
 // three-operand and-or instruction, whose encoding takes no literal operands: D = (w & mask) | magic in one op.
 struct ExpandK {
@@ -119,19 +121,18 @@ struct ExpandK {
   }
   __device__ __forceinline__ uint32_t pair(uint32_t w, int k) const { return (w & mask[k]) | magic; }
   __device__ __forceinline__ bf16x8 x(uint32_t w) const {
-    const uint32_t w6 = w >> 6;
-    u32x4 r = {pair(w, 0), pair(w, 1), pair(w, 2), pair(w6, 0)};
+    u32x4 r = {pair(w, 0), pair(w, 1), pair(w, 2), pair(w >> 2, 2)};
     return __builtin_bit_cast(bf16x8, r);
   }
   __device__ __forceinline__ bf16x8 y(uint32_t w) const {
-    const uint32_t w8 = w >> 8, w14 = w >> 14;
-    u32x4 r = {pair(w8, 0), pair(w8, 1), pair(w8, 2), pair(w14, 0)};
+    const uint32_t w8 = w >> 8;
+    u32x4 r = {pair(w8, 0), pair(w8, 1), pair(w8, 2), pair(w >> 10, 2)};
     return __builtin_bit_cast(bf16x8, r);
   }
 };
-// exponent k (factor 4^k) carried by pair i of either operand: {0,1,2,0} (the Y operand shifts by 8 and 14 so that
+// exponent k (factor 4^k) carried by pair i of either operand: {0,1,2,2} (the Y operand shifts by 8 and 10 so that
 // it repeats the X pattern; one set of pre-divided weights then serves both)
-__device__ __forceinline__ int pair_exp(int i) { return i == 3 ? 0 : i; }
+__device__ __forceinline__ int pair_exp(int i) { return i == 3 ? 2 : i; }
 constexpr float kCodeBias = 128.0f; // the 2^7 every expanded code carries
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
