@@ -1,14 +1,15 @@
 // Read path of the AKVQ-VL cache: decode attention straight from the packed 2-bit + bfloat16 cache
 // (decode step of Section II-A over the cache of Section III-C, arXiv 2501.15021).
 //
-// A workgroup of four wavefronts owns one (batch, kv-head, KV-split); the wavefronts take its 64-token (MHA) or
-// 32-token (GQA) tiles round-robin and merge their partial softmaxes through LDS.  Both contractions run on the
-// matrix cores with the 2-bit codes expanded to bfloat16 integers in registers (one and-or per two codes, see
-// akvq_device.h):
-//   scores  S = Q~ * C_K^T   : rows = the query vector split into bfloat16 terms, K-dim = 128 channels,
-//   output  O = W  * C_V     : rows = (softmax weight x scale) split into bfloat16 terms, K-dim = 32 tokens.
+// A workgroup of four (or eight) wavefronts owns one (batch, kv-head, KV-split); the wavefronts take its 64-token (MHA)
+// or 32-token (GQA) tiles round-robin and merge their partial softmaxes through LDS.  Both contractions run on the
+// matrix cores with the 2-bit codes expanded in registers (see akvq_device.h):
+//   scores  S = Q~ * C_K^T   : rows = the query vector as fixed-point digits, K-dim = 128 channels; the codes as int8
+//                              (MHA) or as 4-bit floats (GQA),
+//   output  O = W  * C_V     : rows = (softmax weight x scale) split into bfloat16 terms, K-dim = 32 tokens; the codes as
+//                              bfloat16 numbers, one and-or per two codes.
 // Scale, zero-point and the constants of the expansion are applied to the small side of each product
-// (per token for S, per channel-class for O), so the streamed bytes are touched once, by one and-or each.
+// (per token for S, per channel-class for O), so the streamed bytes are touched once.
 // The cache block layout makes each lane's 128-bit load its own matrix-core operand: no shuffles.  The next
 // tile's loads are issued before the current tile is consumed.
 #include <mutex>
@@ -47,7 +48,19 @@ hipError_t decode_static_scratch(void **ptr) {
 
 namespace {
 
-constexpr int kWaves = 4;  // wavefronts per workgroup
+// Wavefronts per workgroup (template parameter NW).  Four when the launch has more than one workgroup per CU; eight when
+// it has one, where a wavefront walks its tiles at the latency of its own chain and the only thing that shortens the
+// call is fewer tiles per wavefront (see launch_decode_attention).
+constexpr int kWaves = 4, kWavesWide = 8;
+constexpr int kCus = 256;
+
+// Barrier for data exchanged through LDS: unlike __syncthreads() it does not wait for outstanding global loads, so the
+// first tiles stay in flight across the staging of the query.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // ------------------------------------------------------------------------------------------------
 // Orthonormal 128-point Walsh-Hadamard transform (Section III-C.2) of a vector held by one wavefront, two elements
@@ -81,25 +94,6 @@ __device__ __forceinline__ void rotate_query(const uint16_t *q_row, float &x0, f
   }
   if (!q_rotated) wht128_wave(x0, x1, lane);
 }
-// ... and leave it in LDS (the caller synchronises before other waves read it)
-__device__ __forceinline__ void rotate_query_lds(const uint16_t *q_row, float *qf, bool q_rotated,
-                                                 const uint16_t *cos_row, const uint16_t *sin_row, int lane) {
-  float x0, x1;
-  rotate_query(q_row, x0, x1, q_rotated, cos_row, sin_row, lane);
-  qf[lane] = x0;
-  qf[lane + 64] = x1;
-}
-
-// exponent k of the 4^k factor that the expansion attaches to channel e of a K row (see the K block layout:
-// channel e sits in code pair e%8 of its word; pairs 0..3 are the X operand, 4..7 the Y operand)
-__device__ __forceinline__ int k_channel_exp(int e) { return pair_exp(e & 3); }
-// position of channel e inside the 128-entry A-operand image of a K row: MFMA kc = 2*(e/64) + (e%8)/4, lane group
-// qd = (e%32)/8, pair i = e%4, element 2i + (e/32)%2
-__device__ __forceinline__ int k_operand_pos(int e) {
-  const int m = e >> 5, j = (e >> 3) & 3, ie = e & 7;
-  const int kc = 2 * (m >> 1) + (ie >> 2);
-  return (4 * kc + j) * 8 + 2 * (ie & 3) + (m & 1);
-}
 // position of channel e inside the 128-byte A-operand image of the int8 score product: word kc = e/64, lane group
 // qd = (e%32)/8, code slot s = 8*((e/32)%2) + e%8 -> register j = s%4, byte b = s/4 -> byte 4j + b of the lane's 16
 __device__ __forceinline__ int k_digit_pos(int e) {
@@ -110,6 +104,31 @@ __device__ __forceinline__ float pow4_neg(int k) { return k == 0 ? 1.0f : (k == 
 
 __device__ __forceinline__ uint32_t pack16(uint32_t lo, uint32_t hi) { return (lo & 0xFFFFu) | (hi << 16); }
 __device__ __forceinline__ uint32_t hi16(float f) { return __float_as_uint(f) >> 16; }
+
+// Keeps the wavefronts that share a SIMD in step.  Among wavefronts of equal priority the oldest one issues first, so of
+// the two workgroups of a CU one ran ahead and the other then finished alone, at the latency of its own chain: with 28/4
+// heads, 32 sequences of 32768 tokens and 4 splits the workgroups ended between 46 and 68 us, now between 57 and 63 us.
+// A wavefront therefore lowers its priority when half, three quarters and seven eighths of its tiles are done: whoever is
+// behind goes first, and what is left of a lead is part of an eighth.  Only where the whole launch is resident at once
+// (launch_decode_stream): with several rounds of workgroups the ones that have just started would hold up the ones about
+// to make room (32 heads, 64 sequences of 8192 tokens: 202 -> 221 us), and a stream that waits for memory and not for
+// issue slots gains nothing (the one-head kernel, 16 sequences of 4096 tokens: 28.9 us either way).
+struct StreamPace {
+  int at, left;  // next tile count that lowers the priority; tiles behind it
+  int level;
+  __device__ __forceinline__ StreamPace(int n, bool on) : at(on ? n - n / 2 : 0x7FFFFFFF), left(n / 2), level(3) {
+    if (on) __builtin_amdgcn_s_setprio(3);
+  }
+  __device__ __forceinline__ void done(int k) {  // k tiles are done (uniform over the wavefront)
+    if (k < at) return;
+    if (level == 3) __builtin_amdgcn_s_setprio(2);
+    else if (level == 2) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+    --level;
+    at += left - left / 2;
+    left /= 2;
+  }
+};
 
 struct Meta {
   float scale, zero;
@@ -135,10 +154,10 @@ __device__ __forceinline__ float minus_bf16(uint32_t pair, uint32_t sel, float w
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pair), __builtin_bit_cast(bf16x2_t, sel), w, false);
 }
 
-// two-term bfloat16 split, w ~= hi + lo (16 significant bits): hi is w truncated to its upper 16 bits (so storing
-// the upper half of the register stores hi), lo is the exactly representable remainder rounded to bfloat16
+// two-term bfloat16 split, w ~= hi + lo (17 significant bits): hi is w rounded to bfloat16, lo the exactly representable
+// remainder rounded to bfloat16; both as floats whose lower halves are zero (storing the upper half stores the term)
 __device__ __forceinline__ void split2(float w, float &hif, float &lof) {
-  hif = __uint_as_float(__float_as_uint(w) & 0xFFFF0000u);
+  hif = __uint_as_float(pack_bf16x2(w, 0.0f) << 16);
   lof = __uint_as_float(pack_bf16x2(w - hif, 0.0f) << 16);
 }
 constexpr float kLog2e = 1.4426950408889634f;
@@ -178,12 +197,11 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return (lane_bcast(v, 0) + lane_bcast(v, 16)) + (lane_bcast(v, 32) + lane_bcast(v, 48));
 }
 
-// Final step: `row` (LDS, 128 floats, complete and visible to this wavefront) is the merged, normalised o~; rotate
-// it back (H is its own inverse) unless the caller wants it rotated, and store.  One wavefront does the whole row.
+// Final step: one wavefront holds the merged, normalised o~ (x0 = element `lane`, x1 = element `lane + 64`); rotate it
+// back (H is its own inverse) unless the caller wants it rotated, and store.
 // `out` is the output array ([B][Hq][128] fp32, or binary16 when out_half), `row_index` the (batch, query-head) row.
-__device__ __forceinline__ void unrotate_store_wave(const float *row, void *out, size_t row_index, bool out_rotated,
+__device__ __forceinline__ void unrotate_store_wave(float x0, float x1, void *out, size_t row_index, bool out_rotated,
                                                     bool out_half, int lane) {
-  float x0 = row[lane], x1 = row[lane + 64];
   if (!out_rotated) wht128_wave(x0, x1, lane);
   if (out_half) {
     uint16_t *o = static_cast<uint16_t *>(out) + row_index * kD;
@@ -193,6 +211,32 @@ __device__ __forceinline__ void unrotate_store_wave(const float *row, void *out,
     float *o = static_cast<float *>(out) + row_index * kD;
     o[lane] = x0;
     o[lane + 64] = x1;
+  }
+}
+// One wavefront merges the NW partial softmaxes of a workgroup for one head (m, l: per wavefront; rows: LDS, 128 floats
+// each, row_stride apart) and finishes the row, or stores the split's partial result.
+template <int NW>
+__device__ __forceinline__ void merge_waves_and_store(const DecodeArgs &a, const float *m, const float *l, int ml_stride,
+                                                      const float *rows, int row_stride, size_t bhq, int split, int lane) {
+  float m_all = -INFINITY, l_all = 0.0f, o0 = 0.0f, o1 = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, m[w * ml_stride]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float mw = m[w * ml_stride];
+    const float wgt = mw == -INFINITY ? 0.0f : fast_exp2(mw - m_all);  // a wavefront without rows has sums of 0
+    l_all += wgt * l[w * ml_stride];
+    o0 += wgt * rows[w * row_stride + lane];
+    o1 += wgt * rows[w * row_stride + lane + 64];
+  }
+  if (a.n_split == 1) {
+    if (a.lse && lane == 0) a.lse[bhq] = (m_all + __log2f(l_all)) * kLn2;
+    unrotate_store_wave(o0 / l_all, o1 / l_all, a.out, bhq, a.out_rotated != 0, a.out_half != 0, lane);
+  } else {
+    float *dst = a.partial + (bhq * a.n_split + split) * kPartialStride;
+    if (lane == 0) { dst[0] = m_all; dst[1] = l_all; }
+    dst[4 + lane] = o0;
+    dst[4 + lane + 64] = o1;
   }
 }
 
@@ -211,19 +255,18 @@ struct MhaTile {
 // PAIRS: the cache holds 4-bit tokens as (coarse, fine) pairs of 2-bit rows on (even, odd) rows, flagged in
 // a.fine_mask: the two rows' scores add up to the token's score, the token enters the softmax sum once, and each row
 // takes the token's weight times its own scale in the value product.
-template <int G, bool PAIRS>
+template <int G, bool PAIRS, int NW>
 __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
   constexpr int NG = kD / G;
-  __shared__ float qf[kD];
   // three signed 7-bit digits of q~[e] / U (U a power of two, |q~|/U < 2^20), as int8, in A-operand order of the
   // 16x16x64 int8 product (see k_digit_pos): the code stream's A operand, 16 bytes per lane
   __shared__ __attribute__((aligned(16))) int8_t q_digit[4][kD];  // row 3 stays zero: operand rows that carry nothing
-  __shared__ float q_red[kWaves];
+  __shared__ float q_scal[NG + 1];  // U and, per group, the sum of the digitised query in units of U
   __shared__ __attribute__((aligned(16))) uint16_t q_plain[4][kD];  // terms of q~[e], natural order; row 3 stays zero
-  __shared__ __attribute__((aligned(16))) uint16_t w_lds_all[kWaves][2][NG][2][kTokBlock];
+  __shared__ __attribute__((aligned(16))) uint16_t w_lds_all[NW][2][NG][3][kTokBlock];
   __shared__ __attribute__((aligned(16))) uint16_t zero16[64];  // 128 zero bytes: operand rows that carry nothing
-  __shared__ float mrg_m[kWaves], mrg_l[kWaves];
-  __shared__ float mrg_o[kWaves][kD];
+  __shared__ float mrg_m[NW], mrg_l[NW];
+  __shared__ float mrg_o[NW][kD];
 
   const int tid = threadIdx.x;
   // the wavefront index as a scalar: everything derived from it (tile indices, tile addresses) then lives in scalar
@@ -276,9 +319,9 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
   // as a vector load of a uniform address it would be moved to a scalar register, and waited for, right here)
   const int sal_cnt_early = reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(
       reinterpret_cast<uintptr_t>(a.sal_cnt))[bh];
-  const int n_mine = tile_begin + wave < tile_end ? (tile_end - tile_begin - wave + kWaves - 1) / kWaves : 0;
-  const int last_tile = tile_begin + wave + kWaves * max(n_mine - 1, 0);
-  auto tile_at = [&](int k) { return min(tile_begin + wave + kWaves * k, last_tile); };
+  const int n_mine = tile_begin + wave < tile_end ? (tile_end - tile_begin - wave + NW - 1) / NW : 0;
+  const int last_tile = tile_begin + wave + NW * max(n_mine - 1, 0);
+  auto tile_at = [&](int k) { return min(tile_begin + wave + NW * k, last_tile); };
   MhaTile<NG> tb[3];
   // Fused decode step: the workgroups of the split that owns the row's tile first write the new row (wavefront 1
   // the K row, wavefront 2 the V row, while wavefront 0 stages the query); the barrier below orders those stores
@@ -297,54 +340,54 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
     append_row_wave<G>(a.step, bh, wave - 1, lane, step_codes[wave - 1], step_row[wave - 1]);
   }
 
-  if (tid < 64) zero16[tid] = 0;
-  if (tid < kD) { q_digit[3][tid] = 0; q_plain[3][tid] = 0; }
-  if (wave == 0) rotate_query_lds(a.q + (size_t)bh * kD, qf, a.q_rotated != 0,
-                                  a.rope_cos ? a.rope_cos + (size_t)(bh / a.Hkv) * a.rope_stride : nullptr,
-                                  a.rope_sin ? a.rope_sin + (size_t)(bh / a.Hkv) * a.rope_stride : nullptr, lane);
-  __syncthreads();
+  // Wavefront 0 stages the query on its own (two channels per lane, reductions inside the wavefront); the others wait at
+  // one barrier, with the loads of their first tiles in flight.
+  if (wave == NW - 1) {
+    zero16[lane] = 0;
+    q_digit[3][lane] = 0; q_digit[3][lane + 64] = 0;
+    q_plain[3][lane] = 0; q_plain[3][lane + 64] = 0;
+  }
+  if (wave == 0) {
+    float x[2];
+    rotate_query(a.q + (size_t)bh * kD, x[0], x[1], a.q_rotated != 0,
+                 a.rope_cos ? a.rope_cos + (size_t)(bh / a.Hkv) * a.rope_stride : nullptr,
+                 a.rope_sin ? a.rope_sin + (size_t)(bh / a.Hkv) * a.rope_stride : nullptr, lane);
+    // fixed-point unit of the query: U = 2^ceil(log2 max|q~|) / 2^20 (the digits then cover it exactly, 21 bits)
+    const float mx = wave_max_dpp(fmaxf(fabsf(x[0]), fabsf(x[1])));
+    const uint32_t e_biased = min(max(__float_as_uint(mx) >> 23, 20u), 250u);  // mx < 2^(e_biased - 126)
+    const float unit_inv = __uint_as_float((273u - e_biased) << 23);           // 2^20 / 2^(e_biased - 126)
+    float n_of[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int e = lane + 64 * i;
+      uint32_t hi, mid, lo;
+      split3_bf16(x[i], hi, mid, lo);
+      q_plain[0][e] = (uint16_t)hi; q_plain[1][e] = (uint16_t)mid; q_plain[2][e] = (uint16_t)lo;
+      const int n = (int)rintf(x[i] * unit_inv);                    // |n| <= 2^20
+      const int d2 = (n << 25) >> 25, n1 = (n - d2) >> 7;           // balanced base-128 digits, each in [-64, 64]
+      const int d1 = (n1 << 25) >> 25, d0 = (n1 - d1) >> 7;
+      const int p = k_digit_pos(e);
+      q_digit[0][p] = (int8_t)d0; q_digit[1][p] = (int8_t)d1; q_digit[2][p] = (int8_t)d2;
+      n_of[i] = (float)n;                                           // the value the digits represent, in units of U
+    }
+    if constexpr (NG == 2) {
+      const float s0 = wave_sum_dpp(n_of[0]), s1 = wave_sum_dpp(n_of[1]);
+      if (lane == 0) { q_scal[0] = 1.0f / unit_inv; q_scal[1] = s0; q_scal[2] = s1; }
+    } else {
+      const float s0 = wave_sum_dpp(n_of[0] + n_of[1]);
+      if (lane == 0) { q_scal[0] = 1.0f / unit_inv; q_scal[1] = s0; }
+    }
+  }
+  if (appends) __syncthreads();  // also orders the new row's stores before the loads below
+  else lds_barrier();
   if (defer_loads) {
     load_tile(tile_at(0), tb[0]);
     load_tile(tile_at(1), tb[1]);
   }
-  // fixed-point unit of the query: U = 2^ceil(log2 max|q~|) / 2^20 (the digits then cover it exactly, 21 bits)
-  float q_unit_inv;
-  {
-    float mx = tid < kD ? fabsf(qf[tid]) : 0.0f;
-    mx = wave_max_dpp(mx);
-    if (lane == 0) q_red[wave] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(q_red[0], q_red[1]), fmaxf(q_red[2], q_red[3]));
-    const uint32_t e_biased = min(max(__float_as_uint(mx) >> 23, 20u), 250u);  // mx < 2^(e_biased - 126)
-    q_unit_inv = __uint_as_float((273u - e_biased) << 23);                     // 2^20 / 2^(e_biased - 126)
-  }
-  const float q_unit = 1.0f / q_unit_inv;
-  if (tid < kD) {
-    const int e = tid;
-    const float v = qf[e];
-    uint32_t hi, mid, lo;
-    split3_bf16(v, hi, mid, lo);
-    q_plain[0][e] = (uint16_t)hi; q_plain[1][e] = (uint16_t)mid; q_plain[2][e] = (uint16_t)lo;
-    const int n = (int)rintf(v * q_unit_inv);                     // |n| <= 2^20
-    const int d2 = (n << 25) >> 25, n1 = (n - d2) >> 7;           // balanced base-128 digits, each in [-64, 64]
-    const int d1 = (n1 << 25) >> 25, d0 = (n1 - d1) >> 7;
-    const int p = k_digit_pos(e);
-    q_digit[0][p] = (int8_t)d0; q_digit[1][p] = (int8_t)d1; q_digit[2][p] = (int8_t)d2;
-    qf[e] = (float)n;                                             // the value the digits represent, in units of U
-  }
-  __syncthreads();
-
-  // ---- per-group sums of the (digitised) query, in units of U ----
+  const float q_unit = q_scal[0];
   float qsum[NG];
-  {
-    float qsum_part[NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) qsum_part[g] = 0.0f;
-#pragma unroll
-    for (int rep = 0; rep < 2; ++rep) qsum_part[(NG == 2) ? rep : 0] += qf[lane + 64 * rep];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) qsum[g] = wave_sum_dpp(qsum_part[g]);
-  }
+  for (int g = 0; g < NG; ++g) qsum[g] = q_scal[1 + g];
 
   // ---- A operands for the code stream, per token group g: row 4g+digit carries that digit, other rows are zero.
   // They stay in LDS (two 128-bit reads per product) instead of 32 registers: the kernel then fits three
@@ -490,8 +533,9 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
   auto bf16_units = [&](const uint16_t *ks_base, const uint16_t *vs_base, int cnt, auto &&row_ok) {
     const int n_units = (cnt + 63) / 64;
     // fused decode step: the 16-bit rows (one of which may be the new row) are read by the appending split only
-    const int unit_step = a.fused_append ? kWaves : kWaves * a.n_split;
-    const int unit_first = a.fused_append ? (appends ? wave : n_units) : split + wave * a.n_split;
+    // (dealt from the last wavefront on: when the tiles do not divide evenly, the last ones have one tile less)
+    const int unit_step = a.fused_append ? NW : NW * a.n_split;
+    const int unit_first = a.fused_append ? (appends ? NW - 1 - wave : n_units) : split + (NW - 1 - wave) * a.n_split;
     for (int unit = unit_first; unit < n_units; unit += unit_step) {
       const int s_lane = unit * 64 + lane;
       // only the token groups (16 slots) and blocks (32 slots) that hold rows are touched; the first block of value
@@ -520,16 +564,19 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
       float p;
       if (!softmax_step(score, ok, true, p)) continue;
       {
+        // three terms here: a head that looks at one pivot has that row's rounding of the weight in its result
+        const float w = ok ? p : 0.0f;
         float hif, lof;
-        split2(ok ? p : 0.0f, hif, lof);
+        split2(w, hif, lof);
         w_lds[blk_of_lane][0][0][slot] = (uint16_t)hi16(hif);
         w_lds[blk_of_lane][0][1][slot] = (uint16_t)hi16(lof);
+        w_lds[blk_of_lane][0][2][slot] = (uint16_t)f32_to_bf16_rne((w - hif) - lof);
       }
       wave_lds_sync();
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) {
         if (b2 >= n_blk) break;
-        const uint16_t *src = mrow < 2 ? &w_lds[b2][0][mrow][8 * qd] : zero16;
+        const uint16_t *src = mrow < 3 ? &w_lds[b2][0][mrow][8 * qd] : zero16;
         const bf16x8 a_v = *reinterpret_cast<const bf16x8 *>(src);
         // which of this lane's 8 K-slots (pair i, half) are real rows: mask the others (unwritten memory)
         uint32_t keep[4];
@@ -575,7 +622,7 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
     });
   }
 
-  // ================= merge the four wavefronts, then either finish (one split) or store the partial =================
+  // ================= merge the wavefronts, then either finish (one split) or store the partial =================
   {
     const float l_tot = wave_sum_dpp(l_run);
     float corr[NG];  // what the expansion constant and the zero-points added to every channel of the group
@@ -585,43 +632,16 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
     if (lane < 16) {
 #pragma unroll
       for (int nb = 0; nb < 8; ++nb) {
-        mrg_o[wave][16 * nb + lane] = (acc_o[nb][0] + acc_o[nb][1]) - corr[(NG == 2) ? (nb >> 2) : 0];
+        mrg_o[wave][16 * nb + lane] = (acc_o[nb][0] + acc_o[nb][1]) + acc_o[nb][2] - corr[(NG == 2) ? (nb >> 2) : 0];
       }
     }
   }
-  __syncthreads();
-  float m_all = -INFINITY, l_all = 0.0f, o = 0.0f;
-  if (tid < kD) {
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, mrg_m[w]);
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      if (mrg_m[w] == -INFINITY) continue;
-      const float wgt = fast_exp2(mrg_m[w] - m_all);
-      l_all += wgt * mrg_l[w];
-      o += wgt * mrg_o[w][tid];
-    }
-  }
-  if (a.n_split == 1) {
-    if (tid < kD) qf[tid] = o / l_all;  // the query is no longer needed: its buffer carries the row to wavefront 0
-    if (a.lse && tid == 0) a.lse[bh] = (m_all + __log2f(l_all)) * kLn2;
-    __syncthreads();
-    if (wave == 0) unrotate_store_wave(qf, a.out, (size_t)bh, a.out_rotated != 0, a.out_half != 0, lane);
-  } else if (tid < kD) {
-    float *dst = a.partial + ((size_t)bh * a.n_split + split) * kPartialStride;
-    if (tid == 0) { dst[0] = m_all; dst[1] = l_all; }
-    dst[4 + tid] = o;
-  }
+  lds_barrier();
+  if (wave == 0) merge_waves_and_store<NW>(a, mrg_m, mrg_l, 1, &mrg_o[0][0], kD, (size_t)bh, split, lane);
 }
 
-__global__ __launch_bounds__(64 * kWaves) void decode_mha_kernel_g128(DecodeArgs a) { decode_mha_body<128, false>(a); }
-__global__ __launch_bounds__(64 * kWaves) void decode_mha_kernel_g64(DecodeArgs a) { decode_mha_body<64, false>(a); }
-__global__ __launch_bounds__(64 * kWaves) void decode_mha_pairs_kernel_g128(DecodeArgs a) {
-  decode_mha_body<128, true>(a);
-}
-__global__ __launch_bounds__(64 * kWaves) void decode_mha_pairs_kernel_g64(DecodeArgs a) {
-  decode_mha_body<64, true>(a);
-}
+template <int G, bool PAIRS, int NW>
+__global__ __launch_bounds__(64 * NW) void decode_mha_kernel(DecodeArgs a) { decode_mha_body<G, PAIRS, NW>(a); }
 
 // ------------------------------------------------------------------------------------------------
 // GQA (R = Hq/Hkv query heads share a KV head, 2 <= R <= 8; also valid for R = 1).  A tile is one cache block
@@ -635,17 +655,17 @@ struct GqaTile {
   uint32_t fm;  // fine-half mask word of the block (only loaded by the PAIRS instantiations)
 };
 
-template <int G, bool PAIRS>
-__global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
+template <int G, bool PAIRS, int NW>
+__global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
   constexpr int NG = kD / G;
   __shared__ __attribute__((aligned(16))) int q_int[8][kD];           // queries as integers, in units of their head's U
   __shared__ __attribute__((aligned(16))) uint16_t q_plain[16][kD];   // row 2h+term, natural order
   __shared__ __attribute__((aligned(16))) uint32_t a_lds[2][6][kWave];  // the two operand images of the code stream
   __shared__ float q_sum[8][NG];                                      // per head and group: sum of the queries
   __shared__ uint32_t q_exp[8];                                       // biased exponent above the head's largest query
-  __shared__ __attribute__((aligned(16))) uint16_t w_lds_all[kWaves][NG][16][kTokBlock];  // [group][row][slot]
-  __shared__ float mrg_m[kWaves][8], mrg_l[kWaves][8];
-  __shared__ float mrg_o[kWaves][8][kD];
+  __shared__ __attribute__((aligned(16))) uint16_t w_lds_all[NW][NG][16][kTokBlock];  // [group][row][slot]
+  __shared__ float mrg_m[NW][8], mrg_l[NW][8];
+  __shared__ float mrg_o[NW][8][kD];
 
   const int tid = threadIdx.x;
   // the wavefront index as a scalar: everything derived from it (tile indices, tile addresses) then lives in scalar
@@ -660,20 +680,72 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   const ExpandF4 ex4;
   auto &w_lds = w_lds_all[wave];
 
-  // Fused decode step: the workgroups of the split that owns the row's tile first write the new row (wavefront 3 the
-  // K row, wavefront 2 the V row); the barrier below orders those stores before this workgroup's loads, which all
-  // come later, and no other workgroup reads that tile.
+  // ---- tile bookkeeping and the first two tiles' loads come first: they do not depend on the queries ----
+  const int n_tiles = (a.t_win + kGqaTileRows - 1) / kGqaTileRows;  // rows from t_win on are read from the recent-window rings
+  int tile_begin, tile_end;
+  decode_split_range(n_tiles, a.n_split, split, tile_begin, tile_end);
+  const size_t plane_blocks = (size_t)a.T_cap / kTokBlock;
+  // plane bases and tile indices are uniform (scalar registers); a lane adds a fixed 32-bit offset (see the MHA kernel)
+  const gptr_u32 kc_plane = as_global(a.k_codes) + (size_t)bh * plane_blocks * kBlockWords;
+  const gptr_u32 vc_plane = as_global(a.v_codes) + (size_t)bh * plane_blocks * kBlockWords;
+  const gptr_u32 km_plane = as_global(a.k_meta) + (size_t)bh * a.T_cap * NG;
+  const gptr_u32 vm_plane = as_global(a.v_meta) + (size_t)bh * a.T_cap * NG;
+  const uint32_t lane_code = (uint32_t)lane * 4u, lane_meta = (uint32_t)mrow * NG;
+
+  const uint32_t *fm_base = PAIRS ? a.fine_mask + (size_t)b * plane_blocks : nullptr;
+  auto load_tile = [&](int tile, GqaTile<NG> &t) {
+    if constexpr (PAIRS) t.fm = fm_base[tile];
+    gptr_u32 kc_t = kc_plane + (size_t)tile * kBlockWords, vc_t = vc_plane + (size_t)tile * kBlockWords;
+    gptr_u32 km_t = km_plane + (size_t)tile * (32 * NG), vm_t = vm_plane + (size_t)tile * (32 * NG);
+    keep_scalar(kc_t); keep_scalar(vc_t); keep_scalar(km_t); keep_scalar(vm_t);
+    t.kc = stream_load_x4(kc_t + lane_code);
+    t.vc = stream_load_x4(vc_t + lane_code);
+#pragma unroll
+    for (int tg = 0; tg < 2; ++tg) {
+      if constexpr (NG == 2) {
+        const u32x2 k2 = stream_load_x2(km_t + 16 * tg * NG + lane_meta);
+        const u32x2 v2 = stream_load_x2(vm_t + 16 * tg * NG + lane_meta);
+        t.km[tg][0] = k2[0]; t.km[tg][1] = k2[1];
+        t.vm[tg][0] = v2[0]; t.vm[tg][1] = v2[1];
+      } else {
+        t.km[tg][0] = stream_load_x1(km_t + 16 * tg * NG + lane_meta);
+        t.vm[tg][0] = stream_load_x1(vm_t + 16 * tg * NG + lane_meta);
+      }
+    }
+  };
+
+  // the length of the salient list is asked for now and looked at after the stream (the append of a fused decode
+  // step does not change it): the 16-bit rows then cost one memory round trip, not three dependent ones
+  // (read through the constant address space: a scalar load, whose wait the compiler puts in front of the first use;
+  // as a vector load of a uniform address it would be moved to a scalar register, and waited for, right here)
+  const int sal_cnt_early = reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(
+      reinterpret_cast<uintptr_t>(a.sal_cnt))[bh];
+  const int n_mine = tile_begin + wave < tile_end ? (tile_end - tile_begin - wave + NW - 1) / NW : 0;
+  const int last_tile = tile_begin + wave + NW * max(n_mine - 1, 0);
+  auto tile_at = [&](int k) { return min(tile_begin + wave + NW * k, last_tile); };
+  GqaTile<NG> tb[3];
+  // Fused decode step: the workgroups of the split that owns the row's tile first write the new row (the last wavefront
+  // the K row, the one before it the V row); the barrier below orders those stores before this workgroup's loads of that
+  // tile, and no other workgroup reads it.  A wavefront whose first two tiles include it asks for them after the barrier.
   const bool appends = a.fused_append != 0 && split == a.append_split;  // uniform over the workgroup
-  if (appends && wave >= 2) {
+  const bool defer_loads = appends && a.t_win == a.T_len && n_mine > 0 &&
+                           (tile_at(0) == n_tiles - 1 || tile_at(1) == n_tiles - 1);
+  if (n_mine > 0 && !defer_loads) {
+    load_tile(tile_at(0), tb[0]);
+    load_tile(tile_at(1), tb[1]);
+  }
+  if (appends && wave >= NW - 2) {
     __shared__ __attribute__((aligned(16))) uint8_t step_codes[2][kD];
     __shared__ __attribute__((aligned(16))) uint16_t step_row[2][kD];
-    append_row_wave<G>(a.step, bh, 3 - wave, lane, step_codes[3 - wave], step_row[3 - wave]);
+    append_row_wave<G>(a.step, bh, NW - 1 - wave, lane, step_codes[NW - 1 - wave], step_row[NW - 1 - wave]);
   }
   // Queries, one head per wavefront at a time, two channels (lane, lane + 64) per lane.  sm_scale * log2(e) is folded in,
   // so the products already are base-2 logits.  For the 16-bit rows: two bfloat16 terms.  For the code stream: integers
   // of up to 20 bits in units of a power of two U (|q| < 2^19 U), and their sums per group.
   const float sm2 = a.sm_scale * kLog2e;
-  for (int h = wave; h < 8; h += kWaves) {
+#pragma unroll
+  for (int hi = 0; hi < 8 / NW; ++hi) {
+    const int h = wave + NW * hi;
     float x0 = 0.0f, x1 = 0.0f;
     if (h < R)  // uniform
       rotate_query(a.q + ((size_t)b * a.Hq + hkv * R + h) * kD, x0, x1, a.q_rotated != 0,
@@ -701,7 +773,12 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
       if (lane == 0) { q_sum[h][0] = s0; q_exp[h] = e_biased; }
     }
   }
-  __syncthreads();
+  if (appends) __syncthreads();  // also orders the new row's stores before the loads below
+  else lds_barrier();
+  if (defer_loads) {
+    load_tile(tile_at(0), tb[0]);
+    load_tile(tile_at(1), tb[1]);
+  }
 
   // Row operands of the code stream: the integer of a channel is four balanced base-32 digits, |digit| <= 16, which E2M3
   // holds exactly as digit / 8.  Image 0 holds digit 3 in row 2h and digit 2 in row 2h+1, image 1 digits 1 and 0; the
@@ -733,7 +810,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) a_lds[wave][i][lane] = img[i];
   }
-  __syncthreads();
+  lds_barrier();
   // with two groups per row each group's operand has zeros in the other group's slots (half of the registers)
   u32x6 a_k[2][NG];
 #pragma unroll
@@ -828,39 +905,6 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   };
 
   // ================= code stream =================
-  const int n_tiles = (a.t_win + kGqaTileRows - 1) / kGqaTileRows;  // rows from t_win on are read from the recent-window rings
-  int tile_begin, tile_end;
-  decode_split_range(n_tiles, a.n_split, split, tile_begin, tile_end);
-  const size_t plane_blocks = (size_t)a.T_cap / kTokBlock;
-  // plane bases and tile indices are uniform (scalar registers); a lane adds a fixed 32-bit offset (see the MHA kernel)
-  const gptr_u32 kc_plane = as_global(a.k_codes) + (size_t)bh * plane_blocks * kBlockWords;
-  const gptr_u32 vc_plane = as_global(a.v_codes) + (size_t)bh * plane_blocks * kBlockWords;
-  const gptr_u32 km_plane = as_global(a.k_meta) + (size_t)bh * a.T_cap * NG;
-  const gptr_u32 vm_plane = as_global(a.v_meta) + (size_t)bh * a.T_cap * NG;
-  const uint32_t lane_code = (uint32_t)lane * 4u, lane_meta = (uint32_t)mrow * NG;
-
-  const uint32_t *fm_base = PAIRS ? a.fine_mask + (size_t)b * plane_blocks : nullptr;
-  auto load_tile = [&](int tile, GqaTile<NG> &t) {
-    if constexpr (PAIRS) t.fm = fm_base[tile];
-    gptr_u32 kc_t = kc_plane + (size_t)tile * kBlockWords, vc_t = vc_plane + (size_t)tile * kBlockWords;
-    gptr_u32 km_t = km_plane + (size_t)tile * (32 * NG), vm_t = vm_plane + (size_t)tile * (32 * NG);
-    keep_scalar(kc_t); keep_scalar(vc_t); keep_scalar(km_t); keep_scalar(vm_t);
-    t.kc = stream_load_x4(kc_t + lane_code);
-    t.vc = stream_load_x4(vc_t + lane_code);
-#pragma unroll
-    for (int tg = 0; tg < 2; ++tg) {
-      if constexpr (NG == 2) {
-        const u32x2 k2 = stream_load_x2(km_t + 16 * tg * NG + lane_meta);
-        const u32x2 v2 = stream_load_x2(vm_t + 16 * tg * NG + lane_meta);
-        t.km[tg][0] = k2[0]; t.km[tg][1] = k2[1];
-        t.vm[tg][0] = v2[0]; t.vm[tg][1] = v2[1];
-      } else {
-        t.km[tg][0] = stream_load_x1(km_t + 16 * tg * NG + lane_meta);
-        t.vm[tg][0] = stream_load_x1(vm_t + 16 * tg * NG + lane_meta);
-      }
-    }
-  };
-
   // Only the last tile of the stream can hold rows at or beyond t_win, whose meta words are arbitrary bits.  For that
   // tile the words of such rows are replaced, in registers, by "salient, scale 0" (K) and "scale 0" (V); everything
   // below then needs no validity mask at all: a salient row gets a score of -inf, hence a weight of exactly 0, and the
@@ -964,19 +1008,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
     wave_lds_sync();
   };
   // three tile buffers, two tiles of loads in flight (see the MHA kernel)
-  // the length of the salient list is asked for now and looked at after the stream (the append of a fused decode
-  // step does not change it): the 16-bit rows then cost one memory round trip, not three dependent ones
-  // (read through the constant address space: a scalar load, whose wait the compiler puts in front of the first use;
-  // as a vector load of a uniform address it would be moved to a scalar register, and waited for, right here)
-  const int sal_cnt_early = reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(
-      reinterpret_cast<uintptr_t>(a.sal_cnt))[bh];
-  const int n_mine = tile_begin + wave < tile_end ? (tile_end - tile_begin - wave + kWaves - 1) / kWaves : 0;
-  const int last_tile = tile_begin + wave + kWaves * max(n_mine - 1, 0);
-  auto tile_at = [&](int k) { return min(tile_begin + wave + kWaves * k, last_tile); };
-  GqaTile<NG> tb[3];
   if (n_mine > 0) {
-    load_tile(tile_at(0), tb[0]);
-    load_tile(tile_at(1), tb[1]);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       settle(tb[i].kc); settle(tb[i].vc);
@@ -985,7 +1017,9 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) { settle(tb[i].km[tg][g]); settle(tb[i].vm[tg][g]); }
     }
+    StreamPace pace(n_mine, a.paced != 0);
     for (int k = 0; k < n_mine; k += 3) {
+      pace.done(k);
       load_tile(tile_at(k + 2), tb[2]);
       process(tb[0], tile_at(k));
       if (k + 1 >= n_mine) break;
@@ -1002,8 +1036,8 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
   auto bf16_units = [&](const uint16_t *ks_base, const uint16_t *vs_base, int cnt, auto &&row_ok) {
     const int n_units = (cnt + 31) / 32;
     // fused decode step: the 16-bit rows (one of which may be the new row) are read by the appending split only
-    const int unit_step = a.fused_append ? kWaves : kWaves * a.n_split;
-    const int first_unit = a.fused_append ? (appends ? wave : n_units) : split + wave * a.n_split;
+    const int unit_step = a.fused_append ? NW : NW * a.n_split;
+    const int first_unit = a.fused_append ? (appends ? NW - 1 - wave : n_units) : split + (NW - 1 - wave) * a.n_split;
     if (first_unit >= n_units) return;
     bf16x8 a_s[4];
 #pragma unroll
@@ -1096,7 +1130,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
     });
   }
 
-  // ================= merge the four wavefronts =================
+  // ================= merge the wavefronts =================
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     const int h = h0 + hh;
@@ -1111,33 +1145,13 @@ __global__ __launch_bounds__(64 * kWaves) void decode_gqa_kernel(DecodeArgs a) {
       mrg_o[wave][h][16 * nb + mrow] = (acc_o[nb][2 * hh] + acc_o[nb][2 * hh + 1]) - corr[(NG == 2) ? (nb >> 2) : 0];
     }
   }
-  __syncthreads();
-  for (int h = 0; h < R; ++h) {
-    float m_all = -INFINITY, l_all = 0.0f, o = 0.0f;
-    if (tid < kD) {
+  lds_barrier();
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, mrg_m[w][h]);
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const float wgt = fast_exp2(mrg_m[w][h] - m_all);  // a wavefront without scores has kNoScore and sums of 0
-        l_all += wgt * mrg_l[w][h];
-        o += wgt * mrg_o[w][h][tid];
-      }
-    }
-    const size_t bhq = (size_t)b * a.Hq + hkv * R + h;
-    if (a.n_split == 1) {
-      if (tid < kD) reinterpret_cast<float *>(q_int[h])[tid] = o / l_all;  // the queries are no longer needed: their buffers carry the rows
-      if (a.lse && tid == 0) a.lse[bhq] = (m_all + __log2f(l_all)) * kLn2;
-    } else if (tid < kD) {
-      float *dst = a.partial + (bhq * a.n_split + split) * kPartialStride;
-      if (tid == 0) { dst[0] = m_all; dst[1] = l_all; }
-      dst[4 + tid] = o;
-    }
-  }
-  if (a.n_split == 1) {
-    __syncthreads();
-    for (int h = wave; h < R; h += kWaves)
-      unrotate_store_wave(reinterpret_cast<const float *>(q_int[h]), a.out, (size_t)b * a.Hq + hkv * R + h, a.out_rotated != 0, a.out_half != 0, lane);
+  for (int hi = 0; hi < 8 / NW; ++hi) {
+    const int h = wave + NW * hi;
+    if (h < R)  // uniform
+      merge_waves_and_store<NW>(a, &mrg_m[0][h], &mrg_l[0][h], 8, &mrg_o[0][h][0], 8 * kD, (size_t)b * a.Hq + hkv * R + h,
+                                split, lane);
   }
 }
 
@@ -1205,14 +1219,31 @@ __global__ __launch_bounds__(64 * kCombineWaves) void decode_combine_kernel(Deco
     o0 += wgt * of[w][lane];
     o1 += wgt * of[w][lane + 64];
   }
-  of[0][lane] = o0 / l_all;
-  of[0][lane + 64] = o1 / l_all;
-  wave_lds_sync();
   if (a.lse && lane == 0) a.lse[bhq] = (m_all + __log2f(l_all)) * kLn2;
-  unrotate_store_wave(of[0], a.out, (size_t)bhq, a.out_rotated != 0, a.out_half != 0, lane);
+  unrotate_store_wave(o0 / l_all, o1 / l_all, a.out, (size_t)bhq, a.out_rotated != 0, a.out_half != 0, lane);
 }
 
 }  // namespace
+
+template <int G, bool PAIRS>
+static void launch_decode_stream(DecodeArgs a, hipStream_t stream) {
+  const dim3 grid(a.n_split, a.B * a.Hkv);
+  const bool mha = a.Hq == a.Hkv;
+  const int rows = mha ? kMhaTileRows : kGqaTileRows;
+  // At most one workgroup per CU: with four wavefronts every SIMD would hold a single one, so the workgroups get eight.
+  // (Beyond that, eight need more registers than two workgroups of a CU have between them: 384 of them, tiered rows,
+  // took 21.7 us instead of 18.7.)
+  const long workgroups = (long)a.B * a.Hkv * a.n_split;
+  const bool wide = workgroups <= kCus && decode_tiles_per_split((a.t_win + rows - 1) / rows, a.n_split) > kWaves;
+  a.paced = !wide && workgroups <= 2 * kCus;
+  if (mha) {
+    if (wide) hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWavesWide>), grid, dim3(64 * kWavesWide), 0, stream, a);
+    else hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWaves>), grid, dim3(64 * kWaves), 0, stream, a);
+  } else {
+    if (wide) hipLaunchKernelGGL((decode_gqa_kernel<G, PAIRS, kWavesWide>), grid, dim3(64 * kWavesWide), 0, stream, a);
+    else hipLaunchKernelGGL((decode_gqa_kernel<G, PAIRS, kWaves>), grid, dim3(64 * kWaves), 0, stream, a);
+  }
+}
 
 hipError_t launch_decode_attention(const DecodeArgs &a_in, int G, hipStream_t stream) {
   DecodeArgs a = a_in;
@@ -1220,21 +1251,12 @@ hipError_t launch_decode_attention(const DecodeArgs &a_in, int G, hipStream_t st
     const int rows = a.Hq == a.Hkv ? kMhaTileRows : kGqaTileRows;
     a.append_split = decode_last_tile_split((a.t_win + rows - 1) / rows, a.n_split);
   }
-  dim3 grid(a.n_split, a.B * a.Hkv), block(64 * kWaves);
-  if (a.Hq == a.Hkv) {
-    if (a.fine_mask) {
-      if (G == 128) hipLaunchKernelGGL(decode_mha_pairs_kernel_g128, grid, block, 0, stream, a);
-      else hipLaunchKernelGGL(decode_mha_pairs_kernel_g64, grid, block, 0, stream, a);
-    } else {
-      if (G == 128) hipLaunchKernelGGL(decode_mha_kernel_g128, grid, block, 0, stream, a);
-      else hipLaunchKernelGGL(decode_mha_kernel_g64, grid, block, 0, stream, a);
-    }
-  } else if (a.fine_mask) {
-    if (G == 128) hipLaunchKernelGGL((decode_gqa_kernel<128, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((decode_gqa_kernel<64, true>), grid, block, 0, stream, a);
+  if (a.fine_mask) {
+    if (G == 128) launch_decode_stream<128, true>(a, stream);
+    else launch_decode_stream<64, true>(a, stream);
   } else {
-    if (G == 128) hipLaunchKernelGGL((decode_gqa_kernel<128, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((decode_gqa_kernel<64, false>), grid, block, 0, stream, a);
+    if (G == 128) launch_decode_stream<128, false>(a, stream);
+    else launch_decode_stream<64, false>(a, stream);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split == 1) return e;
