@@ -284,6 +284,32 @@ __global__ __launch_bounds__(256, 4) void psa_row_stats_kernel(SelectArgs a) {  
   }
 }
 
+// Reference and reciprocal sum of one tail row over all chunks.  The chunks' statistics are requested kMergeBatch at a
+// time, independent of one another: one memory round trip per batch, where a loop with a wait per load spent two per
+// chunk in front of every workgroup of the second pass.
+constexpr int kMergeBatch = 16;
+__device__ __forceinline__ void merge_chunk_stats(const SelectArgs &a, int bhq, int row, float &m_out, float &il_out) {
+  const float *src = a.row_stats + ((size_t)bhq * a.n_chunk * a.W + row) * 2;
+  float mm = -INFINITY, ll = 0.0f;
+  for (int c0 = 0; c0 < a.n_chunk; c0 += kMergeBatch) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    f32x2 ml[kMergeBatch];  // past the end: the last chunk again, left out below
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i)
+      ml[i] = *reinterpret_cast<const f32x2 *>(src + (size_t)min(c0 + i, a.n_chunk - 1) * a.W * 2);
+    float m_new = mm;
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i) m_new = fmaxf(m_new, ml[i][0]);
+    if (mm != -INFINITY) ll *= fast_exp2(mm - m_new);
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i)
+      if (c0 + i < a.n_chunk && ml[i][0] != -INFINITY) ll += ml[i][1] * fast_exp2(ml[i][0] - m_new);
+    mm = m_new;
+  }
+  m_out = mm;
+  il_out = 1.0f / ll;
+}
+
 // pass 2: per (b, hkv, chunk): mass[t] = sum over the group's heads and the tail rows of 2^(s - m_row) / l_row
 template <int NRB>
 __global__ __launch_bounds__(256, 4) void psa_mass_kernel(SelectArgs a) {  // registers and LDS sized for 4 workgroups per CU
@@ -306,19 +332,7 @@ __global__ __launch_bounds__(256, 4) void psa_mass_kernel(SelectArgs a) {  // re
 #pragma unroll
     for (int p = 0; p < kKeyDepth; ++p) load_key_group(k_rows, t_wave + 64 * p, a.T, mrow, qd, ring[p]);
     __syncthreads();
-    if (threadIdx.x < a.W) {  // merge the chunk statistics of this row
-      const int row = threadIdx.x;
-      const float *src = a.row_stats + ((size_t)bhq * a.n_chunk * a.W + row) * 2;
-      float mm = -INFINITY;
-      for (int c = 0; c < a.n_chunk; ++c) mm = fmaxf(mm, src[(size_t)c * a.W * 2]);
-      float ll = 0.0f;
-      for (int c = 0; c < a.n_chunk; ++c) {
-        const float mc = src[(size_t)c * a.W * 2];
-        if (mc != -INFINITY) ll += src[(size_t)c * a.W * 2 + 1] * fast_exp2(mc - mm);
-      }
-      row_m[row] = mm;
-      row_il[row] = 1.0f / ll;
-    }
+    if (threadIdx.x < a.W) merge_chunk_stats(a, bhq, threadIdx.x, row_m[threadIdx.x], row_il[threadIdx.x]);
     stage_query_rows<NRB>(a.q_tail + (size_t)bhq * a.W * kD, wave, mrow, qd, q_lds);
     __syncthreads();
 #pragma unroll
@@ -618,18 +632,9 @@ __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_mass_gqa_ke
     return;
   }
   if constexpr (!kFeeder) request_block(k_rows, t_chunk, a.T, first, stride, mrow, qd, st);
-  if (lane < 16 * NRB) {  // merge the chunk statistics of this wavefront's rows
+  if (lane < 16 * NRB) {
     const int row = 16 * rb0 + lane;
-    const float *src = a.row_stats + ((size_t)bhq * a.n_chunk * a.W + row) * 2;
-    float mm = -INFINITY;
-    for (int c = 0; c < a.n_chunk; ++c) mm = fmaxf(mm, src[(size_t)c * a.W * 2]);
-    float ll = 0.0f;
-    for (int c = 0; c < a.n_chunk; ++c) {
-      const float mc = src[(size_t)c * a.W * 2];
-      if (mc != -INFINITY) ll += src[(size_t)c * a.W * 2 + 1] * fast_exp2(mc - mm);
-    }
-    stat_m[head][row] = mm;
-    stat_il[head][row] = 1.0f / ll;
+    merge_chunk_stats(a, bhq, row, stat_m[head][row], stat_il[head][row]);
   }
   bf16x8 q[NRB * 4];
   load_query_rows<NRB>(a.q_tail + (size_t)bhq * a.W * kD, rb0, mrow, qd, q);
