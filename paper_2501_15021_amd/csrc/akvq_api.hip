@@ -75,14 +75,18 @@ int akvq_cache_bytes(const akvq_cache *shape, size_t out_bytes[8]) {
   return AKVQ_OK;
 }
 
-static int select_chunks(int T) { return (int)(((long)T + akvq::kScoreChunk - 1) / akvq::kScoreChunk); }
+static int select_chunks(int T, int chunk) { return (int)(((long)T + chunk - 1) / chunk); }
 
-size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W) {
-  if (B <= 0 || Hq <= 0 || Hkv <= 0 || T <= 0 || W <= 0) return 0;
-  const size_t stats = (size_t)B * Hq * select_chunks(T) * W * 2 * sizeof(float);
+static size_t select_bytes(int B, int Hq, int Hkv, int T, int W, int chunk) {
+  const size_t stats = (size_t)B * Hq * select_chunks(T, chunk) * W * 2 * sizeof(float);
   const size_t mass = (size_t)B * Hkv * T * sizeof(float);
   const size_t shared = (size_t)B * T * sizeof(float);  // AKVQ_MODE_PSA_SHARED: the kv-heads' masses added
   return round_up(stats, 256) + round_up(mass, 256) + round_up(shared, 256);
+}
+
+size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W) {
+  if (B <= 0 || Hq <= 0 || Hkv <= 0 || T <= 0 || W <= 0) return 0;
+  return select_bytes(B, Hq, Hkv, T, W, akvq::score_chunk(B, Hq, Hkv, T, W));
 }
 
 size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
@@ -137,11 +141,15 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   if (top_k > c->S_cap) return AKVQ_ERR_CAPACITY;
   if (mass_out && !aligned16(mass_out)) return AKVQ_ERR_INVALID_ARG;
   if (!workspace || !aligned16(workspace)) return AKVQ_ERR_INVALID_ARG;
-  if (workspace_bytes < akvq_select_workspace_bytes(c->B, Hq, c->Hkv, T, W)) return AKVQ_ERR_WORKSPACE;
+  // a workspace too small for the finer chunks of a small problem still serves the coarse ones
+  int chunk = akvq::score_chunk(c->B, Hq, c->Hkv, T, W);
+  if (workspace_bytes < select_bytes(c->B, Hq, c->Hkv, T, W, chunk)) chunk = akvq::kScoreChunk;
+  if (workspace_bytes < select_bytes(c->B, Hq, c->Hkv, T, W, chunk)) return AKVQ_ERR_WORKSPACE;
   a.q_tail = static_cast<const uint16_t *>(q_tail);
   a.k = static_cast<const uint16_t *>(k);
   a.Hq = Hq; a.W = W; a.top_k = top_k; a.sm_scale = sm_scale;
-  a.n_chunk = select_chunks(T);
+  a.chunk = chunk;
+  a.n_chunk = select_chunks(T, chunk);
   a.row_stats = static_cast<float *>(workspace);
   const size_t stats = round_up((size_t)c->B * Hq * a.n_chunk * W * 2 * sizeof(float), 256);
   const size_t mass_bytes = round_up((size_t)c->B * c->Hkv * T * sizeof(float), 256);

@@ -88,7 +88,8 @@ struct SelectArgs {
   int32_t *sal_idx, *sal_cnt;
   float *mass;               // [B][Hkv][T] fp32 (user buffer or workspace)
   float *row_stats;          // workspace: [B][Hq][n_chunk][W][2]
-  int B, Hq, Hkv, T, W, top_k, S_cap, n_chunk;
+  int B, Hq, Hkv, T, W, top_k, S_cap;
+  int chunk, n_chunk;        // keys per scoring workgroup (score_chunk) and how many of them cover T
   float sm_scale;
   // massive-activation mode: hidden states, one score row per batch element, zero keys are never selected
   const uint16_t *hidden;    // [B][T][d_model] binary16
@@ -98,7 +99,24 @@ struct SelectArgs {
   int skip_zero;
   float *mass_shared;        // token-level pivots: [B][T] sums of the kv-heads' masses (workspace), null: per-head lists
 };
-constexpr int kScoreChunk = 2048;  // keys per scoring workgroup
+// Keys per scoring workgroup: kScoreChunk, or less where that would leave most of the chip idle (scoring windows of 64
+// rows only; the kernels for smaller windows have it built in).  Halved until there is a workgroup per CU, two with one
+// head per KV head (four wavefronts each instead of up to eighteen), but not below two blocks of keys, where the staging
+// of the rows would outweigh the scoring, and not beyond 64 chunks, whose statistics the second pass merges in four round
+// trips.  Selection with chunks of 2048 and with this rule, one prompt: 32 heads, 640 tokens 29.1 -> 18.7 us, 4096 tokens
+// 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096 tokens 142 -> 35, 32768 tokens 160 -> 76.  Twice the
+// workgroups: 37.6 us at 32 heads, 4096 tokens, and 101 instead of 76 us at 32/8 heads, 4 prompts of 8192 tokens.
+constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64;
+inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
+  const int R = Hkv > 0 ? Hq / Hkv : 0;
+  if (W != 64 || R < 1 || R > 8) return kScoreChunk;
+  const long want = R == 1 ? 512 : 256;
+  int chunk = kScoreChunk;
+  while (chunk > kScoreChunkMin && (long)B * Hkv * (((long)T + chunk - 1) / chunk) < want &&
+         ((long)T + chunk / 2 - 1) / (chunk / 2) <= kScoreMaxFineChunks)
+    chunk /= 2;
+  return chunk;
+}
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_massive(const SelectArgs &a, hipStream_t stream);

@@ -405,11 +405,10 @@ __global__ __launch_bounds__(256, 4) void psa_mass_kernel(SelectArgs a) {  // re
 // wavefronts load, convert and score their own keys, that is 2-7 % per pass with one head per KV head.
 constexpr int kGqaBlockGroups = 4;                                // groups of 16 keys per block
 constexpr int kGqaBlockKeys = 16 * kGqaBlockGroups;               // 64
-constexpr int kGqaBlocks = kScoreChunk / kGqaBlockKeys;           // blocks per chunk
 constexpr int kGqaItems = kGqaBlockGroups * 4;                    // 1 KB pieces (four whole keys each) of a block
 constexpr int kGqaMaxHeads = 8;                                   // query heads per KV head
 constexpr int kGqaFeederItems = kGqaItems / 2;                    // MAXIT from this on: feeder wavefronts bring in the keys
-static_assert(kScoreChunk % kGqaBlockKeys == 0, "a chunk is a whole number of blocks");
+static_assert(kScoreChunkMin % kGqaBlockKeys == 0 && kScoreChunk % kScoreChunkMin == 0, "a chunk is a whole number of blocks");
 static_assert(kGqaBlockGroups % 2 == 0, "the first pass walks a block two groups at a time");
 static_assert(kGqaItems % (2 * kGqaMaxHeads) == 0, "up to sixteen scoring wavefronts share a block's pieces evenly");
 
@@ -500,8 +499,8 @@ __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_row_stats_g
   const int bhq = b * a.Hq + hkv * R + head;
   const uint16_t *k_rows = a.k + (size_t)bh * a.T * kD;
   const float scale2 = a.sm_scale * kLog2e;
-  const int t_chunk = chunk * kScoreChunk;
-  const int n_blk = min(kGqaBlocks, (a.T - t_chunk + kGqaBlockKeys - 1) / kGqaBlockKeys);  // blocks that hold keys
+  const int t_chunk = chunk * a.chunk;
+  const int n_blk = (min(a.chunk, a.T - t_chunk) + kGqaBlockKeys - 1) / kGqaBlockKeys;  // blocks that hold keys
   // feeders (kGqaItems / MAXIT wavefronts behind the scoring ones) take consecutive pieces; without feeders the
   // scoring wavefronts take pieces wave, wave + kMaxWaves, ...
   constexpr bool kFeeder = MAXIT >= kGqaFeederItems;
@@ -598,8 +597,8 @@ __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_mass_gqa_ke
   const int bhq = b * a.Hq + hkv * R + head;
   const uint16_t *k_rows = a.k + (size_t)bh * a.T * kD;
   const float scale2 = a.sm_scale * kLog2e;
-  const int t_chunk = chunk * kScoreChunk;
-  const int n_blk = min(kGqaBlocks, (a.T - t_chunk + kGqaBlockKeys - 1) / kGqaBlockKeys);
+  const int t_chunk = chunk * a.chunk;
+  const int n_blk = (min(a.chunk, a.T - t_chunk) + kGqaBlockKeys - 1) / kGqaBlockKeys;
   // feeders (kGqaItems / MAXIT wavefronts behind the scoring ones) take consecutive pieces; without feeders the
   // scoring wavefronts take pieces wave, wave + kMaxWaves, ...
   constexpr bool kFeeder = MAXIT >= kGqaFeederItems;
