@@ -737,6 +737,7 @@ constexpr int kTopkStageMax = 32768;  // keys (128 KB of LDS)
 constexpr int kTopkListMax = 256;     // selected positions ordered through LDS when k is at most this
 constexpr int kTopkCandMax = 512;     // candidates the short cut ranks among themselves
 constexpr int kTopkWideFrom = 8192, kTopkWideRows = 512, kTopkWideThreads = 1024;  // see launch_topk
+constexpr int kTopkBatch = 8;         // keys a thread requests together
 // NT threads per workgroup (256, or 1024 for long rows: the passes over the keys are what takes the time there)
 template <bool STAGED, int NT>
 __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
@@ -746,11 +747,10 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
   __shared__ uint32_t sh_prefix;
   __shared__ int sh_need;
   __shared__ int list_n;
-  __shared__ int list[kTopkListMax];
+  __shared__ __attribute__((aligned(16))) int list[kTopkListMax + 8];
   __shared__ uint32_t thread_max[NT];
   __shared__ int cand_n;
-  __shared__ uint32_t cand_key[kTopkCandMax];
-  __shared__ int cand_pos[kTopkCandMax];
+  __shared__ __attribute__((aligned(16))) uint64_t cand[kTopkCandMax + 8];  // key, then the position inverted: larger comes first
   const int bh = blockIdx.x, lane = threadIdx.x & 63;
   const float *mass = a.mass + (size_t)(a.mass_per_batch ? bh / a.Hkv : bh) * a.T;
   int32_t *out = a.sal_idx + (size_t)bh * a.S_cap;
@@ -758,10 +758,16 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
   const uint32_t lowest = a.skip_zero ? 1u : 0u;  // keys below this bit pattern (i.e. +0) are never selected
   if (STAGED) {
     uint32_t mine = 0u;  // largest key this thread staged (bit patterns of non-negative floats order like the floats)
-    for (int t = threadIdx.x; t < a.T; t += NT) {
-      const float x = mass[t];
-      keys_lds[t] = x;
-      mine = max(mine, __float_as_uint(x));
+    for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
+      float x[kTopkBatch];  // requested together; positions past the end read the last key and are dropped
+#pragma unroll
+      for (int i = 0; i < kTopkBatch; ++i) x[i] = mass[min(t0 + i * NT, a.T - 1)];
+#pragma unroll
+      for (int i = 0; i < kTopkBatch; ++i)
+        if (t0 + i * NT < a.T) {
+          keys_lds[t0 + i * NT] = x[i];
+          mine = max(mine, __float_as_uint(x[i]));
+        }
     }
     if (threadIdx.x == 0) { list_n = 0; cand_n = 0; }
     thread_max[threadIdx.x] = mine;
@@ -781,36 +787,50 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
         for (int jj = 0; jj < NT / 256; ++jj) v = max(v, thread_max[lane + 64 * i + 256 * jj]);
         mx[i] = v;
       }
+      // Sixteen bits of it (the sign is 0: exponent and eight bits of the fraction) are enough: a bound that is lower by
+      // up to 2^-8 of itself lets a few more candidates through, and each bit is a step of a serial chain.
       uint32_t bound = 0u;
-      for (int bit = 31; bit >= 0; --bit) {
+#pragma unroll
+      for (int bit = 30; bit >= 15; --bit) {
         const uint32_t cand = bound | (1u << bit);
         const int n_ge = __popcll(__ballot(mx[0] >= cand)) + __popcll(__ballot(mx[1] >= cand)) +
                          __popcll(__ballot(mx[2] >= cand)) + __popcll(__ballot(mx[3] >= cand));
         if (n_ge >= k) bound = cand;
       }
-      for (int t = threadIdx.x; t < a.T; t += NT) {
-        const uint32_t bits = __float_as_uint(keys_lds[t]);
-        if (bits >= bound && bits >= lowest) {
-          const int at = atomicAdd(&cand_n, 1);
-          if (at < kTopkCandMax) { cand_key[at] = bits; cand_pos[at] = t; }
-        }
+      for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
+        uint32_t bits[kTopkBatch];
+#pragma unroll
+        for (int i = 0; i < kTopkBatch; ++i) bits[i] = __float_as_uint(keys_lds[min(t0 + i * NT, a.T - 1)]);
+#pragma unroll
+        for (int i = 0; i < kTopkBatch; ++i)
+          if (t0 + i * NT < a.T && bits[i] >= bound && bits[i] >= lowest) {
+            const int at = atomicAdd(&cand_n, 1);
+            if (at < kTopkCandMax) cand[at] = ((uint64_t)bits[i] << 32) | ~(uint32_t)(t0 + i * NT);
+          }
       }
       __syncthreads();
       const int n_cand = cand_n;
       if (n_cand <= kTopkCandMax) {  // uniform
+        if (threadIdx.x < 8) cand[n_cand + threadIdx.x] = 0u;  // the ranking below reads eight at a time; 0 ranks behind all
+        __syncthreads();
         for (int c = threadIdx.x; c < n_cand; c += NT) {
-          const uint32_t key = cand_key[c];
-          const int pos = cand_pos[c];
+          const uint64_t mine_key = cand[c];
           int beaten_by = 0;
-          for (int j = 0; j < n_cand; ++j) beaten_by += (cand_key[j] > key) || (cand_key[j] == key && cand_pos[j] < pos);
-          if (beaten_by < k) list[atomicAdd(&list_n, 1)] = pos;
+          for (int j = 0; j < n_cand; j += 8)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) beaten_by += cand[j + i] > mine_key;
+          if (beaten_by < k) list[atomicAdd(&list_n, 1)] = (int)~(uint32_t)mine_key;
         }
         __syncthreads();
         const int n_kept = list_n;  // k, or fewer when zero keys are excluded
+        if (threadIdx.x < 8) list[n_kept + threadIdx.x] = 0x7FFFFFFF;
+        __syncthreads();
         if ((int)threadIdx.x < n_kept) {
           const int mine_pos = list[threadIdx.x];
           int rank = 0;
-          for (int j = 0; j < n_kept; ++j) rank += list[j] < mine_pos;
+          for (int j = 0; j < n_kept; j += 8)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) rank += list[j + i] < mine_pos;
           if (rank < a.S_cap) out[rank] = mine_pos;
         }
         if (threadIdx.x == 0) a.sal_cnt[bh] = n_kept;
