@@ -13,39 +13,56 @@ namespace akvq {
 
 namespace {
 
-// ---- ordered compaction helpers (256-thread workgroup) -----------------------------------------------
-// exclusive prefix of a 0/1 flag over the workgroup, plus the workgroup total
-__device__ __forceinline__ int block_flag_scan(bool flag, int *wave_tot, int &total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned long long ballot = __ballot(flag);
-  const int within = __popcll(ballot & ((1ull << lane) - 1ull));
-  __syncthreads();  // previous use of wave_tot finished
-  if (lane == 0) wave_tot[wave] = __popcll(ballot);
-  __syncthreads();
-  int before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const int c = wave_tot[w];
-    if (w < wave) before += c;
-    tot += c;
-  }
-  total = tot;
-  return before + within;
-}
-
+// Text positions of one batch element, listed for all of its kv-heads by one workgroup per (batch, kv-head).  Latency is
+// all there is to it: a row of a few KB, scanned once.  Each thread takes kTsaBytes consecutive positions at a time, so a
+// round of loads, one workgroup scan and two barriers cover 4096 positions (256 before: 4001 positions of 256 heads took
+// 11.2 us, now 5.9 us).
+constexpr int kTsaBytes = 16;
 __global__ __launch_bounds__(256) void select_tsa_kernel(SelectArgs a) {
-  __shared__ int wave_tot[4];
+  __shared__ int wave_tot[2][4];
   const int bh = blockIdx.x, b = bh / a.Hkv;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint8_t *mask = a.is_text + (size_t)b * a.T;
   int32_t *out = a.sal_idx + (size_t)bh * a.S_cap;
-  int base_count = 0;
-  for (int base = 0; base < a.T; base += 256) {
-    const int t = base + threadIdx.x;
-    const bool flag = t < a.T && mask[t] != 0;
-    int total;
-    const int pos = base_count + block_flag_scan(flag, wave_tot, total);
-    if (flag && pos < a.S_cap) out[pos] = t;
-    base_count += total;
+  const bool aligned = (reinterpret_cast<uintptr_t>(mask) & 15u) == 0;  // uniform: whole rows of 16-byte loads
+  int base_count = 0, copy = 0;
+  for (int base = 0; base < a.T; base += 256 * kTsaBytes, copy ^= 1) {
+    const int t0 = base + threadIdx.x * kTsaBytes;
+    uint32_t set = 0u;  // bit i: position t0 + i is text
+    if (aligned && t0 + kTsaBytes <= a.T) {
+      const u32x4 m = *reinterpret_cast<const u32x4 *>(mask + t0);
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) set |= ((m[w] >> (8 * i)) & 0xFFu) != 0u ? 1u << (4 * w + i) : 0u;
+    } else {
+      uint8_t m[kTsaBytes];  // positions past the end read the last one and are dropped
+#pragma unroll
+      for (int i = 0; i < kTsaBytes; ++i) m[i] = mask[min(t0 + i, a.T - 1)];
+#pragma unroll
+      for (int i = 0; i < kTsaBytes; ++i) set |= (t0 + i < a.T && m[i] != 0) ? 1u << i : 0u;
+    }
+    int upto = __popc(set);  // inclusive prefix over the wavefront, then over the workgroup
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int up = __shfl_up(upto, off, kWave);
+      if (lane >= off) upto += up;
+    }
+    if (lane == kWave - 1) wave_tot[copy][wave] = upto;
+    __syncthreads();  // (two copies: the next round's totals do not overwrite these)
+    int pos = base_count + upto - __popc(set);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int c = wave_tot[copy][w];
+      if (w < wave) pos += c;
+      base_count += c;
+    }
+    while (set != 0u) {
+      const int i = __ffs((int)set) - 1;
+      set &= set - 1u;
+      if (pos < a.S_cap) out[pos] = t0 + i;
+      ++pos;
+    }
   }
   if (threadIdx.x == 0) a.sal_cnt[bh] = base_count;
 }
