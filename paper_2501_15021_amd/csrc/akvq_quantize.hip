@@ -136,16 +136,20 @@ __device__ __forceinline__ float rope_mix(uint32_t x, uint32_t c, uint32_t xp, u
   }
   return r;
 }
+// two floats -> packed binary16 pair (lo = a, hi = b), round to nearest even, one conversion instruction
+__device__ __forceinline__ uint32_t pack_half2(float a, float b) {
+  uint32_t r;
+  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 __device__ __forceinline__ void rope_row_quad(u32x4 (&raw)[4], const u32x4 (&cw)[2], const u32x4 (&sw)[2]) {
 #pragma unroll
   for (int mm = 0; mm < 2; ++mm)
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const uint32_t lo = raw[mm][w], hi = raw[mm + 2][w], c = cw[mm][w], sn = sw[mm][w];
-      raw[mm][w] = float_to_half_bits_rne(rope_mix<0>(lo, c, hi, sn, true)) |
-                   (float_to_half_bits_rne(rope_mix<1>(lo, c, hi, sn, true)) << 16);
-      raw[mm + 2][w] = float_to_half_bits_rne(rope_mix<0>(hi, c, lo, sn, false)) |
-                       (float_to_half_bits_rne(rope_mix<1>(hi, c, lo, sn, false)) << 16);
+      raw[mm][w] = pack_half2(rope_mix<0>(lo, c, hi, sn, true), rope_mix<1>(lo, c, hi, sn, true));
+      raw[mm + 2][w] = pack_half2(rope_mix<0>(hi, c, lo, sn, false), rope_mix<1>(hi, c, lo, sn, false));
     }
 }
 
@@ -269,6 +273,11 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int (*s
     }
   }
   wave_lds_sync();
+
+  // any row that is not a plain one: codes then go through the field extraction of code_bits_tiered, which leaves no
+  // constant part behind  (uniform over the wavefront; never without tiers)
+  bool no_bias = false;
+  if constexpr (TIERED) no_bias = __ballot(tier[0] != AKVQ_TIER_2BIT || tier[1] != AKVQ_TIER_2BIT) != 0ull;
 
   // recent window: is this whole block new and inside the window?  (uniform over the wavefront)
   bool win_block = false;
@@ -412,39 +421,39 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int (*s
       if (tier[h] == AKVQ_TIER_4BIT_COARSE) code_shift = 2u;
       if (tier[h] == AKVQ_TIER_PAD) code_keep = 0u;
     }
-    constexpr uint32_t kBias16 = TIERED ? 0u : kPack16Bias;
-    auto row_code = [&](float x, const GroupQ &q) {
-      if constexpr (TIERED) return code_bits_tiered(x, q, code_top, code_shift, code_keep);
-      else return code_bits(x, q);
-    };
-
-    // ---- codes ----
-    if (tensor == 0) {
-      // K word (m/2): slot 8*(m%2)+i at bits 2*slot; built from the top slot down by shift-adds
+    auto pack_codes = [&](auto &&row_code, uint32_t bias16) {
+      if (tensor == 0) {
+        // K word (m/2): slot 8*(m%2)+i at bits 2*slot; built from the top slot down by shift-adds
 #pragma unroll
-      for (int wq = 0; wq < 2; ++wq) {
-        uint32_t word = 0;
+        for (int wq = 0; wq < 2; ++wq) {
+          uint32_t word = 0;
 #pragma unroll
-        for (int slot = 15; slot >= 0; --slot) {
-          const int m = 2 * wq + (slot >> 3), i = slot & 7;
-          word = (word << 2) + row_code(u[m][i], gq[m / (4 / NG)]);
-          asm("" : "+v"(word));  // keep the chain one shift-add per code (re-association costs more instructions)
+          for (int slot = 15; slot >= 0; --slot) {
+            const int m = 2 * wq + (slot >> 3), i = slot & 7;
+            word = (word << 2) + row_code(u[m][i], gq[m / (4 / NG)]);
+            asm("" : "+v"(word));  // keep the chain one shift-add per code (re-association costs more instructions)
+          }
+          kw[h][wq] = word - bias16;
         }
-        kw[h][wq] = word - kBias16;
+      } else {
+        // V: byte lanes of a partial word: token half h, X (m even) / Y (m odd); biases removed after both halves
+#pragma unroll
+        for (int mp = 0; mp < 2; ++mp)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t bx = row_code(u[2 * mp][i], gq[(2 * mp) / (4 / NG)]);
+            const uint32_t by = row_code(u[2 * mp + 1][i], gq[(2 * mp + 1) / (4 / NG)]);
+            const uint32_t part = (by << 8) + bx;
+            if (h == 0) vcode[mp][i] = part; else vcode[mp][i] = (part << 16) + vcode[mp][i];
+          }
+        if (valid[h]) vmask_part |= 0x0303u << (16 * h);
       }
-    } else {
-      // V: byte lanes of a partial word: token half h, X (m even) / Y (m odd); biases removed after both halves
-#pragma unroll
-      for (int mp = 0; mp < 2; ++mp)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint32_t bx = row_code(u[2 * mp][i], gq[(2 * mp) / (4 / NG)]);
-          const uint32_t by = row_code(u[2 * mp + 1][i], gq[(2 * mp + 1) / (4 / NG)]);
-          const uint32_t part = (by << 8) + bx;
-          if (h == 0) vcode[mp][i] = part; else vcode[mp][i] = (part << 16) + vcode[mp][i];
-        }
-      if (valid[h]) vmask_part |= 0x0303u << (16 * h);
-    }
+    };
+    // ---- codes ----  (a tiered block whose rows are all plain, most blocks of a prompt, takes the plain path)
+    if (no_bias)
+      pack_codes([&](float x, const GroupQ &q) { return code_bits_tiered(x, q, code_top, code_shift, code_keep); }, 0u);
+    else
+      pack_codes([&](float x, const GroupQ &q) { return code_bits(x, q); }, kPack16Bias);
   }
 
   // ---- meta ----
@@ -479,13 +488,15 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int (*s
     mask |= dpp_move_u<kRowRor4>(mask);
     mask |= dpp_move_u<kRowRor8>(mask);
     if (mask != 0u) {  // uniform over the four rows of a chunk; in practice over the wavefront
+      const uint32_t shifted_bias = no_bias ? 0u : 0u - (kPack4Bias << (2 * ii));
       // all cross-lane work first, outside any divergent control flow: complete words of the lane's eight chunks
       uint32_t w[2][8];
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int mp = 0; mp < 2; ++mp) {
-          uint32_t x = (vcode[mp][i] - (TIERED ? 0u : kPack4Bias)) << (2 * ii);
+          // (the patterns' constant part is taken off after the shift, where both are one shift-add)
+          uint32_t x = (vcode[mp][i] << (2 * ii)) + shifted_bias;
           x |= dpp_move_u<kRowRor4>(x);
           x |= dpp_move_u<kRowRor8>(x);
           w[mp][i] = x;
