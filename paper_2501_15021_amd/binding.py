@@ -137,12 +137,15 @@ def _check(status: int, what: str):
         raise AkvqError(f"{what}: {L.akvq_strerror(status).decode()} (status {status}, hip {L.akvq_last_hip_error()})")
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+# Pointers and streams are handed to ctypes as plain integers (the argtypes convert them), and the stream is read as the
+# raw handle (0.3 us; the Stream object of torch.cuda.current_stream() takes 2.7): a small decode step is bound by this
+# module and not by the GPU.  One sequence of 640 tokens, 32 heads: 14.6 -> 11.6 us a step, 6.5 of them GPU time.
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Cache:
@@ -353,13 +356,14 @@ def decode_step(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, q: torch
                 lse: Optional[torch.Tensor] = None, rope=None):
     """akvq_decode_step: append one row per (batch, kv-head) and run decode attention over the cache including it, in
     one launch; advances cache.T_len.  Returns (out, lse)."""
-    assert k_new.dtype == torch.float16 and v_new.dtype == torch.float16 and q.dtype == torch.float16
+    fp16, L = torch.float16, lib()
+    assert k_new.dtype is fp16 and v_new.dtype is fp16 and q.dtype is fp16
     assert k_new.is_contiguous() and v_new.is_contiguous() and q.is_contiguous()
-    assert tuple(k_new.shape) == (cache.B, cache.Hkv, 1, D) and k_new.shape == v_new.shape
+    assert k_new.shape == (cache.B, cache.Hkv, 1, D) and k_new.shape == v_new.shape
     B, Hq, _ = q.shape
     if n_split <= 0:
-        n_split = lib().akvq_decode_default_splits(cache.B, cache.Hkv, cache.T_len + 1)
-    ws = cache.workspace("decode", lib().akvq_decode_workspace_bytes(B, Hq, n_split))
+        n_split = L.akvq_decode_default_splits(cache.B, cache.Hkv, cache.T_len + 1)
+    ws = cache.workspace("decode", L.akvq_decode_workspace_bytes(B, Hq, n_split))
     if out is None:
         out = torch.empty(B, Hq, D, dtype=torch.float32, device=q.device)
     if lse is None:
@@ -367,9 +371,9 @@ def decode_step(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, q: torch
     c = cache.struct()
     win = cache.window_struct()
     rs = _rope_struct(rope, B, 1) if rope is not None else None
-    _check(lib().akvq_decode_step(C.byref(c), _ptr(cache.fine_mask), C.byref(win) if win else None, _ptr(k_new),
-                                  _ptr(v_new), _ptr(q), C.byref(rs) if rs is not None else None, Hq, clip, sm_scale,
-                                  _ptr(out), _ptr(lse), n_split, _ptr(ws), ws.numel(), flags, _stream()),
+    _check(L.akvq_decode_step(C.byref(c), _ptr(cache.fine_mask), C.byref(win) if win else None, _ptr(k_new),
+                              _ptr(v_new), _ptr(q), C.byref(rs) if rs is not None else None, Hq, clip, sm_scale,
+                              _ptr(out), _ptr(lse), n_split, _ptr(ws), ws.numel(), flags, _stream()),
            "akvq_decode_step")
     cache.T_len += 1
     return out, lse
