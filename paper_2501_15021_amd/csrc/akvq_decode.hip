@@ -658,6 +658,11 @@ struct GqaTile {
 template <int G, bool PAIRS, int NW>
 __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
   constexpr int NG = kD / G;
+  // With two groups per row a group's product takes zeros in the other group's slots: in the query operands, which never
+  // change (half of 24 registers), or, in the kernel that also tells row pairs apart, in the code operands: it then stays
+  // at 168 registers, three wavefronts per SIMD, instead of 176 and two (64/8 heads, 80 sequences of 4572 rows, 4-bit
+  // text: 65.6 -> 61.6 us; 28/4 heads, 200 sequences: 85.7 -> 82.2; up to 512 workgroups, where two are enough, the same).
+  constexpr bool kMaskCodes = PAIRS && NG == 2;
   __shared__ __attribute__((aligned(16))) int q_int[8][kD];           // queries as integers, in units of their head's U
   __shared__ __attribute__((aligned(16))) uint16_t q_plain[16][kD];   // row 2h+term, natural order
   __shared__ __attribute__((aligned(16))) uint32_t a_lds[2][6][kWave];  // the two operand images of the code stream
@@ -727,9 +732,12 @@ __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
   // Fused decode step: the workgroups of the split that owns the row's tile first write the new row (the last wavefront
   // the K row, the one before it the V row); the barrier below orders those stores before this workgroup's loads of that
   // tile, and no other workgroup reads it.  A wavefront whose first two tiles include it asks for them after the barrier.
+  // (So does the four-wavefront kernel of tiered caches with two groups, everywhere: what it keeps across the staging
+  // otherwise overflows the scalar registers, and scratch memory is reserved for them; same time either way.)
   const bool appends = a.fused_append != 0 && split == a.append_split;  // uniform over the workgroup
-  const bool defer_loads = appends && a.t_win == a.T_len && n_mine > 0 &&
-                           (tile_at(0) == n_tiles - 1 || tile_at(1) == n_tiles - 1);
+  const bool defer_loads = (kMaskCodes && NW == kWaves && n_mine > 0) ||
+                           (appends && a.t_win == a.T_len && n_mine > 0 &&
+                            (tile_at(0) == n_tiles - 1 || tile_at(1) == n_tiles - 1));
   if (n_mine > 0 && !defer_loads) {
     load_tile(tile_at(0), tb[0]);
     load_tile(tile_at(1), tb[1]);
@@ -811,14 +819,14 @@ __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
     for (int i = 0; i < 6; ++i) a_lds[wave][i][lane] = img[i];
   }
   lds_barrier();
-  // with two groups per row each group's operand has zeros in the other group's slots (half of the registers)
-  u32x6 a_k[2][NG];
+  constexpr int kOperands = kMaskCodes ? 1 : NG;
+  u32x6 a_k[2][kOperands];
 #pragma unroll
   for (int img = 0; img < 2; ++img)
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < kOperands; ++g)
 #pragma unroll
-      for (int i = 0; i < 6; ++i) a_k[img][g][i] = (NG == 1 || i / 3 == g) ? a_lds[img][i][lane] : 0u;
+      for (int i = 0; i < 6; ++i) a_k[img][g][i] = (kOperands == 1 || i / 3 == g) ? a_lds[img][i][lane] : 0u;
 
   // this lane scores heads h0 = 2*qd and h0+1
   const int h0 = 2 * qd;
@@ -929,11 +937,19 @@ __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
     for (int tg = 0; tg < 2; ++tg) {
       f32x4 acc[NG];
       const u32x2 c0 = ex4(cur.kc[2 * tg]), c1 = ex4(cur.kc[2 * tg + 1]);
-      const u32x4 codes = {c0[0], c0[1], c1[0], c1[1]};
+      u32x4 codes[kMaskCodes ? 2 : 1];
+      if constexpr (kMaskCodes) {
+        codes[0] = (u32x4){c0[0], c0[1], 0u, 0u};
+        codes[1] = (u32x4){0u, 0u, c1[0], c1[1]};
+      } else {
+        codes[0] = (u32x4){c0[0], c0[1], c1[0], c1[1]};
+      }
 #pragma unroll
-      for (int g = 0; g < NG; ++g) acc[g] = mfma_f6f4(a_k[0][g], a_scale[0], codes, (f32x4){0.f, 0.f, 0.f, 0.f});
+      for (int g = 0; g < NG; ++g)
+        acc[g] = mfma_f6f4(a_k[0][g % kOperands], a_scale[0], codes[kMaskCodes ? g : 0], (f32x4){0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-      for (int g = 0; g < NG; ++g) acc[g] = mfma_f6f4(a_k[1][g], a_scale[1], codes, acc[g]);
+      for (int g = 0; g < NG; ++g)
+        acc[g] = mfma_f6f4(a_k[1][g % kOperands], a_scale[1], codes[kMaskCodes ? g : 0], acc[g]);
       // bit 15 of every meta word of a salient row is set: as a binary16 pattern the low half is then negative
       const bool off = meta_is_salient(km[tg][0]);
       ok[tg] = !off;
