@@ -53,7 +53,7 @@ typedef enum {
   AKVQ_ERR_INVALID_ARG = -1, /* null / misaligned pointer, non-positive size, Hq not a multiple of Hkv, W > T ... */
   AKVQ_ERR_UNSUPPORTED = -2, /* G not in {64,128}, Hq/Hkv > 8, W not a multiple of 16 ... */
   AKVQ_ERR_CAPACITY = -3,    /* T_len + n_new > T_cap, top_k > S_cap */
-  AKVQ_ERR_WORKSPACE = -4,   /* workspace smaller than akvq_*_workspace_bytes() */
+  AKVQ_ERR_WORKSPACE = -4,   /* workspace smaller than akvq_*_workspace_bytes() (selection accepts less, see there) */
   AKVQ_ERR_HIP = -5          /* a kernel launch failed; see akvq_last_hip_error() */
 } akvq_status;
 
@@ -118,7 +118,8 @@ int akvq_version(void);
  * (order: k_codes, v_codes, k_meta, v_meta, k_sal, v_sal, sal_idx, sal_cnt).  Returns AKVQ_OK or an error. */
 int akvq_cache_bytes(const akvq_cache *shape, size_t out_bytes[8]);
 
-/* Host helpers: device workspace each call needs (bytes; 0 on invalid arguments). */
+/* Host helpers: device workspace each call needs (bytes; 0 on invalid arguments).  Neither shrinks when B or T (n_split)
+ * grows with the other arguments kept, so a workspace sized for the largest batch and the longest prompt serves all. */
 size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W);
 size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split);
 /* Host helper: number of KV splits akvq_decode_attention uses when n_split <= 0 is passed. */
@@ -142,7 +143,10 @@ int akvq_decode_split_range(int n_tiles, int n_split, int split, int *begin, int
  *   mode AKVQ_MODE_PSA_SHARED: token-level pivots as in the paper (one pivot set per layer): the masses of a batch
  *       element's kv-heads are added (head order, fp32) and every kv-head gets the top_k positions of the sum.
  *   Output: c->sal_idx (ascending) and c->sal_cnt.  mass_out (device, [B][Hkv][T] fp32) is optional (PSA).
- *   workspace: device, akvq_select_workspace_bytes() bytes (PSA only; may be NULL for TSA).
+ *   workspace: device, akvq_select_workspace_bytes() bytes (PSA only; may be NULL for TSA).  Less is accepted down to
+ *   the row statistics of 2048-key chunks, B * Hq * ceil(T / 2048) * W * 8 bytes, beside the masses (B * Hkv * T * 4) and
+ *   their sums (B * T * 4), each rounded up to 256: it costs speed where a prompt would be scored in shorter chunks,
+ *   and, as the statistics are then added in another order, can change the last bits of the masses.
  */
 int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, const void *q_tail, int Hq,
                         const void *k, int T, int W, int top_k, float sm_scale, float *mass_out,

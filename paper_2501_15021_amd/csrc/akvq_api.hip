@@ -77,8 +77,9 @@ int akvq_cache_bytes(const akvq_cache *shape, size_t out_bytes[8]) {
 
 static int select_chunks(int T, int chunk) { return (int)(((long)T + chunk - 1) / chunk); }
 
-static size_t select_bytes(int B, int Hq, int Hkv, int T, int W, int chunk) {
-  const size_t stats = (size_t)B * Hq * select_chunks(T, chunk) * W * 2 * sizeof(float);
+// triples: (batch, head, chunk) combinations whose row statistics are kept
+static size_t select_bytes(size_t triples, int B, int Hkv, int T, int W) {
+  const size_t stats = triples * W * 2 * sizeof(float);
   const size_t mass = (size_t)B * Hkv * T * sizeof(float);
   const size_t shared = (size_t)B * T * sizeof(float);  // AKVQ_MODE_PSA_SHARED: the kv-heads' masses added
   return round_up(stats, 256) + round_up(mass, 256) + round_up(shared, 256);
@@ -86,7 +87,7 @@ static size_t select_bytes(int B, int Hq, int Hkv, int T, int W, int chunk) {
 
 size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || T <= 0 || W <= 0) return 0;
-  return select_bytes(B, Hq, Hkv, T, W, akvq::score_chunk(B, Hq, Hkv, T, W));
+  return select_bytes(akvq::score_max_triples(B, Hq, Hkv, T, W), B, Hkv, T, W);
 }
 
 size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
@@ -141,10 +142,11 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   if (top_k > c->S_cap) return AKVQ_ERR_CAPACITY;
   if (mass_out && !aligned16(mass_out)) return AKVQ_ERR_INVALID_ARG;
   if (!workspace || !aligned16(workspace)) return AKVQ_ERR_INVALID_ARG;
-  // a workspace too small for the finer chunks of a small problem still serves the coarse ones
+  // a workspace too small for the finer chunks of a small problem still serves the finest ones that fit
   int chunk = akvq::score_chunk(c->B, Hq, c->Hkv, T, W);
-  if (workspace_bytes < select_bytes(c->B, Hq, c->Hkv, T, W, chunk)) chunk = akvq::kScoreChunk;
-  if (workspace_bytes < select_bytes(c->B, Hq, c->Hkv, T, W, chunk)) return AKVQ_ERR_WORKSPACE;
+  auto needed = [&](int keys) { return select_bytes((size_t)c->B * Hq * select_chunks(T, keys), c->B, c->Hkv, T, W); };
+  while (chunk < akvq::kScoreChunk && workspace_bytes < needed(chunk)) chunk *= 2;
+  if (workspace_bytes < needed(chunk)) return AKVQ_ERR_WORKSPACE;
   a.q_tail = static_cast<const uint16_t *>(q_tail);
   a.k = static_cast<const uint16_t *>(k);
   a.Hq = Hq; a.W = W; a.top_k = top_k; a.sm_scale = sm_scale;

@@ -108,15 +108,28 @@ struct SelectArgs {
 // 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096 tokens 142 -> 35, 32768 tokens 160 -> 76.  Twice the
 // workgroups: 37.6 us at 32 heads, 4096 tokens, and 101 instead of 76 us at 32/8 heads, 4 prompts of 8192 tokens.
 constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64;
+inline bool score_fine_chunks(int Hq, int Hkv, int W) { return W == 64 && Hq >= Hkv && Hq / Hkv <= 8; }
+inline long score_want(int Hq, int Hkv) { return Hq == Hkv ? 512 : 256; }  // workgroups
 inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
-  const int R = Hkv > 0 ? Hq / Hkv : 0;
-  if (W != 64 || R < 1 || R > 8) return kScoreChunk;
-  const long want = R == 1 ? 512 : 256;
+  if (!score_fine_chunks(Hq, Hkv, W)) return kScoreChunk;
+  const long want = score_want(Hq, Hkv);
   int chunk = kScoreChunk;
   while (chunk > kScoreChunkMin && (long)B * Hkv * (((long)T + chunk - 1) / chunk) < want &&
          ((long)T + chunk / 2 - 1) / (chunk / 2) <= kScoreMaxFineChunks)
     chunk /= 2;
   return chunk;
+}
+// Most (batch, head, chunk) triples that score_chunk makes of any batch up to B and any prompt up to T: it grows with B
+// and T, which the triples of one shape do not (a longer prompt can have fewer, larger chunks).  A shape with chunks of c
+// keys has fewer than `want` workgroups at 2c, hence fewer than 2 * want at c, each of Hq / Hkv heads.
+inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
+  const size_t heads = (size_t)B * Hq, coarse = heads * (((size_t)T + kScoreChunk - 1) / kScoreChunk);
+  if (!score_fine_chunks(Hq, Hkv, W)) return coarse;
+  size_t fine = heads * (((size_t)T + kScoreChunkMin - 1) / kScoreChunkMin);
+  if (fine > heads * kScoreMaxFineChunks) fine = heads * kScoreMaxFineChunks;
+  const size_t filled = (size_t)(2 * score_want(Hq, Hkv)) * (Hq / Hkv);
+  if (fine > filled) fine = filled;
+  return fine > coarse ? fine : coarse;
 }
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream);

@@ -54,3 +54,33 @@ def test_chunk_sizes(B, Hq, Hkv, T):
         assert ((mass.double() - want).abs() <= 4e-5 * want + 1e-12).all(), nbytes
         order = torch.sort(mass, dim=-1, descending=True, stable=True).indices[..., :w.top_k].sort(-1).values
         assert torch.equal(c.sal_idx[..., :w.top_k].long(), order), nbytes
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,longest", [(1, 28, 4, 16384, 16400), (1, 4, 4, 4096, 40000), (3, 8, 4, 1000, 2500)])
+def test_workspace_of_a_longer_prompt(B, Hq, Hkv, T, longest):
+    """One workspace sized for the longest prompt scores a shorter one in the chunks of its own size (same bits), and each
+    smaller workspace down to that of 2048-key chunks in the finest ones that fit, up to the order of the sums."""
+    w = synth.small(f"longer{T}", B=B, Hq=Hq, Hkv=Hkv, T=T, G=128, n_text_head=5, n_text_tail=3, top_k=8, W=64)
+    d = synth.generate(w, seed=523, device="cuda")
+    want = _masses(d, w)
+    L = akvq.lib()
+    c = akvq.Cache(B, Hkv, 128, (T + 63) // 64 * 64, 64, fill=0)
+    s = c.struct()
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+
+    def masses(nbytes):
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+        mass = torch.full((B, Hkv, T), float("nan"), device="cuda")
+        st = L.akvq_select_salient(C.byref(s), akvq.MODE_PSA, None, d["q_tail"].data_ptr(), Hq, d["k"].data_ptr(), T, 64,
+                                   w.top_k, w.sm_scale, mass.data_ptr(), ws.data_ptr(), nbytes,
+                                   torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        torch.cuda.synchronize()
+        assert ((mass.double() - want).abs() <= 4e-5 * want + 1e-12).all(), nbytes
+        return mass
+
+    own = masses(L.akvq_select_workspace_bytes(B, Hq, Hkv, T, 64))
+    assert torch.equal(masses(L.akvq_select_workspace_bytes(B, Hq, Hkv, longest, 64)), own)
+    rest = up(B * Hkv * T * 4) + up(B * T * 4)
+    for chunk in (128, 256, 512, 1024, 2048):
+        masses(up(B * Hq * ((T + chunk - 1) // chunk) * 64 * 8) + rest)

@@ -82,6 +82,24 @@ def test_decode_split_partition(L):
     assert L.akvq_decode_split_range(4, 2, 0, None, C.byref(e)) == -1
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(32, 32), (28, 4), (4, 4), (8, 1), (64, 8), (9, 1)])
+@pytest.mark.parametrize("W", [16, 64])
+def test_select_workspace_of_the_largest_call_serves_all(L, Hq, Hkv, W):
+    """The size never shrinks when the batch or the prompt grows, and holds the statistics of at least one chunk per 2048
+    keys beside the masses."""
+    Ts = sorted({W, 640, *range(W, 70000, 997), *(2 ** n + d for n in range(7, 17) for d in (-1, 0, 1, 17))})
+    Bs = [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 31, 32, 33, 64, 65, 128, 200]
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    below = [0] * len(Ts)
+    for B in Bs:
+        sizes = [L.akvq_select_workspace_bytes(B, Hq, Hkv, T, W) for T in Ts]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), B
+        assert all(a <= b for a, b in zip(below, sizes)), B
+        for T, n in zip(Ts, sizes):
+            assert n >= up(B * Hq * ((T + 2047) // 2048) * W * 8) + up(B * Hkv * T * 4) + up(B * T * 4)
+        below = sizes
+
+
 def test_argument_errors_launch_nothing(L):
     """Null pointers are rejected on the host before any launch (safe without a GPU)."""
     from paper_2501_15021_amd.binding import akvq_cache
