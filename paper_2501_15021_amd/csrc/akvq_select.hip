@@ -755,6 +755,7 @@ constexpr int kTopkListMax = 256;     // selected positions ordered through LDS 
 constexpr int kTopkCandMax = 512;     // candidates the short cut ranks among themselves
 constexpr int kTopkWideFrom = 8192, kTopkWideRows = 512, kTopkWideThreads = 1024;  // see launch_topk
 constexpr int kTopkBatch = 8;         // keys a thread requests together
+constexpr int kTopkMaximaMax = 192;   // of the 256 maxima: beyond, the candidate bound is searched to its last bit
 // NT threads per workgroup (256, or 1024 for long rows: the passes over the keys are what takes the time there)
 template <bool STAGED, int NT>
 __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
@@ -804,16 +805,23 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
         for (int jj = 0; jj < NT / 256; ++jj) v = max(v, thread_max[lane + 64 * i + 256 * jj]);
         mx[i] = v;
       }
-      // Sixteen bits of it (the sign is 0: exponent and eight bits of the fraction) are enough: a bound that is lower by
-      // up to 2^-8 of itself lets a few more candidates through, and each bit is a step of a serial chain.
+      // Sixteen bits of it (the sign is 0: exponent and eight bits of the fraction) are mostly enough: a bound that is
+      // lower by up to 2^-8 of itself lets a few more candidates through, and each bit is a step of a serial chain.  Where
+      // the largest keys lie so close together that most of the 256 maxima reach that bound, the other bits are searched
+      // too: at three quarters of them, keys in any order give about 256 ln 4 = 355 candidates; much beyond that they
+      // overflow the list and end in the radix passes.
       uint32_t bound = 0u;
+      int n_at = 256;  // maxima that reach it
+      auto try_bit = [&](int bit) {
+        const uint32_t x = bound | (1u << bit);
+        const int n_ge = __popcll(__ballot(mx[0] >= x)) + __popcll(__ballot(mx[1] >= x)) + __popcll(__ballot(mx[2] >= x)) +
+                         __popcll(__ballot(mx[3] >= x));
+        if (n_ge >= k) { bound = x; n_at = n_ge; }
+      };
 #pragma unroll
-      for (int bit = 30; bit >= 15; --bit) {
-        const uint32_t cand = bound | (1u << bit);
-        const int n_ge = __popcll(__ballot(mx[0] >= cand)) + __popcll(__ballot(mx[1] >= cand)) +
-                         __popcll(__ballot(mx[2] >= cand)) + __popcll(__ballot(mx[3] >= cand));
-        if (n_ge >= k) bound = cand;
-      }
+      for (int bit = 30; bit >= 15; --bit) try_bit(bit);
+      if (__builtin_expect(n_at > kTopkMaximaMax, 0))
+        for (int bit = 14; bit >= 0; --bit) try_bit(bit);
       for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
         uint32_t bits[kTopkBatch];
 #pragma unroll

@@ -32,3 +32,20 @@ def test_topk_of_given_scores(T, Hkv, spread):
         assert (c.counts().cpu() == n).all()
         want = order[:n].sort().values.int()
         assert (c.sal_idx[0, :, :n].cpu() == want[None]).all(), (k, spread)
+
+
+@pytest.mark.parametrize("T,Hkv", [(640, 4), (8191, 2), (9000, 2), (20000, 1)])
+@pytest.mark.parametrize("gain", [0.0, 0.001, 0.003, 0.01, 0.03])
+def test_topk_of_near_flat_masses(T, Hkv, gain):
+    """Masses of nearly uniform attention: from all of the 256 maxima within the bound's sixteen bits to a part of them, so
+    that the bound is searched to its last bit or not.  Sets against the stable order of the call's own masses."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    k = torch.randn(1, Hkv, T, 128, generator=g, device="cuda").half()
+    q = (torch.randn(1, Hkv, 64, 128, generator=g, device="cuda") * gain).half()
+    c = akvq.Cache(1, Hkv, 128, (T + 63) // 64 * 64, 256, fill=0)
+    mass = torch.empty(1, Hkv, T, device="cuda")
+    for top_k in (1, 8, 64, 128):
+        akvq.select_salient(c, akvq.MODE_PSA, q_tail=q, k=k, top_k=top_k, sm_scale=128 ** -0.5, mass_out=mass)
+        order = torch.sort(mass, dim=-1, descending=True, stable=True).indices[..., :top_k].sort(-1).values
+        assert torch.equal(c.sal_idx[..., :top_k].long(), order), top_k
+        assert (c.counts() == top_k).all()
