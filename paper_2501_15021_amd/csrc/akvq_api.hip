@@ -97,11 +97,13 @@ size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
 
 int akvq_decode_default_splits(int B, int Hkv, int T_len) {
   if (B <= 0 || Hkv <= 0 || T_len <= 0) return 1;
-  const long units = (long)B * Hkv;            // one workgroup of four wavefronts per (unit, split)
+  // One workgroup per (unit, split): four wavefronts, or eight where the launch has at most one workgroup per CU.  The
+  // figures below were measured with four.
+  const long units = (long)B * Hkv;
   if (units >= 512) return 1;                  // already two workgroups per CU: finish in one kernel, no merge pass
   const int tiles = (T_len + 63) / 64;
   long want = (512 + units - 1) / units;       // two workgroups per CU; more splits only add merge work
-  long cap = tiles / 16 > 1 ? tiles / 16 : 1;  // keep at least four 64-token tiles per wavefront
+  long cap = tiles / 16 > 1 ? tiles / 16 : 1;  // keep at least 16 64-token tiles per workgroup
   if (want > cap) want = cap;
   if (want > 64) want = 64;
   if (want < 1) want = 1;

@@ -109,10 +109,14 @@ __device__ __forceinline__ uint32_t hi16(float f) { return __float_as_uint(f) >>
 // the two workgroups of a CU one ran ahead and the other then finished alone, at the latency of its own chain: with 28/4
 // heads, 32 sequences of 32768 tokens and 4 splits the workgroups ended between 46 and 68 us, now between 57 and 63 us.
 // A wavefront therefore lowers its priority when half, three quarters and seven eighths of its tiles are done: whoever is
-// behind goes first, and what is left of a lead is part of an eighth.  Only where the whole launch is resident at once
-// (launch_decode_stream): with several rounds of workgroups the ones that have just started would hold up the ones about
-// to make room (32 heads, 64 sequences of 8192 tokens: 202 -> 221 us), and a stream that waits for memory and not for
-// issue slots gains nothing (the one-head kernel, 16 sequences of 4096 tokens: 28.9 us either way).
+// behind goes first, and what is left of a lead is part of an eighth.  It looks every third tile and goes down one level at
+// a time, so a wavefront of few tiles skips the later marks (up to five tiles: all of them) and keeps the level it has
+// through the 16-bit rows and the merge.  Catching up on skipped marks and ending the stream at level 0 was no faster, and
+// up to 2 % slower (28/4 heads, 64 sequences of 16384 tokens, 64 tiles a wavefront: 75.1 -> 76.4 us; 12/2 heads, 100 of 8000
+// tokens, 31 tiles: 35.5 -> 36.4).  Only grouped-query launches that are resident at once (launch_decode_stream): with several
+// rounds of workgroups the ones that have just started would hold up the ones about to make room (32 heads, 64 sequences
+// of 8192 tokens: 202 -> 221 us), and a stream that waits for memory and not for issue slots gains nothing (the one-head
+// kernel, 16 sequences of 4096 tokens: 28.9 us either way; it has no such steps).
 struct StreamPace {
   int at, left;  // next tile count that lowers the priority; tiles behind it
   int level;
@@ -645,8 +649,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mha_kernel(DecodeArgs a) { dec
 
 // ------------------------------------------------------------------------------------------------
 // GQA (R = Hq/Hkv query heads share a KV head, 2 <= R <= 8; also valid for R = 1).  A tile is one cache block
-// (32 tokens, two token groups of 16).  Rows 2h+term of the A operand carry the two bfloat16 terms of head h,
-// so lane (n, q) receives heads 2q, 2q+1 of token n, and the same lanes own those heads' output rows.
+// (32 tokens, two token groups of 16).  Rows 2h and 2h+1 of an A operand belong to head h: for the code stream they carry
+// its query as base-32 digits of a 20-bit integer, for 16-bit rows and weights as two bfloat16 terms.  Lane (n, q) so
+// receives heads 2q, 2q+1 of token n, and the same lanes own those heads' output rows.
 // ------------------------------------------------------------------------------------------------
 template <int NG>
 struct GqaTile {
@@ -749,7 +754,9 @@ __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
   }
   // Queries, one head per wavefront at a time, two channels (lane, lane + 64) per lane.  sm_scale * log2(e) is folded in,
   // so the products already are base-2 logits.  For the 16-bit rows: two bfloat16 terms.  For the code stream: integers
-  // of up to 20 bits in units of a power of two U (|q| < 2^19 U), and their sums per group.
+  // of up to 20 bits in units of a power of two U (2^18 U <= largest |q| < 2^19 U), and their sums per group.  Every channel
+  // is off by at most U/2 <= 2^-19 of the largest one: as a vector the query is as exact as with 16 significant bits per
+  // channel (2^-17 of its norm), but a channel below 1/4 of the largest one carries less than it would then.
   const float sm2 = a.sm_scale * kLog2e;
 #pragma unroll
   for (int hi = 0; hi < 8 / NW; ++hi) {
@@ -1251,7 +1258,7 @@ static void launch_decode_stream(DecodeArgs a, hipStream_t stream) {
   // took 21.7 us instead of 18.7.)
   const long workgroups = (long)a.B * a.Hkv * a.n_split;
   const bool wide = workgroups <= kCus && decode_tiles_per_split((a.t_win + rows - 1) / rows, a.n_split) > kWaves;
-  a.paced = !wide && workgroups <= 2 * kCus;
+  a.paced = !mha && !wide && workgroups <= 2 * kCus;
   if (mha) {
     if (wide) hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWavesWide>), grid, dim3(64 * kWavesWide), 0, stream, a);
     else hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWaves>), grid, dim3(64 * kWaves), 0, stream, a);

@@ -52,7 +52,7 @@ struct DecodeArgs {
   // read 16-bit rows then.
   int fused_append;
   int append_split;
-  int paced;  // the whole launch is resident at once: wavefronts of a SIMD are kept in step (set by the launcher)
+  int paced;  // grouped-query launch, all of it resident at once: wavefronts of a SIMD are kept in step (set by the launcher)
   QuantArgs step;
   const uint16_t *rope_cos, *rope_sin;  // rotary tables for pre-RoPE queries (null: none), one row of 64 per batch element
   long long rope_stride;
