@@ -1,6 +1,7 @@
 """Decode attention at the borders of its launch shapes (eight wavefronts per workgroup up to 256 workgroups with more than
-four tiles each, wavefronts kept in step up to 512, neither beyond) and of the queries' fixed-point operands (heads of
-very different magnitude in one group, an all-zero head, every number of heads per KV head), against the oracle."""
+four tiles each; with several heads per KV head wavefronts are kept in step up to 512, and not beyond) and of the
+queries' fixed-point operands (heads of very different magnitude in one group, an all-zero head, every number of heads
+per KV head, one channel far above the others), against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -43,8 +44,8 @@ def _check(orc, B, Hkv, R, G, T, n_split, q_gain=None, seed=431):
     assert (np.abs(lse - lse_ref) <= bound).all(), float((np.abs(lse - lse_ref) / bound).max())
 
 
-# workgroups = B * Hkv * n_split: 256 / 257 (eight wavefronts or four), 512 / 514 (kept in step or not); tiles per split
-# around the four that eight wavefronts need
+# workgroups = B * Hkv * n_split: 256 / 257 (eight wavefronts or four), 512 / 514 (several heads per KV head: kept in step
+# or not); tiles per split around the four that eight wavefronts need
 @pytest.mark.parametrize("R,G", [(1, 128), (7, 64)])
 @pytest.mark.parametrize("B,Hkv,n_split,tiles", [(64, 4, 1, 5), (64, 4, 1, 4), (1, 257, 1, 5), (32, 4, 4, 9), (2, 257, 1, 5),
                                                  (2, 2, 1, 17), (2, 2, 3, 40)])
@@ -62,3 +63,38 @@ def test_query_magnitudes(orc, R, G):
 @pytest.mark.parametrize("G", [64, 128])
 def test_query_magnitudes_one_head(orc, G):
     _check(orc, 2, 4, 1, G, 300, 2, q_gain=[1.0, 0.0, 2.0 ** -14, 8.0])
+
+
+@pytest.mark.parametrize("R,G", [(1, 128), (1, 64), (2, 64), (7, 64), (8, 128)])
+@pytest.mark.parametrize("peak", [16.0, 256.0, 4096.0])
+def test_one_dominant_query_channel(orc, R, G, peak):
+    """Queries that arrive rotated with one channel far above the rest, against keys that are small there and large
+    elsewhere.  The code stream takes every channel as an integer of units U = 2^-19 (one head per KV head: 2^-20) times
+    the power of two above the largest channel, so a logit carries 128 roundings of at most U / 2 each times the stored
+    key's channel, however small the channels are that matter.  With one cached row the log-sum-exp is the logit."""
+    B, Hkv = 16, 4
+    rng = np.random.default_rng(int(peak) + R)
+    k = rng.standard_normal((B, Hkv, 1, 128)).astype(np.float16)
+    k[..., :3] *= np.float16(0.02)
+    k[..., 40] *= np.float16(8)
+    q = rng.standard_normal((B, Hkv * R, 128)).astype(np.float16)
+    q[..., 1] = peak
+    c = akvq.Cache(B, Hkv, G, 64, 64, fill=0)
+    akvq.quantize_append(c, torch.from_numpy(k).cuda(), torch.from_numpy(k).cuda(), 0.8, flags=akvq.K_PREROTATED)
+    scale = 128 ** -0.5
+    _, lse = akvq.decode_attention(c, torch.from_numpy(q).cuda(), scale, n_split=1, flags=akvq.Q_PREROTATED)
+    lse = lse.cpu().numpy()
+    worst = 0.0
+    for b in range(B):
+        for h in range(Hkv * R):
+            codes, s16, zero, _ = orc.quantize_row(k[b, h // R, 0], G, 0.8, rotate=False)
+            s, z = s16.view(np.float16).astype(np.float64).repeat(G), zero.astype(np.float64).repeat(G)
+            stored, q64 = s * (codes - z), q[b, h].astype(np.float64)
+            unit = 2.0 ** (-20 if R == 1 else -19) * 2.0 ** (np.floor(np.log2(np.abs(q64).max())) + 1)
+            # independent roundings, uniform over a unit: six standard deviations; sm_scale * log2(e) is folded into several
+            # heads' queries, whose power of two can then be twice as far from the largest channel
+            bound = 6 * (unit if R == 1 else 2 * unit) / 12 ** 0.5 * np.linalg.norm(stored)
+            # 32-bit sums of the code and the zero-point part, a few roundings each
+            bound += 8 * 2.0 ** -24 * (np.abs(q64) * s * (codes + np.abs(z))).sum()
+            worst = max(worst, abs(lse[b, h] / scale - q64 @ stored) / bound)
+    assert worst <= 1.0
