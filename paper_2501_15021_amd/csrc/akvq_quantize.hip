@@ -702,8 +702,12 @@ hipError_t launch_block_ranges(const QuantArgs &a, int B, int G, hipStream_t str
   // Recent window: only the blocks that hold the last win_len new rows write ring slots.  The blocks before them (the
   // bulk of a prompt) take the body without the ring stores: within the same launch if all its workgroups are resident
   // at once (four per CU), as a second launch would only add its latency (one prompt of 700 tokens, 32 heads, window 64:
-  // 11.6 -> 7.6 us; window 128 and tiers 13.8 -> 10.0); else by a launch of their own, without the window's 33 KB of LDS
-  // (16 prompts of 4096 tokens, window 128, 234 us against 286 in one launch; 64 of 300 tokens, 40 heads, 224 / 238).
+  // 11.6 -> 7.6 us; window 128 and tiers 13.8 -> 10.0); else by a launch of their own (16 prompts of 4096 tokens, window
+  // 128: 230 us, 290 in one launch; 64 of 300 tokens, 40 heads: 168 / 185).  What makes the large launch slower is the code
+  // of four bodies in one kernel, 43-59 KB against 19-26, and not the window's 33 KB of LDS: the plain kernel with as much
+  // LDS takes the same time (230.7), and four workgroups fit a CU either way.  The line is drawn on the safe side: 1152
+  // workgroups (2 prompts of 1000 tokens, 32 heads) take 15.1 us in two launches and 11.8 in one, 3328 (4 of 1500) 27.2
+  // and 24.3, 16896 (8 of 4096) 124 and 148.
   const int t_end = a.T_len + a.n_new;
   const int t_w0 = t_end - a.win_len > a.T_len ? t_end - a.win_len : a.T_len;
   QuantArgs w = a;
