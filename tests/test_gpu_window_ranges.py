@@ -25,8 +25,8 @@ def _append(k, v, W, before):
     return {n: getattr(c, n) for n in names}
 
 
-# (B, heads, rows, window, rows in the cache before): 1024 workgroups and just over; no block, one block and several in
-# front of the window; a window longer than the append; an odd start inside a block
+# (B, heads, rows, window, rows in the cache before): launches of up to 112 and of more than 1024 workgroups; no block, one
+# block and several in front of the window; a window longer than the append; an odd start inside a block
 @pytest.mark.parametrize("B,H,T,W,before", [(16, 8, 512, 64, 0), (16, 8, 545, 64, 0), (33, 8, 130, 64, 0), (3, 4, 63, 64, 0),
                                             (3, 4, 97, 64, 0), (2, 4, 700, 128, 33), (40, 8, 300, 128, 17)])
 def test_window_ranges(B, H, T, W, before):
@@ -40,3 +40,15 @@ def test_window_ranges(B, H, T, W, before):
         alone = _append(k[b:b + 1].contiguous(), v[b:b + 1].contiguous(), W, before)
         for n, t in alone.items():
             assert torch.equal(whole[n][b:b + 1], t), (n, b)
+
+
+# workgroups of the append as one launch (four blocks each, window blocks apart from the others, K and V): the most that one
+# launch takes, one group more, and the same with an odd start and a window that starts inside a block
+@pytest.mark.parametrize("B,H,T,W,before,groups", [(16, 8, 416, 64, 0, 1024), (16, 8, 448, 64, 0, 1024), (16, 8, 480, 64, 0, 1280),
+                                                   (64, 8, 60, 64, 33, 1024), (32, 8, 250, 64, 37, 1536), (32, 8, 150, 64, 37, 1024),
+                                                   (8, 16, 390, 128, 5, 1024), (8, 16, 500, 128, 5, 1280)])
+def test_at_the_largest_single_launch(B, H, T, W, before, groups):
+    first, end = before // 32, (before + T + 31) // 32
+    window_first = max(before + T - W, before) // 32
+    assert ((window_first - first + 3) // 4 + (end - window_first + 3) // 4) * 2 * B * H == groups
+    test_window_ranges(B, H, T, W, before)
