@@ -50,7 +50,7 @@ namespace {
 
 // Wavefronts per workgroup (template parameter NW).  Four when the launch has more than one workgroup per CU; eight when
 // it has one, where a wavefront walks its tiles at the latency of its own chain and the only thing that shortens the
-// call is fewer tiles per wavefront (see launch_decode_attention).
+// call is fewer tiles per wavefront (see launch_decode_stream).
 constexpr int kWaves = 4, kWavesWide = 8;
 constexpr int kCus = 256;
 
@@ -1183,9 +1183,9 @@ __global__ __launch_bounds__(64 * NW) void decode_gqa_kernel(DecodeArgs a) {
 // One workgroup per (batch, query head).  The launch is bound by memory latency, not by its few KB per head: wavefront w
 // takes splits w, w + 4, ... and requests everything it needs of BATCH of them at once (two channels per lane,
 // and the reference and sum of the split), none of it dependent on another load, so that up to 64 splits
-// cost one or two memory round trips.  With a loop over the splits and a wait in every round (12.3 us at 19 splits of 28
-// heads, one KB per split) the whole decode call of that shape took 28.9 us; it takes 19.3 us now.  With 4 splits of 896
-// heads the call went from 80.8 to 79.9 us, with 3 splits of 128 heads from 19.6 to 18.7 us.
+// cost one or two memory round trips.  Against a loop over the splits with a wait in every round (12.3 us at 19 splits of
+// 28 heads, half a KB per split) the whole decode call of that shape went from 28.9 to 19.3 us, with 4 splits of 896 heads
+// from 80.8 to 79.9 us, with 3 splits of 128 heads from 19.6 to 18.7 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int kCombineWaves = 4;
 template <int BATCH>  // splits of one wavefront requested together
