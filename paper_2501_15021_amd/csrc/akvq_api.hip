@@ -147,7 +147,7 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   // a workspace too small for the finer chunks of a small problem still serves the finest ones that fit
   int chunk = akvq::score_chunk(c->B, Hq, c->Hkv, T, W);
   auto needed = [&](int keys) { return select_bytes((size_t)c->B * Hq * select_chunks(T, keys), c->B, c->Hkv, T, W); };
-  while (chunk < akvq::kScoreChunk && workspace_bytes < needed(chunk)) chunk *= 2;
+  while (chunk < akvq::kScoreChunk && workspace_bytes < needed(chunk)) chunk += 64;
   if (workspace_bytes < needed(chunk)) return AKVQ_ERR_WORKSPACE;
   a.q_tail = static_cast<const uint16_t *>(q_tail);
   a.k = static_cast<const uint16_t *>(k);

@@ -100,34 +100,45 @@ struct SelectArgs {
   int skip_zero;
   float *mass_shared;        // token-level pivots: [B][T] sums of the kv-heads' masses (workspace), null: per-head lists
 };
-// Keys per scoring workgroup: kScoreChunk, or less where that would leave most of the chip idle (scoring windows of 64
-// rows only; the kernels for smaller windows have it built in).  Halved until there is a workgroup per CU, two with one
-// head per KV head (four wavefronts each instead of up to eighteen), but not below two blocks of keys, where the staging
-// of the rows would outweigh the scoring, and not beyond 64 chunks, whose statistics the second pass merges in four round
-// trips.  Selection with chunks of 2048 and with this rule, one prompt: 32 heads, 640 tokens 29.1 -> 18.7 us, 4096 tokens
-// 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096 tokens 142 -> 35, 32768 tokens 160 -> 76.  Twice the
-// workgroups: 37.6 us at 32 heads, 4096 tokens, and 101 instead of 76 us at 32/8 heads, 4 prompts of 8192 tokens.
-constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64;
+// Keys per scoring workgroup: kScoreChunk, or less where that leaves the chip idle (scoring windows of 64 rows only; the
+// kernels for smaller windows have it built in, and beyond two workgroups per CU there is nothing to fill).  The prompt is
+// cut into n chunks of equal length, for the n with the least time by this model: the workgroups go in rounds of one or
+// two per CU, each as long as its keys plus the staging of the rows (192 keys' worth); a round of two takes 1.5, 1.75 or
+// 2 times one of one, with one, two or three, and more heads per KV head (4 wavefronts a workgroup, 6 to 8, 10 to 18).
+// Equal lengths, because a chunk's number decides its die (workgroup id mod 8): with 2 chunks the long ones would all go
+// to four of the eight dies.  Not below two blocks of keys, nor beyond 64 chunks, whose statistics the second pass merges
+// in four round trips, nor beyond four workgroups per CU.
+// Over 1053 shapes (1 to 8 heads per KV head, 4 to 600 units, 258 to 32768 tokens) a selection takes 0.69 of its time with
+// chunks of 2048 on average, at most 1.04 (what two runs of one length differ), and 1.03 of the best length tried.  One
+// prompt: 32 heads, 640 tokens 29.1 -> 18.7 us, 4096 tokens 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096
+// tokens 142 -> 35, 32768 tokens 160 -> 76; 40 prompts of 1300 tokens, 28/4 heads, 100 -> 92, and 16 of 4907 142 -> 103,
+// where halving the chunk until every CU has a workgroup, whatever the rounds and lengths, makes 148 and 151.
+constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64, kScoreCus = 256;
 inline bool score_fine_chunks(int Hq, int Hkv, int W) { return W == 64 && Hq >= Hkv && Hq / Hkv <= 8; }
-inline long score_want(int Hq, int Hkv) { return Hq == Hkv ? 512 : 256; }  // workgroups
 inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
-  if (!score_fine_chunks(Hq, Hkv, W)) return kScoreChunk;
-  const long want = score_want(Hq, Hkv);
+  const long units = (long)B * Hkv, n_coarse = ((long)T + kScoreChunk - 1) / kScoreChunk;
+  if (!score_fine_chunks(Hq, Hkv, W) || units * n_coarse > 2 * kScoreCus) return kScoreChunk;
+  const int R = Hq / Hkv;
+  const long one = 4, two = R == 1 ? 6 : R <= 3 ? 7 : 8;  // quarters of a round's time: one workgroup per CU, two
   int chunk = kScoreChunk;
-  while (chunk > kScoreChunkMin && (long)B * Hkv * (((long)T + chunk - 1) / chunk) < want &&
-         ((long)T + chunk / 2 - 1) / (chunk / 2) <= kScoreMaxFineChunks)
-    chunk /= 2;
+  long best = 0;
+  for (long n = n_coarse; n == n_coarse || (n <= kScoreMaxFineChunks && units * n <= 4 * kScoreCus); ++n) {
+    const long keys = ((T + n - 1) / n + 63) / 64 * 64;
+    if (n > n_coarse && keys < kScoreChunkMin) break;
+    const long groups = units * ((T + keys - 1) / keys), rest = groups % (2 * kScoreCus);
+    const long time = (groups / (2 * kScoreCus) * two + (rest == 0 ? 0 : rest <= kScoreCus ? one : two)) * (keys + 192);
+    if (best == 0 || time < best) { best = time; chunk = (int)keys; }
+  }
   return chunk;
 }
 // Most (batch, head, chunk) triples that score_chunk makes of any batch up to B and any prompt up to T: it grows with B
-// and T, which the triples of one shape do not (a longer prompt can have fewer, larger chunks).  A shape with chunks of c
-// keys has fewer than `want` workgroups at 2c, hence fewer than 2 * want at c, each of Hq / Hkv heads.
+// and T, which the triples of one shape do not (a longer prompt can have fewer, larger chunks).
 inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
   const size_t heads = (size_t)B * Hq, coarse = heads * (((size_t)T + kScoreChunk - 1) / kScoreChunk);
   if (!score_fine_chunks(Hq, Hkv, W)) return coarse;
   size_t fine = heads * (((size_t)T + kScoreChunkMin - 1) / kScoreChunkMin);
   if (fine > heads * kScoreMaxFineChunks) fine = heads * kScoreMaxFineChunks;
-  const size_t filled = (size_t)(2 * score_want(Hq, Hkv)) * (Hq / Hkv);
+  const size_t filled = (size_t)(4 * kScoreCus) * (Hq / Hkv);  // four workgroups per CU, of Hq / Hkv heads each
   if (fine > filled) fine = filled;
   return fine > coarse ? fine : coarse;
 }

@@ -425,7 +425,7 @@ constexpr int kGqaBlockKeys = 16 * kGqaBlockGroups;               // 64
 constexpr int kGqaItems = kGqaBlockGroups * 4;                    // 1 KB pieces (four whole keys each) of a block
 constexpr int kGqaMaxHeads = 8;                                   // query heads per KV head
 constexpr int kGqaFeederItems = kGqaItems / 2;                    // MAXIT from this on: feeder wavefronts bring in the keys
-static_assert(kScoreChunkMin % kGqaBlockKeys == 0 && kScoreChunk % kScoreChunkMin == 0, "a chunk is a whole number of blocks");
+static_assert(kGqaBlockKeys == 64 && kScoreChunk % 64 == 0, "a chunk is a whole number of blocks: a multiple of 64 keys");
 static_assert(kGqaBlockGroups % 2 == 0, "the first pass walks a block two groups at a time");
 static_assert(kGqaItems % (2 * kGqaMaxHeads) == 0, "up to sixteen scoring wavefronts share a block's pieces evenly");
 

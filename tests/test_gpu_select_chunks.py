@@ -25,8 +25,8 @@ def _masses(d, w):
     return mass
 
 
-# (B, Hq, Hkv, T): chunks of 128 (last one with one key; exactly full; the tail rows across two and three chunks), 256,
-# 1024 and 2048 keys, one to eight query heads per KV head, the shortest context
+# (B, Hq, Hkv, T): one chunk up to 64 of them, of 64 to 2048 keys, the tail rows across one to three chunks, one to eight
+# query heads per KV head, the shortest context
 @pytest.mark.parametrize("B,Hq,Hkv,T", [(1, 4, 4, 64), (1, 4, 4, 129), (1, 4, 4, 256), (2, 8, 4, 385), (1, 14, 2, 2048 + 1),
                                         (1, 8, 1, 1000), (4, 32, 32, 1300), (2, 64, 64, 4100), (1, 7, 1, 9000),
                                         (1, 4, 2, 16500)])
@@ -84,3 +84,10 @@ def test_workspace_of_a_longer_prompt(B, Hq, Hkv, T, longest):
     rest = up(B * Hkv * T * 4) + up(B * T * 4)
     for chunk in (128, 256, 512, 1024, 2048):
         masses(up(B * Hq * ((T + chunk - 1) // chunk) * 64 * 8) + rest)
+
+
+# as many units as leave the last of two, three and four chunks short, or fill the CUs with one chunk each
+@pytest.mark.parametrize("B,Hq,Hkv,T", [(23, 32, 8, 258), (13, 32, 32, 734), (40, 28, 4, 1300), (43, 12, 6, 2049), (5, 64, 8, 3001),
+                                        (30, 12, 2, 2900), (3, 40, 5, 6000), (64, 8, 8, 640)])
+def test_equal_chunks(B, Hq, Hkv, T):
+    test_chunk_sizes(B, Hq, Hkv, T)
