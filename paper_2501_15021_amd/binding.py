@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libakvq.so (C ABI in include/akvq.h).
+"""Thin binding of libakvq.so (C ABI in include/akvq.h): ctypes, and for the two decode calls the native module
+_akvq_torch (csrc/akvq_torch.cpp), which marshals the same arguments.
 
 Argument marshalling only: torch supplies device memory and the current stream; every step of the
 method runs inside the library's HIP kernels.  There is no fallback: if the library is missing or a
@@ -122,6 +123,22 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The native half of the binding, built with the library (never built here, no fallback)."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _akvq_torch
+        except ImportError as e:
+            raise AkvqError(f"_akvq_torch is missing ({e}): run `python -m paper_2501_15021_amd.build` first") from e
+        _native = _akvq_torch
+    return _native
+
+
 def _rope_struct(rope, B: int, n: int):
     """(cos, sin) fp16 tensors [n, 64] (one table for the batch) or [B, n, 64] -> akvq_rope (tensors stay referenced)."""
     cos, sin = rope
@@ -138,8 +155,8 @@ def _check(status: int, what: str):
 
 
 # Pointers and streams are handed to ctypes as plain integers (the argtypes convert them), and the stream is read as the
-# raw handle (0.3 us; the Stream object of torch.cuda.current_stream() takes 2.7): a small decode step is bound by this
-# module and not by the GPU.  One sequence of 640 tokens, 32 heads: 14.6 -> 11.6 us a step, 6.5 of them GPU time.
+# raw handle (0.3 us; the Stream object of torch.cuda.current_stream() takes 2.7).  The two decode calls go through
+# native() instead: a small step was bound by this module and not by the GPU.
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -308,33 +325,11 @@ def decode_attention(cache: Cache, q: torch.Tensor, sm_scale: float, n_split: in
                      out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None, rope=None):
     """akvq_decode_attention: returns (out [B,Hq,128] fp32, lse [B,Hq] fp32).
     rope = (cos, sin) [1, 64] or [B, 1, 64]: q holds pre-RoPE queries (akvq_decode_attention_rope)."""
-    assert q.dtype == torch.float16 and q.is_contiguous()
-    B, Hq, _ = q.shape
-    if n_split <= 0:
-        n_split = lib().akvq_decode_default_splits(cache.B, cache.Hkv, cache.T_len)
-    ws = cache.workspace("decode", lib().akvq_decode_workspace_bytes(B, Hq, n_split))
-    out_dtype = torch.float16 if flags & OUT_FP16 else torch.float32
-    if out is None:
-        out = torch.empty(B, Hq, D, dtype=out_dtype, device=q.device)
-    assert out.dtype == out_dtype and out.is_contiguous()
-    if lse is None:
-        lse = torch.empty(B, Hq, dtype=torch.float32, device=q.device)
-    c = cache.struct()
-    if rope is not None:
-        win = cache.window_struct()
-        rs = _rope_struct(rope, B, 1)
-        _check(lib().akvq_decode_attention_rope(C.byref(c), _ptr(cache.fine_mask), C.byref(win) if win else None,
-                                                _ptr(q), C.byref(rs), Hq, sm_scale, _ptr(out), _ptr(lse), n_split,
-                                                _ptr(ws), ws.numel(), flags, _stream()), "akvq_decode_attention_rope")
-        return out, lse
-    if cache.fine_mask is not None or cache.W:
-        win = cache.window_struct()
-        _check(lib().akvq_decode_attention_tiered(C.byref(c), _ptr(cache.fine_mask), C.byref(win) if win else None,
-                                                  _ptr(q), Hq, sm_scale, _ptr(out), _ptr(lse), n_split, _ptr(ws),
-                                                  ws.numel(), flags, _stream()), "akvq_decode_attention_tiered")
-        return out, lse
-    _check(lib().akvq_decode_attention(C.byref(c), _ptr(q), Hq, sm_scale, _ptr(out), _ptr(lse), n_split, _ptr(ws),
-                                       ws.numel(), flags, _stream()), "akvq_decode_attention")
+    cos, sin = rope if rope is not None else (None, None)
+    st, out, lse = (_native or native()).decode_attention(cache, q, sm_scale, n_split, flags, out, lse, cos, sin)
+    if st:
+        _check(st, "akvq_decode_attention_rope" if rope is not None else
+               "akvq_decode_attention_tiered" if cache.fine_mask is not None or cache.W else "akvq_decode_attention")
     return out, lse
 
 
@@ -356,24 +351,10 @@ def decode_step(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, q: torch
                 lse: Optional[torch.Tensor] = None, rope=None):
     """akvq_decode_step: append one row per (batch, kv-head) and run decode attention over the cache including it, in
     one launch; advances cache.T_len.  Returns (out, lse)."""
-    fp16, L = torch.float16, lib()
-    assert k_new.dtype is fp16 and v_new.dtype is fp16 and q.dtype is fp16
-    assert k_new.is_contiguous() and v_new.is_contiguous() and q.is_contiguous()
-    assert k_new.shape == (cache.B, cache.Hkv, 1, D) and k_new.shape == v_new.shape
-    B, Hq, _ = q.shape
-    if n_split <= 0:
-        n_split = L.akvq_decode_default_splits(cache.B, cache.Hkv, cache.T_len + 1)
-    ws = cache.workspace("decode", L.akvq_decode_workspace_bytes(B, Hq, n_split))
-    if out is None:
-        out = torch.empty(B, Hq, D, dtype=torch.float32, device=q.device)
-    if lse is None:
-        lse = torch.empty(B, Hq, dtype=torch.float32, device=q.device)
-    c = cache.struct()
-    win = cache.window_struct()
-    rs = _rope_struct(rope, B, 1) if rope is not None else None
-    _check(L.akvq_decode_step(C.byref(c), _ptr(cache.fine_mask), C.byref(win) if win else None, _ptr(k_new),
-                              _ptr(v_new), _ptr(q), C.byref(rs) if rs is not None else None, Hq, clip, sm_scale,
-                              _ptr(out), _ptr(lse), n_split, _ptr(ws), ws.numel(), flags, _stream()),
-           "akvq_decode_step")
+    cos, sin = rope if rope is not None else (None, None)
+    st, out, lse = (_native or native()).decode_step(cache, k_new, v_new, q, clip, sm_scale, n_split, flags, out, lse, cos,
+                                                     sin)
+    if st:
+        _check(st, "akvq_decode_step")
     cache.T_len += 1
     return out, lse

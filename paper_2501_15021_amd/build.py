@@ -1,4 +1,4 @@
-"""Build libakvq.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Build libakvq.so (hand-written HIP for gfx950) in-tree with hipcc, and the Python side of its decode calls with g++."""
 from __future__ import annotations
 
 import os
@@ -14,6 +14,25 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-mfma-vgpr-form",   # keep MFMA accumulators in VGPRs: no AGPR<->VGPR copies around VALU use
          "-Wall", "-Wno-unused-function"]
+NATIVE = os.path.join(HERE, "_akvq_torch.so")
+
+
+def build_native() -> str:
+    """Compile _akvq_torch.so (host code only) against libakvq.so and the installed torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{p}" for p in cpp_extension.include_paths()], "-isystem/opt/rocm/include",
+           "-I" + sysconfig.get_paths()["include"], "-Wall", os.path.join(CSRC, "akvq_torch.cpp"), "-o", NATIVE,
+           "-L" + lib_dir, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"]
+    subprocess.run(cmd, check=True)
+    return NATIVE
 
 
 def build(verbose: bool = False) -> str:
@@ -36,6 +55,7 @@ def build(verbose: bool = False) -> str:
             print(out)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    build_native()
     return LIB
 
 
