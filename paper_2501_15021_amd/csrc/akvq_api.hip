@@ -97,11 +97,24 @@ size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
 
 int akvq_decode_default_splits(int B, int Hkv, int T_len) {
   if (B <= 0 || Hkv <= 0 || T_len <= 0) return 1;
-  // One workgroup per (unit, split): four wavefronts, or eight where the launch has at most one workgroup per CU.  The
-  // figures below were measured with four.
   const long units = (long)B * Hkv;
   if (units >= 512) return 1;                  // already two workgroups per CU: finish in one kernel, no merge pass
   const int tiles = (T_len + 63) / 64;
+  if (units <= 64) {
+    // Few units: one workgroup per CU, of eight wavefronts, and one merge.  From 1024 rows on (below, the merge launch costs
+    // what the split gains: 1 x 700 rows, 28/4 heads, 9.0 us in 1, 4 or 8 splits; 640 rows, 32 heads, 6.7 in 1, 7.7 in 8),
+    // two tiles a workgroup at least, and up to 32 splits: what the merge reads in one round trip (64 where 512 tiles and
+    // more make the streams longer than a second one).  A step of one sequence, us, before (at least 16 tiles per
+    // workgroup, so 19 of them per unit) and now: 28/4 heads, 20011 rows with window and rotary embedding, 16.0 -> 12.7;
+    // 2100 rows 13.7 -> 10.3; 12000 rows 14.0 -> 10.9; 12/2 heads, 4000 rows 14.3 -> 10.2; 32 heads, 2500 rows 10.8 -> 8.8,
+    // 8000 rows 11.9 -> 11.4; 16 x 2000 rows, 28/4 heads, 14.4 -> 13.1.  Over 33 shapes the least time of any split count
+    // is on average 1 % lower, at most 5 %.
+    if (T_len < 1024) return 1;
+    long n = 256 / units;
+    if (n > 32) n = tiles >= 512 && n >= 64 ? 64 : 32;
+    return (int)(n < tiles / 2 ? n : tiles / 2);
+  }
+  // Workgroups of four wavefronts mostly; the figures below were measured with them.
   long want = (512 + units - 1) / units;       // two workgroups per CU; more splits only add merge work
   long cap = tiles / 16 > 1 ? tiles / 16 : 1;  // keep at least 16 64-token tiles per workgroup
   if (want > cap) want = cap;

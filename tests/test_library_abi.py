@@ -205,3 +205,18 @@ def test_every_error_code_of_every_entry_point(L):
     assert sr(P + 4, 64, P, 0, None) == INVALID and sr(P, 64, None, 1, None) == INVALID
     for code in (0, -1, -2, -3, -4, -5):
         assert len(L.akvq_strerror(code)) > 0
+
+
+@pytest.mark.parametrize("B,Hkv", [(1, 1), (1, 2), (3, 2), (1, 32), (1, 40), (2, 32), (3, 32), (4, 32), (32, 4), (16, 32), (64, 32)])
+def test_default_splits(L, B, Hkv):
+    """One workgroup per CU at most with up to 64 units, at least two 64-row tiles each, none below 1024 rows; a workspace
+    sized for the longest context serves every shorter one."""
+    units, last = B * Hkv, 1
+    for T in [1, 640, 1023, 1024, 1025, 1100, 2048, 3001, 8000, 20011, 32767, 32768, 34821, 200000]:
+        n = L.akvq_decode_default_splits(B, Hkv, T)
+        assert 1 <= n <= 64 and last <= n
+        if units <= 64:
+            assert units * n <= 256 and n <= max(1, (T + 63) // 64 // 2) and (T >= 1024 or n == 1)
+        if units >= 512:
+            assert n == 1
+        last = n
