@@ -532,39 +532,59 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
     }
   }
 
-  // ================= bfloat16 rows: units of 64 slots dealt to splits, then to wavefronts =========
+  // ================= bfloat16 rows: units of 32 slots =================
   // Used twice: the salient overlay (slot = rank in the salient list) and the recent-window rings (slot = row mod W).
-  auto bf16_units = [&](const uint16_t *ks_base, const uint16_t *vs_base, int cnt, auto &&row_ok) {
-    const int n_units = (cnt + 63) / 64;
-    // fused decode step: the 16-bit rows (one of which may be the new row) are read by the appending split only
-    // (dealt from the last wavefront on: when the tiles do not divide evenly, the last ones have one tile less)
-    const int unit_step = a.fused_append ? NW : NW * a.n_split;
-    const int unit_first = a.fused_append ? (appends ? NW - 1 - wave : n_units) : split + (NW - 1 - wave) * a.n_split;
-    for (int unit = unit_first; unit < n_units; unit += unit_step) {
-      const int s_lane = unit * 64 + lane;
-      // only the token groups (16 slots) and blocks (32 slots) that hold rows are touched; the first block of value
-      // rows and the row's validity are requested together with the key rows so that the phase costs one round trip
-      const int n_grp = min(4, (cnt - unit * 64 + 15) >> 4), n_blk = min(2, (cnt - unit * 64 + 31) >> 5);
+  // All of a unit is requested at once: key rows, value rows and the rows' validity are one memory round trip.  (Units of
+  // 64 rows, whose four token groups and second block of values each waited for the one before, left two of four
+  // wavefronts of the appending workgroup without rows of a window of 128: a step of 4 x 3001 rows, 32 heads, 4-bit text,
+  // 17.6 us, of which the window cost 3.6; now 15.5.)
+  // (The kernel for plain caches of one group fits four wavefronts per SIMD, which takes asking for the second token group
+  // after the first.)
+  constexpr bool kBothGroups = PAIRS || NG == 2 || NW == kWavesWide;
+  auto bf16_units = [&](const uint16_t *ks_base, const uint16_t *vs_base, int cnt, const RowUnits units, auto &&row_ok) {
+    for (int i = units.first; i < units.limit; i += units.step) {
+      const int unit = units.unit(i), s_lane = unit * kRowUnit + lane;
+      const int n_grp = min(2, (cnt - unit * kRowUnit + 15) >> 4);  // token groups (16 slots) that hold rows
       const bool row_valid = row_ok(s_lane);  // fetched whatever cnt says (clamped address): no load behind a branch
-      const bool lane_ok = (s_lane < cnt) & row_valid;
-      u32x4 vb0[8];
+      const bool ok = (lane < kRowUnit) & (s_lane < cnt) & row_valid;
+      // (scalar bases and 32-bit lane offsets, as for the code stream)
+      u32x4 vb[8];
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb)
-        vb0[nb] = *reinterpret_cast<const u32x4 *>(vs_base + (size_t)(unit * 2) * 4096 + nb * 512 + (16 * qd + mrow) * 8);
+      for (int half_v = 0; half_v < 2; ++half_v) {
+        gptr_u32 v_unit = as_global(reinterpret_cast<const uint32_t *>(vs_base)) + (size_t)unit * 2048 + half_v * 1024;
+        keep_scalar(v_unit);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) vb[4 * half_v + nb] = *(const AKVQ_GLOBAL u32x4 *)(v_unit + nb * 256 + lane_code);
+      }
+      auto request_group = [&](int g, bf16x8 (&kb)[4]) {
+        gptr_u32 k_group = as_global(reinterpret_cast<const uint32_t *>(ks_base)) + (size_t)unit * 2048 + g * 1024;
+        keep_scalar(k_group);
+        const uint32_t lane_row = (uint32_t)(mrow * (kD / 2) + 4 * qd);
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) kb[kc] = __builtin_bit_cast(bf16x8, *(const AKVQ_GLOBAL u32x4 *)(k_group + 16 * kc + lane_row));
+      };
       f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int g = 0; g < n_grp; ++g) {  // one token group at a time keeps the register footprint of this phase small
+      auto score_group = [&](int g, const bf16x8 (&kb)[4]) {
         const int term = mrow - 4 * g;
         const uint16_t *ap = &q_plain[(term >= 0 && term < 3) ? term : 3][8 * qd];
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-          const bf16x8 kb = *reinterpret_cast<const bf16x8 *>(
-              ks_base + (size_t)(unit * 64 + 16 * g + mrow) * kD + 32 * kc + 8 * qd);
-          acc = mfma_bf16(*reinterpret_cast<const bf16x8 *>(ap + 32 * kc), kb, acc);
+        for (int kc = 0; kc < 4; ++kc) acc = mfma_bf16(*reinterpret_cast<const bf16x8 *>(ap + 32 * kc), kb[kc], acc);
+      };
+      if constexpr (kBothGroups) {
+        bf16x8 kb[2][4];
+        request_group(0, kb[0]);
+        if (n_grp > 1) request_group(1, kb[1]);
+        score_group(0, kb[0]);
+        if (n_grp > 1) score_group(1, kb[1]);
+      } else {
+#pragma unroll 1
+        for (int g = 0; g < n_grp; ++g) {
+          bf16x8 kb[4];
+          request_group(g, kb);
+          score_group(g, kb);
         }
       }
       const float score = sm2 * (acc[0] + acc[1] + acc[2]);
-      const bool ok = lane_ok;
       float p;
       if (!softmax_step(score, ok, true, p)) continue;
       {
@@ -577,41 +597,36 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
         w_lds[blk_of_lane][0][2][slot] = (uint16_t)f32_to_bf16_rne((w - hif) - lof);
       }
       wave_lds_sync();
+      const uint16_t *src = mrow < 3 ? &w_lds[0][0][mrow][8 * qd] : zero16;
+      const bf16x8 a_v = *reinterpret_cast<const bf16x8 *>(src);
+      // which of this lane's 8 K-slots (pair i, half) are real rows: mask the others (unwritten memory)
+      uint32_t keep[4];
 #pragma unroll
-      for (int b2 = 0; b2 < 2; ++b2) {
-        if (b2 >= n_blk) break;
-        const uint16_t *src = mrow < 3 ? &w_lds[b2][0][mrow][8 * qd] : zero16;
-        const bf16x8 a_v = *reinterpret_cast<const bf16x8 *>(src);
-        // which of this lane's 8 K-slots (pair i, half) are real rows: mask the others (unwritten memory)
-        uint32_t keep[4];
+      for (int e = 0; e < 4; ++e) {
+        const int s0 = unit * kRowUnit + 4 * qd + e;  // half 0; half 1 is 16 slots further
+        keep[e] = (s0 < cnt ? 0x0000FFFFu : 0u) | (s0 + 16 < cnt ? 0xFFFF0000u : 0u);
+      }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int s0 = unit * 64 + 32 * b2 + 4 * qd + i;  // half 0; half 1 is 16 slots further
-          keep[i] = (s0 < cnt ? 0x0000FFFFu : 0u) | (s0 + 16 < cnt ? 0xFFFF0000u : 0u);
-        }
+      for (int nb = 0; nb < 8; ++nb) {
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) {
-          u32x4 vb = vb0[nb];
-          if (b2 == 1)
-            vb = *reinterpret_cast<const u32x4 *>(vs_base + (size_t)(unit * 2 + 1) * 4096 + nb * 512 + (16 * qd + mrow) * 8);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) vb[i] &= keep[i];
-          acc_o[nb] = mfma_bf16(a_v, __builtin_bit_cast(bf16x8, vb), acc_o[nb]);
-        }
+        for (int e = 0; e < 4; ++e) vb[nb][e] &= keep[e];
+        acc_o[nb] = mfma_bf16(a_v, __builtin_bit_cast(bf16x8, vb[nb]), acc_o[nb]);
       }
       wave_lds_sync();
     }
   };
+  const int cnt_sal = min(max(sal_cnt_early, 0), a.S_cap);
   {
-    const int cnt = min(max(sal_cnt_early, 0), a.S_cap);
     const int32_t *sidx = a.sal_idx + (size_t)bh * a.S_cap;
-    bf16_units(a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, cnt,
+    bf16_units(a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, cnt_sal,
+               salient_units<NW>(a, cnt_sal, split, wave, appends),
                [&](int s) { return sidx[min(s, a.S_cap - 1)] < a.t_win; });  // rows in the window are read there
   }
   if (a.win_len > 0) {
     // slot s holds the row of [t_win, T_len) congruent to s mod W; fine halves and padding rows carry no token
     const int W = a.win_len;
-    bf16_units(a.k_win + (size_t)bh * W * kD, a.v_win + (size_t)bh * W * kD, W, [&](int s) {
+    bf16_units(a.k_win + (size_t)bh * W * kD, a.v_win + (size_t)bh * W * kD, W,
+               window_units<NW>(a, cnt_sal, split, wave, appends), [&](int s) {
       int d = (a.T_len - 1 - s) % W;
       d = d < 0 ? d + W : d;
       const int t = a.T_len - 1 - d;
@@ -645,7 +660,7 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
 }
 
 template <int G, bool PAIRS, int NW>
-__global__ __launch_bounds__(64 * NW) void decode_mha_kernel(DecodeArgs a) { decode_mha_body<G, PAIRS, NW>(a); }
+__global__ __launch_bounds__(64 * NW, !PAIRS && G == 128 && NW == kWaves ? 4 : 1) void decode_mha_kernel(DecodeArgs a) { decode_mha_body<G, PAIRS, NW>(a); }
 
 // ------------------------------------------------------------------------------------------------
 // GQA (R = Hq/Hkv query heads share a KV head, 2 <= R <= 8; also valid for R = 1).  A tile is one cache block

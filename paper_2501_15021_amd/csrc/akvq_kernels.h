@@ -76,6 +76,36 @@ __host__ __device__ inline int decode_last_tile_split(int n_tiles, int n_split) 
   if (n_tiles <= 0) return 0;
   return (n_tiles - 1) / decode_tiles_per_split(n_tiles, n_split);
 }
+// How the units of 32 16-bit rows are dealt in the one-head kernel: index i of a wavefront runs from first in steps of step while it is below
+// limit, and stands for unit(i).  From the last wavefront on (when the tiles do not divide evenly, the last ones have one
+// tile less), to the splits before the wavefronts.
+// In a fused decode step the unit of the new row is read by the workgroups that write it, as the salient rows are (the new
+// one may be among them); the other units of the recent window go to every split.  With one split there is nothing to
+// deal, and both calls take the rows in the same order.
+struct RowUnits {
+  int first, step, limit, special;  // special: the unit that negative indices stand for; no other index does
+  __host__ __device__ inline int unit(int i) const { return i < 0 ? special : i + (i >= special ? 1 : 0); }
+};
+constexpr int kRowUnit = 32;
+template <int NW>
+__host__ __device__ inline RowUnits salient_units(const DecodeArgs &a, int cnt, int split, int wave, bool appends) {
+  const int n = (cnt + kRowUnit - 1) / kRowUnit, back = NW - 1 - wave;
+  if (a.fused_append) return {back, NW, appends ? n : 0, n};
+  return {split + back * a.n_split, NW * a.n_split, n, n};
+}
+template <int NW>
+__host__ __device__ inline RowUnits window_units(const DecodeArgs &a, int cnt_salient, int split, int wave, bool appends) {
+  const int n = a.win_len / kRowUnit, back = NW - 1 - wave, step = NW * a.n_split;
+  if (a.fused_append && a.n_split > 1) {
+    // the appending workgroup's last wavefront has the first salient rows, the one before it the new row
+    const int p = (back + (appends ? NW - 2 : 0)) % NW;
+    const int first = split + p * a.n_split;
+    return {appends && wave == NW - 2 ? first - step : first, step, n - 1, ((a.T_len - 1) % a.win_len) / kRowUnit};
+  }
+  // behind the salient units
+  const int first = split + back * a.n_split - (cnt_salient + kRowUnit - 1) / kRowUnit % step;
+  return {first < 0 ? first + step : first, step, n, n};
+}
 constexpr int kMhaTileRows = 64, kGqaTileRows = 32;  // rows per code-stream tile of the two decode kernels
 hipError_t launch_decode_attention(const DecodeArgs &a, int G, hipStream_t stream);
 // Device address, on the current device, of the library's fixed scratch array for split-KV partials (no allocation).
