@@ -565,12 +565,11 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(QuantArgs a) {
 // lines wherever they come from, are left to the block kernel: 8 prompts of 4001 tokens, 1121 of them text, 32 heads:
 // block kernel 134.7 -> 147.5 us, this pass 52.5 -> 28.7 us, the call 181.2 -> 168.9 us.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void overlay_rows_kernel(QuantArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
+__device__ __forceinline__ void overlay_rows_body(const QuantArgs &a, int group, uint32_t (*vtile_lds)[2048]) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int bh = blockIdx.y;
-  const int s0 = (blockIdx.x * 4 + wave) * kTokBlock;
+  const int s0 = (group * 4 + wave) * kTokBlock;
   const int cnt = min(max(a.sal_cnt[bh], 0), a.S_cap);
   if (s0 >= cnt) return;  // whole wavefront leaves; no block-wide barrier is used below
   const int r = lane >> 2, j = lane & 3;
@@ -640,6 +639,23 @@ __global__ __launch_bounds__(256) void overlay_rows_kernel(QuantArgs a) {
         *reinterpret_cast<const u32x4 *>(vtile_lds[wave] + 256 * x + 4 * lane);
 }
 
+__global__ __launch_bounds__(256) void overlay_rows_kernel(QuantArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
+  overlay_rows_body(a, blockIdx.x, vtile_lds);
+}
+// ... or in the launch of the blocks, half of it beside a unit's K blocks and half beside its V blocks: the pass is bound by
+// memory and the blocks by vector issue.  8 prompts of 4001 tokens, 1121 of them text, 32 heads: 169.2 -> 146.9 us the call,
+// 5 of them the selection; block kernel and pass one after the other took 141 + 27.
+template <int G, bool ROPE>
+__global__ __launch_bounds__(256) void quantize_append_overlay_kernel(QuantArgs a) {
+  __shared__ int slot_of_lds[4][kTokBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
+  const int groups = (a.n_blk + 3) / 4, group = blockIdx.x;
+  if (group >= groups) overlay_rows_body(a, 2 * (group - groups) + blockIdx.z, vtile_lds);
+  else if (blockIdx.z == 0) quantize_append_body<G, false, false, ROPE, 0>(a, group, a.first_blk, a.n_blk, slot_of_lds, nullptr);
+  else quantize_append_body<G, false, false, ROPE, 1>(a, group, a.first_blk, a.n_blk, slot_of_lds, nullptr);
+}
+
 template <int G>
 __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t code_lds[kD];
@@ -685,9 +701,19 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
   if (a.S_cap > 64 && a.row_tier == nullptr) {
     QuantArgs blocks = a;
     blocks.skip_overlay = 1;
+    const int overlay_groups = (a.S_cap / kTokBlock + 3) / 4;
+    if (a.win_len <= 0) {
+      const dim3 grid((a.n_blk + 3) / 4 + (overlay_groups + 1) / 2, B * a.Hkv, 2), block(256);
+      const bool rope = a.rope_cos != nullptr;
+#define AKVQ_LAUNCH_O(GG, RR) hipLaunchKernelGGL((quantize_append_overlay_kernel<GG, RR>), grid, block, 0, stream, blocks)
+      if (G == 128) { if (rope) AKVQ_LAUNCH_O(128, true); else AKVQ_LAUNCH_O(128, false); }
+      else { if (rope) AKVQ_LAUNCH_O(64, true); else AKVQ_LAUNCH_O(64, false); }
+#undef AKVQ_LAUNCH_O
+      return hipGetLastError();
+    }
     hipError_t e = launch_block_ranges(blocks, B, G, stream);
     if (e != hipSuccess) return e;
-    const dim3 grid((a.S_cap / kTokBlock + 3) / 4, B * a.Hkv), block(256);
+    const dim3 grid(overlay_groups, B * a.Hkv), block(256);
     hipLaunchKernelGGL(overlay_rows_kernel, grid, block, 0, stream, a);
     return hipGetLastError();
   }
