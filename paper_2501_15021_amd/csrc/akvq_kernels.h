@@ -172,6 +172,11 @@ inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
   if (fine > filled) fine = filled;
   return fine > coarse ? fine : coarse;
 }
+// Prompts whose selection is one launch (see psa_small_kernel).
+constexpr int kSmallKeys = 768;
+inline bool score_small(int B, int Hq, int Hkv, int T, int W, float sm_scale) {
+  return W == 64 && Hq == Hkv && T <= kSmallKeys && sm_scale > 0.0f;
+}
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_massive(const SelectArgs &a, hipStream_t stream);

@@ -757,9 +757,9 @@ constexpr int kTopkWideFrom = 8192, kTopkWideRows = 512, kTopkWideThreads = 1024
 constexpr int kTopkBatch = 8;         // keys a thread requests together
 constexpr int kTopkMaximaMax = 192;   // of the 256 maxima: beyond, the candidate bound is searched to its last bit
 // NT threads per workgroup (256, or 1024 for long rows: the passes over the keys are what takes the time there)
+// keys: the row of keys in LDS (STAGED; every thread's largest of the keys it wrote there is `mine`), or in memory
 template <bool STAGED, int NT>
-__global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
-  extern __shared__ float keys_lds[];
+__device__ __forceinline__ void topk_row(const SelectArgs &a, int bh, const float *keys, uint32_t mine) {
   __shared__ int hist[256];
   __shared__ int wave_tot[NT / 64];
   __shared__ uint32_t sh_prefix;
@@ -769,24 +769,11 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
   __shared__ uint32_t thread_max[NT];
   __shared__ int cand_n;
   __shared__ __attribute__((aligned(16))) uint64_t cand[kTopkCandMax + 8];  // key, then the position inverted: larger comes first
-  const int bh = blockIdx.x, lane = threadIdx.x & 63;
-  const float *mass = a.mass + (size_t)(a.mass_per_batch ? bh / a.Hkv : bh) * a.T;
+  const int lane = threadIdx.x & 63;
   int32_t *out = a.sal_idx + (size_t)bh * a.S_cap;
   const int k = min(a.top_k, a.T);
   const uint32_t lowest = a.skip_zero ? 1u : 0u;  // keys below this bit pattern (i.e. +0) are never selected
   if (STAGED) {
-    uint32_t mine = 0u;  // largest key this thread staged (bit patterns of non-negative floats order like the floats)
-    for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
-      float x[kTopkBatch];  // requested together; positions past the end read the last key and are dropped
-#pragma unroll
-      for (int i = 0; i < kTopkBatch; ++i) x[i] = mass[min(t0 + i * NT, a.T - 1)];
-#pragma unroll
-      for (int i = 0; i < kTopkBatch; ++i)
-        if (t0 + i * NT < a.T) {
-          keys_lds[t0 + i * NT] = x[i];
-          mine = max(mine, __float_as_uint(x[i]));
-        }
-    }
     if (threadIdx.x == 0) { list_n = 0; cand_n = 0; }
     thread_max[threadIdx.x] = mine;
     __syncthreads();
@@ -825,7 +812,7 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
       for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
         uint32_t bits[kTopkBatch];
 #pragma unroll
-        for (int i = 0; i < kTopkBatch; ++i) bits[i] = __float_as_uint(keys_lds[min(t0 + i * NT, a.T - 1)]);
+        for (int i = 0; i < kTopkBatch; ++i) bits[i] = __float_as_uint(keys[min(t0 + i * NT, a.T - 1)]);
 #pragma unroll
         for (int i = 0; i < kTopkBatch; ++i)
           if (t0 + i * NT < a.T && bits[i] >= bound && bits[i] >= lowest) {
@@ -866,7 +853,6 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
       __syncthreads();
     }
   }
-  const float *keys = STAGED ? keys_lds : mass;
   uint32_t prefix = 0;
   int need = k;
   for (int pass = 3; pass >= 0; --pass) {
@@ -950,6 +936,204 @@ __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
     }
   }
   if (threadIdx.x == 0) a.sal_cnt[bh] = tot_take;
+}
+template <bool STAGED, int NT>
+__global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
+  extern __shared__ float keys_lds[];
+  const int bh = blockIdx.x;
+  const float *mass = a.mass + (size_t)(a.mass_per_batch ? bh / a.Hkv : bh) * a.T;
+  uint32_t mine = 0u;  // largest key this thread staged (bit patterns of non-negative floats order like the floats)
+  if (STAGED)
+    for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
+      float x[kTopkBatch];  // requested together; positions past the end read the last key and are dropped
+#pragma unroll
+      for (int i = 0; i < kTopkBatch; ++i) x[i] = mass[min(t0 + i * NT, a.T - 1)];
+#pragma unroll
+      for (int i = 0; i < kTopkBatch; ++i)
+        if (t0 + i * NT < a.T) {
+          keys_lds[t0 + i * NT] = x[i];
+          mine = max(mine, __float_as_uint(x[i]));
+        }
+    }
+  topk_row<STAGED, NT>(a, bh, STAGED ? keys_lds : mass, mine);
+}
+
+// ---- selection of a short prompt in one launch ------------------------------------------------------------------
+// lane exchanges in registers: within a row of 16 lanes, and between the rows
+template <int CTRL>
+__device__ __forceinline__ float row_dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+// four values per lane, reduced over the lanes l, l ^ 16, l ^ 32, l ^ 48: lane 16 * i + r gets the result of v[i] for r
+template <typename F>
+__device__ __forceinline__ float over_rows_each(const float (&v)[4], F f) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+  const float t0 = f(__uint_as_float(a[0]), __uint_as_float(a[1])), t1 = f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(t0), __float_as_uint(t1), false, false);
+  return f(__uint_as_float(c[0]), __uint_as_float(c[1]));
+}
+// ... and back: lane r of every row gets the values of lanes r, 16 + r, 32 + r, 48 + r
+__device__ __forceinline__ void to_each_row(float x, float (&v)[4]) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);  // rows 0 0 2 2, 1 1 3 3
+  const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const auto c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  v[0] = __uint_as_float(b[0]); v[2] = __uint_as_float(b[1]);
+  v[1] = __uint_as_float(c[0]); v[3] = __uint_as_float(c[1]);
+}
+// (the compiler's own fmaxf first quiets operands it cannot prove quiet)
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// eight values per lane, added up over the 16 lanes of a row: lanes 2 * i and 2 * i + 1 get the sum of v[i]
+__device__ __forceinline__ float row_sums_each(const float (&v)[8], int mrow) {
+  float x[4], y[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // lanes r and 15 - r
+    const float keep = (mrow & 8) ? v[i + 4] : v[i], give = (mrow & 8) ? v[i] : v[i + 4];
+    x[i] = keep + row_dpp<0x140>(give);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // r and 7 - r of each half
+    const float keep = (mrow & 4) ? x[i + 2] : x[i], give = (mrow & 4) ? x[i] : x[i + 2];
+    y[i] = keep + row_dpp<0x141>(give);
+  }
+  const float keep = (mrow & 2) ? y[1] : y[0], give = (mrow & 2) ? y[0] : y[1];
+  const float z = keep + row_dpp<0x1B>(give);  // r and 3 - r of each quad
+  return z + row_dpp<0xB1>(z);                 // r and r ^ 1
+}
+
+// One workgroup per (batch, head), one query head per KV head, W = 64: a wavefront holds 64 keys as operands and, in 64
+// registers, what they make of the 64 tail rows, so that every key is read, multiplied and exponentiated once; the
+// wavefronts' row statistics meet in LDS, and the top-k takes the masses from there.  Up to kSmallKeys keys: what twelve
+// wavefronts of 168 registers, three on a SIMD, hold.
+// Three launches of 5 to 6.6 us each did this before, each waiting for the one in front of it; us per selection, 32 heads,
+// then and now: 1 x 640 keys 16.3 -> 13.3, 1 x 256 15.1 -> 7.8, 16 x 512 37.7 -> 21.3, 64 x 256 72 -> 38, 64 x 768 162 -> 128.
+// Keys come line by line and are turned through LDS: loads in operand order (half lines) took 1.4 us longer at 1 x 640.
+// The time is a chain: rows and keys from memory (one CU brings a head's 164 KB), products, exponentials, three barriers,
+// and about 2.5 us of top-k.  Beyond 768 keys a workgroup runs out of registers; with several query heads per KV head it
+// would score them one after the other on one CU, where the passes below use many.
+// NT: threads, and the most keys (a wavefront takes 64).
+template <int NT>
+__global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
+  __shared__ u32x4 key_tile[NT / 64][256];                              // 16 keys on their way to operands
+  __shared__ u32x4 q_lds[1024];                                         // the tail rows as operands: slot (rb, kc, lane)
+  __shared__ float part_m[NT / 64][64], part_l[NT / 64][64];  // per wavefront and row
+  __shared__ float mass_lds[NT];
+  const int bh = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, mrow = lane & 15, qd = lane >> 4;
+  const int n_waves = (a.T + 63) / 64, t_wave = 64 * wave;
+  const bool scores = wave < n_waves;
+  const uint16_t *k_rows = a.k + (size_t)bh * a.T * kD, *q_rows = a.q_tail + (size_t)bh * 64 * kD;
+  const float scale2 = a.sm_scale * kLog2e;
+  // rows first: they are looked at first, and loads return in order
+  constexpr int kRowPieces = (1024 + NT - 1) / NT;  // 16-byte pieces of the rows per thread; consecutive threads, consecutive pieces
+  u32x4 row_piece[kRowPieces];
+#pragma unroll
+  for (int x = 0; x < kRowPieces; ++x)
+    row_piece[x] = *reinterpret_cast<const u32x4 *>(q_rows + 8 * min((int)threadIdx.x + x * NT, 1023));
+  KeyGroup raw[4];
+  if (scores) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) load_key_lines(k_rows, t_wave + 16 * g, a.T, lane, raw[g]);  // (past the end: masked)
+  }
+#pragma unroll
+  for (int x = 0; x < kRowPieces; ++x) {
+    const int i = (int)threadIdx.x + x * NT, piece = i & 15, row = i >> 4;
+    if (i < 1024)
+      q_lds[((row >> 4) * 4 + (piece >> 2)) * 64 + (piece & 3) * 16 + (row & 15)] = __builtin_bit_cast(u32x4, rows8_as_bf16(row_piece[x]));
+  }
+  __syncthreads();
+  f32x4 s[4][4];  // logits, then exponentials: row 16*rb + mrow, keys 16*g + 4*qd + i
+  float m_row = 0.0f;
+  if (scores) {
+    bf16x8 key[4][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) lines_to_operands(raw[g], key_tile[wave], lane, key[g]);
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) s[rb][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc) {
+        const bf16x8 rows = __builtin_bit_cast(bf16x8, q_lds[(rb * 4 + kc) * 64 + lane]);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) s[rb][g] = mfma_bf16(key[g][kc], rows, s[rb][g]);
+      }
+    }
+    if (t_wave + 63 > a.T - 64) {  // some key is hidden from some row, or past the end: behind position T - 64 + row
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+        int last = a.T - 64 + 16 * rb + mrow - (t_wave + 4 * qd);
+        asm volatile("" : "+v"(last));
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[rb][g][i] = 16 * g + i <= last ? s[rb][g][i] : -INFINITY;
+      }
+    }
+    float x[4];
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      x[rb] = max3(s[rb][0][0], s[rb][0][1], max3(s[rb][0][2], s[rb][0][3], s[rb][1][0]));
+      x[rb] = max3(x[rb], s[rb][1][1], max3(s[rb][1][2], s[rb][1][3], s[rb][2][0]));
+      x[rb] = max3(x[rb], s[rb][2][1], max3(s[rb][2][2], s[rb][2][3], s[rb][3][0]));
+      x[rb] = max3(x[rb], s[rb][3][1], max3(s[rb][3][2], s[rb][3][3], s[rb][3][3]));
+    }
+    // row `lane` of this wavefront's keys (finite where no key is seen)
+    m_row = fmaxf(over_rows_each(x, [](float u, float v) { return max3(u, u, v); }) * scale2, -1e30f);
+    part_m[wave][lane] = m_row;
+    float ref[4];
+    to_each_row(m_row, ref);
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      x[rb] = 0.0f;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[rb][g][i] = fast_exp2(__builtin_fmaf(s[rb][g][i], scale2, -ref[rb]));
+        x[rb] += (s[rb][g][0] + s[rb][g][1]) + (s[rb][g][2] + s[rb][g][3]);
+      }
+    }
+    part_l[wave][lane] = over_rows_each(x, [](float u, float v) { return u + v; });
+  } else {
+    part_m[wave][lane] = -1e30f;
+    part_l[wave][lane] = 0.0f;
+  }
+  __syncthreads();
+  if (scores) {
+    float m_all = -1e30f, l_all = 0.0f;
+    float m_w[NT / 64], l_w[NT / 64];
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) { m_w[w] = part_m[w][lane]; l_w[w] = part_l[w][lane]; }
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) m_all = fmaxf(m_all, m_w[w]);
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) l_all = __builtin_fmaf(l_w[w], fast_exp2(m_w[w] - m_all), l_all);
+    float wgt[4];
+    to_each_row(fast_exp2(m_row - m_all) * (1.0f / l_all), wgt);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      float col[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int g = 2 * half + (i >> 2);
+        col[i] = s[0][g][i & 3] * wgt[0];
+#pragma unroll
+        for (int rb = 1; rb < 4; ++rb) col[i] = __builtin_fmaf(s[rb][g][i & 3], wgt[rb], col[i]);
+      }
+      const float sum = row_sums_each(col, mrow);  // lanes of mrow 2 * (4*(g - 2*half) + i): key 16*g + 4*qd + i
+      const int t = t_wave + 32 * half + 16 * (mrow >> 3) + 4 * qd + ((mrow >> 1) & 3);
+      if ((mrow & 1) == 0 && t < a.T) {
+        mass_lds[t] = sum;
+        a.mass[(size_t)bh * a.T + t] = sum;
+      }
+    }
+  }
+  __syncthreads();
+  topk_row<true, NT>(a, bh, mass_lds, (int)threadIdx.x < a.T ? __float_as_uint(mass_lds[threadIdx.x]) : 0u);
 }
 
 // ---- massive-activation score (Section III-B.2): largest channel magnitude of every token's hidden state ----
@@ -1074,6 +1258,13 @@ static void launch_psa_passes(const SelectArgs &a, hipStream_t stream) {
 }
 
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream) {
+  if (score_small(a.B, a.Hq, a.Hkv, a.T, a.W, a.sm_scale) && a.mass_shared == nullptr) {
+    const dim3 grid(a.B * a.Hkv);
+    if (a.T <= 256) hipLaunchKernelGGL(psa_small_kernel<256>, grid, dim3(256), 0, stream, a);
+    else if (a.T <= 512) hipLaunchKernelGGL(psa_small_kernel<512>, grid, dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL(psa_small_kernel<kSmallKeys>, grid, dim3(kSmallKeys), 0, stream, a);
+    return hipGetLastError();
+  }
   switch (a.W / 16) {
     case 1: launch_psa_passes<1>(a, stream); break;
     case 2: launch_psa_passes<2>(a, stream); break;
