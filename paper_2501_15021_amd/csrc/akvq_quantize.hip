@@ -158,22 +158,48 @@ __device__ __forceinline__ void rope_row_quad(u32x4 (&raw)[4], const u32x4 (&cw)
 constexpr uint32_t kPack16Bias = (uint32_t)(0x4B400000ull * 0x55555555ull);   // sum over s<16 of kMagicBits << 2s
 constexpr uint32_t kPack4Bias = (uint32_t)(0x4B400000ull * 0x01010101ull);    // sum over b<4 of kMagicBits << 8b
 
+// One row as bfloat16 (u holds its sign-carrying transform, scale undoes that) into slot `slot` of row-major K rows or of
+// 32-slot V tiles; zeros for a row that carries no token.
+template <int TENSOR>
+__device__ __forceinline__ void store_bf16_row(const float (&u)[4][8], float scale, int j, uint16_t *k_rows, uint16_t *v_plane,
+                                               int slot, bool token) {
+  if (TENSOR == 0) {
+    uint16_t *dst = k_rows + (size_t)slot * kD;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      u32x4 o;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        o[w] = token ? pack_bf16x2(scaled_row_value(u[m][2 * w], scale), scaled_row_value(u[m][2 * w + 1], scale)) : 0u;
+      *reinterpret_cast<u32x4 *>(dst + 32 * m + 8 * j) = o;
+    }
+  } else {
+    const int sb = slot >> 5, sh = (slot & 31) >> 4, sr = slot & 15, sq = sr >> 2, sii = sr & 3;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int e = 32 * m + 8 * j + i, nb = e >> 4, n = e & 15;
+        v_plane[(size_t)sb * 4096 + nb * 512 + (16 * sq + n) * 8 + 2 * sii + sh] =
+            token ? (uint16_t)pack_bf16x2(scaled_row_value(u[m][i], scale), 0.0f) : (uint16_t)0;
+      }
+  }
+}
+
 // TIERED: rows carry a tier and a source-row index (akvq_quantize_append_tiered); the plain instantiation is the
 // two-bit path with identity row mapping and none of the per-row tier arithmetic.
-// WINDOW: the last win_len appended rows also go to the recent-window rings.
 // ROPE: K rows arrive without their rotary position embedding; it is applied here, in front of the rotation.
 // (the tensor, 0 = K or 1 = V, is a template parameter of the body: the two differ in everything after the transform,
 // and the kernel branches once, on blockIdx.z)
-template <int G, bool TIERED, bool WINDOW, bool ROPE, int TENSOR>
-__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int first_blk, int n_blk,
-                                                     int (*slot_of_lds)[kTokBlock], uint32_t (*vtile_lds)[2048]) {
+template <int G, bool TIERED, bool ROPE, int TENSOR>
+__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int (*slot_of_lds)[kTokBlock]) {
   // the wavefront index as a scalar: the block index, its first row and every base address derived from them then
   // live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int blk_rel = group * 4 + wave;
-  if (blk_rel >= n_blk) return;  // whole wavefront leaves; no block-wide barrier is used below
-  const int blk = first_blk + blk_rel;
+  if (blk_rel >= a.n_blk) return;  // whole wavefront leaves; no block-wide barrier is used below
+  const int blk = a.first_blk + blk_rel;
   const int bh = blockIdx.y;
   constexpr int tensor = TENSOR;
   const int r = lane >> 2, j = lane & 3;
@@ -279,9 +305,6 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
   bool no_bias = false;
   if constexpr (TIERED) no_bias = __ballot(tier[0] != AKVQ_TIER_2BIT || tier[1] != AKVQ_TIER_2BIT) != 0ull;
 
-  // recent window: is this whole block new and inside the window?  (uniform over the wavefront)
-  bool win_block = false;
-  if constexpr (WINDOW) win_block = t0 >= a.T_len && t0 + kTokBlock <= t_end && t0 >= t_end - a.win_len;
   uint32_t kw[2][2];         // K words of token half h: [h][group-of-64 word]
   uint32_t vcode[2][8];      // V: [mpair][i]: raw patterns of (X, Y) x (half 0, half 1) in the four byte lanes
   uint32_t vmask_part = 0;
@@ -308,75 +331,10 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
         }
     }
 
-    // ---- bfloat16 copies: the overlay slot of a salient row (Section III-C.1: salient tokens keep 16-bit
-    // precision) and the ring slot of a row inside the recent window (the last win_len appended rows) ----
-    auto store_bf16_row = [&](uint16_t *k_rows, uint16_t *v_plane, int slot, bool token) {
-      const float scale = kappa_s;
-      if (tensor == 0) {
-        uint16_t *dst = k_rows + (size_t)slot * kD;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          u32x4 o;
-#pragma unroll
-          for (int w = 0; w < 4; ++w)
-            o[w] = token ? pack_bf16x2(scaled_row_value(u[m][2 * w], scale), scaled_row_value(u[m][2 * w + 1], scale)) : 0u;
-          *reinterpret_cast<u32x4 *>(dst + 32 * m + 8 * j) = o;
-        }
-      } else {
-        const int sb = slot >> 5, sh = (slot & 31) >> 4, sr = slot & 15, sq = sr >> 2, sii = sr & 3;
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int e = 32 * m + 8 * j + i, nb = e >> 4, n = e & 15;
-            v_plane[(size_t)sb * 4096 + nb * 512 + (16 * sq + n) * 8 + 2 * sii + sh] =
-                token ? (uint16_t)pack_bf16x2(scaled_row_value(u[m][i], scale), 0.0f) : (uint16_t)0;
-          }
-      }
-    };
+    // ---- bfloat16 copy: the overlay slot of a salient row (Section III-C.1: salient tokens keep 16-bit precision) ----
     // (the V rows of long salient lists are stored by overlay_rows_kernel instead)
     if (valid[h] && slots[h] >= 0 && (tensor == 0 || !a.skip_overlay))
-      store_bf16_row(a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, slots[h], true);
-    if constexpr (WINDOW) {
-      const int t = t0 + 16 * h + r;
-      // fine halves and padding rows carry no token: their ring slots are zeroed
-      const bool token = !TIERED || (tier[h] != AKVQ_TIER_4BIT_FINE && tier[h] != AKVQ_TIER_PAD);
-      if (win_block && tensor == 1) {
-        // The whole block fills one 32-slot tile of the V ring (the prefill case).  In a tile the values of rows r and
-        // r+16 of one channel are neighbours; this lane owns both rows and writes its 16-bit values into the wavefront's
-        // tile in LDS, half 0 and then half 1, and the finished tile goes out as eight fully coalesced 1 KB stores.
-        // (Scattered partial-line stores, as in the row-at-a-time path, are several times slower and would dominate the
-        // tail of a prefill launch.)
-        uint16_t *tile16 = reinterpret_cast<uint16_t *>(vtile_lds[wave]);
-        const int sq = r >> 2, sii = r & 3;
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            const uint32_t pk = token ? pack_bf16x2(scaled_row_value(u[m][2 * w], kappa_s), scaled_row_value(u[m][2 * w + 1], kappa_s)) : 0u;
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-              const int e = 32 * m + 8 * j + 2 * w + c, nb = e >> 4, n = e & 15;
-              tile16[nb * 512 + (16 * sq + n) * 8 + 2 * sii + h] = (uint16_t)(c == 0 ? pk : pk >> 16);
-            }
-          }
-        if (h == 1) {
-          // the tile goes to the ring (slot = row mod W, a multiple of 32 here)
-          uint32_t *ring_out = reinterpret_cast<uint32_t *>(
-              a.v_win + (size_t)bh * a.win_len * kD + (size_t)((t0 % max(a.win_len, 1)) >> 5) * 4096);
-          wave_lds_sync();
-#pragma unroll
-          for (int x = 0; x < 8; ++x)
-            *reinterpret_cast<u32x4 *>(ring_out + 256 * x + 4 * lane) =
-                *reinterpret_cast<const u32x4 *>(vtile_lds[wave] + 256 * x + 4 * lane);
-          wave_lds_sync();
-        }
-      }
-      if (!(win_block && tensor == 1) && valid[h] && t >= t_end - a.win_len) {
-        store_bf16_row(a.k_win + (size_t)bh * a.win_len * kD, a.v_win + (size_t)bh * a.win_len * kD,
-                       t % max(a.win_len, 1), token);
-      }
-    }
+      store_bf16_row<TENSOR>(u, kappa_s, j, a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, slots[h], true);
 
     // ---- group extrema (quad reduction), scale, zero-point ----
     GroupQ gq[NG];
@@ -532,26 +490,121 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
   }
 }
 
-// (batch, kv-head) blockIdx.y, tensor blockIdx.z, blocks 4 * blockIdx.x .. of the appended range.  WINDOW: the last blocks,
-// those that hold window rows (a.n_blk - a.n_plain of them), come first, by the body with the ring stores; the n_plain
-// blocks before them go through the one without (see launch_block_ranges).
-template <int G, bool TIERED, bool WINDOW, bool ROPE>
+// (batch, kv-head) blockIdx.y, tensor blockIdx.z, blocks 4 * blockIdx.x .. of the appended range
+template <int G, bool TIERED, bool ROPE>
 __global__ __launch_bounds__(256) void quantize_append_kernel(QuantArgs a) {
   __shared__ int slot_of_lds[4][kTokBlock];
-  int group = blockIdx.x, n_blk = a.n_blk;
-  if constexpr (WINDOW) {
-    __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];  // one V tile (32 slots x 128 channels, bf16) per wavefront
-    const int n_win = a.n_blk - a.n_plain, win_groups = (n_win + 3) / 4;
-    if (group < win_groups) {
-      if (blockIdx.z == 0) quantize_append_body<G, TIERED, true, ROPE, 0>(a, group, a.first_blk + a.n_plain, n_win, slot_of_lds, vtile_lds);
-      else quantize_append_body<G, TIERED, true, ROPE, 1>(a, group, a.first_blk + a.n_plain, n_win, slot_of_lds, vtile_lds);
-      return;
+  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, blockIdx.x, slot_of_lds);
+  else quantize_append_body<G, TIERED, ROPE, 1>(a, blockIdx.x, slot_of_lds);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The rows of an append that fall into the recent window, as bfloat16 into their ring slots (slot = row mod win_len):
+// one wavefront per 32-row block from win_blk on, by workgroups of their own in the launch of the blocks.  They read and
+// transform their few rows a second time (same butterflies and roundings); the blocks, window or not, all take the body
+// without ring stores.  Bodies that also store ring rows, which the window's blocks used to go through, made one launch
+// of four such bodies slower than two launches (59 KB of code against 26), and the second launch stood alone at the end.
+// Before and after, 16-bit rows of window W: 64 prompts of 300 tokens, 40 heads, W 128: 169 -> 136 us; 8 of 4096 tokens, 32
+// heads, W 512: 136 -> 120; 2 of 1000, W 128: 16.2 -> 12.8; 1 of 700, W 64: 6.9 -> 6.2; 8 of 4096 with tiers and rotary
+// embedding, W 128: 152.5 -> 151.7 (vector issue bounds that launch, and the rows' second transform is part of it).
+// ------------------------------------------------------------------------------------------------
+template <bool TIERED, bool ROPE, int TENSOR>
+__device__ __forceinline__ void ring_rows_body(const QuantArgs &a, int group, uint32_t (*vtile_lds)[2048]) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int bh = blockIdx.y, r = lane >> 2, j = lane & 3;
+  const int t0 = (a.win_blk + group * 4 + wave) * kTokBlock, t_end = a.T_len + a.n_new;
+  if (t0 >= t_end) return;  // whole wavefront leaves; no block-wide barrier is used below
+  const int t_first = max(a.T_len, t_end - a.win_len);
+  const bool rotate = (TENSOR == 0 ? a.rotate_k : a.rotate_v) != 0;
+  const float kappa_s = rotate ? quad_sign(j) * inv_sqrt128() : 1.0f;
+  const uint16_t *src = TENSOR == 0 ? a.k_new : a.v_new;
+  bool valid[2], token[2];
+  u32x4 raw[2][4], rope_c[2][2], rope_s[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int t = t0 + 16 * h + r;
+    valid[h] = t >= t_first && t < t_end;
+    token[h] = true;
+    // rows outside read a clamped (valid) address; nothing derived from them is stored
+    const int rel = min(max(t - a.T_len, 0), a.n_new - 1);
+    int src_row = rel;
+    if constexpr (TIERED) {
+      const size_t at = (size_t)(bh / a.Hkv) * a.n_new + rel;
+      src_row = min(max(a.row_src[at], 0), a.n_src - 1);
+      const int tier = a.row_tier[at];
+      token[h] = tier != AKVQ_TIER_4BIT_FINE && tier != AKVQ_TIER_PAD;  // such rows carry no token: their slots are zeroed
     }
-    group -= win_groups;
-    n_blk = a.n_plain;
+    const uint16_t *row = src + ((size_t)bh * a.n_src + src_row) * kD;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) raw[h][m] = *reinterpret_cast<const u32x4 *>(row + 32 * m + 8 * j);
+    if constexpr (ROPE && TENSOR == 0) {
+      const size_t at = (size_t)(bh / a.Hkv) * a.rope_stride + (size_t)src_row * 64 + 8 * j;
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) {
+        rope_c[h][mm] = *reinterpret_cast<const u32x4 *>(a.rope_cos + at + 32 * mm);
+        rope_s[h][mm] = *reinterpret_cast<const u32x4 *>(a.rope_sin + at + 32 * mm);
+      }
+    }
   }
-  if (blockIdx.z == 0) quantize_append_body<G, TIERED, false, ROPE, 0>(a, group, a.first_blk, n_blk, slot_of_lds, nullptr);
-  else quantize_append_body<G, TIERED, false, ROPE, 1>(a, group, a.first_blk, n_blk, slot_of_lds, nullptr);
+  uint16_t *k_ring = a.k_win + (size_t)bh * a.win_len * kD, *v_ring = a.v_win + (size_t)bh * a.win_len * kD;
+  const bool whole = t0 >= t_first && t0 + kTokBlock <= t_end;  // (uniform over the wavefront)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float u[4][8];  // quad_sign(j) times the (rotated) row
+    if constexpr (ROPE && TENSOR == 0) rope_row_quad(raw[h], rope_c[h], rope_s[h]);
+    if (rotate) {
+      wht128_quad(raw[h], u, j);
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          u[m][2 * w] = half_bits_to_float(raw[h][m][w] & 0xFFFFu);
+          u[m][2 * w + 1] = half_bits_to_float(raw[h][m][w] >> 16);
+        }
+    }
+    if (TENSOR == 1 && whole) {
+      // The whole block fills one 32-slot tile of the V ring (the prefill case).  In a tile the values of rows r and
+      // r+16 of one channel are neighbours; this lane owns both rows and writes its 16-bit values into the wavefront's
+      // tile in LDS, half 0 and then half 1, and the finished tile goes out as eight fully coalesced 1 KB stores.
+      // (Scattered partial-line stores, as for the rows of other blocks, are several times slower.)
+      uint16_t *tile16 = reinterpret_cast<uint16_t *>(vtile_lds[wave]);
+      const int sq = r >> 2, sii = r & 3;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const uint32_t pk = token[h] ? pack_bf16x2(scaled_row_value(u[m][2 * w], kappa_s), scaled_row_value(u[m][2 * w + 1], kappa_s)) : 0u;
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const int e = 32 * m + 8 * j + 2 * w + c, nb = e >> 4, n = e & 15;
+            tile16[nb * 512 + (16 * sq + n) * 8 + 2 * sii + h] = (uint16_t)(c == 0 ? pk : pk >> 16);
+          }
+        }
+      if (h == 1) {
+        uint32_t *ring_out = reinterpret_cast<uint32_t *>(v_ring + (size_t)((t0 % a.win_len) >> 5) * 4096);  // (win_len: a multiple of 64)
+        wave_lds_sync();
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+          *reinterpret_cast<u32x4 *>(ring_out + 256 * x + 4 * lane) = *reinterpret_cast<const u32x4 *>(vtile_lds[wave] + 256 * x + 4 * lane);
+      }
+    } else if (valid[h]) {
+      store_bf16_row<TENSOR>(u, kappa_s, j, k_ring, v_ring, (t0 + 16 * h + r) % a.win_len, token[h]);
+    }
+  }
+}
+template <int G, bool TIERED, bool ROPE>
+__global__ __launch_bounds__(256) void quantize_append_window_kernel(QuantArgs a) {
+  __shared__ int slot_of_lds[4][kTokBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];  // one V tile (32 slots x 128 channels, bf16) per wavefront
+  const int groups = (a.n_blk + 3) / 4, group = blockIdx.x;
+  if (blockIdx.z == 0) {
+    if (group >= groups) ring_rows_body<TIERED, ROPE, 0>(a, group - groups, vtile_lds);
+    else quantize_append_body<G, TIERED, ROPE, 0>(a, group, slot_of_lds);
+  } else {
+    if (group >= groups) ring_rows_body<TIERED, ROPE, 1>(a, group - groups, vtile_lds);
+    else quantize_append_body<G, TIERED, ROPE, 1>(a, group, slot_of_lds);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -652,8 +705,8 @@ __global__ __launch_bounds__(256) void quantize_append_overlay_kernel(QuantArgs 
   __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
   const int groups = (a.n_blk + 3) / 4, group = blockIdx.x;
   if (group >= groups) overlay_rows_body(a, 2 * (group - groups) + blockIdx.z, vtile_lds);
-  else if (blockIdx.z == 0) quantize_append_body<G, false, false, ROPE, 0>(a, group, a.first_blk, a.n_blk, slot_of_lds, nullptr);
-  else quantize_append_body<G, false, false, ROPE, 1>(a, group, a.first_blk, a.n_blk, slot_of_lds, nullptr);
+  else if (blockIdx.z == 0) quantize_append_body<G, false, ROPE, 0>(a, group, slot_of_lds);
+  else quantize_append_body<G, false, ROPE, 1>(a, group, slot_of_lds);
 }
 
 template <int G>
@@ -665,28 +718,32 @@ __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
 
 }  // namespace
 
-constexpr long kResidentGroups = 4 * 256;
-static int window_groups(const QuantArgs &a) { return (a.n_plain + 3) / 4 + (a.n_blk - a.n_plain + 3) / 4; }
-static void launch_blocks(const QuantArgs &a, int B, int G, bool window, hipStream_t stream) {
-  dim3 grid(window ? window_groups(a) : (a.n_blk + 3) / 4, B * a.Hkv, 2), block(256);
-  const bool tiered = a.row_tier != nullptr;
-  const bool rope = a.rope_cos != nullptr;
-#define AKVQ_LAUNCH_Q(GG, TT, WW, RR) \
-  hipLaunchKernelGGL((quantize_append_kernel<GG, TT, WW, RR>), grid, block, 0, stream, a)
-#define AKVQ_LAUNCH_QR(GG, TT, WW) \
-  do { if (rope) AKVQ_LAUNCH_Q(GG, TT, WW, true); else AKVQ_LAUNCH_Q(GG, TT, WW, false); } while (0)
+// The blocks of an append, with the workgroups of its window rows behind every unit's where there is a window.
+static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t stream) {
+  QuantArgs a = a_in;
+  const bool tiered = a.row_tier != nullptr, rope = a.rope_cos != nullptr, window = a.win_len > 0;
+  int groups = (a.n_blk + 3) / 4;
+  if (window) {
+    const int t_end = a.T_len + a.n_new, t_first = t_end - a.win_len > a.T_len ? t_end - a.win_len : a.T_len;
+    a.win_blk = t_first / kTokBlock;
+    groups += (a.first_blk + a.n_blk - a.win_blk + 3) / 4;
+  }
+  const dim3 grid(groups, B * a.Hkv, 2), block(256);
+#define AKVQ_LAUNCH_Q(GG, TT, RR) \
+  do { \
+    if (window) hipLaunchKernelGGL((quantize_append_window_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+    else hipLaunchKernelGGL((quantize_append_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+  } while (0)
+#define AKVQ_LAUNCH_QR(GG, TT) do { if (rope) AKVQ_LAUNCH_Q(GG, TT, true); else AKVQ_LAUNCH_Q(GG, TT, false); } while (0)
   if (G == 128) {
-    if (tiered) { if (window) AKVQ_LAUNCH_QR(128, true, true); else AKVQ_LAUNCH_QR(128, true, false); }
-    else { if (window) AKVQ_LAUNCH_QR(128, false, true); else AKVQ_LAUNCH_QR(128, false, false); }
+    if (tiered) AKVQ_LAUNCH_QR(128, true); else AKVQ_LAUNCH_QR(128, false);
   } else {
-    if (tiered) { if (window) AKVQ_LAUNCH_QR(64, true, true); else AKVQ_LAUNCH_QR(64, true, false); }
-    else { if (window) AKVQ_LAUNCH_QR(64, false, true); else AKVQ_LAUNCH_QR(64, false, false); }
+    if (tiered) AKVQ_LAUNCH_QR(64, true); else AKVQ_LAUNCH_QR(64, false);
   }
 #undef AKVQ_LAUNCH_QR
 #undef AKVQ_LAUNCH_Q
+  return hipGetLastError();
 }
-
-static hipError_t launch_block_ranges(const QuantArgs &a, int B, int G, hipStream_t stream);
 
 hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t stream) {
   if (a.n_new == 1 && a.n_src == 1 && a.row_tier == nullptr) {  // the decode step: one plain row per (batch, kv-head)
@@ -695,8 +752,8 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
     else hipLaunchKernelGGL(append_row_kernel<64>, grid, block, 0, stream, a);
     return hipGetLastError();
   }
-  // Long salient lists (text-salient layers) get their V overlay rows from a pass of their own behind the block kernel;
-  // a handful of pivots (and the rows of a tiered append, whose tiers the block kernel knows) are stored by the block
+  // Long salient lists (text-salient layers) get their V overlay rows from workgroups of their own, in the launch of the
+  // blocks or, where a window's workgroups are in that, in a launch behind it; a handful of pivots (and the rows of a tiered append, whose tiers the block kernel knows) are stored by the block
   // kernel itself.
   if (a.S_cap > 64 && a.row_tier == nullptr) {
     QuantArgs blocks = a;
@@ -711,46 +768,13 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
 #undef AKVQ_LAUNCH_O
       return hipGetLastError();
     }
-    hipError_t e = launch_block_ranges(blocks, B, G, stream);
+    hipError_t e = launch_blocks(blocks, B, G, stream);
     if (e != hipSuccess) return e;
     const dim3 grid(overlay_groups, B * a.Hkv), block(256);
     hipLaunchKernelGGL(overlay_rows_kernel, grid, block, 0, stream, a);
     return hipGetLastError();
   }
-  return launch_block_ranges(a, B, G, stream);
-}
-
-hipError_t launch_block_ranges(const QuantArgs &a, int B, int G, hipStream_t stream) {
-  if (a.win_len <= 0) {
-    launch_blocks(a, B, G, false, stream);
-    return hipGetLastError();
-  }
-  // Recent window: only the blocks that hold the last win_len new rows write ring slots.  The blocks before them (the
-  // bulk of a prompt) take the body without the ring stores: within the same launch if all its workgroups are resident
-  // at once (four per CU), as a second launch would only add its latency (one prompt of 700 tokens, 32 heads, window 64:
-  // 11.6 -> 7.6 us; window 128 and tiers 13.8 -> 10.0); else by a launch of their own (16 prompts of 4096 tokens, window
-  // 128: 230 us, 290 in one launch; 64 of 300 tokens, 40 heads: 168 / 185).  What makes the large launch slower is the code
-  // of four bodies in one kernel, 43-59 KB against 19-26, and not the window's 33 KB of LDS: the plain kernel with as much
-  // LDS takes the same time (230.7), and four workgroups fit a CU either way.  The line is drawn on the safe side: 1152
-  // workgroups (2 prompts of 1000 tokens, 32 heads) take 15.1 us in two launches and 11.8 in one, 3328 (4 of 1500) 27.2
-  // and 24.3, 16896 (8 of 4096) 124 and 148.
-  const int t_end = a.T_len + a.n_new;
-  const int t_w0 = t_end - a.win_len > a.T_len ? t_end - a.win_len : a.T_len;
-  QuantArgs w = a;
-  w.n_plain = t_w0 / kTokBlock - a.first_blk;
-  if (w.n_plain > 0 && window_groups(w) * 2l * B * a.Hkv > kResidentGroups) {
-    QuantArgs head = a;
-    head.n_blk = w.n_plain;
-    head.win_len = 0;
-    launch_blocks(head, B, G, false, stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    w.first_blk += w.n_plain;
-    w.n_blk -= w.n_plain;
-    w.n_plain = 0;
-  }
-  launch_blocks(w, B, G, true, stream);
-  return hipGetLastError();
+  return launch_blocks(a, B, G, stream);
 }
 
 }  // namespace akvq
