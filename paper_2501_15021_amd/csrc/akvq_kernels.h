@@ -25,6 +25,7 @@ struct QuantArgs {
   uint16_t *k_win, *v_win;  // recent-window rings (null: none)
   int win_len;
   int win_blk;  // first block that holds window rows (set by the launcher)
+  int groups, turn;  // workgroups of one unit's tensor, and by how many of them (at most) a unit's order is turned (set by the launcher)
   const uint16_t *rope_cos, *rope_sin;  // rotary tables for pre-RoPE K rows (null: rows arrive embedded), [n_src][64] binary16
   long long rope_stride;                // elements between the tables of consecutive batch elements
   int skip_overlay;  // the block kernel leaves the 16-bit V rows to the overlay pass that follows it

@@ -490,12 +490,16 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
   }
 }
 
-// (batch, kv-head) blockIdx.y, tensor blockIdx.z, blocks 4 * blockIdx.x .. of the appended range
+// (batch, kv-head) blockIdx.y, tensor blockIdx.z, four blocks of the appended range a workgroup.  Workgroups go to the XCDs
+// in turn, so with an even number of them per unit an XCD would work on the same few ranges of every unit; a.turn (see
+// launch_blocks) moves each unit's order on by one, eight in a cycle.
 template <int G, bool TIERED, bool ROPE>
 __global__ __launch_bounds__(256) void quantize_append_kernel(QuantArgs a) {
   __shared__ int slot_of_lds[4][kTokBlock];
-  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, blockIdx.x, slot_of_lds);
-  else quantize_append_body<G, TIERED, ROPE, 1>(a, blockIdx.x, slot_of_lds);
+  int group = blockIdx.x + (blockIdx.y & a.turn);
+  if (group >= a.groups) group -= a.groups;  // (turn < groups)
+  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, group, slot_of_lds);
+  else quantize_append_body<G, TIERED, ROPE, 1>(a, group, slot_of_lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -718,6 +722,7 @@ __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
 
 }  // namespace
 
+constexpr long kResidentGroups = 4 * 256;
 // The blocks of an append, with the workgroups of its window rows behind every unit's where there is a window.
 static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t stream) {
   QuantArgs a = a_in;
@@ -728,6 +733,13 @@ static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t
     a.win_blk = t_first / kTokBlock;
     groups += (a.first_blk + a.n_blk - a.win_blk + 3) / 4;
   }
+  // Turned orders where more workgroups than the card holds at once (four per CU) run over units of an even number of them:
+  // 16 prompts of 4096 tokens (32 workgroups a unit), 32 heads: 227 -> 217 us; 8 of 4064: 113.7 -> 110.3; 8 of 5000 (40):
+  // 136.2 -> 132.9; 8 of 2500 (20): 71.0 -> 69.1.  An odd number moves on by itself, turned orders changed nothing with
+  // the window's workgroups in the launch (119.0, 8 of 4096 with window 512: 119.1) and cost where one round of
+  // workgroups holds everything (one prompt of 2048: 9.67, 9.80) or the overlay's are in it (8 of 1920, 576 slots: 52.3, 56.0).
+  a.groups = groups;
+  a.turn = !window && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
   const dim3 grid(groups, B * a.Hkv, 2), block(256);
 #define AKVQ_LAUNCH_Q(GG, TT, RR) \
   do { \
@@ -753,8 +765,8 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
     return hipGetLastError();
   }
   // Long salient lists (text-salient layers) get their V overlay rows from workgroups of their own, in the launch of the
-  // blocks or, where a window's workgroups are in that, in a launch behind it; a handful of pivots (and the rows of a tiered append, whose tiers the block kernel knows) are stored by the block
-  // kernel itself.
+  // blocks or, where a window's workgroups are in that, in a launch behind it; a handful of pivots (and the rows of a
+  // tiered append, whose tiers the block kernel knows) are stored by the block kernel itself.
   if (a.S_cap > 64 && a.row_tier == nullptr) {
     QuantArgs blocks = a;
     blocks.skip_overlay = 1;
