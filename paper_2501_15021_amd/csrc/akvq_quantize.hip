@@ -186,13 +186,51 @@ __device__ __forceinline__ void store_bf16_row(const float (&u)[4][8], float sca
   }
 }
 
+// One token half of a block into the recent-window rings (slot = row mod win_len).  `whole`: every row of the block is new
+// and inside the window; it then fills one 32-slot tile of the V ring (the prefill case).  In a tile the values of rows r
+// and r+16 of one channel are neighbours; the lane owns both rows and writes its 16-bit values into the wavefront's tile in
+// LDS, half 0 and then half 1, and the finished tile goes out as eight fully coalesced 1 KB stores.  (Scattered partial-line
+// stores, as for the rows of other blocks, are several times slower.)
+template <int TENSOR>
+__device__ __forceinline__ void store_ring_half(const QuantArgs &a, const float (&u)[4][8], float scale, int h, int t0, int lane,
+                                                bool inside, bool token, bool whole, uint32_t *vtile_lds) {
+  const int bh = blockIdx.y, r = lane >> 2, j = lane & 3;
+  uint16_t *k_ring = a.k_win + (size_t)bh * a.win_len * kD, *v_ring = a.v_win + (size_t)bh * a.win_len * kD;
+  if (TENSOR == 1 && whole) {
+    uint16_t *tile16 = reinterpret_cast<uint16_t *>(vtile_lds);
+    const int sq = r >> 2, sii = r & 3;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t pk = token ? pack_bf16x2(scaled_row_value(u[m][2 * w], scale), scaled_row_value(u[m][2 * w + 1], scale)) : 0u;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int e = 32 * m + 8 * j + 2 * w + c, nb = e >> 4, n = e & 15;
+          tile16[nb * 512 + (16 * sq + n) * 8 + 2 * sii + h] = (uint16_t)(c == 0 ? pk : pk >> 16);
+        }
+      }
+    if (h == 1) {
+      uint32_t *ring_out = reinterpret_cast<uint32_t *>(v_ring + (size_t)((t0 % a.win_len) >> 5) * 4096);  // (win_len: a multiple of 64)
+      wave_lds_sync();
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        *reinterpret_cast<u32x4 *>(ring_out + 256 * x + 4 * lane) = *reinterpret_cast<const u32x4 *>(vtile_lds + 256 * x + 4 * lane);
+    }
+  } else if (inside) {
+    store_bf16_row<TENSOR>(u, scale, j, k_ring, v_ring, (t0 + 16 * h + r) % a.win_len, token);
+  }
+}
+
 // TIERED: rows carry a tier and a source-row index (akvq_quantize_append_tiered); the plain instantiation is the
 // two-bit path with identity row mapping and none of the per-row tier arithmetic.
+// RING: a block that holds rows of the recent window (the last win_len appended rows) also stores those to the rings.
 // ROPE: K rows arrive without their rotary position embedding; it is applied here, in front of the rotation.
 // (the tensor, 0 = K or 1 = V, is a template parameter of the body: the two differ in everything after the transform,
 // and the kernel branches once, on blockIdx.z)
-template <int G, bool TIERED, bool ROPE, int TENSOR>
-__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int (*slot_of_lds)[kTokBlock]) {
+template <int G, bool TIERED, bool ROPE, int TENSOR, bool RING = false>
+__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int (*slot_of_lds)[kTokBlock],
+                                                     uint32_t (*vtile_lds)[2048] = nullptr) {
   // the wavefront index as a scalar: the block index, its first row and every base address derived from them then
   // live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -332,9 +370,18 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
     }
 
     // ---- bfloat16 copy: the overlay slot of a salient row (Section III-C.1: salient tokens keep 16-bit precision) ----
-    // (the V rows of long salient lists are stored by overlay_rows_kernel instead)
+    // (the V rows of long salient lists are stored by overlay_rows_body instead)
     if (valid[h] && slots[h] >= 0 && (tensor == 0 || !a.skip_overlay))
       store_bf16_row<TENSOR>(u, kappa_s, j, a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, slots[h], true);
+    if constexpr (RING) {
+      if (blk >= a.win_blk) {  // uniform over the wavefront
+        const int t_first = max(a.T_len, t_end - a.win_len);
+        // fine halves and padding rows carry no token: their ring slots are zeroed
+        const bool token = !TIERED || (tier[h] != AKVQ_TIER_4BIT_FINE && tier[h] != AKVQ_TIER_PAD);
+        store_ring_half<TENSOR>(a, u, kappa_s, h, t0, lane, valid[h] && t0 + 16 * h + r >= t_first, token,
+                                t0 >= t_first && t0 + kTokBlock <= t_end, TENSOR == 1 ? vtile_lds[wave] : nullptr);
+      }
+    }
 
     // ---- group extrema (quad reduction), scale, zero-point ----
     GroupQ gq[NG];
@@ -503,20 +550,19 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(QuantArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// The rows of an append that fall into the recent window, as bfloat16 into their ring slots (slot = row mod win_len):
-// one wavefront per 32-row block from win_blk on, by workgroups of their own in the launch of the blocks.  They read and
-// transform their few rows a second time (same butterflies and roundings); the blocks, window or not, all take the body
-// without ring stores.  Bodies that also store ring rows, which the window's blocks used to go through, made one launch
-// of four such bodies slower than two launches (59 KB of code against 26), and the second launch stood alone at the end.
-// Before and after, 16-bit rows of window W: 64 prompts of 300 tokens, 40 heads, W 128: 169 -> 136 us; 8 of 4096 tokens, 32
-// heads, W 512: 136 -> 120; 2 of 1000, W 128: 16.2 -> 12.8; 1 of 700, W 64: 6.9 -> 6.2; 8 of 4096 with tiers and rotary
-// embedding, W 128: 152.5 -> 151.7 (vector issue bounds that launch, and the rows' second transform is part of it).
+// The rows of an append that fall into the recent window, as bfloat16 into their ring slots: one wavefront per 32-row block
+// from win_blk on, behind the wavefronts of the unit's blocks in the same launch.  They read and transform their rows a
+// second time (same butterflies and roundings), and the blocks take the body without ring stores.  The window's blocks used
+// to go through bodies with them in a launch of their own at the end, or in one launch of four bodies (59 KB of code) where
+// that was small.  Before and now, window W: 8 prompts of 4096 tokens, 32 heads, W 512: 136 -> 122 us; 2 of 1000, W 128: 15.8
+// -> 12.7; 1 of 700, W 64: 6.9 -> 6.3; 1 of 700 with tiers, W 128: 7.8 -> 6.8; 64 of 300, 40 heads, W 128 (ring rows stored
+// by the blocks, all in one launch): 169 -> 121.
 // ------------------------------------------------------------------------------------------------
 template <bool TIERED, bool ROPE, int TENSOR>
-__device__ __forceinline__ void ring_rows_body(const QuantArgs &a, int group, uint32_t (*vtile_lds)[2048]) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+__device__ __forceinline__ void ring_rows_body(const QuantArgs &a, int win_rel, uint32_t *vtile_lds) {
+  const int lane = threadIdx.x & 63;
   const int bh = blockIdx.y, r = lane >> 2, j = lane & 3;
-  const int t0 = (a.win_blk + group * 4 + wave) * kTokBlock, t_end = a.T_len + a.n_new;
+  const int t0 = (a.win_blk + win_rel) * kTokBlock, t_end = a.T_len + a.n_new;
   if (t0 >= t_end) return;  // whole wavefront leaves; no block-wide barrier is used below
   const int t_first = max(a.T_len, t_end - a.win_len);
   const bool rotate = (TENSOR == 0 ? a.rotate_k : a.rotate_v) != 0;
@@ -550,7 +596,6 @@ __device__ __forceinline__ void ring_rows_body(const QuantArgs &a, int group, ui
       }
     }
   }
-  uint16_t *k_ring = a.k_win + (size_t)bh * a.win_len * kD, *v_ring = a.v_win + (size_t)bh * a.win_len * kD;
   const bool whole = t0 >= t_first && t0 + kTokBlock <= t_end;  // (uniform over the wavefront)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -567,60 +612,43 @@ __device__ __forceinline__ void ring_rows_body(const QuantArgs &a, int group, ui
           u[m][2 * w + 1] = half_bits_to_float(raw[h][m][w] >> 16);
         }
     }
-    if (TENSOR == 1 && whole) {
-      // The whole block fills one 32-slot tile of the V ring (the prefill case).  In a tile the values of rows r and
-      // r+16 of one channel are neighbours; this lane owns both rows and writes its 16-bit values into the wavefront's
-      // tile in LDS, half 0 and then half 1, and the finished tile goes out as eight fully coalesced 1 KB stores.
-      // (Scattered partial-line stores, as for the rows of other blocks, are several times slower.)
-      uint16_t *tile16 = reinterpret_cast<uint16_t *>(vtile_lds[wave]);
-      const int sq = r >> 2, sii = r & 3;
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t pk = token[h] ? pack_bf16x2(scaled_row_value(u[m][2 * w], kappa_s), scaled_row_value(u[m][2 * w + 1], kappa_s)) : 0u;
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const int e = 32 * m + 8 * j + 2 * w + c, nb = e >> 4, n = e & 15;
-            tile16[nb * 512 + (16 * sq + n) * 8 + 2 * sii + h] = (uint16_t)(c == 0 ? pk : pk >> 16);
-          }
-        }
-      if (h == 1) {
-        uint32_t *ring_out = reinterpret_cast<uint32_t *>(v_ring + (size_t)((t0 % a.win_len) >> 5) * 4096);  // (win_len: a multiple of 64)
-        wave_lds_sync();
-#pragma unroll
-        for (int x = 0; x < 8; ++x)
-          *reinterpret_cast<u32x4 *>(ring_out + 256 * x + 4 * lane) = *reinterpret_cast<const u32x4 *>(vtile_lds[wave] + 256 * x + 4 * lane);
-      }
-    } else if (valid[h]) {
-      store_bf16_row<TENSOR>(u, kappa_s, j, k_ring, v_ring, (t0 + 16 * h + r) % a.win_len, token[h]);
-    }
+    store_ring_half<TENSOR>(a, u, kappa_s, h, t0, lane, valid[h], token[h], whole, vtile_lds);
   }
 }
 template <int G, bool TIERED, bool ROPE>
 __global__ __launch_bounds__(256) void quantize_append_window_kernel(QuantArgs a) {
   __shared__ int slot_of_lds[4][kTokBlock];
   __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];  // one V tile (32 slots x 128 channels, bf16) per wavefront
-  const int groups = (a.n_blk + 3) / 4, group = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), win_rel = (int)blockIdx.x * 4 + wave - a.n_blk;
   if (blockIdx.z == 0) {
-    if (group >= groups) ring_rows_body<TIERED, ROPE, 0>(a, group - groups, vtile_lds);
-    else quantize_append_body<G, TIERED, ROPE, 0>(a, group, slot_of_lds);
+    if (win_rel >= 0) ring_rows_body<TIERED, ROPE, 0>(a, win_rel, vtile_lds[wave]);
+    else quantize_append_body<G, TIERED, ROPE, 0>(a, blockIdx.x, slot_of_lds);
   } else {
-    if (group >= groups) ring_rows_body<TIERED, ROPE, 1>(a, group - groups, vtile_lds);
-    else quantize_append_body<G, TIERED, ROPE, 1>(a, group, slot_of_lds);
+    if (win_rel >= 0) ring_rows_body<TIERED, ROPE, 1>(a, win_rel, vtile_lds[wave]);
+    else quantize_append_body<G, TIERED, ROPE, 1>(a, blockIdx.x, slot_of_lds);
   }
+}
+// ... or by the blocks themselves (see launch_blocks for which)
+template <int G, bool TIERED, bool ROPE>
+__global__ __launch_bounds__(256) void quantize_append_ring_kernel(QuantArgs a) {
+  __shared__ int slot_of_lds[4][kTokBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];  // one V tile (32 slots x 128 channels, bf16) per wavefront
+  int group = blockIdx.x + (blockIdx.y & a.turn);
+  if (group >= a.groups) group -= a.groups;
+  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0, true>(a, group, slot_of_lds);
+  else quantize_append_body<G, TIERED, ROPE, 1, true>(a, group, slot_of_lds, vtile_lds);
 }
 
 // ------------------------------------------------------------------------------------------------
 // The 16-bit V rows of a long salient list (text-salient layers, Section III-B.1 / III-C.1), as a pass of their own
-// behind the block kernel: one wavefront per 32-slot tile of the overlay.  It gathers the tile's rows through the salient
+// beside the blocks or behind them: one wavefront per 32-slot tile of the overlay.  It gathers the tile's rows through the salient
 // list, transforms them exactly as the block kernel does (same butterflies, same roundings) and stores the tile through
 // LDS as eight coalesced 1 KB pieces, instead of one 2-byte store per value from whichever block a row happens to sit
 // in.  Slots of the tile that are not being written (rows of earlier appends, unused slots) keep their contents: unless
 // every slot is new the tile is read into LDS first.
 // The pass reads its rows a second time and runs at the rate of a copy (5 TB/s in and out), so K rows, which are whole
 // lines wherever they come from, are left to the block kernel: 8 prompts of 4001 tokens, 1121 of them text, 32 heads:
-// block kernel 134.7 -> 147.5 us, this pass 52.5 -> 28.7 us, the call 181.2 -> 168.9 us.
+// block kernel 134.7 -> 147.5 us, this pass (alone) 52.5 -> 28.7 us, the call 181.2 -> 168.9 us.
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ void overlay_rows_body(const QuantArgs &a, int group, uint32_t (*vtile_lds)[2048]) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -723,15 +751,23 @@ __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
 }  // namespace
 
 constexpr long kResidentGroups = 4 * 256;
-// The blocks of an append, with the workgroups of its window rows behind every unit's where there is a window.
+// The blocks of an append, with the wavefronts of its window rows behind those of every unit's blocks where there is a window.
 static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t stream) {
   QuantArgs a = a_in;
   const bool tiered = a.row_tier != nullptr, rope = a.rope_cos != nullptr, window = a.win_len > 0;
   int groups = (a.n_blk + 3) / 4;
+  bool in_blocks = false;
   if (window) {
     const int t_end = a.T_len + a.n_new, t_first = t_end - a.win_len > a.T_len ? t_end - a.win_len : a.T_len;
     a.win_blk = t_first / kTokBlock;
-    groups += (a.first_blk + a.n_blk - a.win_blk + 3) / 4;
+    const int n_win = a.first_blk + a.n_blk - a.win_blk;
+    // Wavefronts of their own read and transform the window's rows a second time, but leave the blocks the short body (26 KB
+    // of code): us, that way and by the blocks themselves: one prompt of 700 tokens, 32 heads, W 64: 6.3, 6.9; 2 of 1000, W
+    // 128: 12.7, 13.4; 8 of 4096, W 512: 122, 125; 8 of 2000, W 256: 64, 68.  Where the window is more than a quarter of the
+    // blocks and there is more than two workgroups a CU that work is worth more: 64 of 300, 40 heads, W 128: 140, 121; W
+    // 64: 126, 109; 33 of 337, 4 heads, W 128: 12.1, 11.7; 4 of 320, 32 heads, W 128: 10.4, 10.0.
+    in_blocks = 4 * n_win > a.n_blk && 2l * groups * B * a.Hkv > 2 * 256;
+    if (!in_blocks) groups = (a.n_blk + n_win + 3) / 4;
   }
   // Turned orders where more workgroups than the card holds at once (four per CU) run over units of an even number of them:
   // 16 prompts of 4096 tokens (32 workgroups a unit), 32 heads: 227 -> 217 us; 8 of 4064: 113.7 -> 110.3; 8 of 5000 (40):
@@ -739,11 +775,12 @@ static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t
   // the window's workgroups in the launch (119.0, 8 of 4096 with window 512: 119.1) and cost where one round of
   // workgroups holds everything (one prompt of 2048: 9.67, 9.80) or the overlay's are in it (8 of 1920, 576 slots: 52.3, 56.0).
   a.groups = groups;
-  a.turn = !window && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
+  a.turn = (!window || in_blocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
   const dim3 grid(groups, B * a.Hkv, 2), block(256);
 #define AKVQ_LAUNCH_Q(GG, TT, RR) \
   do { \
-    if (window) hipLaunchKernelGGL((quantize_append_window_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+    if (in_blocks) hipLaunchKernelGGL((quantize_append_ring_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+    else if (window) hipLaunchKernelGGL((quantize_append_window_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
     else hipLaunchKernelGGL((quantize_append_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
   } while (0)
 #define AKVQ_LAUNCH_QR(GG, TT) do { if (rope) AKVQ_LAUNCH_Q(GG, TT, true); else AKVQ_LAUNCH_Q(GG, TT, false); } while (0)

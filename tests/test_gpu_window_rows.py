@@ -62,3 +62,31 @@ def test_tiered_rows(T, n_rows, W, with_rope):
     no_token = (tier[:, -1] == akvq.TIER_4BIT_FINE) | (tier[:, -1] == akvq.TIER_PAD)
     zero = (got[0].k_win.reshape(B, H, W, 128)[:, :, (n_rows - 1) % W] == 0).all(-1).all(-1)
     assert torch.equal(zero, no_token)
+
+
+# launches whose blocks store the ring rows themselves (a window of more than a quarter of the blocks, more than two
+# workgroups a CU; the last case also in turned orders) against the batch elements alone, which go the other way
+@pytest.mark.parametrize("B,H,T,G,W", [(65, 2, 130, 128, 64), (43, 3, 250, 64, 128), (33, 2, 1010, 128, 512)])
+@pytest.mark.parametrize("tiers,with_rope", [(False, False), (False, True), (True, False), (True, True)])
+def test_blocks_store_the_ring(B, H, T, G, W, tiers, with_rope):
+    k, v, rope = _rows(B, H, T, 7)
+    src = tier = None
+    if tiers:
+        gen = torch.Generator().manual_seed(T)
+        src = torch.randint(0, T, (B, T), generator=gen).to(torch.int32).cuda()
+        tier = torch.randint(0, 4, (B, T), generator=gen).to(torch.uint8).cuda()
+
+    def append(b):
+        c = akvq.Cache(len(range(*b.indices(B))), H, G, (T + 63) // 64 * 64, 64, fill=0)
+        c.sal_idx[:, :, 0] = T // 2
+        c.counts().fill_(1)
+        c.enable_window(W)
+        akvq.quantize_append_tiered(c, k[b].contiguous(), v[b].contiguous(), src[b].clone() if tiers else None,
+                                    tier[b].clone() if tiers else None, 0.8, 0.95, rope=rope if with_rope else None)
+        return c
+
+    whole = append(slice(0, B))
+    for b in (0, 7, B - 1):
+        alone = append(slice(b, b + 1))
+        for n in NAMES + ["k_sal", "v_sal"]:
+            assert torch.equal(getattr(whole, n)[b], getattr(alone, n)[0]), (n, b)
