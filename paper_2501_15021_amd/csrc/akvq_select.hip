@@ -981,11 +981,12 @@ __device__ __forceinline__ void to_each_row(float x, float (&v)[4]) {
   v[0] = __uint_as_float(b[0]); v[2] = __uint_as_float(b[1]);
   v[1] = __uint_as_float(c[0]); v[3] = __uint_as_float(c[1]);
 }
-// (the compiler's own fmaxf first quiets operands it cannot prove quiet)
+// The largest of three by the builtins that become one v_maximum3_f32 (the compiler's fmaxf first quiets operands it cannot
+// prove quiet).  Not by assembly: the operands are fresh matrix products and the result goes into lane swaps, and the wait
+// states that both need (eight behind a product of 16 x 16 x 32, two in front of a swap) are put in for instructions the
+// compiler knows, and for no others.
 __device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 // eight values per lane, added up over the 16 lanes of a row: lanes 2 * i and 2 * i + 1 get the sum of v[i]
 __device__ __forceinline__ float row_sums_each(const float (&v)[8], int mrow) {

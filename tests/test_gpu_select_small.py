@@ -57,3 +57,32 @@ def test_equal_masses(fill):
         assert math.isclose(float(mass.double().sum()), 2 * 64, rel_tol=1e-5)
         order = torch.sort(mass, dim=-1, descending=True, stable=True).indices[..., :16].sort(-1).values
         assert torch.equal(c.sal_idx[..., :16].long(), order)
+
+
+@pytest.mark.parametrize("T", [256, 512, 768])
+def test_one_key_far_above_the_rest(T):
+    """One key about 200 nats above all others, in each of the last sixteen places of a wavefront's 64 keys (one per head) and
+    in every wavefront: an exponent against a reference that misses it would overflow.  Its mass is that of the rows that see
+    it, the others' are below binary32; the rows that don't see it are the softmax of the rest, to the bar above."""
+    w = synth.small("spike", B=T // 64, Hq=16, Hkv=16, T=T, G=128, n_text_head=5, n_text_tail=3, top_k=8, W=64)
+    gen = torch.Generator(device="cuda").manual_seed(637)
+    # normal values, so that the other logits are within 10 nats of 0 (a generated prompt has rows whose own outliers reach
+    # 200 nats: one of 64 rows then has its mass elsewhere): the others' share is below 768 * exp(-190)
+    d = {n: torch.randn(w.B, 16, rows, 128, generator=gen, device="cuda").half() for n, rows in (("q_tail", 64), ("k", T))}
+    d["q_tail"][..., 0] = 4.0
+    d["k"][..., 0] = 0.0
+    at = 64 * torch.arange(w.B)[:, None] + 48 + torch.arange(16)[None, :]
+    for b in range(w.B):
+        for h in range(16):
+            d["k"][b, h, at[b, h]] = 0.0
+            d["k"][b, h, at[b, h], 0] = 200.0 / (4.0 * w.sm_scale)
+    c, mass = _select(w, d, 1)
+    want = _masses(d, w)
+    assert torch.isfinite(mass).all()
+    assert ((mass.double() - want).abs() <= 4e-5 * want + 1e-12).all()
+    order = torch.sort(mass, dim=-1, descending=True, stable=True).indices[..., :1]
+    assert torch.equal(c.sal_idx[..., :1].long(), order)
+    early = at < T - 64
+    assert torch.equal(c.sal_idx[..., 0].cpu().long()[early], at[early])
+    spike = mass.cpu().gather(-1, at[..., None])[..., 0]
+    assert ((spike - 64.0).abs() <= 64 * 4e-5)[early].all()
