@@ -325,8 +325,7 @@ def decode_attention(cache: Cache, q: torch.Tensor, sm_scale: float, n_split: in
                      out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None, rope=None):
     """akvq_decode_attention: returns (out [B,Hq,128] fp32, lse [B,Hq] fp32).
     rope = (cos, sin) [1, 64] or [B, 1, 64]: q holds pre-RoPE queries (akvq_decode_attention_rope)."""
-    cos, sin = rope if rope is not None else (None, None)
-    st, out, lse = (_native or native()).decode_attention(cache, q, sm_scale, n_split, flags, out, lse, cos, sin)
+    st, out, lse = (_native or native()).decode_attention(cache, q, sm_scale, n_split, flags, out, lse, rope)
     if st:
         _check(st, "akvq_decode_attention_rope" if rope is not None else
                "akvq_decode_attention_tiered" if cache.fine_mask is not None or cache.W else "akvq_decode_attention")
@@ -351,9 +350,7 @@ def decode_step(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, q: torch
                 lse: Optional[torch.Tensor] = None, rope=None):
     """akvq_decode_step: append one row per (batch, kv-head) and run decode attention over the cache including it, in
     one launch; advances cache.T_len.  Returns (out, lse)."""
-    cos, sin = rope if rope is not None else (None, None)
-    st, out, lse = (_native or native()).decode_step(cache, k_new, v_new, q, clip, sm_scale, n_split, flags, out, lse, cos,
-                                                     sin)
+    st, out, lse = (_native or native()).decode_step(cache, k_new, v_new, q, clip, sm_scale, n_split, flags, out, lse, rope)
     if st:
         _check(st, "akvq_decode_step")
     cache.T_len += 1

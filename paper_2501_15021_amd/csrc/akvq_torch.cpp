@@ -78,6 +78,7 @@ struct Call {
   akvq_rope rope;
   const akvq_window *win_p = nullptr;
   const akvq_rope *rope_p = nullptr;
+  Held rope_pair;  // keeps its tensors
   uint32_t *fine_mask = nullptr;
   int Hq = 0, n_split = 0;
   uint32_t flags = 0;
@@ -91,7 +92,7 @@ struct Call {
 
 // What both calls share.  more_rows: rows the call itself adds to the cache; check_out: out is looked at.
 void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject *n_split, PyObject *flags, PyObject *out,
-            PyObject *lse, PyObject *cos_obj, PyObject *sin_obj, int64_t more_rows, bool check_out) {
+            PyObject *lse, PyObject *rope, int64_t more_rows, bool check_out) {
   akvq_cache &k = c.cache;
   k.B = (int32_t)int_attr(cache, names.B);
   k.Hkv = (int32_t)int_attr(cache, names.Hkv);
@@ -141,8 +142,14 @@ void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject
   if (check_out) REQUIRE(c.out.scalar_type() == dtype && c.out.is_contiguous());
   if (lse == Py_None) c.lse = at::empty({B, c.Hq}, q.options().dtype(at::kFloat).requires_grad(false));
   else c.lse = tensor(lse);
-  if (cos_obj != Py_None) {
-    const at::Tensor &cos = tensor(cos_obj), &sin = tensor(sin_obj);
+  if (rope != Py_None) {  // (a pair of two tensors: None inside it is an error)
+    c.rope_pair.p = PySequence_Tuple(rope);
+    if (!c.rope_pair.p) throw Failed();
+    if (PyTuple_GET_SIZE(c.rope_pair.p) != 2) {
+      PyErr_SetString(PyExc_ValueError, "rope has to be a pair (cos, sin)");
+      throw Failed();
+    }
+    const at::Tensor &cos = tensor(PyTuple_GET_ITEM(c.rope_pair.p, 0)), &sin = tensor(PyTuple_GET_ITEM(c.rope_pair.p, 1));
     REQUIRE(cos.scalar_type() == at::kHalf && sin.scalar_type() == at::kHalf && cos.is_contiguous() && sin.is_contiguous());
     REQUIRE(cos.sizes() == sin.sizes() && cos.dim() >= 2 && cos.size(-2) == 1 && cos.size(-1) == 64);
     REQUIRE(cos.dim() == 2 || (cos.dim() == 3 && cos.size(0) == k.B));
@@ -159,16 +166,16 @@ PyObject *result(int status, Call &c) {
   return Py_BuildValue("iOO", status, out.p, lse.p);
 }
 
-// decode_attention(cache, q, sm_scale, n_split, flags, out, lse, cos, sin) -> (status, out, lse)
+// decode_attention(cache, q, sm_scale, n_split, flags, out, lse, rope) -> (status, out, lse)
 PyObject *decode_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (n != 9) {
-    PyErr_SetString(PyExc_TypeError, "decode_attention takes 9 arguments");
+  if (n != 8) {
+    PyErr_SetString(PyExc_TypeError, "decode_attention takes 8 arguments");
     return nullptr;
   }
   try {
     Call c;
-    gather(c, a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], 0, true);
+    gather(c, a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], 0, true);
     void *const out = c.out.data_ptr();
     float *const lse = static_cast<float *>(c.lse.data_ptr());
     int status;
@@ -183,11 +190,11 @@ PyObject *decode_attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
-// decode_step(cache, k_new, v_new, q, clip, sm_scale, n_split, flags, out, lse, cos, sin) -> (status, out, lse)
+// decode_step(cache, k_new, v_new, q, clip, sm_scale, n_split, flags, out, lse, rope) -> (status, out, lse)
 PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (n != 12) {
-    PyErr_SetString(PyExc_TypeError, "decode_step takes 12 arguments");
+  if (n != 11) {
+    PyErr_SetString(PyExc_TypeError, "decode_step takes 11 arguments");
     return nullptr;
   }
   try {
@@ -198,7 +205,7 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     REQUIRE(k.sizes() == at::IntArrayRef(shape, 4) && k.sizes() == v.sizes());
     const float clip = (float)number(a[4]);
     Call c;
-    gather(c, a[0], a[3], a[5], a[6], a[7], a[8], a[9], a[10], a[11], 1, false);
+    gather(c, a[0], a[3], a[5], a[6], a[7], a[8], a[9], a[10], 1, false);
     const void *const k_new = k.data_ptr(), *const v_new = v.data_ptr();
     void *const out = c.out.data_ptr();
     float *const lse = static_cast<float *>(c.lse.data_ptr());

@@ -51,3 +51,15 @@ def test_a_cache_without_its_tensors_is_an_attribute_error():
     del c.sal_cnt
     with pytest.raises(AttributeError):
         akvq.decode_attention(c, HALF, 1.0, out=OUT, lse=LSE)
+
+
+# an embedding that is there but not whole is not "no embedding"
+@pytest.mark.parametrize("rope,error", [((None, None), TypeError), ((None, TABLE), TypeError), ((TABLE, None), TypeError),
+                                        ((), ValueError), ((TABLE,), ValueError), (7, TypeError), ([None, None], TypeError)])
+def test_half_a_rotary_embedding_is_refused(rope, error):
+    c = _cache()
+    with pytest.raises(error):
+        akvq.decode_attention(c, HALF, 1.0, out=OUT, lse=LSE, rope=rope)
+    with pytest.raises(error):
+        akvq.decode_step(c, ROW, ROW, HALF, 0.8, 1.0, out=OUT, lse=LSE, rope=rope)
+    assert c.T_len == 3
