@@ -135,6 +135,7 @@ def native():
             from . import _akvq_torch
         except ImportError as e:
             raise AkvqError(f"_akvq_torch is missing ({e}): run `python -m paper_2501_15021_amd.build` first") from e
+        _akvq_torch.plain_cache(*_PLAIN, akvq_cache, akvq_window)
         _native = _akvq_torch
     return _native
 
@@ -223,6 +224,9 @@ class Cache:
     def nbytes(self) -> int:
         return sum(t.numel() * t.element_size() for t in (self.k_codes, self.v_codes, self.k_meta, self.v_meta,
                                                           self.k_sal, self.v_sal, self.sal_idx, self.sal_cnt))
+
+
+_PLAIN = Cache.struct, Cache.window_struct  # native() reads the attributes where a cache has these as they are
 
 
 def select_salient(cache: Cache, mode: int, *, is_text: Optional[torch.Tensor] = None,

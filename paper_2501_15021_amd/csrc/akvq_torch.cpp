@@ -6,6 +6,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cstring>
+
 #include <ATen/ATen.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
@@ -21,8 +23,12 @@ constexpr int64_t kHeadDim = 128;
 // Attribute names of the cache object, made once.
 struct Names {
   PyObject *B, *Hkv, *G, *T_cap, *S_cap, *T_len, *k_codes, *v_codes, *k_meta, *v_meta, *k_sal, *v_sal, *sal_idx, *sal_cnt,
-      *fine_mask, *W, *k_win, *v_win, *workspace, *decode;
+      *fine_mask, *W, *k_win, *v_win, *workspace, *decode, *struct_, *window_struct;
 } names;
+// What the package's own cache class describes itself with, and the types of the descriptions (plain_cache).
+struct Plain {
+  PyObject *struct_ = nullptr, *window_struct = nullptr, *cache_type = nullptr, *window_type = nullptr;
+} plain;
 
 struct Held {  // an owned reference
   PyObject *p = nullptr;
@@ -61,6 +67,37 @@ void *ptr_attr(PyObject *o, PyObject *name, bool optional = false) {
   if (optional && v.p == Py_None) return nullptr;
   return tensor(v.p).data_ptr();
 }
+// A cache whose method `name` is not the package's own (a derived class, a method put on the object) is asked by that method;
+// true: its description is in `out`, which `held` keeps, or it has none.  Otherwise the attributes are read, which say what the
+// own method would say without making the description in Python (3 us).
+template <typename T>
+bool described(PyObject *cache, PyObject *name, PyObject *own, PyObject *type, Held &held, T &out) {
+  Held method(PyObject_GetAttr(cache, name));
+  if (!method.p) {  // nothing to ask
+    if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw Failed();
+    PyErr_Clear();
+    return false;
+  }
+  if (PyMethod_Check(method.p) && PyMethod_GET_FUNCTION(method.p) == own) return false;
+  held.p = PyObject_CallNoArgs(method.p);
+  if (!held.p) throw Failed();
+  if (held.p == Py_None) return true;
+  const int is = type ? PyObject_IsInstance(held.p, type) : 0;
+  if (is < 0) throw Failed();
+  Py_buffer view;
+  if (is == 0 || PyObject_GetBuffer(held.p, &view, PyBUF_SIMPLE) != 0) {
+    PyErr_Format(PyExc_TypeError, "%U() of the cache did not return a descriptor", name);
+    throw Failed();
+  }
+  const bool fits = view.len == (Py_ssize_t)sizeof(T);
+  if (fits) std::memcpy(&out, view.buf, sizeof(T));
+  PyBuffer_Release(&view);
+  if (!fits) {
+    PyErr_Format(PyExc_TypeError, "%U() of the cache returned a descriptor of another size", name);
+    throw Failed();
+  }
+  return true;
+}
 double number(PyObject *o) {
   const double x = PyFloat_AsDouble(o);
   if (x == -1.0 && PyErr_Occurred()) throw Failed();
@@ -78,7 +115,7 @@ struct Call {
   akvq_rope rope;
   const akvq_window *win_p = nullptr;
   const akvq_rope *rope_p = nullptr;
-  Held rope_pair;  // keeps its tensors
+  Held rope_pair, cache_held, win_held;  // keep what the pointers come from
   uint32_t *fine_mask = nullptr;
   int Hq = 0, n_split = 0;
   uint32_t flags = 0;
@@ -94,26 +131,37 @@ struct Call {
 void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject *n_split, PyObject *flags, PyObject *out,
             PyObject *lse, PyObject *rope, int64_t more_rows, bool check_out) {
   akvq_cache &k = c.cache;
-  k.B = (int32_t)int_attr(cache, names.B);
-  k.Hkv = (int32_t)int_attr(cache, names.Hkv);
-  k.G = (int32_t)int_attr(cache, names.G);
-  k.T_cap = (int32_t)int_attr(cache, names.T_cap);
-  k.S_cap = (int32_t)int_attr(cache, names.S_cap);
-  k.T_len = (int32_t)int_attr(cache, names.T_len);
-  k.k_codes = static_cast<uint32_t *>(ptr_attr(cache, names.k_codes));
-  k.v_codes = static_cast<uint32_t *>(ptr_attr(cache, names.v_codes));
-  k.k_meta = static_cast<uint32_t *>(ptr_attr(cache, names.k_meta));
-  k.v_meta = static_cast<uint32_t *>(ptr_attr(cache, names.v_meta));
-  k.k_sal = static_cast<uint16_t *>(ptr_attr(cache, names.k_sal));
-  k.v_sal = static_cast<uint16_t *>(ptr_attr(cache, names.v_sal));
-  k.sal_idx = static_cast<int32_t *>(ptr_attr(cache, names.sal_idx));
-  k.sal_cnt = static_cast<int32_t *>(ptr_attr(cache, names.sal_cnt));
+  const int32_t cache_B = (int32_t)int_attr(cache, names.B), Hkv = (int32_t)int_attr(cache, names.Hkv);
+  const int32_t T_len = (int32_t)int_attr(cache, names.T_len);
+  if (!described(cache, names.struct_, plain.struct_, plain.cache_type, c.cache_held, k)) {
+    k.B = cache_B;
+    k.Hkv = Hkv;
+    k.G = (int32_t)int_attr(cache, names.G);
+    k.T_cap = (int32_t)int_attr(cache, names.T_cap);
+    k.S_cap = (int32_t)int_attr(cache, names.S_cap);
+    k.T_len = T_len;
+    k.k_codes = static_cast<uint32_t *>(ptr_attr(cache, names.k_codes));
+    k.v_codes = static_cast<uint32_t *>(ptr_attr(cache, names.v_codes));
+    k.k_meta = static_cast<uint32_t *>(ptr_attr(cache, names.k_meta));
+    k.v_meta = static_cast<uint32_t *>(ptr_attr(cache, names.v_meta));
+    k.k_sal = static_cast<uint16_t *>(ptr_attr(cache, names.k_sal));
+    k.v_sal = static_cast<uint16_t *>(ptr_attr(cache, names.v_sal));
+    k.sal_idx = static_cast<int32_t *>(ptr_attr(cache, names.sal_idx));
+    k.sal_cnt = static_cast<int32_t *>(ptr_attr(cache, names.sal_cnt));
+  } else if (c.cache_held.p == Py_None) {
+    PyErr_SetString(PyExc_TypeError, "struct() of the cache returned None");
+    throw Failed();
+  }
   c.fine_mask = static_cast<uint32_t *>(ptr_attr(cache, names.fine_mask, true));
   const int64_t W = int_attr(cache, names.W);
-  if (W != 0) {
-    c.win = akvq_window{static_cast<uint16_t *>(ptr_attr(cache, names.k_win)),
-                        static_cast<uint16_t *>(ptr_attr(cache, names.v_win)), (int32_t)W};
-    c.win_p = &c.win;
+  if (more_rows != 0 || W != 0 || c.fine_mask != nullptr || rope != Py_None) {
+    if (described(cache, names.window_struct, plain.window_struct, plain.window_type, c.win_held, c.win)) {
+      if (c.win_held.p != Py_None) c.win_p = &c.win;
+    } else if (W != 0) {
+      c.win = akvq_window{static_cast<uint16_t *>(ptr_attr(cache, names.k_win)),
+                          static_cast<uint16_t *>(ptr_attr(cache, names.v_win)), (int32_t)W};
+      c.win_p = &c.win;
+    }
   }
   const at::Tensor &q = tensor(q_obj);
   REQUIRE(q.scalar_type() == at::kHalf && q.is_contiguous());
@@ -127,7 +175,7 @@ void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject
   c.sm_scale = (float)number(scale);
   c.flags = (uint32_t)integer(flags);
   long n = integer(n_split);
-  if (n <= 0) n = akvq_decode_default_splits(k.B, k.Hkv, (int)(k.T_len + more_rows));
+  if (n <= 0) n = akvq_decode_default_splits(cache_B, Hkv, (int)(T_len + more_rows));
   c.n_split = (int)n;
   Held bytes(PyLong_FromSize_t(akvq_decode_workspace_bytes((int)B, c.Hq, c.n_split)));
   PyObject *args[3] = {cache, names.decode, bytes.p};
@@ -152,7 +200,7 @@ void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject
     const at::Tensor &cos = tensor(PyTuple_GET_ITEM(c.rope_pair.p, 0)), &sin = tensor(PyTuple_GET_ITEM(c.rope_pair.p, 1));
     REQUIRE(cos.scalar_type() == at::kHalf && sin.scalar_type() == at::kHalf && cos.is_contiguous() && sin.is_contiguous());
     REQUIRE(cos.sizes() == sin.sizes() && cos.dim() >= 2 && cos.size(-2) == 1 && cos.size(-1) == 64);
-    REQUIRE(cos.dim() == 2 || (cos.dim() == 3 && cos.size(0) == k.B));
+    REQUIRE(cos.dim() == 2 || (cos.dim() == 3 && cos.size(0) == cache_B));
     c.rope = akvq_rope{static_cast<const uint16_t *>(cos.data_ptr()), static_cast<const uint16_t *>(sin.data_ptr()),
                        cos.dim() == 3 ? 64 : 0};
     c.rope_p = &c.rope;
@@ -221,7 +269,18 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
+// plain_cache(struct, window_struct, cache_type, window_type): the functions of the package's own cache class, and the types
+// they return
+PyObject *plain_cache(PyObject *, PyObject *args) {
+  Plain p;
+  if (!PyArg_ParseTuple(args, "OOOO", &p.struct_, &p.window_struct, &p.cache_type, &p.window_type)) return nullptr;
+  for (PyObject *o : {p.struct_, p.window_struct, p.cache_type, p.window_type}) Py_INCREF(o);
+  plain = p;
+  Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
+    {"plain_cache", plain_cache, METH_VARARGS, nullptr},
     {"decode_attention", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(decode_attention)), METH_FASTCALL, nullptr},
     {"decode_step", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(decode_step)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
@@ -235,7 +294,8 @@ PyMODINIT_FUNC PyInit__akvq_torch(void) {
       {&names.T_len, "T_len"}, {&names.k_codes, "k_codes"}, {&names.v_codes, "v_codes"}, {&names.k_meta, "k_meta"},
       {&names.v_meta, "v_meta"}, {&names.k_sal, "k_sal"}, {&names.v_sal, "v_sal"}, {&names.sal_idx, "sal_idx"},
       {&names.sal_cnt, "sal_cnt"}, {&names.fine_mask, "fine_mask"}, {&names.W, "W"}, {&names.k_win, "k_win"},
-      {&names.v_win, "v_win"}, {&names.workspace, "workspace"}, {&names.decode, "decode"}};
+      {&names.v_win, "v_win"}, {&names.workspace, "workspace"}, {&names.decode, "decode"},
+      {&names.struct_, "struct"}, {&names.window_struct, "window_struct"}};
   for (auto &t : table)
     if ((*t.slot = PyUnicode_InternFromString(t.text)) == nullptr) return nullptr;
   return PyModule_Create(&module);

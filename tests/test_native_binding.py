@@ -63,3 +63,70 @@ def test_half_a_rotary_embedding_is_refused(rope, error):
     with pytest.raises(error):
         akvq.decode_step(c, ROW, ROW, HALF, 0.8, 1.0, out=OUT, lse=LSE, rope=rope)
     assert c.T_len == 3
+
+
+class _Asked(Exception):
+    pass
+
+
+def _ask(self):
+    raise _Asked
+
+
+def _own(cls=akvq.Cache):
+    """An object of the package's class without device memory."""
+    c = cls.__new__(cls)
+    c.__dict__.update(vars(_cache()), _ws={}, k_win=None, v_win=None)
+    return c
+
+
+def _calls(c):
+    yield lambda: akvq.decode_attention(c, HALF, 1.0, out=OUT, lse=LSE, rope=(TABLE, TABLE))
+    yield lambda: akvq.decode_step(c, ROW, ROW, HALF, 0.8, 1.0, out=OUT, lse=LSE)
+
+
+@pytest.mark.parametrize("name", ["struct", "window_struct"])
+@pytest.mark.parametrize("where", ["derived", "object", "class"])
+def test_a_cache_that_describes_itself_is_asked(monkeypatch, name, where):
+    c = _own(type("Derived", (akvq.Cache,), {name: _ask}) if where == "derived" else akvq.Cache)
+    if where == "object":
+        setattr(c, name, types.MethodType(_ask, c))
+    if where == "class":
+        akvq.native()
+        monkeypatch.setattr(akvq.Cache, name, _ask)
+    for call in _calls(c):
+        with pytest.raises(_Asked):
+            call()
+    assert c.T_len == 3
+
+
+@pytest.mark.parametrize("name,answer", [("struct", None), ("struct", 5), ("struct", b"x" * 88), ("struct", akvq.akvq_window()),
+                                         ("window_struct", 5), ("window_struct", akvq.akvq_cache())])
+def test_an_answer_that_is_no_description_is_refused(name, answer):
+    c = _own()
+    setattr(c, name, lambda: answer)
+    for call in _calls(c):
+        with pytest.raises(TypeError):
+            call()
+
+
+@pytest.mark.gpu
+def test_the_description_is_what_the_library_sees():
+    """A group size of 77, a window without memory: refused by the library before anything is launched."""
+    c = _own()
+    said = c.struct()
+    said.G = 77
+    c.struct = lambda: said
+    for call in _calls(c):
+        with pytest.raises(akvq.AkvqError, match="unsupported"):
+            call()
+    c = _own()
+    c.window_struct = lambda: akvq.akvq_window(None, None, 64)
+    for call in _calls(c):
+        with pytest.raises(akvq.AkvqError, match="invalid"):
+            call()
+    c = _own()
+    c.G = 77  # the package's own method: the attribute
+    for call in _calls(c):
+        with pytest.raises(akvq.AkvqError, match="unsupported"):
+            call()
