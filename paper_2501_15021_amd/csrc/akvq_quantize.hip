@@ -228,15 +228,16 @@ __device__ __forceinline__ void store_ring_half(const QuantArgs &a, const float 
 // ROPE: K rows arrive without their rotary position embedding; it is applied here, in front of the rotation.
 // (the tensor, 0 = K or 1 = V, is a template parameter of the body: the two differ in everything after the transform,
 // and the kernel branches once, on blockIdx.z)
+// blk_from, blk_to: the blocks (counted from a.first_blk) whose four-block groups `group` counts
 template <int G, bool TIERED, bool ROPE, int TENSOR, bool RING = false>
-__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int (*slot_of_lds)[kTokBlock],
+__device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int group, int blk_from, int blk_to, int (*slot_of_lds)[kTokBlock],
                                                      uint32_t (*vtile_lds)[2048] = nullptr) {
   // the wavefront index as a scalar: the block index, its first row and every base address derived from them then
   // live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int blk_rel = group * 4 + wave;
-  if (blk_rel >= a.n_blk) return;  // whole wavefront leaves; no block-wide barrier is used below
+  const int blk_rel = blk_from + group * 4 + wave;
+  if (blk_rel >= blk_to) return;  // whole wavefront leaves; no block-wide barrier is used below
   const int blk = a.first_blk + blk_rel;
   const int bh = blockIdx.y;
   constexpr int tensor = TENSOR;
@@ -545,8 +546,8 @@ __global__ __launch_bounds__(256) void quantize_append_kernel(QuantArgs a) {
   __shared__ int slot_of_lds[4][kTokBlock];
   int group = blockIdx.x + (blockIdx.y & a.turn);
   if (group >= a.groups) group -= a.groups;  // (turn < groups)
-  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, group, slot_of_lds);
-  else quantize_append_body<G, TIERED, ROPE, 1>(a, group, slot_of_lds);
+  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, group, 0, a.n_blk, slot_of_lds);
+  else quantize_append_body<G, TIERED, ROPE, 1>(a, group, 0, a.n_blk, slot_of_lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -622,21 +623,35 @@ __global__ __launch_bounds__(256) void quantize_append_window_kernel(QuantArgs a
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), win_rel = (int)blockIdx.x * 4 + wave - a.n_blk;
   if (blockIdx.z == 0) {
     if (win_rel >= 0) ring_rows_body<TIERED, ROPE, 0>(a, win_rel, vtile_lds[wave]);
-    else quantize_append_body<G, TIERED, ROPE, 0>(a, blockIdx.x, slot_of_lds);
+    else quantize_append_body<G, TIERED, ROPE, 0>(a, blockIdx.x, 0, a.n_blk, slot_of_lds);
   } else {
     if (win_rel >= 0) ring_rows_body<TIERED, ROPE, 1>(a, win_rel, vtile_lds[wave]);
-    else quantize_append_body<G, TIERED, ROPE, 1>(a, blockIdx.x, slot_of_lds);
+    else quantize_append_body<G, TIERED, ROPE, 1>(a, blockIdx.x, 0, a.n_blk, slot_of_lds);
   }
 }
-// ... or by the blocks themselves (see launch_blocks for which)
+// ... or by the blocks themselves (see launch_blocks for which), all of a unit's through the body with the ring stores
 template <int G, bool TIERED, bool ROPE>
 __global__ __launch_bounds__(256) void quantize_append_ring_kernel(QuantArgs a) {
   __shared__ int slot_of_lds[4][kTokBlock];
   __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];  // one V tile (32 slots x 128 channels, bf16) per wavefront
   int group = blockIdx.x + (blockIdx.y & a.turn);
   if (group >= a.groups) group -= a.groups;
-  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0, true>(a, group, slot_of_lds);
-  else quantize_append_body<G, TIERED, ROPE, 1, true>(a, group, slot_of_lds, vtile_lds);
+  if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0, true>(a, group, 0, a.n_blk, slot_of_lds);
+  else quantize_append_body<G, TIERED, ROPE, 1, true>(a, group, 0, a.n_blk, slot_of_lds, vtile_lds);
+}
+// ... or the window's blocks alone, in workgroups of their own that come first, and the others through the short body
+template <int G, bool TIERED, bool ROPE>
+__global__ __launch_bounds__(256) void quantize_append_two_bodies_kernel(QuantArgs a) {
+  __shared__ int slot_of_lds[4][kTokBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
+  const int n_plain = a.win_blk - a.first_blk, ring_groups = (a.n_blk - n_plain + 3) / 4, group = (int)blockIdx.x - ring_groups;
+  if (group < 0) {
+    if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0, true>(a, blockIdx.x, n_plain, a.n_blk, slot_of_lds);
+    else quantize_append_body<G, TIERED, ROPE, 1, true>(a, blockIdx.x, n_plain, a.n_blk, slot_of_lds, vtile_lds);
+  } else {
+    if (blockIdx.z == 0) quantize_append_body<G, TIERED, ROPE, 0>(a, group, 0, n_plain, slot_of_lds);
+    else quantize_append_body<G, TIERED, ROPE, 1>(a, group, 0, n_plain, slot_of_lds);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -737,8 +752,8 @@ __global__ __launch_bounds__(256) void quantize_append_overlay_kernel(QuantArgs 
   __shared__ __attribute__((aligned(16))) uint32_t vtile_lds[4][2048];
   const int groups = (a.n_blk + 3) / 4, group = blockIdx.x;
   if (group >= groups) overlay_rows_body(a, 2 * (group - groups) + blockIdx.z, vtile_lds);
-  else if (blockIdx.z == 0) quantize_append_body<G, false, ROPE, 0>(a, group, slot_of_lds);
-  else quantize_append_body<G, false, ROPE, 1>(a, group, slot_of_lds);
+  else if (blockIdx.z == 0) quantize_append_body<G, false, ROPE, 0>(a, group, 0, a.n_blk, slot_of_lds);
+  else quantize_append_body<G, false, ROPE, 1>(a, group, 0, a.n_blk, slot_of_lds);
 }
 
 template <int G>
@@ -750,24 +765,48 @@ __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
 
 }  // namespace
 
-constexpr long kResidentGroups = 4 * 256;
+constexpr long kCus = 256, kResidentGroups = 4 * kCus;
+// Who stores the ring rows of an append (n_win of its n_blk blocks hold window rows; units: batch elements x KV heads).
+enum class Ring { kWavefronts, kBlocks, kTwoBodies };
+static Ring ring_by(int n_blk, int n_win, long units, bool tiered, bool rope) {
+  // Wavefronts of their own leave the blocks the short body, but read and transform the window's rows a second time: that
+  // costs least where they fit into the last workgroup of a unit's blocks, or into CUs that have room.  Otherwise, with the
+  // window more than a quarter of the blocks, the blocks are the better place.  Us, wavefronts / blocks, 16-bit rows:
+  // 64 prompts of 300 tokens, 40 heads, W 128: 140 / 121; 33 of 337, 4 heads, W 128: 12.1 / 11.7; without a workgroup more:
+  // 7 of 150, 32 heads, W 64: 9.3 / 11.2; a small window: 8 of 4096, 32 heads, W 512: 122 / 125.
+  const int groups = (n_blk + 3) / 4, with_ring = (n_blk + n_win + 3) / 4, extra = with_ring - groups;
+  const long in_blocks = 2 * units * groups, alone = 2 * units * with_ring;  // workgroups
+  if (4 * n_win <= n_blk) return Ring::kWavefronts;
+  // (one or two blocks, all of the window, no workgroup more: 16 of 40 tokens, 32 heads, 9.6 / 9.0; 32 of 64, 17.6 / 18.8)
+  if (extra == 0) return n_win == n_blk && in_blocks > 2 * kCus && in_blocks <= kResidentGroups ? Ring::kBlocks : Ring::kWavefronts;
+  if (in_blocks <= 2 * kCus) {
+    // Up to two workgroups a CU it is the rounds of workgroups that count.  Two more are never worth it: 7 of 128, 32 heads,
+    // W 128 (448 or 896 workgroups) 11.2 / 9.3.  One more is not where their number doubles (33 of 128, 4 heads: 8.8 / 8.2;
+    // within the first round 5.9 / 6.2) and, with the rotary embedding or tiers, where ring and block wavefronts share a
+    // workgroup (rotary: 4 of 200, 32 heads, W 128: 9.3 / 8.5, but 2 of 256, 8 blocks: 6.5 / 7.4; both, 3 of 64: 7.4 / 6.6).
+    const long rounds = (alone + kCus - 1) / kCus - (in_blocks + kCus - 1) / kCus;
+    const bool doubled = extra >= groups, shared = n_blk % 4 != 0;
+    const bool dear = tiered ? doubled && shared : (doubled && in_blocks > kCus) || (rope && shared && 2 * extra >= groups && in_blocks >= kCus);
+    if (rounds == 0 || (rounds == 1 && !dear)) return Ring::kWavefronts;
+  }
+  // A window of up to a third of the blocks whose groups come out even, all workgroups resident: 4 of 300, 32 heads, W 64: 9.65 by
+  // wavefronts, 9.24 by the body with the ring stores for all blocks, 8.78 by both bodies.
+  const bool same_groups = (n_blk - n_win + 3) / 4 + (n_win + 3) / 4 == groups;
+  if (3 * n_win <= n_blk && same_groups && in_blocks <= kResidentGroups) return Ring::kTwoBodies;
+  return Ring::kBlocks;
+}
 // The blocks of an append, with the wavefronts of its window rows behind those of every unit's blocks where there is a window.
 static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t stream) {
   QuantArgs a = a_in;
   const bool tiered = a.row_tier != nullptr, rope = a.rope_cos != nullptr, window = a.win_len > 0;
   int groups = (a.n_blk + 3) / 4;
-  bool in_blocks = false;
+  Ring ring = Ring::kWavefronts;
   if (window) {
     const int t_end = a.T_len + a.n_new, t_first = t_end - a.win_len > a.T_len ? t_end - a.win_len : a.T_len;
     a.win_blk = t_first / kTokBlock;
     const int n_win = a.first_blk + a.n_blk - a.win_blk;
-    // Wavefronts of their own read and transform the window's rows a second time, but leave the blocks the short body (26 KB
-    // of code): us, that way and by the blocks themselves: one prompt of 700 tokens, 32 heads, W 64: 6.3, 6.9; 2 of 1000, W
-    // 128: 12.7, 13.4; 8 of 4096, W 512: 122, 125; 8 of 2000, W 256: 64, 68.  Where the window is more than a quarter of the
-    // blocks and there is more than two workgroups a CU that work is worth more: 64 of 300, 40 heads, W 128: 140, 121; W
-    // 64: 126, 109; 33 of 337, 4 heads, W 128: 12.1, 11.7; 4 of 320, 32 heads, W 128: 10.4, 10.0.
-    in_blocks = 4 * n_win > a.n_blk && 2l * groups * B * a.Hkv > 2 * 256;
-    if (!in_blocks) groups = (a.n_blk + n_win + 3) / 4;
+    ring = ring_by(a.n_blk, n_win, (long)B * a.Hkv, tiered, rope);
+    if (ring == Ring::kWavefronts) groups = (a.n_blk + n_win + 3) / 4;
   }
   // Turned orders where more workgroups than the card holds at once (four per CU) run over units of an even number of them:
   // 16 prompts of 4096 tokens (32 workgroups a unit), 32 heads: 227 -> 217 us; 8 of 4064: 113.7 -> 110.3; 8 of 5000 (40):
@@ -775,11 +814,12 @@ static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t
   // the window's workgroups in the launch (119.0, 8 of 4096 with window 512: 119.1) and cost where one round of
   // workgroups holds everything (one prompt of 2048: 9.67, 9.80) or the overlay's are in it (8 of 1920, 576 slots: 52.3, 56.0).
   a.groups = groups;
-  a.turn = (!window || in_blocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
+  a.turn = (!window || ring == Ring::kBlocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
   const dim3 grid(groups, B * a.Hkv, 2), block(256);
 #define AKVQ_LAUNCH_Q(GG, TT, RR) \
   do { \
-    if (in_blocks) hipLaunchKernelGGL((quantize_append_ring_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+    if (ring == Ring::kTwoBodies) hipLaunchKernelGGL((quantize_append_two_bodies_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
+    else if (ring == Ring::kBlocks) hipLaunchKernelGGL((quantize_append_ring_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
     else if (window) hipLaunchKernelGGL((quantize_append_window_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
     else hipLaunchKernelGGL((quantize_append_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
   } while (0)
