@@ -847,9 +847,21 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
   if (a.S_cap > 64 && a.row_tier == nullptr) {
     QuantArgs blocks = a;
     blocks.skip_overlay = 1;
-    const int overlay_groups = (a.S_cap / kTokBlock + 3) / 4;
-    if (a.win_len <= 0) {
-      const dim3 grid((a.n_blk + 3) / 4 + (overlay_groups + 1) / 2, B * a.Hkv, 2), block(256);
+    const int overlay_groups = (a.S_cap / kTokBlock + 3) / 4, n_units = B * a.Hkv;
+    // (Not for one or two blocks of so many units that the blocks' workgroups alone fill the card: the overlay's, most of them
+    // with nothing to do, then stand in the way of the blocks.  128 prompts of 8 tokens, 8 heads, 128 slots: 10.7 us in a
+    // launch behind the blocks, 15.3 in theirs.)
+    if (a.win_len <= 0 && !(a.n_blk <= 2 && 2l * n_units >= kResidentGroups)) {
+      // Workgroups go to the XCDs in turn: with four a unit the blocks' all sit on the same two of eight, with any even number
+      // some XCDs have more of the blocks than others.  One idle workgroup a unit more, where the launch is large enough for that
+      // to show, us without and with it: 16 prompts of 80 tokens, 32 heads, 576 slots, 17 rows before: 24.8, 14.1 (two
+      // launches: 10.8); 32 of 300, 1152 slots: 89, 36 (42.4); below, it costs: 4 of 100, 1152 slots, 5.8, 7.5.  At exactly four
+      // workgroups a CU, four a unit: 4 of 100, 576 slots, 8.6, 6.0, but 4 of 8, one block a unit, 4.7, 5.7.
+      int groups = (a.n_blk + 3) / 4 + (overlay_groups + 1) / 2;
+      const long launch = 2l * n_units * groups;
+      const bool filled = launch > kResidentGroups || (launch == kResidentGroups && a.n_blk > 2);
+      if (groups % 2 == 0 && (launch > 6 * kCus || (groups % 4 == 0 && filled))) ++groups;
+      const dim3 grid(groups, n_units, 2), block(256);
       const bool rope = a.rope_cos != nullptr;
 #define AKVQ_LAUNCH_O(GG, RR) hipLaunchKernelGGL((quantize_append_overlay_kernel<GG, RR>), grid, block, 0, stream, blocks)
       if (G == 128) { if (rope) AKVQ_LAUNCH_O(128, true); else AKVQ_LAUNCH_O(128, false); }
@@ -859,7 +871,7 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
     }
     hipError_t e = launch_blocks(blocks, B, G, stream);
     if (e != hipSuccess) return e;
-    const dim3 grid(overlay_groups, B * a.Hkv), block(256);
+    const dim3 grid(overlay_groups, n_units), block(256);
     hipLaunchKernelGGL(overlay_rows_kernel, grid, block, 0, stream, a);
     return hipGetLastError();
   }

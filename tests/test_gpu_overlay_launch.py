@@ -41,3 +41,22 @@ def test_overlay_rows(B, H, T, G, slots, n, pieces, with_rope):
         for tile in range((m + 31) // 32):
             assert torch.equal(long.v_sal[:, :, s // 32 + tile], short.v_sal[:, :, tile]), (s, tile)
         assert torch.equal(long.k_codes, short.k_codes) and torch.equal(long.v_codes, short.v_codes)
+
+
+# many units, against batch elements appended alone (few units: no idle workgroup, one launch): an idle workgroup a unit (four and
+# six without it), behind rows that leave a block half full, and one or two blocks whose overlay goes out in a second launch
+@pytest.mark.parametrize("B,H,T,slots,before", [(65, 2, 80, 576, 17), (43, 6, 300, 1152, 0), (256, 2, 40, 128, 0), (103, 5, 9, 192, 50),
+                                                (60, 5, 100, 256, 30)])
+@pytest.mark.parametrize("with_rope", [False, True])
+def test_overlay_of_many_units(B, H, T, slots, before, with_rope):
+    n = before + T
+    d = synth.generate(synth.small("ovm", B=B, Hq=H, Hkv=H, T=n, G=128, n_text_head=5, n_text_tail=3, top_k=8, W=16 if n < 64 else 64), seed=93,
+                       device="cuda")
+    rope = tuple(torch.from_numpy(t).cuda() for t in synth.rope_tables(torch.arange(n).numpy())) if with_rope else None
+    rows = sorted(torch.randperm(n, generator=torch.Generator().manual_seed(n))[:min(slots, n)].tolist())
+    cuts = (0, before, n) if before else (0, n)
+    whole = _append(d["k"], d["v"], 128, rows, slots, rope, cuts)
+    for b in (0, 7, B - 1):
+        alone = _append(d["k"][b:b + 1], d["v"][b:b + 1], 128, rows, slots, rope, cuts)
+        for name in ("k_sal", "v_sal", "k_codes", "v_codes", "k_meta", "v_meta"):
+            assert torch.equal(getattr(whole, name)[b], getattr(alone, name)[0]), (name, b)
