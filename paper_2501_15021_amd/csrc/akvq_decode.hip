@@ -1272,7 +1272,11 @@ static void launch_decode_stream(DecodeArgs a, hipStream_t stream) {
   // (Beyond that, eight need more registers than two workgroups of a CU have between them: 384 of them, tiered rows,
   // took 21.7 us instead of 18.7.)
   const long workgroups = (long)a.B * a.Hkv * a.n_split;
-  const bool wide = workgroups <= kCus && decode_tiles_per_split((a.t_win + rows - 1) / rows, a.n_split) > kWaves;
+  // Eight also where a split's few tiles would do with four, but a fused step leaves one split more 16-bit rows than those have
+  // units for (the salient ones, and the window's in the grouped-query kernel): 1100 rows, 28/4 heads, window 512, 8 splits:
+  // 19.2 us with four, 15.7 with eight.
+  const int alone = !a.fused_append || a.n_split == 1 ? 0 : mha ? a.S_cap : a.S_cap + (a.win_len < a.T_len ? a.win_len : a.T_len);
+  const bool wide = workgroups <= kCus && (decode_tiles_per_split((a.t_win + rows - 1) / rows, a.n_split) > kWaves || alone > kWaves * kRowUnit);
   a.paced = !mha && !wide && workgroups <= 2 * kCus;
   if (mha) {
     if (wide) hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWavesWide>), grid, dim3(64 * kWavesWide), 0, stream, a);

@@ -32,7 +32,7 @@ def _rows_plan(n_rows, tiers, B):
         T -= 1
 
 
-def _steps(orc, B, Hkv, R, G, tiles, n_split, window, tiers, n_steps=2):
+def _steps(orc, B, Hkv, R, G, tiles, n_split, window, tiers, n_steps=2, slots=64):
     tile = 64 if R == 1 else 32
     # all steps append to the last of `tiles` tiles of every split's run
     T0, plan = _rows_plan((tiles * n_split - 1) * tile + tile // 2, tiers, B)
@@ -41,9 +41,11 @@ def _steps(orc, B, Hkv, R, G, tiles, n_split, window, tiers, n_steps=2):
     t_cap = (rows0 + n_steps + 63) // 64 * 64
     rng = np.random.default_rng(B * 1000 + tiles * 10 + R)
     k, v = (rng.standard_normal((B, Hkv, T0 + n_steps, 128)).astype(np.float16) for _ in range(2))
-    oc = orc.OracleCache(B, Hkv, G, t_cap, 64, fill=0)
-    step, apart = (akvq.Cache(B, Hkv, G, t_cap, 64, fill=0) for _ in range(2))
+    oc = orc.OracleCache(B, Hkv, G, t_cap, slots, fill=0)
+    step, apart = (akvq.Cache(B, Hkv, G, t_cap, slots, fill=0) for _ in range(2))
     listed = [3, rows0 - 40, rows0 + 1] if plan is None else [rows0 + 1]  # one of the new rows is salient
+    if slots > 64:
+        listed = list(range(1, 2 * min(slots - 20, rows0 // 2 - 20), 2)) + listed[-1:]
     oc.sal_idx[:, :, :len(listed)] = listed
     oc.sal_cnt[:] = len(listed)
     for c in (step, apart):
@@ -97,3 +99,11 @@ def test_beyond_two_workgroups_per_cu(orc, R, G, B):  # 512 and 520 workgroups
 @pytest.mark.parametrize("window,tiers", [(0, False), (64, False), (0, True), (128, True)])
 def test_eight_wavefronts(orc, R, G, tiles, n_split, window, tiers):
     _steps(orc, 2, 3, R, G, tiles, n_split, window, tiers)
+
+
+# up to four tiles a split, but a step with more 16-bit rows than four wavefronts have units for: eight all the same
+@pytest.mark.parametrize("R,G,window,slots", [(7, 64, 512, 64), (4, 128, 128, 64), (6, 64, 0, 192), (1, 128, 0, 256), (1, 64, 512, 192)])
+@pytest.mark.parametrize("tiles,n_split", [(2, 8), (4, 3)])
+@pytest.mark.parametrize("tiers", [False, True])
+def test_eight_wavefronts_of_few_tiles(orc, R, G, window, slots, tiles, n_split, tiers):
+    _steps(orc, 2, 3, R, G, tiles, n_split, window, tiers, slots=slots if not tiers else 64 if slots == 64 else 128)
