@@ -122,7 +122,8 @@ int akvq_cache_bytes(const akvq_cache *shape, size_t out_bytes[8]);
  * grows with the other arguments kept, so a workspace sized for the largest batch and the longest prompt serves all. */
 size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W);
 size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split);
-/* Host helper: number of KV splits akvq_decode_attention uses when n_split <= 0 is passed. */
+/* Host helper: the most KV splits the decode calls use when n_split <= 0 is passed (fewer where a short context does not gain
+ * from them); what their workspace has to be sized for then.  Does not shrink when T_len grows. */
 int akvq_decode_default_splits(int B, int Hkv, int T_len);
 
 /* Host helper: how the decode kernels deal the n_tiles tiles of the code stream (64 rows each when Hq == Hkv, else 32)
@@ -193,7 +194,8 @@ int akvq_quantize_append(const akvq_cache *c, const void *k_new, const void *v_n
  *   fp32 accumulation.  Output is rotated back by H_128 unless AKVQ_OUT_ROTATED.
  *   q: device [B][Hq][128] binary16.  out: device [B][Hq][128] fp32 (binary16 with AKVQ_OUT_FP16).  lse_out: optional
  *   device [B][Hq] fp32.
- *   n_split <= 0 picks akvq_decode_default_splits().  workspace: device, akvq_decode_workspace_bytes() bytes.
+ *   n_split <= 0 lets the library choose, akvq_decode_default_splits() at most.  workspace: device,
+ *   akvq_decode_workspace_bytes() bytes of n_split, or of that maximum.
  */
 int akvq_decode_attention(const akvq_cache *c, const void *q, int Hq, float sm_scale, void *out, float *lse_out,
                           int n_split, void *workspace, size_t workspace_bytes, uint32_t flags, void *stream);
@@ -265,8 +267,8 @@ int akvq_decode_attention_rope(const akvq_cache *c, const uint32_t *fine_mask, c
  *   [B][Hkv][1][128] binary16) are written to cache row T_len exactly as akvq_quantize_append_rope would write a single
  *   plain row (codes, meta, the recent-window rings, the overlay if the row is listed in c->sal_idx), then decode
  *   attention runs over the T_len + 1 rows as akvq_decode_attention_rope would: the cache holds the bits of the
- *   separate append, the output those of the separate decode call when n_split is 1 (with more splits the 16-bit rows
- *   are all read by one split, so they enter the sums in another order).  The new row is written by the workgroups
+ *   separate append, the output those of the separate decode call when n_split is 1 (with more splits 16-bit rows are
+ *   dealt to other splits than in that call, so they enter the sums in another order).  The new row is written by the workgroups
  *   of the KV split that holds the row's tile (akvq_decode_split_range) before they read it; no other workgroup
  *   reads it.
  *   c->T_len is the number of rows already cached (0 is allowed); advance it by one

@@ -97,33 +97,7 @@ size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
 
 int akvq_decode_default_splits(int B, int Hkv, int T_len) {
   if (B <= 0 || Hkv <= 0 || T_len <= 0) return 1;
-  const long units = (long)B * Hkv;
-  if (units >= 512) return 1;                  // already two workgroups per CU: finish in one kernel, no merge pass
-  const int tiles = (T_len + 63) / 64;
-  if (units <= 64) {
-    // Few units: one workgroup per CU, of eight wavefronts, and one merge.  From 1024 rows on (below, the merge launch costs
-    // what the split gains: 1 x 700 rows, 28/4 heads, 9.0 us in 1, 4 or 8 splits; 640 rows, 32 heads, 6.7 in 1, 7.7 in 8),
-    // two tiles a workgroup at least, and up to 32 splits: what the merge reads in one round trip (64 where 512 tiles and
-    // more make the streams longer than a second one).  A step of one sequence, us, before (at least 16 tiles per
-    // workgroup, so 19 of them per unit) and now: 28/4 heads, 20011 rows with window and rotary embedding, 16.0 -> 12.7;
-    // 2100 rows 13.7 -> 10.3; 12000 rows 14.0 -> 10.9; 12/2 heads, 4000 rows 14.3 -> 10.2; 32 heads, 2500 rows 10.8 -> 8.8,
-    // 8000 rows 11.9 -> 11.4; 16 x 2000 rows, 28/4 heads, 14.4 -> 13.1.  Over 33 shapes the least time of any split count
-    // is on average 1 % lower, at most 5 %.
-    if (T_len < 1024) return 1;
-    long n = 256 / units;
-    if (n > 32) n = tiles >= 512 && n >= 64 ? 64 : 32;
-    return (int)(n < tiles / 2 ? n : tiles / 2);
-  }
-  // Workgroups of four wavefronts mostly; the figures below were measured with them.
-  long want = (512 + units - 1) / units;       // two workgroups per CU; more splits only add merge work
-  long cap = tiles / 16 > 1 ? tiles / 16 : 1;  // keep at least 16 64-token tiles per workgroup
-  if (want > cap) want = cap;
-  if (want > 64) want = 64;
-  if (want < 1) want = 1;
-  // A split adds the merge launch (about 8 us end to end): with more than 128 units it only pays when every workgroup
-  // still streams at least 48 tiles (measured: 256 units of 64 tiles run 19.7 us unsplit, 21.7 us in two splits).
-  if (units > 128 && tiles / want < 48) want = tiles / 48 > 1 ? tiles / 48 : 1;
-  return (int)want;
+  return akvq::decode_most_splits((long)B * Hkv, T_len);
 }
 
 int akvq_decode_split_range(int n_tiles, int n_split, int split, int *begin, int *end) {
@@ -318,9 +292,9 @@ int akvq_decode_attention_static(const akvq_cache *c, const void *q, int Hq, flo
                                  int n_split, uint32_t flags, void *stream) {
   // size check first, on the host, so that an oversize request launches nothing and touches no device state
   if (!c || c->B <= 0 || c->Hkv <= 0 || Hq <= 0) return AKVQ_ERR_INVALID_ARG;
-  if (n_split <= 0) n_split = akvq_decode_default_splits(c->B, c->Hkv, c->T_len);
   if (n_split > 1024) return AKVQ_ERR_INVALID_ARG;
-  if (akvq_decode_workspace_bytes(c->B, Hq, n_split) > akvq::kDecodeStaticScratchBytes) return AKVQ_ERR_WORKSPACE;
+  const int most = n_split > 0 ? n_split : akvq_decode_default_splits(c->B, c->Hkv, c->T_len);
+  if (akvq_decode_workspace_bytes(c->B, Hq, most) > akvq::kDecodeStaticScratchBytes) return AKVQ_ERR_WORKSPACE;
   void *ws = nullptr;
   const hipError_t e = akvq::decode_static_scratch(&ws);
   if (e != hipSuccess) return hip_status(e);
@@ -337,7 +311,7 @@ int akvq_decode_attention_tiered(const akvq_cache *c, const uint32_t *fine_mask,
 
 static int decode_args(const akvq_cache *c, const uint32_t *fine_mask, const akvq_window *win, const void *q,
                        const akvq_rope *rope, int Hq, float sm_scale, void *out, float *lse_out, int n_split,
-                       void *workspace, size_t workspace_bytes, uint32_t flags, akvq::DecodeArgs &a) {
+                       void *workspace, size_t workspace_bytes, uint32_t flags, bool fused, akvq::DecodeArgs &a) {
   if (fine_mask && !aligned16(fine_mask)) return AKVQ_ERR_INVALID_ARG;
   int st = check_rope(rope, flags & AKVQ_Q_PREROTATED);
   if (st != AKVQ_OK) return st;
@@ -353,7 +327,8 @@ static int decode_args(const akvq_cache *c, const uint32_t *fine_mask, const akv
   if (Hq <= 0 || Hq % c->Hkv != 0) return AKVQ_ERR_INVALID_ARG;
   if (Hq / c->Hkv > 8) return AKVQ_ERR_UNSUPPORTED;
   if (too_many_units((long)c->B * c->Hkv)) return AKVQ_ERR_UNSUPPORTED;
-  if (n_split <= 0) n_split = akvq_decode_default_splits(c->B, c->Hkv, c->T_len);
+  const bool choose = n_split <= 0;
+  if (choose) n_split = akvq_decode_default_splits(c->B, c->Hkv, c->T_len);
   if (n_split > 1024) return AKVQ_ERR_INVALID_ARG;
   if (!workspace || !aligned16(workspace)) return AKVQ_ERR_INVALID_ARG;
   if (workspace_bytes < akvq_decode_workspace_bytes(c->B, Hq, n_split)) return AKVQ_ERR_WORKSPACE;
@@ -370,7 +345,8 @@ static int decode_args(const akvq_cache *c, const uint32_t *fine_mask, const akv
   a.partial = static_cast<float *>(workspace);
   a.out = out; a.lse = lse_out;
   a.B = c->B; a.Hq = Hq; a.Hkv = c->Hkv; a.T_cap = c->T_cap; a.S_cap = c->S_cap; a.T_len = c->T_len;
-  a.n_split = n_split; a.sm_scale = sm_scale;
+  a.n_split = choose ? akvq::decode_splits(a, fused) : n_split;
+  a.sm_scale = sm_scale;
   if (rope) { a.rope_cos = rope->cos; a.rope_sin = rope->sin; a.rope_stride = rope->batch_stride; }
   a.q_rotated = (flags & AKVQ_Q_PREROTATED) ? 1 : 0;
   a.out_rotated = (flags & AKVQ_OUT_ROTATED) ? 1 : 0;
@@ -383,7 +359,7 @@ int akvq_decode_attention_rope(const akvq_cache *c, const uint32_t *fine_mask, c
                                void *workspace, size_t workspace_bytes, uint32_t flags, void *stream) {
   akvq::DecodeArgs a;
   const int st = decode_args(c, fine_mask, win, q, rope, Hq, sm_scale, out, lse_out, n_split, workspace,
-                             workspace_bytes, flags, a);
+                             workspace_bytes, flags, false, a);
   if (st != AKVQ_OK) return st;
   return hip_status(akvq::launch_decode_attention(a, c->G, static_cast<hipStream_t>(stream)));
 }
@@ -400,7 +376,7 @@ int akvq_decode_step(const akvq_cache *c, const uint32_t *fine_mask, const akvq_
   after.T_len = c->T_len + 1;
   akvq::DecodeArgs a;
   st = decode_args(&after, fine_mask, win, q, rope, Hq, sm_scale, out, lse_out, n_split, workspace, workspace_bytes,
-                   flags, a);
+                   flags, true, a);
   if (st != AKVQ_OK) return st;
   a.fused_append = 1;
   a.step = qa;

@@ -77,6 +77,66 @@ __host__ __device__ inline int decode_last_tile_split(int n_tiles, int n_split) 
   if (n_tiles <= 0) return 0;
   return (n_tiles - 1) / decode_tiles_per_split(n_tiles, n_split);
 }
+// ---- how many KV splits: one workgroup per (unit, split), unit = (batch, kv-head) ----
+// Two workgroups per CU, measured with workgroups of four wavefronts, which most launches of more than 64 units have.
+inline int decode_splits_by_two(long units, int tiles) {
+  if (units >= 512) return 1;                  // already two workgroups per CU: finish in one kernel, no merge pass
+  long want = (512 + units - 1) / units;       // more splits only add merge work
+  const long cap = tiles / 16 > 1 ? tiles / 16 : 1;  // keep at least 16 64-token tiles per workgroup
+  if (want > cap) want = cap;
+  if (want > 64) want = 64;
+  // A split adds the merge launch (about 8 us end to end): with more than 128 units it only pays when every workgroup
+  // still streams at least 48 tiles (measured: 256 units of 64 tiles run 19.7 us unsplit, 21.7 us in two splits).
+  if (units > 128 && tiles / want < 48) want = tiles / 48 > 1 ? tiles / 48 : 1;
+  return (int)want;
+}
+// Up to 64 units: one workgroup per CU at most, of eight wavefronts, and one merge; two tiles a workgroup at least, and up to 32
+// splits, what the merge reads in one round trip (64 where 512 tiles and more make the streams longer than a second one).
+// None below 1024 rows (1 x 700 rows, 28/4 heads, 9.0 us in 1, 4 or 8 splits; 640 rows, 32 heads, 6.7 in 1, 7.7 in 8).
+// Us in decode_splits_by_two and so: a step of 20011 rows, 28/4 heads, with window and rotary embedding, 16.0, 12.7; 12000 rows
+// 14.0, 10.9; 12/2 heads, 4000 rows 14.3, 10.2; 32 heads, 2500 rows 10.8, 8.8, 8000 rows 11.9, 11.4.  Rounding 256 / units
+// down leaves up to a fifth of the CUs idle, and is still faster at 33 to 60 units: decode of 52 units, 28/4 heads, 2048 / 8192 /
+// 32768 rows, 13.5 / 18.5 / 41.9 us in 2 / 8 / 10 splits and 12.5 / 17.7 / 37.1 in 4; 104 shapes of 1 to 64 units, 2048 to
+// 131072 rows: nowhere slower.  (Two full rounds of four wavefronts, 512 / units, are better still on long streams that leave
+// CUs idle: 52 units of 32768 rows, 9 splits, 35.3; 44 and 60 units: equal.)
+inline int decode_most_splits(long units, int T_len) {
+  const int tiles = (T_len + 63) / 64;
+  if (units > 64) return decode_splits_by_two(units, tiles);
+  if (T_len < 1024) return 1;
+  long n = 256 / units;
+  if (n > 32) n = tiles >= 512 && n >= 64 ? 64 : 32;
+  return (int)(n < tiles / 2 ? n : tiles / 2);
+}
+// What a call without a split count gets: as many, or decode_splits_by_two where the streams are so short that the merge
+// launch costs what the splits gain.  Where that is depends on how much of the work the splits share: 16-bit rows are dealt to
+// them too (good from 1024 rows on: 2 x 1024 rows, 28/4 heads, window 512, 1 split or 8: 12.9 and 10.2 us), but a fused step
+// of the grouped-query kernel leaves all of them, and one of either kernel the salient ones, to the split that appends (same
+// shape, a step: 14.6 and 15.8).  It depends on how many splits there are: with more than 48 units four or five share what
+// eight wavefronts did in one (60 x 1024, 8/1 heads: 9.6, 10.8).  Steps of 13 to 48 units with such rows pay later (4 x 1024
+// rows, 32/8 heads, window 64: 11.2, 12.5).  5772 calls of 1 to 64 units, 1024 to 5000 rows, against decode_splits_by_two for
+// all: with decode_most_splits for all 848 were more than 2.5 % slower, 224 of them more than 10 %; so 97 and none.
+inline int decode_splits(const DecodeArgs &a, bool fused) {
+  const long units = (long)a.B * a.Hkv;
+  const int most = decode_most_splits(units, a.T_len);
+  if (units > 64 || most == 1) return most;
+  const bool mha = a.Hq == a.Hkv;
+  const int win = a.T_len - a.t_win, listed = a.S_cap > 64 ? a.S_cap : 0;
+  int from;  // rows from which on the splits pay
+  if (!fused && win + listed >= 256) from = 1024;
+  else if (mha && fused) from = units > 48 ? 1153 : 1024;
+  else if (mha) from = units > 48 ? (win > 0 ? 1473 : 1985) : units > 32 && win == 0 ? 1473 : 1024;
+  else if (units > 48) from = 1729;
+  else if (fused) from = units > 12 && win + listed > 0 ? 1217 : 1024;
+  else from = 1281;
+  if (fused) {
+    const int alone = (mha ? 0 : win) + listed;
+    if (alone > 128) from += 5 * (alone - 128) / 2;
+    if (mha && listed > 0 && units > 12) from += 256;
+  }
+  if (a.T_len >= from) return most;
+  const int few = decode_splits_by_two(units, (a.T_len + 63) / 64);
+  return few < most ? few : most;
+}
 // How the units of 32 16-bit rows are dealt in the one-head kernel: index i of a wavefront runs from first in steps of step while it is below
 // limit, and stands for unit(i).  From the last wavefront on (when the tiles do not divide evenly, the last ones have one
 // tile less), to the splits before the wavefronts.

@@ -174,10 +174,10 @@ void gather(Call &c, PyObject *cache, PyObject *q_obj, PyObject *scale, PyObject
   c.q = q.data_ptr();
   c.sm_scale = (float)number(scale);
   c.flags = (uint32_t)integer(flags);
-  long n = integer(n_split);
-  if (n <= 0) n = akvq_decode_default_splits(cache_B, Hkv, (int)(T_len + more_rows));
-  c.n_split = (int)n;
-  Held bytes(PyLong_FromSize_t(akvq_decode_workspace_bytes((int)B, c.Hq, c.n_split)));
+  const long n = integer(n_split);
+  c.n_split = n > 0 ? (int)n : 0;
+  const int most = n > 0 ? (int)n : akvq_decode_default_splits(cache_B, Hkv, (int)(T_len + more_rows));
+  Held bytes(PyLong_FromSize_t(akvq_decode_workspace_bytes((int)B, c.Hq, most)));
   PyObject *args[3] = {cache, names.decode, bytes.p};
   Held ws(PyObject_VectorcallMethod(names.workspace, args, 3 | PY_VECTORCALL_ARGUMENTS_OFFSET, nullptr));
   if (!ws.p) throw Failed();
