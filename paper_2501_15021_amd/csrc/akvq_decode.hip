@@ -541,21 +541,33 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
   // (The kernel for plain caches of one group fits four wavefronts per SIMD, which takes asking for the second token group
   // after the first.)
   constexpr bool kBothGroups = PAIRS || NG == 2 || NW == kWavesWide;
+  const int cnt_sal = min(max(sal_cnt_early, 0), a.S_cap), win_rows = min(a.win_len, a.T_len);  // (slots behind T_len hold no row)
+  // In launches of a workgroup per CU and more without splits (a.row_pairs) issue takes the time and not latency: two units
+  // share a softmax step, the second requested behind the first.  Us by units and by pairs of them: 512 workgroups of 400 rows,
+  // window 128 (five units for four wavefronts) 13.7, 12.9; 1024 of 64 rows, 64 of them pivots, 11.2, 10.2; up to two workgroups
+  // per CU, a unit or none for each wavefront: 320 of 400 rows, 64 of them pivots, 9.6, 10.5.
+  const int n_units = (cnt_sal + kRowUnit - 1) / kRowUnit + (win_rows + kRowUnit - 1) / kRowUnit;
+  // (eight wavefronts: no longer where the pairs take a second round: 576 salient rows, 256 workgroups of 1000 rows, 20.6, 22.0)
+  const bool pairs = a.row_pairs > 0 && n_units >= a.row_pairs && (NW == kWaves || n_units <= 2 * NW + 1);
   auto bf16_units = [&](const uint16_t *ks_base, const uint16_t *vs_base, int cnt, const RowUnits units, auto &&row_ok) {
     for (int i = units.first; i < units.limit; i += units.step) {
-      const int unit = units.unit(i), s_lane = unit * kRowUnit + lane;
-      const int n_grp = min(2, (cnt - unit * kRowUnit + 15) >> 4);  // token groups (16 slots) that hold rows
+      const int unit = pairs ? 2 * i : units.unit(i), s_lane = unit * kRowUnit + lane;
+      if (unit * kRowUnit >= cnt) continue;
+      const int n_grp = min(pairs ? 4 : 2, (cnt - unit * kRowUnit + 15) >> 4);  // token groups (16 slots) that hold rows
       const bool row_valid = row_ok(s_lane);  // fetched whatever cnt says (clamped address): no load behind a branch
-      const bool ok = (lane < kRowUnit) & (s_lane < cnt) & row_valid;
+      const bool ok = (pairs | (lane < kRowUnit)) & (s_lane < cnt) & row_valid;
       // (scalar bases and 32-bit lane offsets, as for the code stream)
       u32x4 vb[8];
+      auto request_values = [&](int b2) {
 #pragma unroll
-      for (int half_v = 0; half_v < 2; ++half_v) {
-        gptr_u32 v_unit = as_global(reinterpret_cast<const uint32_t *>(vs_base)) + (size_t)unit * 2048 + half_v * 1024;
-        keep_scalar(v_unit);
+        for (int half_v = 0; half_v < 2; ++half_v) {
+          gptr_u32 v_unit = as_global(reinterpret_cast<const uint32_t *>(vs_base)) + (size_t)(unit + b2) * 2048 + half_v * 1024;
+          keep_scalar(v_unit);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) vb[4 * half_v + nb] = *(const AKVQ_GLOBAL u32x4 *)(v_unit + nb * 256 + lane_code);
-      }
+          for (int nb = 0; nb < 4; ++nb) vb[4 * half_v + nb] = *(const AKVQ_GLOBAL u32x4 *)(v_unit + nb * 256 + lane_code);
+        }
+      };
+      request_values(0);
       auto request_group = [&](int g, bf16x8 (&kb)[4]) {
         gptr_u32 k_group = as_global(reinterpret_cast<const uint32_t *>(ks_base)) + (size_t)unit * 2048 + g * 1024;
         keep_scalar(k_group);
@@ -576,6 +588,11 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
         if (n_grp > 1) request_group(1, kb[1]);
         score_group(0, kb[0]);
         if (n_grp > 1) score_group(1, kb[1]);
+#pragma unroll 1
+        for (int g = 2; g < n_grp; ++g) {
+          request_group(g, kb[0]);
+          score_group(g, kb[0]);
+        }
       } else {
 #pragma unroll 1
         for (int g = 0; g < n_grp; ++g) {
@@ -597,36 +614,42 @@ __device__ __forceinline__ void decode_mha_body(const DecodeArgs &a) {
         w_lds[blk_of_lane][0][2][slot] = (uint16_t)f32_to_bf16_rne((w - hif) - lof);
       }
       wave_lds_sync();
-      const uint16_t *src = mrow < 3 ? &w_lds[0][0][mrow][8 * qd] : zero16;
-      const bf16x8 a_v = *reinterpret_cast<const bf16x8 *>(src);
-      // which of this lane's 8 K-slots (pair i, half) are real rows: mask the others (unwritten memory)
-      uint32_t keep[4];
+      auto add_values = [&](int b2) {
+        const uint16_t *src = mrow < 3 ? &w_lds[b2][0][mrow][8 * qd] : zero16;
+        const bf16x8 a_v = *reinterpret_cast<const bf16x8 *>(src);
+        // which of this lane's 8 K-slots (pair i, half) are real rows: mask the others (unwritten memory)
+        uint32_t keep[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int s0 = unit * kRowUnit + 4 * qd + e;  // half 0; half 1 is 16 slots further
-        keep[e] = (s0 < cnt ? 0x0000FFFFu : 0u) | (s0 + 16 < cnt ? 0xFFFF0000u : 0u);
-      }
+        for (int e = 0; e < 4; ++e) {
+          const int s0 = (unit + b2) * kRowUnit + 4 * qd + e;  // half 0; half 1 is 16 slots further
+          keep[e] = (s0 < cnt ? 0x0000FFFFu : 0u) | (s0 + 16 < cnt ? 0xFFFF0000u : 0u);
+        }
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
+        for (int nb = 0; nb < 8; ++nb) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) vb[nb][e] &= keep[e];
-        acc_o[nb] = mfma_bf16(a_v, __builtin_bit_cast(bf16x8, vb[nb]), acc_o[nb]);
+          for (int e = 0; e < 4; ++e) vb[nb][e] &= keep[e];
+          acc_o[nb] = mfma_bf16(a_v, __builtin_bit_cast(bf16x8, vb[nb]), acc_o[nb]);
+        }
+      };
+      add_values(0);
+      if (n_grp > 2) {
+        request_values(1);
+        add_values(1);
       }
       wave_lds_sync();
     }
   };
-  const int cnt_sal = min(max(sal_cnt_early, 0), a.S_cap);
   {
     const int32_t *sidx = a.sal_idx + (size_t)bh * a.S_cap;
     bf16_units(a.k_sal + (size_t)bh * a.S_cap * kD, a.v_sal + (size_t)bh * a.S_cap * kD, cnt_sal,
-               salient_units<NW>(a, cnt_sal, split, wave, appends),
+               pairs ? paired_units<NW>(cnt_sal, 0, wave) : salient_units<NW>(a, cnt_sal, split, wave, appends),
                [&](int s) { return sidx[min(s, a.S_cap - 1)] < a.t_win; });  // rows in the window are read there
   }
   if (a.win_len > 0) {
     // slot s holds the row of [t_win, T_len) congruent to s mod W; fine halves and padding rows carry no token
     const int W = a.win_len;
-    bf16_units(a.k_win + (size_t)bh * W * kD, a.v_win + (size_t)bh * W * kD, W,
-               window_units<NW>(a, cnt_sal, split, wave, appends), [&](int s) {
+    bf16_units(a.k_win + (size_t)bh * W * kD, a.v_win + (size_t)bh * W * kD, win_rows,
+               pairs ? paired_units<NW>(win_rows, cnt_sal, wave) : window_units<NW>(a, cnt_sal, split, wave, appends), [&](int s) {
       int d = (a.T_len - 1 - s) % W;
       d = d < 0 ? d + W : d;
       const int t = a.T_len - 1 - d;
@@ -1277,6 +1300,15 @@ static void launch_decode_stream(DecodeArgs a, hipStream_t stream) {
   // 19.2 us with four, 15.7 with eight.
   const int alone = !a.fused_append || a.n_split == 1 ? 0 : mha ? a.S_cap : a.S_cap + (a.win_len < a.T_len ? a.win_len : a.T_len);
   const bool wide = workgroups <= kCus && (decode_tiles_per_split((a.t_win + rows - 1) / rows, a.n_split) > kWaves || alone > kWaves * kRowUnit);
+  // From how many units of 16-bit rows on they are taken in pairs.  Beyond two workgroups per CU always where the last round of
+  // them, four or three per CU by registers, is nearly full (a short one is latency again: 1280 workgroups of 200 rows, 64 of
+  // them in the window, 18.9 us by units, 20.6 by pairs).
+  constexpr long kRound = (!PAIRS && G == 128 ? 4 : 3) * kCus;
+  const long last_round = (workgroups - 1) % kRound + 1;
+  if (!mha || a.n_split > 1 || 4 * workgroups <= 3 * kCus) a.row_pairs = 0;
+  else if (workgroups <= kCus) a.row_pairs = wide ? kWavesWide + 1 : kWaves + 3;
+  else if (workgroups <= 2 * kCus) a.row_pairs = kWaves + 1;
+  else a.row_pairs = 8 * last_round >= 5 * kRound ? 1 : 0;
   a.paced = !mha && !wide && workgroups <= 2 * kCus;
   if (mha) {
     if (wide) hipLaunchKernelGGL((decode_mha_kernel<G, PAIRS, kWavesWide>), grid, dim3(64 * kWavesWide), 0, stream, a);

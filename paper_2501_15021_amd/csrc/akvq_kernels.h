@@ -54,6 +54,7 @@ struct DecodeArgs {
   int fused_append;
   int append_split;
   int paced;  // grouped-query launch, all of it resident at once: wavefronts of a SIMD are kept in step (set by the launcher)
+  int row_pairs;  // one-head launch: units of 16-bit rows from which on they are taken in pairs, 0: never (set by the launcher)
   QuantArgs step;
   const uint16_t *rope_cos, *rope_sin;  // rotary tables for pre-RoPE queries (null: none), one row of 64 per batch element
   long long rope_stride;
@@ -166,6 +167,12 @@ __host__ __device__ inline RowUnits window_units(const DecodeArgs &a, int cnt_sa
   // behind the salient units
   const int first = split + back * a.n_split - (cnt_salient + kRowUnit - 1) / kRowUnit % step;
   return {first < 0 ? first + step : first, step, n, n};
+}
+// ... and in pairs of units (one split): index i stands for units 2 * i and 2 * i + 1; behind the pairs of `before` rows
+template <int NW>
+__host__ __device__ inline RowUnits paired_units(int rows, int before, int wave) {
+  const int n = (rows + 2 * kRowUnit - 1) / (2 * kRowUnit), first = (NW - 1 - wave) - (before + 2 * kRowUnit - 1) / (2 * kRowUnit) % NW;
+  return {first < 0 ? first + NW : first, NW, n, n};
 }
 constexpr int kMhaTileRows = 64, kGqaTileRows = 32;  // rows per code-stream tile of the two decode kernels
 hipError_t launch_decode_attention(const DecodeArgs &a, int G, hipStream_t stream);

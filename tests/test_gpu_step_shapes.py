@@ -107,3 +107,18 @@ def test_eight_wavefronts(orc, R, G, tiles, n_split, window, tiers):
 @pytest.mark.parametrize("tiers", [False, True])
 def test_eight_wavefronts_of_few_tiles(orc, R, G, window, slots, tiles, n_split, tiers):
     _steps(orc, 2, 3, R, G, tiles, n_split, window, tiers, slots=slots if not tiers else 64 if slots == 64 else 128)
+
+
+# 16-bit rows two units at a time (more than one workgroup per CU and more units than wavefronts, or more than two per CU), with
+# odd numbers of units, windows that are not full yet and long salient lists
+@pytest.mark.parametrize("Hkv,window,slots,tiles", [(4, 128, 64, 5), (4, 512, 64, 3), (4, 192, 192, 7), (4, 0, 256, 8), (8, 64, 64, 2), (8, 0, 64, 2),
+                                                    (8, 512, 64, 1), (8, 128, 128, 5)])
+@pytest.mark.parametrize("G,tiers", [(128, False), (64, False), (128, True), (64, True)])
+def test_pairs_of_row_units(orc, Hkv, window, slots, tiles, G, tiers):
+    _steps(orc, 65, Hkv, 1, G, tiles, 1, window, tiers, slots=slots if not tiers else min(slots, 128))
+
+
+@pytest.mark.parametrize("window,slots,tiles", [(256, 64, 4), (256, 64, 9), (512, 64, 12), (0, 320, 11), (192, 192, 3)])  # a workgroup per CU
+@pytest.mark.parametrize("G,tiers", [(128, False), (64, True)])
+def test_pairs_of_row_units_with_four_and_eight_wavefronts(orc, window, slots, tiles, G, tiers):
+    _steps(orc, 64, 4, 1, G, tiles, 1, window, tiers, slots=slots if not tiers else min(slots, 128))

@@ -35,7 +35,20 @@ template <int NW> int check(int n_split, int win, int T_len, int cnt, int fused)
   }
   return 0;
 }
+template <int NW> int check_pairs(int win, int cnt) {
+  for (const int rows : {cnt, win}) {
+    std::vector<int> seen((rows + 63) / 64);
+    for (int v = 0; v < NW; ++v) {
+      const RowUnits u = rows == cnt ? paired_units<NW>(cnt, 0, v) : paired_units<NW>(win, cnt, v);
+      for (int i = u.first; i < u.limit; i += u.step) ++seen.at(i);
+    }
+    for (int n : seen) if (n != 1) return 5;
+  }
+  return 0;
+}
 int main() {
+  for (int win : {1, 31, 64, 100, 128, 192, 512, 1024}) for (int cnt : {0, 1, 31, 32, 33, 64, 65, 200, 1121})
+    if (check_pairs<4>(win, cnt)) { std::printf("pairs: window %d salient %d\n", win, cnt); return 1; }
   for (int n_split : {1, 2, 3, 5, 8, 32, 64}) for (int win : {64, 128, 192, 1024}) for (int cnt : {0, 1, 31, 32, 33, 64, 200, 1121})
     for (int T_len : {1, 2, 33, 64, 65, 100, 127, 128, 129, 3002, 20012}) for (int fused : {0, 1}) {
       const int a = check<4>(n_split, win, T_len, cnt, fused), b = check<8>(n_split, win, T_len, cnt, fused);
