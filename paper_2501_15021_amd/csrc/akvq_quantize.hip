@@ -808,13 +808,13 @@ static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t
     ring = ring_by(a.n_blk, n_win, (long)B * a.Hkv, tiered, rope);
     if (ring == Ring::kWavefronts) groups = (a.n_blk + n_win + 3) / 4;
   }
-  // Turned orders where more workgroups than the card holds at once (four per CU) run over units of an even number of them:
-  // 16 prompts of 4096 tokens (32 workgroups a unit), 32 heads: 227 -> 217 us; 8 of 4064: 113.7 -> 110.3; 8 of 5000 (40):
-  // 136.2 -> 132.9; 8 of 2500 (20): 71.0 -> 69.1.  An odd number moves on by itself, turned orders changed nothing with
-  // the window's workgroups in the launch (119.0, 8 of 4096 with window 512: 119.1) and cost where one round of
-  // workgroups holds everything (one prompt of 2048: 9.67, 9.80) or the overlay's are in it (8 of 1920, 576 slots: 52.3, 56.0).
+  // Turned orders in launches of ten rounds of workgroups (four per CU) and more, over units of an even number of them: 16
+  // prompts of 4096 tokens (32 workgroups a unit), 32 heads, 229.5 -> 221 us; 16 of 5000 (40) 290 -> 274; 8 of 5000 145.4 ->
+  // 137.6.  An odd number moves on by itself.  In shorter launches they gain nothing or cost: 2 of 4000 the same, 12 of 1000
+  // 40.2 -> 41.1, 3 of 1000 13.8 -> 14.8, one of 4096 with rotary embedding 17.1 -> 18.4; so they do with the window's workgroups
+  // in the launch (8 of 4096 with window 512: 119.0, 119.1) or the overlay's (8 of 1920, 576 slots: 52.3, 56.0).
   a.groups = groups;
-  a.turn = (!window || ring == Ring::kBlocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv > kResidentGroups ? 7 : 0;
+  a.turn = (!window || ring == Ring::kBlocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv >= 10 * kResidentGroups ? 7 : 0;
   const dim3 grid(groups, B * a.Hkv, 2), block(256);
 #define AKVQ_LAUNCH_Q(GG, TT, RR) \
   do { \

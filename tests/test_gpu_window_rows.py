@@ -1,5 +1,5 @@
-"""The ring rows of an append, stored by workgroups of their own in the launch of the blocks, are bit for bit those that
-the same rows leave when they are appended one at a time or in ragged pieces, and the blocks beside them do not change."""
+"""The ring rows of an append, stored by wavefronts of their own in the launch of the blocks or by the blocks, are bit for bit
+those that the same rows leave when they are appended one at a time or in ragged pieces, and the blocks do not change."""
 import pytest
 import torch
 
@@ -66,7 +66,7 @@ def test_tiered_rows(T, n_rows, W, with_rope):
 
 # launches whose blocks store the ring rows themselves (a window of more than a quarter of the blocks, more than two
 # workgroups a CU; the last case also in turned orders) against the batch elements alone, which go the other way
-@pytest.mark.parametrize("B,H,T,G,W", [(65, 2, 130, 128, 64), (43, 3, 250, 64, 128), (33, 2, 1010, 128, 512)])
+@pytest.mark.parametrize("B,H,T,G,W", [(65, 2, 130, 128, 64), (43, 3, 250, 64, 128), (33, 2, 1010, 128, 512), (160, 4, 1010, 128, 512)])
 @pytest.mark.parametrize("tiers,with_rope", [(False, False), (False, True), (True, False), (True, True)])
 def test_blocks_store_the_ring(B, H, T, G, W, tiers, with_rope):
     k, v, rope = _rows(B, H, T, 7)
