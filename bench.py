@@ -710,7 +710,7 @@ def main():
 
     rooflines = {
         "decode": roof("decode", dec_bytes, tot["decode"], "decode_mha_kernel/decode_gqa_kernel (+combine)"),
-        "quantize": roof("quantize", q_bytes, tot["quantize"], "quantize_append_kernel (+overlay_rows_kernel in text-salient layers)"),
+        "quantize": roof("quantize", q_bytes, tot["quantize"], "quantize_append_kernel (quantize_append_overlay_kernel in text-salient layers)"),
     }
     # quantize_append is bound by vector-instruction issue, not by HBM (counters: vector unit busy 97 % of the kernel):
     # the same launch against the vector peak without packed fp32 (256 CUs x 64 lanes x 2.4 GHz lane-operations/s),

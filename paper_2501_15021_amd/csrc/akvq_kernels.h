@@ -49,8 +49,9 @@ struct DecodeArgs {
   int q_rotated, out_rotated, out_half;
   // the decode step in one launch: row T_len - 1 is first quantized from step.k_new / step.v_new (step.T_len is that
   // row) by the workgroups of split append_split: the split whose tile range holds the tile of that row (see
-  // decode_split_range), so that the row is written and read by the same workgroup.  They are also the only ones to
-  // read 16-bit rows then.
+  // decode_split_range), so that the row is written and read by the same workgroup.  For the same reason they are the only
+  // ones to read the salient rows then, and the new row's unit of the recent window (the one-head kernel deals the window's
+  // other units to all splits, the grouped-query kernel leaves the whole window to them).
   int fused_append;
   int append_split;
   int paced;  // grouped-query launch, all of it resident at once: wavefronts of a SIMD are kept in step (set by the launcher)

@@ -842,8 +842,8 @@ hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t 
     return hipGetLastError();
   }
   // Long salient lists (text-salient layers) get their V overlay rows from workgroups of their own, in the launch of the
-  // blocks or, where a window's workgroups are in that, in a launch behind it; a handful of pivots (and the rows of a
-  // tiered append, whose tiers the block kernel knows) are stored by the block kernel itself.
+  // blocks or (beside a window's ring rows, or one or two blocks of many units) in a launch behind it; a handful of pivots
+  // (and the rows of a tiered append, whose tiers the block kernel knows) are stored by the block kernel itself.
   if (a.S_cap > 64 && a.row_tier == nullptr) {
     QuantArgs blocks = a;
     blocks.skip_overlay = 1;
