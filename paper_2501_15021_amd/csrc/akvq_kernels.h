@@ -54,8 +54,10 @@ struct DecodeArgs {
   // other units to all splits, the grouped-query kernel leaves the whole window to them).
   int fused_append;
   int append_split;
-  int paced;  // grouped-query launch, all of it resident at once: wavefronts of a SIMD are kept in step (set by the launcher)
-  int row_pairs;  // one-head launch: units of 16-bit rows from which on they are taken in pairs, 0: never (set by the launcher)
+  // (16 bits each: with an int more in front of them the step's arguments lie 8 bytes further, and a fused step of 20011 rows,
+  // 28/4 heads, window and rotary embedding, took 12.47 us instead of 12.35)
+  short paced;  // grouped-query launch, all of it resident at once: wavefronts of a SIMD are kept in step (set by the launcher)
+  short row_pairs;  // one-head launch: units of 16-bit rows from which on they are taken in pairs, 0: never (set by the launcher)
   QuantArgs step;
   const uint16_t *rope_cos, *rope_sin;  // rotary tables for pre-RoPE queries (null: none), one row of 64 per batch element
   long long rope_stride;
