@@ -146,7 +146,8 @@ int akvq_decode_split_range(int n_tiles, int n_split, int split, int *begin, int
  *   Output: c->sal_idx (ascending) and c->sal_cnt.  mass_out (device, [B][Hkv][T] fp32) is optional (PSA).
  *   workspace: device, akvq_select_workspace_bytes() bytes (PSA only; may be NULL for TSA).  Less is accepted down to
  *   the row statistics of 2048-key chunks, B * Hq * ceil(T / 2048) * W * 8 bytes, beside the masses (B * Hkv * T * 4) and
- *   their sums (B * T * 4), each rounded up to 256: it costs speed where a prompt would be scored in shorter chunks,
+ *   their sums (B * T * 4), each rounded up to 256: it costs speed where a prompt would be scored in shorter chunks
+ *   or in one pass over its keys,
  *   and, as the statistics are then added in another order, can change the last bits of the masses.
  */
 int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, const void *q_tail, int Hq,

@@ -35,6 +35,17 @@ def build_native() -> str:
     return NATIVE
 
 
+def build_nowait(out: str) -> str:
+    """The library again, behind build(), with a pivot scoring that looks for other workgroups' statistics only once (a test of
+    what a workgroup does that does not find them)."""
+    obj = os.path.join(CSRC, "akvq_select_nowait.o")
+    subprocess.run([HIPCC, *FLAGS, "-DAKVQ_ONCE_POLLS=0", "-c", os.path.join(CSRC, "akvq_select.hip"), "-o", obj], check=True,
+                   stderr=subprocess.DEVNULL)
+    objs = [os.path.join(CSRC, src.replace(".hip", ".o")) for src in SOURCES if src != "akvq_select.hip"]
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out, *objs, obj], check=True)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     """Compile every kernel source and link the shared library.  Always recompiles."""
     objs = []

@@ -87,7 +87,8 @@ static size_t select_bytes(size_t triples, int B, int Hkv, int T, int W) {
 
 size_t akvq_select_workspace_bytes(int B, int Hq, int Hkv, int T, int W) {
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || T <= 0 || W <= 0) return 0;
-  return select_bytes(akvq::score_max_triples(B, Hq, Hkv, T, W), B, Hkv, T, W);
+  return select_bytes(akvq::score_max_triples(B, Hq, Hkv, T, W), B, Hkv, T, W) +
+         round_up(akvq::score_max_head_masses(B, Hq, Hkv, T, W) * sizeof(float), 256);
 }
 
 size_t akvq_decode_workspace_bytes(int B, int Hq, int n_split) {
@@ -135,6 +136,14 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   int chunk = akvq::score_chunk(c->B, Hq, c->Hkv, T, W);
   auto needed = [&](int keys) { return select_bytes((size_t)c->B * Hq * select_chunks(T, keys), c->B, c->Hkv, T, W); };
   while (chunk < akvq::kScoreChunk && workspace_bytes < needed(chunk)) chunk += 64;
+  // ... and one without room for what a single pass over the keys keeps there serves two passes
+  const size_t heads = round_up(akvq::score_head_masses(c->B, Hq, c->Hkv, T) * sizeof(float), 256);
+  const int path = akvq::score_path(c->B, Hq, c->Hkv, T, W, sm_scale, mode == AKVQ_MODE_PSA_SHARED);
+  const int once = path == akvq::kScoreOnce ? akvq::kOnceKeys : T;  // keys per chunk
+  if (path != akvq::kScoreTwoPasses && workspace_bytes >= needed(once) + heads) {
+    a.score_path = path;
+    chunk = once;
+  }
   if (workspace_bytes < needed(chunk)) return AKVQ_ERR_WORKSPACE;
   a.q_tail = static_cast<const uint16_t *>(q_tail);
   a.k = static_cast<const uint16_t *>(k);
@@ -144,7 +153,14 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   a.row_stats = static_cast<float *>(workspace);
   const size_t stats = round_up((size_t)c->B * Hq * a.n_chunk * W * 2 * sizeof(float), 256);
   const size_t mass_bytes = round_up((size_t)c->B * c->Hkv * T * sizeof(float), 256);
+  const size_t shared_bytes = round_up((size_t)c->B * T * sizeof(float), 256);
   a.mass = mass_out ? mass_out : reinterpret_cast<float *>(static_cast<char *>(workspace) + stats);
+  a.score = a.mass;
+  a.score_stride = T;
+  if (Hq > c->Hkv) {
+    a.score = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes + shared_bytes);
+    a.score_stride = akvq::score_stride(T);
+  }
   if (mode == AKVQ_MODE_PSA_SHARED)
     a.mass_shared = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes);
   return hip_status(akvq::launch_select_psa(a, s));

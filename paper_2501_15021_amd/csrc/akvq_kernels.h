@@ -199,6 +199,9 @@ struct SelectArgs {
   float floor;
   int mass_per_batch;        // top-k reads mass[b][T] (shared by the batch element's kv-heads) instead of mass[b][hkv][T]
   int skip_zero;
+  int score_path;            // ScorePath
+  float *score;              // where the scoring of kScoreSmall and kScoreOnce leaves a query head's masses, rows of score_stride: mass
+  int score_stride;          // itself, or workspace with several heads per KV head (16-byte aligned rows)
   float *mass_shared;        // token-level pivots: [B][T] sums of the kv-heads' masses (workspace), null: per-head lists
 };
 // Keys per scoring workgroup: kScoreChunk, or less where that leaves the chip idle (scoring windows of 64 rows only; the
@@ -214,6 +217,7 @@ struct SelectArgs {
 // prompt: 32 heads, 640 tokens 29.1 -> 18.7 us, 4096 tokens 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096
 // tokens 142 -> 35, 32768 tokens 160 -> 76; 40 prompts of 1300 tokens, 28/4 heads, 100 -> 92, and 16 of 4907 142 -> 103,
 // where halving the chunk until every CU has a workgroup, whatever the rounds and lengths, makes 148 and 151.
+constexpr int kSmallKeys = 768, kOnceKeys = 512, kOnceMaxChunks = 64;  // see score_path
 constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64, kScoreCus = 256;
 inline bool score_fine_chunks(int Hq, int Hkv, int W) { return W == 64 && Hq >= Hkv && Hq / Hkv <= 8; }
 inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
@@ -235,18 +239,55 @@ inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
 // Most (batch, head, chunk) triples that score_chunk makes of any batch up to B and any prompt up to T: it grows with B
 // and T, which the triples of one shape do not (a longer prompt can have fewer, larger chunks).
 inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
-  const size_t heads = (size_t)B * Hq, coarse = heads * (((size_t)T + kScoreChunk - 1) / kScoreChunk);
+  const size_t heads = (size_t)B * Hq;
+  size_t coarse = heads * (((size_t)T + kScoreChunk - 1) / kScoreChunk);
   if (!score_fine_chunks(Hq, Hkv, W)) return coarse;
+  if (Hq == Hkv) {  // a prompt read once
+    const size_t keys = T < kOnceKeys * kOnceMaxChunks ? T : kOnceKeys * kOnceMaxChunks;
+    const size_t once = heads * ((keys + kOnceKeys - 1) / kOnceKeys);
+    if (once > coarse) coarse = once;
+  }
   size_t fine = heads * (((size_t)T + kScoreChunkMin - 1) / kScoreChunkMin);
   if (fine > heads * kScoreMaxFineChunks) fine = heads * kScoreMaxFineChunks;
   const size_t filled = (size_t)(4 * kScoreCus) * (Hq / Hkv);  // four workgroups per CU, of Hq / Hkv heads each
   if (fine > filled) fine = filled;
   return fine > coarse ? fine : coarse;
 }
-// Prompts whose selection is one launch (see psa_small_kernel).
-constexpr int kSmallKeys = 768;
-inline bool score_small(int B, int Hq, int Hkv, int T, int W, float sm_scale) {
-  return W == 64 && Hq == Hkv && T <= kSmallKeys && sm_scale > 0.0f;
+// How a prompt's pivots are scored.  Two passes over the keys serve everything; where a head's exponentials fit into registers
+// until its row statistics are known, one does: one workgroup per query head (psa_small_kernel), or as many as the keys need
+// (psa_once_kernel: a launch more, which clears the words they exchange).
+// One head per KV head: in one pass up to kOnceKeys * kOnceMaxChunks keys (beyond, the words a workgroup collects are a
+// quarter of its keys and more).  110 shapes of 513 to 768 keys: 0.76 of the time of two passes; the small kernel up to
+// 512 workgroups, two rounds of them on the CUs: 16 x 640 keys, 32 heads, 33.3 us in small, 33.9 in once, 32 x 640 63.9 and 57.8.
+// Several heads per KV head: each head reads and converts the keys for itself, which costs what the second pass did (64 x 768
+// keys, 32/8 heads, 101 us in two passes, 112 in one; 16 x 8192, 28/4 heads, 150 and 209), so one pass pays where everything is
+// resident at once: it is a launch less, or the same three with shorter ones (2 x 1000, 12/2 heads, 26.2 -> 18.2).  In the small
+// kernel up to 512 keys that is 512 workgroups, two per CU, beyond one per CU; up to 256 keys with four per CU it is faster at any
+// number (73 x 256, 28/4 heads, 64 -> 38), but not with eight heads, whose two passes have no feeders to wait for (32 x 256,
+// 64/8 heads, 1.05 of the time).  671 shapes of 256 to 4096 keys, 2 to 8 heads: 0.87 of the time of two passes, none slower
+// by more than 1 %.
+enum ScorePath { kScoreTwoPasses, kScoreSmall, kScoreOnce };
+inline int score_path(int B, int Hq, int Hkv, int T, int W, float sm_scale, bool shared) {
+  const long heads = (long)B * Hq, chunks = ((long)T + kOnceKeys - 1) / kOnceKeys;
+  if (W != 64 || Hq > 8 * Hkv || !(sm_scale > 0.0f) || chunks > kOnceMaxChunks) return kScoreTwoPasses;
+  if (Hq == Hkv) {
+    if (T <= 512 || (T <= kSmallKeys && heads <= 2 * kScoreCus)) return shared ? kScoreTwoPasses : kScoreSmall;
+    return kScoreOnce;
+  }
+  if (shared) return kScoreTwoPasses;  // (each KV head's mass is needed before they are added)
+  const long small = T <= 256 ? (Hq < 8 * Hkv ? heads : 2 * kScoreCus) : T <= 512 ? 2 * kScoreCus : T <= kSmallKeys ? kScoreCus : 0;
+  if (heads <= small) return kScoreSmall;
+  return heads * chunks <= 2 * kScoreCus ? kScoreOnce : kScoreTwoPasses;
+}
+// Masses of single query heads, with several per KV head: elements of a shape, and the most of any batch up to B and prompt up to T
+inline int score_stride(int T) { return (T + 3) / 4 * 4; }
+inline size_t score_head_masses(int B, int Hq, int Hkv, int T) { return Hq > Hkv ? (size_t)B * Hq * score_stride(T) : 0; }
+inline size_t score_max_head_masses(int B, int Hq, int Hkv, int T, int W) {
+  if (Hq <= Hkv || W != 64 || Hq > 8 * Hkv) return 0;
+  const size_t heads = (size_t)B * Hq, all = heads * score_stride(T);
+  const size_t resident = (size_t)2 * kScoreCus * (kOnceKeys + 4), few_keys = heads * (T < 256 ? score_stride(T) : 256);
+  const size_t most = resident > few_keys ? resident : few_keys;
+  return all < most ? all : most;
 }
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream);

@@ -2,8 +2,8 @@
 //   TSA layers: the salient set is the text positions -> ordered stream compaction of the modality mask.
 //   PSA layers: pivot tokens are the few tokens that receive most of the attention (Section I / III-A.3); the score
 //   is the attention-column mass of the last W prompt rows, computed on the matrix cores (bfloat16 operands, fp32
-//   accumulate, fp32 softmax) in two streaming passes over K (row statistics, then column sums), followed by an
-//   exact top-k (radix select on the fp32 bit patterns, ties to the lower position).
+//   accumulate, fp32 softmax) in two streaming passes over K (row statistics, then column sums) or, where the exponentials
+//   can wait in registers for the statistics, in one, followed by an exact top-k (radix select on the fp32 bit patterns, ties to the lower position).
 #include <atomic>
 
 #include "akvq_device.h"
@@ -937,13 +937,36 @@ __device__ __forceinline__ void topk_row(const SelectArgs &a, int bh, const floa
   }
   if (threadIdx.x == 0) a.sal_cnt[bh] = tot_take;
 }
-template <bool STAGED, int NT>
+// SUM: the keys are the query heads' masses of a KV head, added up in head order (and stored)
+template <bool STAGED, int NT, bool SUM = false>
 __global__ __launch_bounds__(NT) void topk_kernel(SelectArgs a) {
   extern __shared__ float keys_lds[];
   const int bh = blockIdx.x;
   const float *mass = a.mass + (size_t)(a.mass_per_batch ? bh / a.Hkv : bh) * a.T;
   uint32_t mine = 0u;  // largest key this thread staged (bit patterns of non-negative floats order like the floats)
-  if (STAGED)
+  if constexpr (SUM) {
+    // four positions a thread, all heads requested together
+    const int R = a.Hq / a.Hkv;
+    const float *heads = a.score + (size_t)bh * R * a.score_stride;
+    float *mass_out = a.mass + (size_t)bh * a.T;
+    for (int t0 = 4 * threadIdx.x; t0 < a.T; t0 += 4 * NT) {
+      f32x4 x[kGqaMaxHeads];
+#pragma unroll
+      for (int h = 0; h < kGqaMaxHeads; ++h)
+        if (h < R) x[h] = *reinterpret_cast<const f32x4 *>(heads + (size_t)h * a.score_stride + t0);
+      f32x4 sum = x[0];
+#pragma unroll
+      for (int h = 1; h < kGqaMaxHeads; ++h)
+        if (h < R) sum += x[h];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (t0 + i < a.T) {
+          keys_lds[t0 + i] = sum[i];
+          mass_out[t0 + i] = sum[i];
+          mine = max(mine, __float_as_uint(sum[i]));
+        }
+    }
+  } else if (STAGED)
     for (int t0 = threadIdx.x; t0 < a.T; t0 += kTopkBatch * NT) {
       float x[kTopkBatch];  // requested together; positions past the end read the last key and are dropped
 #pragma unroll
@@ -1006,28 +1029,110 @@ __device__ __forceinline__ float row_sums_each(const float (&v)[8], int mrow) {
   return z + row_dpp<0xB1>(z);                 // r and r ^ 1
 }
 
-// One workgroup per (batch, head), one query head per KV head, W = 64: a wavefront holds 64 keys as operands and, in 64
-// registers, what they make of the 64 tail rows, so that every key is read, multiplied and exponentiated once; the
-// wavefronts' row statistics meet in LDS, and the top-k takes the masses from there.  Up to kSmallKeys keys: what twelve
-// wavefronts of 168 registers, three on a SIMD, hold.
+// NG groups of 16 keys against the 64 tail rows: s = exponentials, row 16*rb + mrow, keys t_lane + GROUP_STEP * g + i;
+// t_last: the last of them; m_row, l_row: reference and sum of row `lane`.  STEP: groups multiplied at a time (their
+// operands take 16 registers each, but the rows are read from LDS once for each step).
+template <int NG, int STEP, int GROUP_STEP>
+__device__ __forceinline__ void score_wave_keys(const KeyGroup (&raw)[NG], u32x4 *tile, const u32x4 *q_lds, int t_lane, int t_last, int T,
+                                                float scale2, int lane, f32x4 (&s)[4][NG], float &m_row, float &l_row) {
+  const int mrow = lane & 15;
+#pragma unroll
+  for (int g0 = 0; g0 < NG; g0 += STEP) {
+    bf16x8 key[STEP][4];
+#pragma unroll
+    for (int g = 0; g < STEP; ++g) lines_to_operands(raw[g0 + g], tile, lane, key[g]);
+    uint32_t lane_off = (uint32_t)lane;
+    if (STEP < NG) asm volatile("" : "+v"(lane_off));  // (not kept in registers from step to step)
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+#pragma unroll
+      for (int g = 0; g < STEP; ++g) s[rb][g0 + g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc) {
+        const bf16x8 rows = __builtin_bit_cast(bf16x8, q_lds[(rb * 4 + kc) * 64 + lane_off]);
+#pragma unroll
+        for (int g = 0; g < STEP; ++g) s[rb][g0 + g] = mfma_bf16(key[g][kc], rows, s[rb][g0 + g]);
+      }
+    }
+    if (STEP < NG) __builtin_amdgcn_sched_barrier(0);
+  }
+  if (t_last > T - 64) {  // some key is hidden from some row, or past the end: behind position T - 64 + row
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      int last = T - 64 + 16 * rb + mrow - t_lane;
+      asm volatile("" : "+v"(last));
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[rb][g][i] = GROUP_STEP * g + i <= last ? s[rb][g][i] : -INFINITY;
+    }
+  }
+  float x[4];
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb) {
+    x[rb] = s[rb][0][0];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) x[rb] = max3(max3(x[rb], s[rb][g][0], s[rb][g][1]), s[rb][g][2], s[rb][g][3]);
+  }
+  // row `lane` of this wavefront's keys (finite where no key is seen)
+  m_row = fmaxf(over_rows_each(x, [](float u, float v) { return max3(u, u, v); }) * scale2, -1e30f);
+  float ref[4];
+  to_each_row(m_row, ref);
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb) {
+    x[rb] = 0.0f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[rb][g][i] = fast_exp2(__builtin_fmaf(s[rb][g][i], scale2, -ref[rb]));
+      x[rb] += (s[rb][g][0] + s[rb][g][1]) + (s[rb][g][2] + s[rb][g][3]);
+    }
+  }
+  l_row = over_rows_each(x, [](float u, float v) { return u + v; });
+}
+// column sums of such exponentials, each row times its weight (row `lane`): store(g, i, sum), each key by one lane
+template <int NG, typename F>
+__device__ __forceinline__ void column_sums(const f32x4 (&s)[4][NG], float weight, int lane, F store) {
+  const int mrow = lane & 15;
+  float wgt[4];
+  to_each_row(weight, wgt);
+#pragma unroll
+  for (int half = 0; half < NG / 2; ++half) {
+    float col[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int g = 2 * half + (i >> 2);
+      col[i] = s[0][g][i & 3] * wgt[0];
+#pragma unroll
+      for (int rb = 1; rb < 4; ++rb) col[i] = __builtin_fmaf(s[rb][g][i & 3], wgt[rb], col[i]);
+    }
+    const float sum = row_sums_each(col, mrow);  // lanes of mrow 2 * (4*(g - 2*half) + i): key 16*g + 4*qd + i
+    if ((mrow & 1) == 0) store(2 * half + (mrow >> 3), (mrow >> 1) & 3, sum);
+  }
+}
+
+// One workgroup per (batch, query head), W = 64: a wavefront holds 64 keys as operands and, in 64 registers, what they make of
+// the 64 tail rows, so that every key is read, multiplied and exponentiated once; the wavefronts' row statistics meet in
+// LDS.  With one query head per KV head (TOPK) the top-k takes the masses from there; several heads leave theirs to
+// topk_kernel, which adds them up.  Up to kSmallKeys keys: what twelve wavefronts of 168 registers, three on a SIMD, hold.
 // Three launches of 5 to 6.6 us each did this before, each waiting for the one in front of it; us per selection, 32 heads,
-// then and now: 1 x 640 keys 16.3 -> 13.3, 1 x 256 15.1 -> 7.8, 16 x 512 37.7 -> 21.3, 64 x 256 72 -> 38, 64 x 768 162 -> 128.
+// then and now: 1 x 640 keys 16.3 -> 13.3, 1 x 256 15.1 -> 7.8, 16 x 512 37.7 -> 21.3, 64 x 256 72 -> 38, 64 x 768 162 -> 128;
+// in two launches, several heads per KV head: 1 x 368, 32/8 heads, 20.8 -> 13.1, 16 x 275, 28/4 heads, 29.6 -> 22.3.
 // Keys come line by line and are turned through LDS: loads in operand order (half lines) took 1.4 us longer at 1 x 640.
 // The time is a chain: rows and keys from memory (one CU brings a head's 164 KB), products, exponentials, three barriers,
-// and about 2.5 us of top-k.  Beyond 768 keys a workgroup runs out of registers; with several query heads per KV head it
-// would score them one after the other on one CU, where the passes below use many.
+// and about 2.5 us of top-k.
 // NT: threads, and the most keys (a wavefront takes 64).
-template <int NT>
+template <int NT, bool TOPK>
 __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
   __shared__ u32x4 key_tile[NT / 64][256];                              // 16 keys on their way to operands
   __shared__ u32x4 q_lds[1024];                                         // the tail rows as operands: slot (rb, kc, lane)
   __shared__ float part_m[NT / 64][64], part_l[NT / 64][64];  // per wavefront and row
   __shared__ float mass_lds[NT];
-  const int bh = blockIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, mrow = lane & 15, qd = lane >> 4;
+  const int bh = blockIdx.x;  // (batch, query head)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, qd = lane >> 4;
   const int n_waves = (a.T + 63) / 64, t_wave = 64 * wave;
   const bool scores = wave < n_waves;
-  const uint16_t *k_rows = a.k + (size_t)bh * a.T * kD, *q_rows = a.q_tail + (size_t)bh * 64 * kD;
+  const uint16_t *k_rows = a.k + (size_t)(TOPK ? bh : bh / (a.Hq / a.Hkv)) * a.T * kD, *q_rows = a.q_tail + (size_t)bh * 64 * kD;
   const float scale2 = a.sm_scale * kLog2e;
   // rows first: they are looked at first, and loads return in order
   constexpr int kRowPieces = (1024 + NT - 1) / NT;  // 16-byte pieces of the rows per thread; consecutive threads, consecutive pieces
@@ -1047,62 +1152,11 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
       q_lds[((row >> 4) * 4 + (piece >> 2)) * 64 + (piece & 3) * 16 + (row & 15)] = __builtin_bit_cast(u32x4, rows8_as_bf16(row_piece[x]));
   }
   __syncthreads();
-  f32x4 s[4][4];  // logits, then exponentials: row 16*rb + mrow, keys 16*g + 4*qd + i
-  float m_row = 0.0f;
-  if (scores) {
-    bf16x8 key[4][4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) lines_to_operands(raw[g], key_tile[wave], lane, key[g]);
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) s[rb][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kc = 0; kc < 4; ++kc) {
-        const bf16x8 rows = __builtin_bit_cast(bf16x8, q_lds[(rb * 4 + kc) * 64 + lane]);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) s[rb][g] = mfma_bf16(key[g][kc], rows, s[rb][g]);
-      }
-    }
-    if (t_wave + 63 > a.T - 64) {  // some key is hidden from some row, or past the end: behind position T - 64 + row
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        int last = a.T - 64 + 16 * rb + mrow - (t_wave + 4 * qd);
-        asm volatile("" : "+v"(last));
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s[rb][g][i] = 16 * g + i <= last ? s[rb][g][i] : -INFINITY;
-      }
-    }
-    float x[4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      x[rb] = max3(s[rb][0][0], s[rb][0][1], max3(s[rb][0][2], s[rb][0][3], s[rb][1][0]));
-      x[rb] = max3(x[rb], s[rb][1][1], max3(s[rb][1][2], s[rb][1][3], s[rb][2][0]));
-      x[rb] = max3(x[rb], s[rb][2][1], max3(s[rb][2][2], s[rb][2][3], s[rb][3][0]));
-      x[rb] = max3(x[rb], s[rb][3][1], max3(s[rb][3][2], s[rb][3][3], s[rb][3][3]));
-    }
-    // row `lane` of this wavefront's keys (finite where no key is seen)
-    m_row = fmaxf(over_rows_each(x, [](float u, float v) { return max3(u, u, v); }) * scale2, -1e30f);
-    part_m[wave][lane] = m_row;
-    float ref[4];
-    to_each_row(m_row, ref);
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      x[rb] = 0.0f;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[rb][g][i] = fast_exp2(__builtin_fmaf(s[rb][g][i], scale2, -ref[rb]));
-        x[rb] += (s[rb][g][0] + s[rb][g][1]) + (s[rb][g][2] + s[rb][g][3]);
-      }
-    }
-    part_l[wave][lane] = over_rows_each(x, [](float u, float v) { return u + v; });
-  } else {
-    part_m[wave][lane] = -1e30f;
-    part_l[wave][lane] = 0.0f;
-  }
+  f32x4 s[4][4];  // exponentials: row 16*rb + mrow, keys 16*g + 4*qd + i
+  float m_row = -1e30f, l_row = 0.0f;
+  if (scores) score_wave_keys<4, 4, 16>(raw, key_tile[wave], q_lds, t_wave + 4 * qd, t_wave + 63, a.T, scale2, lane, s, m_row, l_row);
+  part_m[wave][lane] = m_row;
+  part_l[wave][lane] = l_row;
   __syncthreads();
   if (scores) {
     float m_all = -1e30f, l_all = 0.0f;
@@ -1113,28 +1167,217 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
     for (int w = 0; w < NT / 64; ++w) m_all = fmaxf(m_all, m_w[w]);
 #pragma unroll
     for (int w = 0; w < NT / 64; ++w) l_all = __builtin_fmaf(l_w[w], fast_exp2(m_w[w] - m_all), l_all);
-    float wgt[4];
-    to_each_row(fast_exp2(m_row - m_all) * (1.0f / l_all), wgt);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      float col[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int g = 2 * half + (i >> 2);
-        col[i] = s[0][g][i & 3] * wgt[0];
-#pragma unroll
-        for (int rb = 1; rb < 4; ++rb) col[i] = __builtin_fmaf(s[rb][g][i & 3], wgt[rb], col[i]);
+    column_sums(s, fast_exp2(m_row - m_all) * (1.0f / l_all), lane, [&](int g, int i, float sum) {
+      const int t = t_wave + 16 * g + 4 * qd + i;
+      if (t < a.T) {
+        if constexpr (TOPK) mass_lds[t] = sum;
+        a.score[(size_t)bh * a.score_stride + t] = sum;
       }
-      const float sum = row_sums_each(col, mrow);  // lanes of mrow 2 * (4*(g - 2*half) + i): key 16*g + 4*qd + i
-      const int t = t_wave + 32 * half + 16 * (mrow >> 3) + 4 * qd + ((mrow >> 1) & 3);
-      if ((mrow & 1) == 0 && t < a.T) {
-        mass_lds[t] = sum;
-        a.mass[(size_t)bh * a.T + t] = sum;
-      }
-    }
+    });
   }
-  __syncthreads();
-  topk_row<true, NT>(a, bh, mass_lds, (int)threadIdx.x < a.T ? __float_as_uint(mass_lds[threadIdx.x]) : 0u);
+  if constexpr (TOPK) {
+    __syncthreads();
+    topk_row<true, NT>(a, bh, mass_lds, (int)threadIdx.x < a.T ? __float_as_uint(mass_lds[threadIdx.x]) : 0u);
+  }
+}
+
+// ---- pivot scoring with every key read once, W = 64 -------------------------------------------------------------------
+// As psa_small_kernel, over as many workgroups per head as its keys need: a workgroup's exponentials (512 keys, 64 registers
+// a lane) wait in registers while the row statistics go around between the workgroups of a head, so that every key is read,
+// converted, multiplied and exponentiated once instead of twice.
+// The statistics of a chunk are 64 words (reference and sum of a row) that say themselves whether they are there: a
+// published word is never zero (the sum is at least 1 unless no key is seen, and then the reference is -1e30), and a launch
+// in front clears them; so nothing has to be ordered but the word itself.  A head's workgroups are consecutive, and
+// workgroups are dispatched in order: those of the oldest unfinished head are resident together.  Where they are not after all
+// (fewer places than chunks), a workgroup that has looked kOncePolls times scores a missing chunk itself: same code, same
+// words, so the result does not depend on it, and every wait ends.
+// What bounds it: neither issue (vector unit about 45 % busy, matrix pipe 20 %) nor the exchange (without waiting for the
+// words it takes as long) but the loads between: two workgroups of eight wavefronts per CU, 128 registers each, leave room to
+// request half of the next head's keys behind the first look at the words and no more.  The same loop without the
+// arithmetic takes 0.94 of the time, without the loads 0.8.  Keys are dealt to the wavefronts four at a time, so that
+// all wavefronts' loads are 8 KB in a row (64 keys each, 16 KB in a row: 251 -> 239 us at 8 x 32 x 16384).
+// Us per selection, two passes and this: 32 heads, 8 x 16384 keys 357 -> 239, 16 x 4096 184 -> 127, 33 x 2170 314 -> 150,
+// 2 x 32768 187 -> 137, 1 x 1024 16.9 -> 16.3.  Not kept: 256 registers and 128 keys a wavefront (252 at 8 x 16384; a
+// lone wavefront per SIMD and workgroup waits for its own chains), four wavefronts a workgroup, three workgroups a CU and
+// all keys requested ahead (143 at 16 x 4096), six wavefronts (they do not spread evenly over four SIMDs: one workgroup a CU).
+constexpr int kOnceGroups = 4;  // groups of 16 keys of a wavefront
+constexpr int kOnceWaves = kOnceKeys / (16 * kOnceGroups);
+constexpr int kOnceStep = 16 * kOnceWaves;  // keys from one group of a wavefront to its next
+static_assert(kOnceWaves == 8, "rows are staged by 512 threads, statistics merged for 8 wavefronts");
+#ifndef AKVQ_ONCE_POLLS
+#define AKVQ_ONCE_POLLS (1 << 14)
+#endif
+constexpr int kOncePolls = AKVQ_ONCE_POLLS;  // looks at missing words, about a microsecond each
+constexpr int kOnceBatch = 4;                // chunks whose words a wavefront requests together
+constexpr int kOnceWords = (kOnceMaxChunks + kOnceWaves - 1) / kOnceWaves;  // chunks whose words it collects, at most
+
+__global__ __launch_bounds__(256) void clear_stats_kernel(u32x4 *words, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) words[i] = (u32x4){0u, 0u, 0u, 0u};
+}
+
+// Memory through a buffer descriptor: what lies past the end reads as zero and is not written (the sum of the lane's and the
+// scalar offset is checked, also where the scalar one alone lies past the end: measured), and a tile of accesses needs
+// one address register.
+struct Buffer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ Buffer(const void *p, uint32_t bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000)) {}
+  static constexpr int kStream = 2;                    // non-temporal
+  static constexpr int kAgent = 16 | (int)0x80000000;  // past the caches that other workgroups don't share; never merged or moved
+  template <int POLICY>
+  __device__ __forceinline__ u32x4 load_x4(uint32_t lane_bytes, uint32_t bytes) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_bytes, (int)bytes, POLICY);
+  }
+  template <int POLICY>
+  __device__ __forceinline__ u32x2 load_x2(uint32_t lane_bytes, uint32_t bytes) const {
+    return __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane_bytes, (int)bytes, POLICY);
+  }
+  template <int POLICY>
+  __device__ __forceinline__ void store_x2(u32x2 v, uint32_t lane_bytes, uint32_t bytes) const {
+    __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)lane_bytes, (int)bytes, POLICY);
+  }
+  __device__ __forceinline__ void store(float v, uint32_t lane_bytes) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, (int)lane_bytes, 0, 0);
+  }
+};
+
+// A workgroup barrier that orders LDS only: loads and stores in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// WORDS: chunks whose words one wavefront collects, at most; AHEAD: groups of the next head's keys that are requested ahead.
+// gridDim.y workgroup rows take the heads in turn.
+template <int WORDS, int AHEAD>
+__global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs a) {  // 4 wavefronts per SIMD: at most 128 registers
+  __shared__ u32x4 key_tile[kOnceWaves][256];
+  __shared__ u32x4 q_lds[2][1024];
+  __shared__ float part_m[kOnceWaves][64], part_l[kOnceWaves][64], got_m[kOnceWaves][64], got_l[kOnceWaves][64];
+  __shared__ uint32_t missing[kOnceWaves];
+  const int own = (blockIdx.x + blockIdx.y) % gridDim.x, n_heads = a.B * a.Hq, group = a.Hq / a.Hkv;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tid = threadIdx.x;
+  const float scale2 = a.sm_scale * kLog2e;
+  KeyGroup raw[kOnceGroups];
+  u32x4 row_piece[2];
+  auto request_keys = [&](int bhq, int c, int g0, int g1) {
+    const Buffer keys(a.k + (size_t)(bhq / group) * a.T * kD, bhq < n_heads ? a.T * (kD * 2) : 0);
+#pragma unroll
+    for (int g = g0; g < g1; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        raw[g].raw[i] = keys.load_x4<Buffer::kStream>(16 * (tid & 63), (c * kOnceKeys + kOnceStep * g + 4 * kOnceWaves * i + 4 * wave) * (kD * 2));
+  };
+  auto request_first = [&](int bhq, int c) {  // the rows (consecutive threads, consecutive pieces) and half of the keys
+    const Buffer rows(a.q_tail + (size_t)bhq * 64 * kD, bhq < n_heads ? 64 * kD * 2 : 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) row_piece[x] = rows.load_x4<0>(16 * tid + 8192 * x, 0);
+    request_keys(bhq, c, 0, AHEAD);
+  };
+  auto keep_rows = [&](u32x4 *q) {  // as operands: slot (rb, kc, lane)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      q[((tid >> 8) * 4 + ((tid & 15) >> 2)) * 64 + (tid & 3) * 16 + ((tid >> 4) & 15) + 512 * x] =
+          __builtin_bit_cast(u32x4, rows8_as_bf16(row_piece[x]));
+  };
+  auto merge = [&](const float (&pm)[kOnceWaves][64], const float (&pl)[kOnceWaves][64], float &m_all, float &l_all) {
+    const int lane = tid & 63;
+    m_all = -1e30f;  // the wavefronts' statistics of row `lane`
+    l_all = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kOnceWaves; ++w) m_all = fmaxf(m_all, pm[w][lane]);
+#pragma unroll
+    for (int w = 0; w < kOnceWaves; ++w) l_all = __builtin_fmaf(pl[w][lane], fast_exp2(pm[w][lane] - m_all), l_all);
+  };
+  int bhq = blockIdx.y, c = own, buf = 0;
+  request_first(bhq, c);
+  keep_rows(q_lds[0]);
+  lds_barrier();
+  for (;;) {
+    asm volatile("" : "+v"(tid));  // no address of the lane's is kept from round to round
+    const int lane = tid & 63, t_lane = c * kOnceKeys + 4 * kOnceWaves * (lane >> 4) + 4 * wave;
+    const Buffer words(reinterpret_cast<uint64_t *>(a.row_stats) + (size_t)bhq * a.n_chunk * 64, a.n_chunk * 512);
+    request_keys(bhq, c, AHEAD, kOnceGroups);
+    f32x4 s[4][kOnceGroups];
+    float m_row = -1e30f, l_row = 0.0f, m_all, l_all;
+    score_wave_keys<kOnceGroups, 2, kOnceStep>(raw, key_tile[wave], q_lds[buf], t_lane, (c + 1) * kOnceKeys - 1, a.T, scale2, lane, s, m_row, l_row);
+    part_m[wave][lane] = m_row;
+    part_l[wave][lane] = l_row;
+    lds_barrier();
+    if (wave == 0) {
+      merge(part_m, part_l, m_all, l_all);
+      words.store_x2<Buffer::kAgent>((u32x2){__float_as_uint(l_all), __float_as_uint(m_all)}, 8 * lane, 512 * c);
+    }
+    // This wavefront collects chunks wave, wave + 8, ..., kOnceBatch at a time.  The next head's first requests go out
+    // behind the first look: loads return in order.
+    const int next_bhq = bhq + gridDim.y;
+    float mm = -1e30f, ll = 0.0f;
+    uint32_t need_all = 0u;
+    int polls = 0;
+#pragma unroll
+    for (int b = 0; b < WORDS; b += kOnceBatch) {
+      u32x2 got[kOnceBatch];
+      uint32_t need = 0u;
+      auto look = [&](int i) {
+        got[i] = words.load_x2<Buffer::kAgent>(8 * lane, 512 * min(wave + kOnceWaves * (b + i), a.n_chunk - 1));
+      };
+      auto is_there = [&](int i) { return __ballot((got[i][0] | got[i][1]) == 0u) == 0ull; };
+#pragma unroll
+      for (int i = 0; i < kOnceBatch; ++i) look(i);
+      if (b == 0) request_first(next_bhq, own);
+#pragma unroll
+      for (int i = 0; i < kOnceBatch; ++i) need |= is_there(i) ? 0u : 1u << i;
+      while (need != 0u && polls < kOncePolls) {
+        ++polls;
+        __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+        for (int i = 0; i < kOnceBatch; ++i)
+          if ((need >> i) & 1u) look(i);
+#pragma unroll
+        for (int i = 0; i < kOnceBatch; ++i)
+          if (((need >> i) & 1u) && is_there(i)) need &= ~(1u << i);
+      }
+      float m_new = mm, m_got[kOnceBatch];
+#pragma unroll
+      for (int i = 0; i < kOnceBatch; ++i) {
+        m_got[i] = wave + kOnceWaves * (b + i) < a.n_chunk ? __uint_as_float(got[i][1]) : -INFINITY;
+        m_new = fmaxf(m_new, m_got[i]);
+      }
+      ll *= fast_exp2(mm - m_new);
+#pragma unroll
+      for (int i = 0; i < kOnceBatch; ++i) ll = __builtin_fmaf(__uint_as_float(got[i][0]), fast_exp2(m_got[i] - m_new), ll);
+      mm = m_new;
+      need_all |= need << b;
+    }
+    got_m[wave][lane] = mm;
+    got_l[wave][lane] = ll;
+    if (lane == 0) missing[wave] = need_all;
+    keep_rows(q_lds[buf ^ 1]);
+    lds_barrier();
+    merge(got_m, got_l, m_all, l_all);
+    const uint32_t left = missing[lane & (kOnceWaves - 1)];  // one wavefront's per lane
+    const uint64_t who = __ballot(left != 0u);
+    if (__builtin_expect(who != 0ull || c != own, 0)) {
+      c = own;
+      if (who != 0ull) {
+        const int w = __ffsll((long long)who) - 1;
+        c = min(w + kOnceWaves * (__ffs(__builtin_amdgcn_readlane((int)left, w)) - 1), a.n_chunk - 1);
+      }
+      lds_barrier();  // `missing` has been read
+      request_first(bhq, c);
+      continue;
+    }
+    const Buffer mass(a.score + (size_t)bhq * a.score_stride, a.T * 4);
+    asm volatile("" : "+v"(tid));
+    const int t_mass = own * kOnceKeys + 4 * kOnceWaves * ((tid >> 4) & 3) + 4 * wave;
+    column_sums(s, fast_exp2(m_row - m_all) * __builtin_amdgcn_rcpf(l_all), tid & 63,
+                [&](int g, int i, float sum) { mass.store(sum, 4 * (t_mass + kOnceStep * g + i)); });
+    bhq = next_bhq;
+    buf ^= 1;
+    if (bhq >= n_heads) break;
+  }
 }
 
 // ---- massive-activation score (Section III-B.2): largest channel magnitude of every token's hidden state ----
@@ -1171,11 +1414,13 @@ static hipError_t topk_allow_large_lds() {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && ((done.load(std::memory_order_acquire) >> dev) & 1ull)) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_kernel<true, kTopkWideThreads>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTopkStageMax * sizeof(float)));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_kernel<true, 256>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTopkStageMax * sizeof(float)));
+  const void *kernels[] = {reinterpret_cast<const void *>(&topk_kernel<true, kTopkWideThreads>),
+                           reinterpret_cast<const void *>(&topk_kernel<true, 256>),
+                           reinterpret_cast<const void *>(&topk_kernel<true, kTopkWideThreads, true>),
+                           reinterpret_cast<const void *>(&topk_kernel<true, 256, true>)};
+  for (const void *kernel : kernels)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTopkStageMax * sizeof(float)));
   if (e == hipSuccess && dev >= 0 && dev < 64) done.fetch_or(1ull << dev, std::memory_order_release);
   return e;
 }
@@ -1191,7 +1436,10 @@ static hipError_t launch_topk(const SelectArgs &k, hipStream_t stream) {
     hipError_t e = topk_allow_large_lds();
     if (e != hipSuccess) return e;
   }
-  if (k.T > kTopkStageMax) {
+  if (k.score_path != kScoreTwoPasses && k.Hq > k.Hkv) {  // (of at most kTopkStageMax keys)
+    if (wide) hipLaunchKernelGGL((topk_kernel<true, kTopkWideThreads, true>), grid, dim3(kTopkWideThreads), lds, stream, k);
+    else hipLaunchKernelGGL((topk_kernel<true, 256, true>), grid, dim3(256), lds, stream, k);
+  } else if (k.T > kTopkStageMax) {
     if (wide) hipLaunchKernelGGL((topk_kernel<false, kTopkWideThreads>), grid, dim3(kTopkWideThreads), 0, stream, k);
     else hipLaunchKernelGGL((topk_kernel<false, 256>), grid, dim3(256), 0, stream, k);
   } else {
@@ -1258,14 +1506,29 @@ static void launch_psa_passes(const SelectArgs &a, hipStream_t stream) {
   hipLaunchKernelGGL(psa_mass_kernel<NRB>, dim3(a.n_chunk, a.B * a.Hkv), block, 0, stream, a);
 }
 
+static void launch_psa_once(const SelectArgs &a, hipStream_t stream) {
+  const size_t pairs = (size_t)a.B * a.Hq * a.n_chunk * 32;  // of words
+  hipLaunchKernelGGL(clear_stats_kernel, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, stream,
+                     reinterpret_cast<u32x4 *>(a.row_stats), pairs);
+  // as many heads abreast as two workgroups per CU hold, in rounds of equal length
+  const int heads = a.B * a.Hq, most = 2 * kScoreCus / a.n_chunk, rounds = (heads + most - 1) / most;
+  const dim3 grid(a.n_chunk, (heads + rounds - 1) / rounds), block(64 * kOnceWaves);
+  if (a.n_chunk <= kOnceBatch * kOnceWaves) hipLaunchKernelGGL((psa_once_kernel<kOnceBatch, 2>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((psa_once_kernel<kOnceWords, 1>), grid, block, 0, stream, a);
+}
+
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream) {
-  if (score_small(a.B, a.Hq, a.Hkv, a.T, a.W, a.sm_scale) && a.mass_shared == nullptr) {
-    const dim3 grid(a.B * a.Hkv);
-    if (a.T <= 256) hipLaunchKernelGGL(psa_small_kernel<256>, grid, dim3(256), 0, stream, a);
-    else if (a.T <= 512) hipLaunchKernelGGL(psa_small_kernel<512>, grid, dim3(512), 0, stream, a);
-    else hipLaunchKernelGGL(psa_small_kernel<kSmallKeys>, grid, dim3(kSmallKeys), 0, stream, a);
-    return hipGetLastError();
+  if (a.score_path == kScoreSmall) {
+    const dim3 grid(a.B * a.Hq);
+    const bool whole = a.Hq == a.Hkv;  // with the top-k
+    if (a.T <= 256) hipLaunchKernelGGL((whole ? psa_small_kernel<256, true> : psa_small_kernel<256, false>), grid, dim3(256), 0, stream, a);
+    else if (a.T <= 512) hipLaunchKernelGGL((whole ? psa_small_kernel<512, true> : psa_small_kernel<512, false>), grid, dim3(512), 0, stream, a);
+    else hipLaunchKernelGGL((whole ? psa_small_kernel<kSmallKeys, true> : psa_small_kernel<kSmallKeys, false>), grid, dim3(kSmallKeys), 0, stream, a);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || whole ? e : launch_topk(a, stream);
   }
+  if (a.score_path == kScoreOnce) launch_psa_once(a, stream);
+  else
   switch (a.W / 16) {
     case 1: launch_psa_passes<1>(a, stream); break;
     case 2: launch_psa_passes<2>(a, stream); break;
