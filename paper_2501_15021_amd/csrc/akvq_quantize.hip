@@ -332,10 +332,26 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
     const int e2 = idx < cnt ? sidx[idx] : 0x7FFFFFFF;
     if (e2 >= t0 && e2 < t0 + kTokBlock) slot_of[e2 - t0] = idx;
   } else {
-    for (int base = 0; base < cnt; base += 64) {
-      const int e = base + lane < cnt ? sidx[base + lane] : 0x7FFFFFFF;
-      if (e >= t0 && e < t0 + kTokBlock) slot_of[e - t0] = base + lane;
+    // Lists of more than 2048 entries: the stretch between two samples is sampled again until the run starts within 96
+    // entries of its first, and two loads cover it.  (Reading the whole list, 64 entries a step, took longer than all the
+    // rest from there on: 7 prompts of 15167 tokens, 2463 of them text, 28/4 heads, 109.6 us,
+    // now 58; 1 of 20000, 32 heads, 182 -> 83.)
+    int below = __popcll(__ballot(e1 < t0));  // (an int: the builtin's own type is unsigned)
+    int base = max(below - 1, 0) * stride, span = stride;
+    while (span > 96) {
+      const int step = (span + 63) >> 6;
+      const int at = base + lane * step;
+      const int e = lane * step < span && at < cnt ? sidx[at] : 0x7FFFFFFF;
+      below = __popcll(__ballot(e < t0));
+      base += max(below - 1, 0) * step;
+      span = step;
     }
+    int e2[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) e2[x] = base + 64 * x + lane < cnt ? sidx[base + 64 * x + lane] : 0x7FFFFFFF;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      if (e2[x] >= t0 && e2[x] < t0 + kTokBlock) slot_of[e2[x] - t0] = base + 64 * x + lane;
   }
   wave_lds_sync();
 
