@@ -16,17 +16,19 @@ namespace {
 // Text positions of one batch element, listed for all of its kv-heads by one workgroup per (batch, kv-head).  Latency is
 // all there is to it: a row of a few KB, scanned once.  Each thread takes kTsaBytes consecutive positions at a time, so a
 // round of loads, one workgroup scan and two barriers cover 4096 positions (256 before: 4001 positions of 256 heads took
-// 11.2 us, now 5.9 us).
+// 11.2 us, now 5.9 us), or 16384 with 1024 threads, which longer rows get where two workgroups per CU hold
+// them all (us per call: 28 heads of 15167 positions 8.4 -> 6.3, 32 of 32768 9.7 -> 5.8; but 2048 of 8192 8.3 and 15.9).
 constexpr int kTsaBytes = 16;
-__global__ __launch_bounds__(256) void select_tsa_kernel(SelectArgs a) {
-  __shared__ int wave_tot[2][4];
+template <int NT>
+__global__ __launch_bounds__(NT) void select_tsa_kernel(SelectArgs a) {
+  __shared__ int wave_tot[2][NT / 64];
   const int bh = blockIdx.x, b = bh / a.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint8_t *mask = a.is_text + (size_t)b * a.T;
   int32_t *out = a.sal_idx + (size_t)bh * a.S_cap;
   const bool aligned = (reinterpret_cast<uintptr_t>(mask) & 15u) == 0;  // uniform: whole rows of 16-byte loads
   int base_count = 0, copy = 0;
-  for (int base = 0; base < a.T; base += 256 * kTsaBytes, copy ^= 1) {
+  for (int base = 0; base < a.T; base += NT * kTsaBytes, copy ^= 1) {
     const int t0 = base + threadIdx.x * kTsaBytes;
     uint32_t set = 0u;  // bit i: position t0 + i is text
     if (aligned && t0 + kTsaBytes <= a.T) {
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(256) void select_tsa_kernel(SelectArgs a) {
     __syncthreads();  // (two copies: the next round's totals do not overwrite these)
     int pos = base_count + upto - __popc(set);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
       const int c = wave_tot[copy][w];
       if (w < wave) pos += c;
       base_count += c;
@@ -1458,7 +1460,9 @@ hipError_t launch_select_massive(const SelectArgs &a, hipStream_t stream) {
 }
 
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream) {
-  hipLaunchKernelGGL(select_tsa_kernel, dim3(a.B * a.Hkv), dim3(256), 0, stream, a);
+  const dim3 grid(a.B * a.Hkv);
+  if (a.T <= 256 * kTsaBytes || a.B * a.Hkv > 2 * kScoreCus) hipLaunchKernelGGL(select_tsa_kernel<256>, grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(select_tsa_kernel<1024>, grid, dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 
