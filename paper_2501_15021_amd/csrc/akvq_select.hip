@@ -171,6 +171,7 @@ __device__ __forceinline__ void stage_query_rows(const uint16_t *q_head, int wav
 }
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kStatsMost = 1152921504606846976.0f;  // 2^60: a row's sum beyond it (or infinite, or NaN) has its reference raised
 constexpr float kLazyRaise = 12.0f;  // a row reference is raised only for logits this far (base 2) above it
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }  // bare v_exp_f32
 
@@ -229,6 +230,17 @@ __device__ __forceinline__ void stats_add_group(RowStats &s, const f32x4 (&acc)[
       s.l[rb] += (fast_exp2(x[rb][0]) + fast_exp2(x[rb][1])) + (fast_exp2(x[rb][2]) + fast_exp2(x[rb][3]));
   } else {
     stats_raise_and_add<NRB>(s, acc, scale2, t_first, T, W, mrow, qd, row0);
+  }
+}
+// ... without a look at how far above the reference they are: the sums tell (kStatsMost)
+template <int NRB>
+__device__ __forceinline__ void stats_add_unseen(RowStats &s, const f32x4 (&acc)[4], float scale2) {
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) {
+    float e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = fast_exp2(__builtin_fmaf(acc[rb][i], scale2, -s.m[rb]));
+    s.l[rb] += (e[0] + e[1]) + (e[2] + e[3]);
   }
 }
 // the row's four lanes share the reference: their sums add up (lanes of quarter 0 hold the result)
@@ -505,7 +517,11 @@ __device__ __forceinline__ void score_block_group(const bf16x8 (&q)[NRB * 4], co
 
 // pass 1: per (b, hq, chunk): reference and sum of exponentials (base 2) of every tail row, as psa_row_stats_kernel.
 // NRB: row blocks per wavefront (4: one wavefront per head; 2: two).
-template <int NRB, int MAXIT>
+// LONG: chunks of 2048 keys.  Their blocks are added up without a look at the logits, branch-free, and the sums tell whether one
+// lay far above its row's reference: such a block is done again, group by group.  Us per selection, without and with it:
+// 32 x 32768 keys, 28/4 heads, 1207 -> 1152 (of which this pass is half), 16 x 8192, 32/8 heads, 226.5 -> 221.7; with shorter chunks
+// the first references cost what it gains or more (20 x 2500, 28/4 heads, 77.6 -> 79.9).
+template <int NRB, int MAXIT, bool LONG>
 __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_row_stats_gqa_kernel(SelectArgs a) {
   constexpr int kHeadWaves = 4 / NRB;                      // wavefronts per query head
   constexpr int kMaxWaves = kGqaMaxHeads * kHeadWaves;     // scoring wavefronts of a workgroup, at most
@@ -555,11 +571,24 @@ __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_row_stats_g
     }
     const u32x4 *buf = kbuf[j & 1];
     const int t_block = t_chunk + j * kGqaBlockKeys;
+    bool again = true;  // the block's groups one by one, references raised as needed
     if (t_block + kGqaBlockKeys - 1 <= a.T - a.W) {
       // Every key of the block is seen by every tail row (all but the last blocks of a context): no masks; keys are
       // read from LDS one group ahead of their products, the products issued one group ahead of the exponentials.
+      again = false;
       f32x4 acc_a[4], acc_b[4];
       bf16x8 kb_a[4], kb_b[4];
+      if (LONG && j == 0) {  // references from the chunk's first group
+        score_block_group<NRB, true>(q, buf, 0, lane, acc_a);
+        stats_raise_and_add<NRB>(st_row, acc_a, scale2, t_block, a.T, a.W, mrow, qd, 16 * rb0);
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) st_row.l[rb] = 0.0f;
+      }
+      const RowStats before = st_row;
+      auto add = [&](const f32x4 (&acc)[4], int g) {
+        if constexpr (LONG) stats_add_unseen<NRB>(st_row, acc, scale2);
+        else stats_add_group<NRB>(st_row, acc, scale2, t_block + 16 * g, a.T, a.W, mrow, qd, 16 * rb0);
+      };
       read_block_group(buf, 0, lane, kb_a);
       read_block_group(buf, 1, lane, kb_b);
       products_of_group<NRB, true>(q, kb_a, acc_a);
@@ -567,14 +596,22 @@ __global__ __launch_bounds__(64 * kGqaMaxHeads * (4 / NRB)) void psa_row_stats_g
       for (int g = 0; g < kGqaBlockGroups; g += 2) {
         if (g + 2 < kGqaBlockGroups) read_block_group(buf, g + 2, lane, kb_a);
         products_of_group<NRB, true>(q, kb_b, acc_b);
-        stats_add_group<NRB>(st_row, acc_a, scale2, t_block + 16 * g, a.T, a.W, mrow, qd, 16 * rb0);
+        add(acc_a, g);
         if (g + 2 < kGqaBlockGroups) {
           read_block_group(buf, g + 3, lane, kb_b);
           products_of_group<NRB, true>(q, kb_a, acc_a);
         }
-        stats_add_group<NRB>(st_row, acc_b, scale2, t_block + 16 * g + 16, a.T, a.W, mrow, qd, 16 * rb0);
+        add(acc_b, g + 1);
       }
-    } else {
+      if constexpr (LONG) {
+        bool far = false;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) far |= !(st_row.l[rb] <= kStatsMost);
+        again = __ballot(far) != 0ull;
+        if (again) st_row = before;
+      }
+    }
+    if (again) {
       for (int g = 0; g < kGqaBlockGroups; ++g) {
         const int t_first = t_block + 16 * g;
         if (t_first >= a.T) break;  // uniform over the workgroup
@@ -1487,8 +1524,10 @@ static void launch_psa_gqa_passes(const SelectArgs &a, hipStream_t stream) {
   const dim3 grid(a.n_chunk, a.B * a.Hkv);
   // first pass: two wavefronts per head and two feeders (one feeder would be the slowest wavefront of the workgroup:
   // about 240 vector instructions per block against 150 of a scoring wavefront); second pass: one per head, one feeder
-  hipLaunchKernelGGL((psa_row_stats_gqa_kernel<2, FEEDER ? kGqaItems / 2 : kGqaItems / (2 * kGqaMaxHeads)>), grid,
-                     dim3(64 * (2 * R + (FEEDER ? 2 : 0))), 0, stream, a);
+  constexpr int kItems = FEEDER ? kGqaItems / 2 : kGqaItems / (2 * kGqaMaxHeads);
+  const dim3 block(64 * (2 * R + (FEEDER ? 2 : 0)));
+  if (a.chunk == kScoreChunk) hipLaunchKernelGGL((psa_row_stats_gqa_kernel<2, kItems, true>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((psa_row_stats_gqa_kernel<2, kItems, false>), grid, block, 0, stream, a);
   if (R == 1) {
     // one head: a single scoring wavefront would leave the workgroup at two wavefronts; two of 32 rows and two feeders
     hipLaunchKernelGGL((psa_mass_gqa_kernel<2, kGqaItems / 2>), grid, dim3(64 * 4), 0, stream, a);
