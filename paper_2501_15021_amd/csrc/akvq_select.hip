@@ -1068,13 +1068,10 @@ __device__ __forceinline__ float row_sums_each(const float (&v)[8], int mrow) {
   return z + row_dpp<0xB1>(z);                 // r and r ^ 1
 }
 
-// NG groups of 16 keys against the 64 tail rows: s = exponentials, row 16*rb + mrow, keys t_lane + GROUP_STEP * g + i;
-// t_last: the last of them; m_row, l_row: reference and sum of row `lane`.  STEP: groups multiplied at a time (their
-// operands take 16 registers each, but the rows are read from LDS once for each step).
-template <int NG, int STEP, int GROUP_STEP>
-__device__ __forceinline__ void score_wave_keys(const KeyGroup (&raw)[NG], u32x4 *tile, const u32x4 *q_lds, int t_lane, int t_last, int T,
-                                                float scale2, int lane, f32x4 (&s)[4][NG], float &m_row, float &l_row) {
-  const int mrow = lane & 15;
+// NG groups of 16 keys against the 64 tail rows: s = products, row 16*rb + mrow, keys t_lane + GROUP_STEP * g + i;
+// STEP: groups multiplied at a time (their operands take 16 registers each, but the rows are read from LDS once for each step).
+template <int NG, int STEP>
+__device__ __forceinline__ void score_wave_keys(const KeyGroup (&raw)[NG], u32x4 *tile, const u32x4 *q_lds, int lane, f32x4 (&s)[4][NG]) {
 #pragma unroll
   for (int g0 = 0; g0 < NG; g0 += STEP) {
     bf16x8 key[STEP][4];
@@ -1095,6 +1092,12 @@ __device__ __forceinline__ void score_wave_keys(const KeyGroup (&raw)[NG], u32x4
     }
     if (STEP < NG) __builtin_amdgcn_sched_barrier(0);
   }
+}
+// ... turned into exponentials; t_last: the last of the keys; m_row, l_row: reference and sum of row `lane`
+template <int NG, int GROUP_STEP>
+__device__ __forceinline__ void exponentials_of_keys(f32x4 (&s)[4][NG], int t_lane, int t_last, int T, float scale2, int lane, float &m_row,
+                                                     float &l_row) {
+  const int mrow = lane & 15;
   if (t_last > T - 64) {  // some key is hidden from some row, or past the end: behind position T - 64 + row
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb) {
@@ -1156,7 +1159,7 @@ __device__ __forceinline__ void column_sums(const f32x4 (&s)[4][NG], float weigh
 // topk_kernel, which adds them up.  Up to kSmallKeys keys: what twelve wavefronts of 168 registers, three on a SIMD, hold.
 // Three launches of 5 to 6.6 us each did this before, each waiting for the one in front of it; us per selection, 32 heads,
 // then and now: 1 x 640 keys 16.3 -> 13.3, 1 x 256 15.1 -> 7.8, 16 x 512 37.7 -> 21.3, 64 x 256 72 -> 38, 64 x 768 162 -> 128;
-// in two launches, several heads per KV head: 1 x 368, 32/8 heads, 20.8 -> 13.1, 16 x 275, 28/4 heads, 29.6 -> 22.3.
+// in two launches, several heads per KV head: 1 x 368, 32/8 heads, 20.8 -> 13.1, 16 x 275, 28/4 heads, 29.6 -> 19.5.
 // Keys come line by line and are turned through LDS: loads in operand order (half lines) took 1.4 us longer at 1 x 640.
 // The time is a chain: rows and keys from memory (one CU brings a head's 164 KB), products, exponentials, three barriers,
 // and about 2.5 us of top-k.
@@ -1174,6 +1177,8 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
   const uint16_t *k_rows = a.k + (size_t)(TOPK ? bh : bh / (a.Hq / a.Hkv)) * a.T * kD, *q_rows = a.q_tail + (size_t)bh * 64 * kD;
   const float scale2 = a.sm_scale * kLog2e;
   // rows first: they are looked at first, and loads return in order
+  // eight wavefronts: two workgroups a CU, which 128 registers allow (18 x 500 keys, 28/4 heads: 27.5 us a selection with 144, 24.5)
+  constexpr int kStep = NT == 512 && !TOPK ? 2 : 4;
   constexpr int kRowPieces = (1024 + NT - 1) / NT;  // 16-byte pieces of the rows per thread; consecutive threads, consecutive pieces
   u32x4 row_piece[kRowPieces];
 #pragma unroll
@@ -1193,7 +1198,10 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
   __syncthreads();
   f32x4 s[4][4];  // exponentials: row 16*rb + mrow, keys 16*g + 4*qd + i
   float m_row = -1e30f, l_row = 0.0f;
-  if (scores) score_wave_keys<4, 4, 16>(raw, key_tile[wave], q_lds, t_wave + 4 * qd, t_wave + 63, a.T, scale2, lane, s, m_row, l_row);
+  if (scores) {
+    score_wave_keys<4, kStep>(raw, key_tile[wave], q_lds, lane, s);
+    exponentials_of_keys<4, 16>(s, t_wave + 4 * qd, t_wave + 63, a.T, scale2, lane, m_row, l_row);
+  }
   part_m[wave][lane] = m_row;
   part_l[wave][lane] = l_row;
   __syncthreads();
@@ -1232,13 +1240,16 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
 // words, so the result does not depend on it, and every wait ends.
 // What bounds it: neither issue (vector unit about 45 % busy, matrix pipe 20 %) nor the exchange (without waiting for the
 // words it takes as long) but the loads between: two workgroups of eight wavefronts per CU, 128 registers each, leave room to
-// request half of the next head's keys behind the first look at the words and no more.  The same loop without the
-// arithmetic takes 0.94 of the time, without the loads 0.8.  Keys are dealt to the wavefronts four at a time, so that
-// all wavefronts' loads are 8 KB in a row (64 keys each, 16 KB in a row: 251 -> 239 us at 8 x 32 x 16384).
-// Us per selection, two passes and this: 32 heads, 8 x 16384 keys 357 -> 239, 16 x 4096 184 -> 127, 33 x 2170 314 -> 150,
-// 2 x 32768 187 -> 137, 1 x 1024 16.9 -> 16.3.  Not kept: 256 registers and 128 keys a wavefront (252 at 8 x 16384; a
+// request half of the next head's keys ahead and no more.  They are requested as soon as the products have taken the
+// registers of the present ones, in front of the exponentials: behind the first look at the words, 5 us later, 8 x 32 x 16384
+// took 240 us, now 234.  (Timing builds of that one: without the arithmetic 0.94 of the time, without the loads 0.8.)  Keys are
+// dealt to the wavefronts four at a time, so that all wavefronts' loads are 8 KB in a row (64 keys each, 16 KB in a row: 251
+// -> 239).
+// Us per selection, two passes and this: 32 heads, 8 x 16384 keys 357 -> 234, 16 x 4096 184 -> 127, 33 x 2170 314 -> 147,
+// 2 x 32768 187 -> 137, 1 x 1024 16.9 -> 16.5.  Not kept: 256 registers and 128 keys a wavefront (252 when this took 250; a
 // lone wavefront per SIMD and workgroup waits for its own chains), four wavefronts a workgroup, three workgroups a CU and
-// all keys requested ahead (143 at 16 x 4096), six wavefronts (they do not spread evenly over four SIMDs: one workgroup a CU).
+// all keys requested ahead (143 at 16 x 4096), six wavefronts (they do not spread evenly over four SIMDs: one workgroup a CU),
+// the other half of the keys requested between the halves of the column sums (237).
 constexpr int kOnceGroups = 4;  // groups of 16 keys of a wavefront
 constexpr int kOnceWaves = kOnceKeys / (16 * kOnceGroups);
 constexpr int kOnceStep = 16 * kOnceWaves;  // keys from one group of a wavefront to its next
@@ -1341,7 +1352,11 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     request_keys(bhq, c, AHEAD, kOnceGroups);
     f32x4 s[4][kOnceGroups];
     float m_row = -1e30f, l_row = 0.0f, m_all, l_all;
-    score_wave_keys<kOnceGroups, 2, kOnceStep>(raw, key_tile[wave], q_lds[buf], t_lane, (c + 1) * kOnceKeys - 1, a.T, scale2, lane, s, m_row, l_row);
+    score_wave_keys<kOnceGroups, 2>(raw, key_tile[wave], q_lds[buf], lane, s);
+    const int next_bhq = bhq + gridDim.y;
+    request_first(next_bhq, own);
+    __builtin_amdgcn_sched_barrier(0);  // (not behind the exponentials)
+    exponentials_of_keys<kOnceGroups, kOnceStep>(s, t_lane, (c + 1) * kOnceKeys - 1, a.T, scale2, lane, m_row, l_row);
     part_m[wave][lane] = m_row;
     part_l[wave][lane] = l_row;
     lds_barrier();
@@ -1349,9 +1364,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
       merge(part_m, part_l, m_all, l_all);
       words.store_x2<Buffer::kAgent>((u32x2){__float_as_uint(l_all), __float_as_uint(m_all)}, 8 * lane, 512 * c);
     }
-    // This wavefront collects chunks wave, wave + 8, ..., kOnceBatch at a time.  The next head's first requests go out
-    // behind the first look: loads return in order.
-    const int next_bhq = bhq + gridDim.y;
+    // This wavefront collects chunks wave, wave + 8, ..., kOnceBatch at a time (loads return in order: behind the keys).
     float mm = -1e30f, ll = 0.0f;
     uint32_t need_all = 0u;
     int polls = 0;
@@ -1365,7 +1378,6 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
       auto is_there = [&](int i) { return __ballot((got[i][0] | got[i][1]) == 0u) == 0ull; };
 #pragma unroll
       for (int i = 0; i < kOnceBatch; ++i) look(i);
-      if (b == 0) request_first(next_bhq, own);
 #pragma unroll
       for (int i = 0; i < kOnceBatch; ++i) need |= is_there(i) ? 0u : 1u << i;
       while (need != 0u && polls < kOncePolls) {
