@@ -29,7 +29,8 @@ def _append(d, b, G, clip, before, rope, tiers):
 # two to 33 blocks, the number of units no multiple of four (a group that ends behind the last block), rows that leave the first
 # block partly old; just above two workgroups per CU and at it
 @pytest.mark.parametrize("B,H,T,G,before", [(131, 1, 33, 128, 0), (33, 4, 70, 64, 0), (67, 2, 140, 128, 17), (43, 3, 200, 64, 5), (33, 2, 400, 128, 0),
-                                            (23, 2, 690, 128, 31), (15, 2, 1040, 64, 0), (64, 1, 150, 128, 0), (128, 2, 30, 128, 9)])
+                                            (23, 2, 690, 128, 31), (15, 2, 1040, 64, 0), (64, 1, 150, 128, 0), (128, 2, 30, 128, 9),
+                                            (259, 1, 33, 128, 0), (67, 4, 70, 64, 0), (27, 3, 919, 128, 0)])
 @pytest.mark.parametrize("kind", ["plain", "rope", "tiers"])
 def test_flat_groups(B, H, T, G, before, kind):
     d = synth.generate(synth.small("flat", B=B, Hq=H, Hkv=H, T=T, G=G, n_text_head=5, n_text_tail=3, top_k=8, W=16), seed=97, device="cuda")
