@@ -1266,9 +1266,9 @@ __global__ __launch_bounds__(256) void clear_stats_kernel(u32x4 *words, size_t n
   if (i < n) words[i] = (u32x4){0u, 0u, 0u, 0u};
 }
 
-// Memory through a buffer descriptor: what lies past the end reads as zero and is not written (the sum of the lane's and the
-// scalar offset is checked, also where the scalar one alone lies past the end: measured), and a tile of accesses needs
-// one address register.
+// Memory through a buffer descriptor: what lies past the end reads as zero and is not written, and a tile of accesses needs one
+// address register.  Only the lane's offset is certain to be compared with the end: an access that may pass it has no scalar
+// offset (those of load_x2 and store_x2 stay inside).
 struct Buffer {
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ __forceinline__ Buffer(const void *p, uint32_t bytes)
@@ -1276,8 +1276,8 @@ struct Buffer {
   static constexpr int kStream = 2;                    // non-temporal
   static constexpr int kAgent = 16 | (int)0x80000000;  // past the caches that other workgroups don't share; never merged or moved
   template <int POLICY>
-  __device__ __forceinline__ u32x4 load_x4(uint32_t lane_bytes, uint32_t bytes) const {
-    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_bytes, (int)bytes, POLICY);
+  __device__ __forceinline__ u32x4 load_x4(uint32_t lane_bytes) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_bytes, 0, POLICY);
   }
   template <int POLICY>
   __device__ __forceinline__ u32x2 load_x2(uint32_t lane_bytes, uint32_t bytes) const {
@@ -1314,16 +1314,20 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
   u32x4 row_piece[2];
   auto request_keys = [&](int bhq, int c, int g0, int g1) {
     const Buffer keys(a.k + (size_t)(bhq / group) * a.T * kD, bhq < n_heads ? a.T * (kD * 2) : 0);
+    int at = 16 * (tid & 63) + (c * kOnceKeys + kOnceStep * g0 + 4 * wave) * (kD * 2);
 #pragma unroll
     for (int g = g0; g < g1; ++g)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        raw[g].raw[i] = keys.load_x4<Buffer::kStream>(16 * (tid & 63), (c * kOnceKeys + kOnceStep * g + 4 * kOnceWaves * i + 4 * wave) * (kD * 2));
+      for (int i = 0; i < 4; ++i) {
+        asm volatile("" : "+v"(at));  // one register, moved on from load to load
+        raw[g].raw[i] = keys.load_x4<Buffer::kStream>(at);
+        at += 4 * kOnceWaves * (kD * 2);
+      }
   };
   auto request_first = [&](int bhq, int c) {  // the rows (consecutive threads, consecutive pieces) and half of the keys
     const Buffer rows(a.q_tail + (size_t)bhq * 64 * kD, bhq < n_heads ? 64 * kD * 2 : 0);
 #pragma unroll
-    for (int x = 0; x < 2; ++x) row_piece[x] = rows.load_x4<0>(16 * tid + 8192 * x, 0);
+    for (int x = 0; x < 2; ++x) row_piece[x] = rows.load_x4<0>(16 * tid + 8192 * x);
     request_keys(bhq, c, 0, AHEAD);
   };
   auto keep_rows = [&](u32x4 *q) {  // as operands: slot (rb, kc, lane)
