@@ -279,6 +279,28 @@ inline int score_path(int B, int Hq, int Hkv, int T, int W, float sm_scale, bool
   if (heads <= small) return kScoreSmall;
   return heads * chunks <= 2 * kScoreCus ? kScoreOnce : kScoreTwoPasses;
 }
+// How long a workgroup of psa_once_kernel waits for the statistics of its head's other chunks before it scores a missing one itself:
+// kOncePolls looks for a whole head, and none any more for that head once they have run out.  The head behind one that
+// ran out gets kOnceFewPolls, and kOncePolls again behind one that did not.  So a row of workgroups whose siblings are never
+// resident waits 16 ms once and 64 us for each later head, and scores every chunk of its heads itself.
+#ifndef AKVQ_ONCE_POLLS
+#define AKVQ_ONCE_POLLS (1 << 14)
+#endif
+constexpr int kOncePolls = AKVQ_ONCE_POLLS;  // about a microsecond each
+constexpr int kOnceFewPolls = kOncePolls < 64 ? kOncePolls : 64;
+struct OnceWait {
+  int left = kOncePolls;  // looks at missing words
+  bool gave_up = false;
+  __host__ __device__ bool look_again() { return left > 0 && left-- > 0; }
+  __host__ __device__ void give_up() { left = 0; gave_up = true; }
+  __host__ __device__ void next_head() { left = gave_up ? kOnceFewPolls : kOncePolls; gave_up = false; }
+};
+// The missing chunk (set bits) that the workgroup of chunk `own` scores: the first one from its own on, so that those who wait
+// for the same chunks do not all begin with the same one.
+__host__ __device__ inline int once_chunk_to_score(uint64_t missing, int own) {
+  const uint64_t ahead = missing >> own << own;
+  return __builtin_ctzll(ahead ? ahead : missing);
+}
 // Masses of single query heads, with several per KV head: elements of a shape, and the most of any batch up to B and prompt up to T
 inline int score_stride(int T) { return (T + 3) / 4 * 4; }
 inline size_t score_head_masses(int B, int Hq, int Hkv, int T) { return Hq > Hkv ? (size_t)B * Hq * score_stride(T) : 0; }

@@ -1236,8 +1236,8 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
 // published word is never zero (the sum is at least 1 unless no key is seen, and then the reference is -1e30), and a launch
 // in front clears them; so nothing has to be ordered but the word itself.  A head's workgroups are consecutive, and
 // workgroups are dispatched in order: those of the oldest unfinished head are resident together.  Where they are not after all
-// (fewer places than chunks), a workgroup that has looked kOncePolls times scores a missing chunk itself: same code, same
-// words, so the result does not depend on it, and every wait ends.
+// (fewer places than chunks, or another kernel in them), a workgroup that has looked often enough (OnceWait) scores a missing
+// chunk itself: same code, same words, so the result does not depend on it, and every wait ends.
 // What bounds it: neither issue (vector unit about 45 % busy, matrix pipe 20 %) nor the exchange (without waiting for the
 // words it takes as long) but the loads between: two workgroups of eight wavefronts per CU, 128 registers each, leave room to
 // request half of the next head's keys ahead and no more.  They are requested as soon as the products have taken the
@@ -1253,11 +1253,8 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
 constexpr int kOnceGroups = 4;  // groups of 16 keys of a wavefront
 constexpr int kOnceWaves = kOnceKeys / (16 * kOnceGroups);
 constexpr int kOnceStep = 16 * kOnceWaves;  // keys from one group of a wavefront to its next
+static_assert(kOnceMaxChunks <= 64, "missing chunks are the bits of a ballot");
 static_assert(kOnceWaves == 8, "rows are staged by 512 threads, statistics merged for 8 wavefronts");
-#ifndef AKVQ_ONCE_POLLS
-#define AKVQ_ONCE_POLLS (1 << 14)
-#endif
-constexpr int kOncePolls = AKVQ_ONCE_POLLS;  // looks at missing words, about a microsecond each
 constexpr int kOnceBatch = 4;                // chunks whose words a wavefront requests together
 constexpr int kOnceWords = (kOnceMaxChunks + kOnceWaves - 1) / kOnceWaves;  // chunks whose words it collects, at most
 
@@ -1346,6 +1343,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     for (int w = 0; w < kOnceWaves; ++w) l_all = __builtin_fmaf(pl[w][lane], fast_exp2(pm[w][lane] - m_all), l_all);
   };
   int bhq = blockIdx.y, c = own, buf = 0;
+  OnceWait wait;
   request_first(bhq, c);
   keep_rows(q_lds[0]);
   lds_barrier();
@@ -1371,7 +1369,6 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     // This wavefront collects chunks wave, wave + 8, ..., kOnceBatch at a time (loads return in order: behind the keys).
     float mm = -1e30f, ll = 0.0f;
     uint32_t need_all = 0u;
-    int polls = 0;
 #pragma unroll
     for (int b = 0; b < WORDS; b += kOnceBatch) {
       u32x2 got[kOnceBatch];
@@ -1384,8 +1381,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
       for (int i = 0; i < kOnceBatch; ++i) look(i);
 #pragma unroll
       for (int i = 0; i < kOnceBatch; ++i) need |= is_there(i) ? 0u : 1u << i;
-      while (need != 0u && polls < kOncePolls) {
-        ++polls;
+      while (need != 0u && wait.look_again()) {
         __builtin_amdgcn_s_sleep(1);
 #pragma unroll
         for (int i = 0; i < kOnceBatch; ++i)
@@ -1412,13 +1408,13 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     keep_rows(q_lds[buf ^ 1]);
     lds_barrier();
     merge(got_m, got_l, m_all, l_all);
-    const uint32_t left = missing[lane & (kOnceWaves - 1)];  // one wavefront's per lane
-    const uint64_t who = __ballot(left != 0u);
+    // chunk `lane`, which wavefront lane % 8 has looked for
+    const uint64_t who = __ballot(lane < a.n_chunk && ((missing[lane % kOnceWaves] >> (lane / kOnceWaves)) & 1u));
     if (__builtin_expect(who != 0ull || c != own, 0)) {
       c = own;
       if (who != 0ull) {
-        const int w = __ffsll((long long)who) - 1;
-        c = min(w + kOnceWaves * (__ffs(__builtin_amdgcn_readlane((int)left, w)) - 1), a.n_chunk - 1);
+        wait.give_up();
+        c = once_chunk_to_score(who, own);
       }
       lds_barrier();  // `missing` has been read
       request_first(bhq, c);
@@ -1429,6 +1425,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     const int t_mass = own * kOnceKeys + 4 * kOnceWaves * ((tid >> 4) & 3) + 4 * wave;
     column_sums(s, fast_exp2(m_row - m_all) * __builtin_amdgcn_rcpf(l_all), tid & 63,
                 [&](int g, int i, float sum) { mass.store(sum, 4 * (t_mass + kOnceStep * g + i)); });
+    wait.next_head();
     bhq = next_bhq;
     buf ^= 1;
     if (bhq >= n_heads) break;

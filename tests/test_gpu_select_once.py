@@ -112,3 +112,37 @@ def test_replays_of_a_captured_selection():
         run()
         torch.cuda.synchronize()
         assert torch.equal(got, mass) and torch.equal(idx, c.sal_idx)
+
+
+def test_beside_other_work():
+    """Two selections of more workgroups than are resident, and a decode call, on three streams at once: the bits of each alone."""
+    parts = [(w, d, akvq.Cache(w.B, w.Hkv, 128, (w.T + 63) // 64 * 64, 64, fill=0), torch.zeros(w.B, w.Hkv, w.T, device="cuda"))
+             for w, d in (_inputs(12, 16, 16, 4500, seed=1), _inputs(3, 24, 24, 17000, seed=2))]
+    w, d = _inputs(8, 16, 16, 2000, seed=3)
+    c = akvq.Cache(w.B, w.Hkv, 128, 2048, 64, fill=0)
+    akvq.quantize_append(c, d["k"], d["v"], 0.8)
+    q = d["q_tail"][:, :, -1].contiguous()
+
+    def select(i):
+        w, d, c, mass = parts[i]
+        akvq.select_salient(c, akvq.MODE_PSA, q_tail=d["q_tail"], k=d["k"], top_k=8, sm_scale=w.sm_scale, mass_out=mass)
+        return mass, c.sal_idx
+
+    calls = [lambda: select(0), lambda: select(1), lambda: akvq.decode_attention(c, q, w.sm_scale)]
+    alone = []
+    for call in calls:
+        alone.append([t.clone() for t in call()])
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(3):
+        for _, _, cache, mass in parts:
+            mass.fill_(float("nan"))
+            cache.sal_idx.fill_(-1)
+        torch.cuda.synchronize()
+        got = []
+        for stream, call in zip(streams, calls):
+            with torch.cuda.stream(stream):
+                got.append([t.clone() for t in call()])
+        torch.cuda.synchronize()
+        for one, other in zip(alone, got):
+            assert all(torch.equal(x[..., :8] if x.dtype == torch.int32 else x, y[..., :8] if y.dtype == torch.int32 else y) for x, y in zip(one, other))
