@@ -157,9 +157,9 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   a.mass = mass_out ? mass_out : reinterpret_cast<float *>(static_cast<char *>(workspace) + stats);
   a.score = a.mass;
   a.score_stride = T;
-  if (Hq > c->Hkv) {
+  if (a.score_path != akvq::kScoreTwoPasses && Hq > c->Hkv) {
     a.score = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes + shared_bytes);
-    a.score_stride = akvq::score_stride(T);
+    a.score_stride = (int)akvq::score_stride(T);  // (prompts of at most kOnceKeys * kOnceMaxChunks keys)
   }
   if (mode == AKVQ_MODE_PSA_SHARED)
     a.mass_shared = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes);

@@ -302,7 +302,7 @@ __host__ __device__ inline int once_chunk_to_score(uint64_t missing, int own) {
   return __builtin_ctzll(ahead ? ahead : missing);
 }
 // Masses of single query heads, with several per KV head: elements of a shape, and the most of any batch up to B and prompt up to T
-inline int score_stride(int T) { return (T + 3) / 4 * 4; }
+inline size_t score_stride(int T) { return ((size_t)T + 3) / 4 * 4; }
 inline size_t score_head_masses(int B, int Hq, int Hkv, int T) { return Hq > Hkv ? (size_t)B * Hq * score_stride(T) : 0; }
 inline size_t score_max_head_masses(int B, int Hq, int Hkv, int T, int W) {
   if (Hq <= Hkv || W != 64 || Hq > 8 * Hkv) return 0;

@@ -47,6 +47,16 @@ int main() {
     (void)akvq_decode_default_splits(B, Hkv, T_cap);
     for (int ns : {1, 5, 1024}) (void)akvq_decode_workspace_bytes(B, Hkv * 8, ns);
   }
+  // the size queries take any int: a prompt one token longer never needs less, up to the largest
+  for (int B : {1, 64}) for (int Hq : {4, 8, 28, 32, 36}) for (int W : {16, 64}) {
+    size_t before = 0;
+    for (int T : {2147483580, 2147483584, 2147483643, 2147483644, 2147483645, 2147483646, 2147483647}) {
+      const size_t now = akvq_select_workspace_bytes(B, Hq, 4, T, W);
+      if (now < before || now < (size_t)B * 4 * T * sizeof(float)) return 5;
+      before = now;
+      (void)akvq_massive_workspace_bytes(B, T);
+    }
+  }
   int b = 0, e = 0;
   for (int n_tiles = 0; n_tiles < 300; ++n_tiles) for (int ns = 1; ns < 40; ++ns) for (int s = 0; s < ns; ++s)
     if (akvq_decode_split_range(n_tiles, ns, s, &b, &e) < 0 || b > e || e > n_tiles) return 3;
@@ -63,6 +73,9 @@ int main() {
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA, nullptr, P, 4, P, 200, 64, 16, 0.1f, nullptr, P, big, nullptr), AKVQ_OK);
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA_SHARED, nullptr, P, 4, P, 200, 16, 64, 0.1f, static_cast<float *>(P), P, big, nullptr), AKVQ_OK);
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA, nullptr, P, 4, P, 200, 64, 16, 0.1f, nullptr, P, 100, nullptr), AKVQ_ERR_WORKSPACE);
+  akvq_cache longest = cache(2, 2, 128, 2147483584, 64, 100);
+  for (int T : {2147483583, 2147483584}) for (int W : {16, 64}) for (int Hq : {2, 4, 14})
+    EXPECT(akvq_select_salient(&longest, AKVQ_MODE_PSA, nullptr, P, Hq, P, T, W, 16, 0.1f, nullptr, P, (size_t)1 << 46, nullptr), AKVQ_OK);
   EXPECT(akvq_select_massive(&c, P, 200, 1024, 15, 100.f, nullptr, P, big, nullptr), AKVQ_OK);
   EXPECT(akvq_fold_hadamard(P, static_cast<char *>(P) + 4096, 256, 128, 0, nullptr), AKVQ_OK);
   EXPECT(akvq_fold_hadamard(P, P, 256, 128, 1, nullptr), AKVQ_OK);
