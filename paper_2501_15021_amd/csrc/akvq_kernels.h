@@ -104,7 +104,7 @@ inline int decode_splits_by_two(long units, int tiles) {
 // 131072 rows: nowhere slower.  (Two full rounds of four wavefronts, 512 / units, are better still on long streams that leave
 // CUs idle: 52 units of 32768 rows, 9 splits, 35.3; 44 and 60 units: equal.)
 inline int decode_most_splits(long units, int T_len) {
-  const int tiles = (T_len + 63) / 64;
+  const int tiles = (int)(((long)T_len + 63) / 64);
   if (units > 64) return decode_splits_by_two(units, tiles);
   if (T_len < 1024) return 1;
   long n = 256 / units;

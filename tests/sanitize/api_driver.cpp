@@ -55,6 +55,7 @@ int main() {
       if (now < before || now < (size_t)B * 4 * T * sizeof(float)) return 5;
       before = now;
       (void)akvq_massive_workspace_bytes(B, T);
+      if (akvq_decode_default_splits(B, 4, T) != akvq_decode_default_splits(B, 4, 2147483584)) return 6;
     }
   }
   int b = 0, e = 0;
