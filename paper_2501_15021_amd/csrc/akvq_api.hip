@@ -138,7 +138,11 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
   while (chunk < akvq::kScoreChunk && workspace_bytes < needed(chunk)) chunk += 64;
   // ... and one without room for what a single pass over the keys keeps there serves two passes
   const size_t heads = round_up(akvq::score_head_masses(c->B, Hq, c->Hkv, T) * sizeof(float), 256);
-  const int path = akvq::score_path(c->B, Hq, c->Hkv, T, W, sm_scale, mode == AKVQ_MODE_PSA_SHARED);
+  // (or the single launch that took prompts of up to kSmallKeys keys of any number of heads before: 64 x 768 keys, 32 heads, 128 us,
+  // 162 in two passes)
+  const bool shared = mode == AKVQ_MODE_PSA_SHARED;
+  int path = akvq::score_path(c->B, Hq, c->Hkv, T, W, sm_scale, shared);
+  if (path == akvq::kScoreOnce && Hq == c->Hkv && T <= akvq::kSmallKeys && !shared && workspace_bytes < needed(akvq::kOnceKeys)) path = akvq::kScoreSmall;
   const int once = path == akvq::kScoreOnce ? akvq::kOnceKeys : T;  // keys per chunk
   if (path != akvq::kScoreTwoPasses && workspace_bytes >= needed(once) + heads) {
     a.score_path = path;
@@ -161,7 +165,7 @@ int akvq_select_salient(const akvq_cache *c, int mode, const uint8_t *is_text, c
     a.score = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes + shared_bytes);
     a.score_stride = (int)akvq::score_stride(T);  // (prompts of at most kOnceKeys * kOnceMaxChunks keys)
   }
-  if (mode == AKVQ_MODE_PSA_SHARED)
+  if (shared)
     a.mass_shared = reinterpret_cast<float *>(static_cast<char *>(workspace) + stats + mass_bytes);
   return hip_status(akvq::launch_select_psa(a, s));
 }

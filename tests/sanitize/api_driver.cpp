@@ -9,7 +9,7 @@
 #include "../../include/akvq.h"
 #include "../../paper_2501_15021_amd/csrc/akvq_kernels.h"
 
-static int g_launches = 0;
+static int g_launches = 0, g_path = -1;
 namespace akvq {
 hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t) {
   if (a.n_blk <= 0 || a.first_blk < 0 || B <= 0 || (G != 64 && G != 128)) abort();
@@ -21,7 +21,7 @@ hipError_t launch_decode_attention(const DecodeArgs &a, int G, hipStream_t) {
 }
 hipError_t decode_static_scratch(void **ptr) { *ptr = reinterpret_cast<void *>(0x7F0000100000ull); return hipSuccess; }
 hipError_t launch_select_tsa(const SelectArgs &, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_select_psa(const SelectArgs &a, hipStream_t) { if (a.n_chunk <= 0) abort(); ++g_launches; return hipSuccess; }
+hipError_t launch_select_psa(const SelectArgs &a, hipStream_t) { if (a.n_chunk <= 0) abort(); g_path = a.score_path; ++g_launches; return hipSuccess; }
 hipError_t launch_select_massive(const SelectArgs &, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_fold_hadamard(const uint16_t *, uint16_t *, int, int, int, hipStream_t) { ++g_launches; return hipSuccess; }
 hipError_t launch_stream_read(const void *, size_t, uint32_t *, int, hipStream_t) { ++g_launches; return hipSuccess; }
@@ -74,6 +74,27 @@ int main() {
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA, nullptr, P, 4, P, 200, 64, 16, 0.1f, nullptr, P, big, nullptr), AKVQ_OK);
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA_SHARED, nullptr, P, 4, P, 200, 16, 64, 0.1f, static_cast<float *>(P), P, big, nullptr), AKVQ_OK);
   EXPECT(akvq_select_salient(&c, AKVQ_MODE_PSA, nullptr, P, 4, P, 200, 64, 16, 0.1f, nullptr, P, 100, nullptr), AKVQ_ERR_WORKSPACE);
+  // which kernels score a prompt in workspace of the size asked for and in as little as is accepted (row statistics of 2048-key
+  // chunks): 513 to 768 keys of more than two workgroups per CU in one launch then, what needs more in two passes
+  auto path_in = [&](int B, int Hq, int Hkv, int T, int mode, bool least) {
+    akvq_cache one = cache(B, Hkv, 128, (T + 63) / 64 * 64, 64, 0);
+    const auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+    const size_t bytes = least ? up((size_t)B * Hq * ((T + 2047) / 2048) * 64 * 8) + up((size_t)B * Hkv * T * 4) + up((size_t)B * T * 4)
+                               : akvq_select_workspace_bytes(B, Hq, Hkv, T, 64);
+    g_path = -1;
+    return akvq_select_salient(&one, mode, nullptr, P, Hq, P, T, 64, 16, 0.1f, nullptr, P, bytes, nullptr) == AKVQ_OK ? g_path : -2;
+  };
+  for (int least : {0, 1}) {
+    EXPECT(path_in(64, 32, 32, 513, AKVQ_MODE_PSA, least), least ? akvq::kScoreSmall : akvq::kScoreOnce);
+    EXPECT(path_in(17, 32, 32, 768, AKVQ_MODE_PSA, least), least ? akvq::kScoreSmall : akvq::kScoreOnce);
+    EXPECT(path_in(64, 32, 32, 768, AKVQ_MODE_PSA_SHARED, least), least ? akvq::kScoreTwoPasses : akvq::kScoreOnce);
+    EXPECT(path_in(64, 32, 32, 769, AKVQ_MODE_PSA, least), least ? akvq::kScoreTwoPasses : akvq::kScoreOnce);
+    EXPECT(path_in(1, 32, 32, 640, AKVQ_MODE_PSA, least), akvq::kScoreSmall);
+    EXPECT(path_in(1, 32, 32, 640, AKVQ_MODE_PSA_SHARED, least), akvq::kScoreTwoPasses);
+    EXPECT(path_in(1, 28, 4, 640, AKVQ_MODE_PSA, least), least ? akvq::kScoreTwoPasses : akvq::kScoreSmall);
+    EXPECT(path_in(1, 28, 4, 1640, AKVQ_MODE_PSA, least), least ? akvq::kScoreTwoPasses : akvq::kScoreOnce);
+    EXPECT(path_in(64, 28, 4, 640, AKVQ_MODE_PSA, least), akvq::kScoreTwoPasses);
+  }
   akvq_cache longest = cache(2, 2, 128, 2147483584, 64, 100);
   for (int T : {2147483583, 2147483584}) for (int W : {16, 64}) for (int Hq : {2, 4, 14})
     EXPECT(akvq_select_salient(&longest, AKVQ_MODE_PSA, nullptr, P, Hq, P, T, W, 16, 0.1f, nullptr, P, (size_t)1 << 46, nullptr), AKVQ_OK);

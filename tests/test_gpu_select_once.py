@@ -66,9 +66,10 @@ def test_several_heads(B, Hq, Hkv, T):
     _check(w, d, c, mass)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,T", [(1, 4, 4, 3000), (1, 28, 4, 400), (1, 12, 2, 1200)])
+@pytest.mark.parametrize("B,Hq,Hkv,T", [(1, 4, 4, 3000), (1, 28, 4, 400), (1, 12, 2, 1200), (17, 32, 32, 700)])
 def test_smaller_workspaces_take_two_passes(B, Hq, Hkv, T):
-    """What held the statistics of 2048-key chunks before still does; a byte less than the one pass needs takes two."""
+    """What held the statistics of 2048-key chunks before still does; a byte less than the one pass needs takes two (or, up to
+    768 keys with one head per KV head, the launch of a workgroup per head)."""
     w, d = _inputs(B, Hq, Hkv, T)
     full, up = akvq.lib().akvq_select_workspace_bytes(B, Hq, Hkv, T, 64), lambda n: (n + 255) // 256 * 256
     rest = up(B * Hkv * T * 4) + up(B * T * 4)
