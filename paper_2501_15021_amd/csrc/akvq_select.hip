@@ -1423,7 +1423,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     const Buffer mass(a.score + (size_t)bhq * a.score_stride, a.T * 4);
     asm volatile("" : "+v"(tid));
     const int t_mass = own * kOnceKeys + 4 * kOnceWaves * ((tid >> 4) & 3) + 4 * wave;
-    column_sums(s, fast_exp2(m_row - m_all) * __builtin_amdgcn_rcpf(l_all), tid & 63,
+    column_sums(s, fast_exp2(m_row - m_all) * (1.0f / l_all), tid & 63,
                 [&](int g, int i, float sum) { mass.store(sum, 4 * (t_mass + kOnceStep * g + i)); });
     wait.next_head();
     bhq = next_bhq;
