@@ -1132,12 +1132,16 @@ __device__ __forceinline__ void exponentials_of_keys(f32x4 (&s)[4][NG], int t_la
   }
   l_row = over_rows_each(x, [](float u, float v) { return u + v; });
 }
-// column sums of such exponentials, each row times its weight (row `lane`): store(g, i, sum), each key by one lane
-template <int NG, typename F>
-__device__ __forceinline__ void column_sums(const f32x4 (&s)[4][NG], float weight, int lane, F store) {
+// column sums of such exponentials, each row times its weight (row `lane`): store(t, sum), each key by one lane.  A weight that is
+// infinite or no number makes the sum of every key its row sees no number, and of no other: row r sees the keys up to T - 64 + r.
+template <int NG, int GROUP_STEP, typename F>
+__device__ __forceinline__ void column_sums(const f32x4 (&s)[4][NG], float weight, int t_lane, int T, int lane, F store) {
   const int mrow = lane & 15;
+  const bool finite = weight <= 3.4028235e38f;
+  const uint64_t spoilt = __ballot(!finite);
+  const int spoilt_to = T - 1 - __builtin_clzll(spoilt | 1u) - (spoilt ? 0 : T);  // (none: in front of the first key)
   float wgt[4];
-  to_each_row(weight, wgt);
+  to_each_row(finite ? weight : 0.0f, wgt);
 #pragma unroll
   for (int half = 0; half < NG / 2; ++half) {
     float col[8];
@@ -1149,7 +1153,8 @@ __device__ __forceinline__ void column_sums(const f32x4 (&s)[4][NG], float weigh
       for (int rb = 1; rb < 4; ++rb) col[i] = __builtin_fmaf(s[rb][g][i & 3], wgt[rb], col[i]);
     }
     const float sum = row_sums_each(col, mrow);  // lanes of mrow 2 * (4*(g - 2*half) + i): key 16*g + 4*qd + i
-    if ((mrow & 1) == 0) store(2 * half + (mrow >> 3), (mrow >> 1) & 3, sum);
+    const int t = t_lane + GROUP_STEP * (2 * half + (mrow >> 3)) + ((mrow >> 1) & 3);
+    if ((mrow & 1) == 0) store(t, t <= spoilt_to ? __builtin_nanf("") : sum);
   }
 }
 
@@ -1214,8 +1219,7 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
     for (int w = 0; w < NT / 64; ++w) m_all = fmaxf(m_all, m_w[w]);
 #pragma unroll
     for (int w = 0; w < NT / 64; ++w) l_all = __builtin_fmaf(l_w[w], fast_exp2(m_w[w] - m_all), l_all);
-    column_sums(s, fast_exp2(m_row - m_all) * (1.0f / l_all), lane, [&](int g, int i, float sum) {
-      const int t = t_wave + 16 * g + 4 * qd + i;
+    column_sums<4, 16>(s, fast_exp2(m_row - m_all) * (1.0f / l_all), t_wave + 4 * qd, a.T, lane, [&](int t, float sum) {
       if (t < a.T) {
         if constexpr (TOPK) mass_lds[t] = sum;
         a.score[(size_t)bh * a.score_stride + t] = sum;
@@ -1423,8 +1427,8 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     const Buffer mass(a.score + (size_t)bhq * a.score_stride, a.T * 4);
     asm volatile("" : "+v"(tid));
     const int t_mass = own * kOnceKeys + 4 * kOnceWaves * ((tid >> 4) & 3) + 4 * wave;
-    column_sums(s, fast_exp2(m_row - m_all) * (1.0f / l_all), tid & 63,
-                [&](int g, int i, float sum) { mass.store(sum, 4 * (t_mass + kOnceStep * g + i)); });
+    column_sums<kOnceGroups, kOnceStep>(s, fast_exp2(m_row - m_all) * (1.0f / l_all), t_mass, a.T, tid & 63,
+                                        [&](int t, float sum) { mass.store(sum, 4 * t); });
     wait.next_head();
     bhq = next_bhq;
     buf ^= 1;
