@@ -8,6 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libakvq.so")
+NOWAIT = os.path.join(HERE, "libakvq_nowait.so")
 SOURCES = ["akvq_api.hip", "akvq_quantize.hip", "akvq_decode.hip", "akvq_select.hip", "akvq_fold.hip", "akvq_stream.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -35,37 +36,33 @@ def build_native() -> str:
     return NATIVE
 
 
-def build_nowait(out: str) -> str:
-    """The library again, behind build(), with a pivot scoring that looks for other workgroups' statistics only once (a test of
-    what a workgroup does that does not find them)."""
-    obj = os.path.join(CSRC, "akvq_select_nowait.o")
-    subprocess.run([HIPCC, *FLAGS, "-DAKVQ_ONCE_POLLS=0", "-c", os.path.join(CSRC, "akvq_select.hip"), "-o", obj], check=True,
-                   stderr=subprocess.DEVNULL)
-    objs = [os.path.join(CSRC, src.replace(".hip", ".o")) for src in SOURCES if src != "akvq_select.hip"]
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out, *objs, obj], check=True)
-    return out
-
-
 def build(verbose: bool = False) -> str:
-    """Compile every kernel source and link the shared library.  Always recompiles."""
-    objs = []
+    """Compile every kernel source and link the shared library, and with it NOWAIT: the same library with a pivot scoring that looks for
+    other workgroups' statistics only once (a test of what a workgroup does that does not find them).  Always recompiles."""
+    jobs = [(src, src.replace(".hip", ".o"), []) for src in SOURCES] + [("akvq_select.hip", "akvq_select_nowait.o", ["-DAKVQ_ONCE_POLLS=0"])]
+    for lib in (LIB, NOWAIT):  # none of an earlier build stays where this one fails
+        if os.path.exists(lib):
+            os.remove(lib)
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    for src, obj, extra in jobs:
+        cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(CSRC, obj)]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        objs.append(obj)
-    for src, p in procs:
+        procs.append((obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    failed = []
+    for obj, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
-        if verbose and out.strip():
+            failed.append(f"hipcc failed on {obj}:\n{out}")
+        elif verbose and out.strip():
             print(out)
-    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
-    subprocess.run(cmd, check=True)
+    if failed:
+        raise RuntimeError("\n".join(failed))
+    objs = [os.path.join(CSRC, src.replace(".hip", ".o")) for src in SOURCES]
+    select, nowait = (os.path.join(CSRC, obj) for obj in ("akvq_select.o", "akvq_select_nowait.o"))
+    for lib, parts in ((LIB, objs), (NOWAIT, [nowait if obj == select else obj for obj in objs])):
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *parts], check=True)
     build_native()
     return LIB
 

@@ -2,17 +2,16 @@
 row statistics.  Masses against binary64 on the operands the call documents, index sets against the top-k of the call's
 own masses, at the borders of the rule that chooses it (score_path), of its chunks of 512 keys and of its rounds of heads."""
 import ctypes as C
-import os
 
 import pytest
 import torch
 
 from paper_2501_15021_amd import binding as akvq
 from paper_2501_15021_amd import synth
+from paper_2501_15021_amd.build import NOWAIT
 from test_gpu_select_chunks import _masses
 
 pytestmark = pytest.mark.gpu
-HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 def _inputs(B, Hq, Hkv, T, seed=811):
@@ -84,7 +83,7 @@ def test_smaller_workspaces_take_two_passes(B, Hq, Hkv, T):
 def test_missing_chunks_are_scored_by_who_waits(B, Hq, Hkv, T):
     """The same kernels built to look for a missing word once: a workgroup that does not find its siblings' statistics scores
     their chunks itself, to the same bits."""
-    lib = C.CDLL(os.path.join(HERE, "libakvq_nowait.so"))
+    lib = C.CDLL(NOWAIT)
     w, d = _inputs(B, Hq, Hkv, T)
     c, mass = _select(w, d)
     c2, mass2 = _select(w, d, lib=lib)
