@@ -31,6 +31,25 @@ struct QuantArgs {
   int skip_overlay;  // the block kernel leaves the 16-bit V rows to the overlay pass (in its launch or behind it)
 };
 hipError_t launch_quantize_append(const QuantArgs &a, int B, int G, hipStream_t stream);
+constexpr long kAppendCus = 256;
+// Whether the groups of four blocks of an append (units: batch elements x KV heads, of n_blk blocks each; two tensors) run on from unit
+// to unit.  Units whose last group is short leave wavefronts without a block, and with an even number of groups the
+// short ones all fall on the same XCDs: from two workgroups a CU on, and a twelfth of the wavefronts idle, the groups run on
+// from unit to unit instead (up to 33 blocks).  29 prompts of 397 tokens, 32 heads, 61.5 -> 52.3 us; 64 of 150, 75 -> 54.
+// With fewer idle it gains nothing (16 of 8200, 4 heads, takes 1.1).  Up to five rounds of workgroups there has to be a round less:
+// a CU whose last workgroup was a short one has four full wavefronts instead (3 of 275, 40 heads, rotary, 720 workgroups to 540, three
+// rounds both: 8.9 -> 9.6; 13 of 350, 8 heads, 8.8 -> 9.5; but 5 of 144, 40 heads, 800 to 500, 11.0 -> 8.1).  Beyond, equal rounds gain
+// as well (4 of 919, 32 heads, eight both: 17.9 -> 16.6).  Of 72 shapes of 512 to 3072 workgroups 54 pass: 0.91 of the time, at most 1.023.
+inline bool append_runs_on(long units, int n_blk, bool window) {
+  const int groups = (n_blk + 3) / 4, idle = 4 * groups - n_blk;
+  const long blocks = units * n_blk, in_units = 2 * units * groups, in_row = 2 * ((blocks + 3) / 4);  // workgroups
+  const auto rounds = [](long workgroups) { return (workgroups + kAppendCus - 1) / kAppendCus; };
+  return !window && n_blk > 1 && 3 * idle >= groups && in_units > 2 * kAppendCus && (in_units > 5 * kAppendCus || rounds(in_row) < rounds(in_units)) &&
+         blocks * n_blk < (1l << 32);
+}
+// Block `at` of such an append is one of unit (at * reciprocal_of_blocks(n_blk)) >> 32: with blocks * n_blk below 2^32 the rounding up
+// does not reach the next unit.
+inline uint32_t reciprocal_of_blocks(int n_blk) { return (uint32_t)(((1ull << 32) + n_blk - 1) / n_blk); }
 
 struct DecodeArgs {
   const uint32_t *k_codes, *v_codes, *k_meta, *v_meta;

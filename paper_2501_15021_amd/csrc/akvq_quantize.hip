@@ -795,7 +795,7 @@ __global__ __launch_bounds__(64) void append_row_kernel(QuantArgs a) {
 
 }  // namespace
 
-constexpr long kCus = 256, kResidentGroups = 4 * kCus;
+constexpr long kCus = kAppendCus, kResidentGroups = 4 * kCus;
 // Who stores the ring rows of an append (n_win of its n_blk blocks hold window rows; units: batch elements x KV heads).
 enum class Ring { kWavefronts, kBlocks, kTwoBodies };
 static Ring ring_by(int n_blk, int n_win, long units, bool tiered, bool rope) {
@@ -845,23 +845,13 @@ static hipError_t launch_blocks(const QuantArgs &a_in, int B, int G, hipStream_t
   // in the launch (8 of 4096 with window 512: 119.0, 119.1) or the overlay's (8 of 1920, 576 slots: 52.3, 56.0).
   a.groups = groups;
   a.turn = (!window || ring == Ring::kBlocks) && groups >= 8 && groups % 2 == 0 && 2l * groups * B * a.Hkv >= 10 * kResidentGroups ? 7 : 0;
-  // Units whose last group of four blocks is short leave wavefronts without a block, and with an even number of groups the
-  // short ones all fall on the same XCDs: from two workgroups a CU on, and a twelfth of the wavefronts idle, the groups run on
-  // from unit to unit instead (up to 33 blocks).  29 prompts of 397 tokens, 32 heads, 61.5 -> 52.3 us; 64 of 150, 75 -> 54.
-  // With fewer idle it gains nothing (16 of 8200, 4 heads, takes 1.1).  Up to five rounds of workgroups there has to be a round less:
-  // a CU whose last workgroup was a short one has four full wavefronts instead (3 of 275, 40 heads, rotary, 720 workgroups to 540, three
-  // rounds both: 8.9 -> 9.6; 13 of 350, 8 heads, 8.8 -> 9.5; but 5 of 144, 40 heads, 800 to 500, 11.0 -> 8.1).  Beyond, equal rounds gain
-  // as well (4 of 919, 32 heads, eight both: 17.9 -> 16.6).  Of 72 shapes of 512 to 3072 workgroups 54 pass: 0.91 of the time, at most 1.02.
-  const long blocks = (long)B * a.Hkv * a.n_blk, in_units = 2l * groups * B * a.Hkv, in_row = 2 * ((blocks + 3) / 4);  // workgroups
-  const auto rounds = [](long workgroups) { return (workgroups + kCus - 1) / kCus; };
-  const int idle = 4 * groups - a.n_blk;
-  const bool flat = !window && a.n_blk > 1 && 3 * idle >= groups && in_units > 2 * kCus && (in_units > 5 * kCus || rounds(in_row) < rounds(in_units)) &&
-                    blocks * a.n_blk < (1l << 32);
+  const long blocks = (long)B * a.Hkv * a.n_blk;
+  const bool flat = append_runs_on((long)B * a.Hkv, a.n_blk, window);
   if (flat) {
     a.groups = (int)blocks;
-    a.turn = (int)(((1ull << 32) + a.n_blk - 1) / a.n_blk);
+    a.turn = (int)reciprocal_of_blocks(a.n_blk);
   }
-  const dim3 grid(flat ? (unsigned)(in_row / 2) : groups, flat ? 1 : B * a.Hkv, 2), block(256);
+  const dim3 grid(flat ? (unsigned)((blocks + 3) / 4) : groups, flat ? 1 : B * a.Hkv, 2), block(256);
 #define AKVQ_LAUNCH_Q(GG, TT, RR) \
   do { \
     if (flat) hipLaunchKernelGGL((quantize_append_flat_kernel<GG, TT, RR>), grid, block, 0, stream, a); \
