@@ -37,7 +37,11 @@ def _select(w, d, top_k=8, lib=None, nbytes=None, mode=akvq.MODE_PSA):
 def _check(w, d, c, mass, top_k=8):
     want = _masses(d, w)
     # the bar of the pivot score: 4e-5 of the element (32-bit sums and exponentials), 1e-12 absolute
+    # (the smallest ones': their logits lie up to 450 below the row's reference, base 2, and are rounded there: 1.9e-5)
     assert ((mass.double() - want).abs() <= 4e-5 * want + 1e-12).all()
+    # ... and of all together, which are those near the reference: about twenty roundings of 2^-24 (an exponential, the row's sums,
+    # the division, the column's sums over rows and heads); 3e-8 to 5e-7 here
+    assert (mass.double() - want).norm() <= 1.2e-6 * want.norm()
     order = torch.sort(mass, dim=-1, descending=True, stable=True).indices[..., :top_k].sort(-1).values
     assert torch.equal(c.sal_idx[..., :top_k].long(), order) and (c.counts() == top_k).all()
 
