@@ -233,11 +233,12 @@ struct SelectArgs {
 // in four round trips, nor beyond four workgroups per CU.
 // Over 1053 shapes (1 to 8 heads per KV head, 4 to 600 units, 258 to 32768 tokens) a selection takes 0.69 of its time with
 // chunks of 2048 on average, at most 1.04 (what two runs of one length differ), and 1.03 of the best length tried.  One
-// prompt, in two passes (score_path has most of those with one head per KV head read once): 32 heads, 640 tokens 29.1 -> 18.7 us, 4096 tokens 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096
+// prompt, in two passes (score_path has most of those with one head per KV head read once): 32 heads, 640 tokens 29.1 -> 18.7 us,
+// 4096 tokens 72.3 -> 31.0, 16384 tokens 82.4 -> 62.8; 28/4 heads, 4096
 // tokens 142 -> 35, 32768 tokens 160 -> 76; 40 prompts of 1300 tokens, 28/4 heads, 100 -> 92, and 16 of 4907 142 -> 103,
 // where halving the chunk until every CU has a workgroup, whatever the rounds and lengths, makes 148 and 151.
-constexpr int kSmallKeys = 768, kOnceKeys = 512, kOnceMaxChunks = 64;  // see score_path
 constexpr int kScoreChunk = 2048, kScoreChunkMin = 128, kScoreMaxFineChunks = 64, kScoreCus = 256;
+constexpr int kSmallKeys = 768, kOnceKeys = 512, kOnceMaxChunks = 64;  // keys of the two kernels that read them once (score_path)
 inline bool score_fine_chunks(int Hq, int Hkv, int W) { return W == 64 && Hq >= Hkv && Hq / Hkv <= 8; }
 inline int score_chunk(int B, int Hq, int Hkv, int T, int W) {
   const long units = (long)B * Hkv, n_coarse = ((long)T + kScoreChunk - 1) / kScoreChunk;

@@ -1237,8 +1237,8 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
 // a lane) wait in registers while the row statistics go around between the workgroups of a head, so that every key is read,
 // converted, multiplied and exponentiated once instead of twice.
 // The statistics of a chunk are 64 words (reference and sum of a row) that say themselves whether they are there: a
-// published word is never zero (the sum is at least 1 unless no key is seen, and then the reference is -1e30), and a launch
-// in front clears them; so nothing has to be ordered but the word itself.  A head's workgroups are consecutive, and
+// published word is never zero (where the reference is 0, the key it comes from adds 1 to the sum; where no key is seen, it is
+// -1e30), and a launch in front clears them; so nothing has to be ordered but the word itself.  A head's workgroups are consecutive, and
 // workgroups are dispatched in order: those of the oldest unfinished head are resident together.  Where they are not after all
 // (fewer places than chunks, or another kernel in them), a workgroup that has looked often enough (OnceWait) scores a missing
 // chunk itself: same code, same words, so the result does not depend on it, and every wait ends.
@@ -1275,7 +1275,7 @@ struct Buffer {
   __device__ __forceinline__ Buffer(const void *p, uint32_t bytes)
       : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000)) {}
   static constexpr int kStream = 2;                    // non-temporal
-  static constexpr int kAgent = 16 | (int)0x80000000;  // past the caches that other workgroups don't share; never merged or moved
+  static constexpr int kShared = 16 | (int)0x80000000;  // with other workgroups: volatile (never merged or moved), which makes it system scope (sc0 sc1)
   template <int POLICY>
   __device__ __forceinline__ u32x4 load_x4(uint32_t lane_bytes) const {
     return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_bytes, 0, POLICY);
@@ -1368,7 +1368,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
     lds_barrier();
     if (wave == 0) {
       merge(part_m, part_l, m_all, l_all);
-      words.store_x2<Buffer::kAgent>((u32x2){__float_as_uint(l_all), __float_as_uint(m_all)}, 8 * lane, 512 * c);
+      words.store_x2<Buffer::kShared>((u32x2){__float_as_uint(l_all), __float_as_uint(m_all)}, 8 * lane, 512 * c);
     }
     // This wavefront collects chunks wave, wave + 8, ..., kOnceBatch at a time (loads return in order: behind the keys).
     float mm = -1e30f, ll = 0.0f;
@@ -1378,7 +1378,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, 4) void psa_once_kernel(SelectArgs
       u32x2 got[kOnceBatch];
       uint32_t need = 0u;
       auto look = [&](int i) {
-        got[i] = words.load_x2<Buffer::kAgent>(8 * lane, 512 * min(wave + kOnceWaves * (b + i), a.n_chunk - 1));
+        got[i] = words.load_x2<Buffer::kShared>(8 * lane, 512 * min(wave + kOnceWaves * (b + i), a.n_chunk - 1));
       };
       auto is_there = [&](int i) { return __ballot((got[i][0] | got[i][1]) == 0u) == 0ull; };
 #pragma unroll
@@ -1587,13 +1587,15 @@ hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream) {
     const hipError_t e = hipGetLastError();
     return e != hipSuccess || whole ? e : launch_topk(a, stream);
   }
-  if (a.score_path == kScoreOnce) launch_psa_once(a, stream);
-  else
-  switch (a.W / 16) {
-    case 1: launch_psa_passes<1>(a, stream); break;
-    case 2: launch_psa_passes<2>(a, stream); break;
-    case 3: launch_psa_passes<3>(a, stream); break;
-    default: launch_psa_passes<4>(a, stream); break;
+  if (a.score_path == kScoreOnce) {
+    launch_psa_once(a, stream);
+  } else {
+    switch (a.W / 16) {
+      case 1: launch_psa_passes<1>(a, stream); break;
+      case 2: launch_psa_passes<2>(a, stream); break;
+      case 3: launch_psa_passes<3>(a, stream); break;
+      default: launch_psa_passes<4>(a, stream); break;
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
