@@ -4,8 +4,8 @@
   on small exact-size heap buffers (tests/sanitize/oracle_driver.c).
 * The host side of the C ABI (csrc/akvq_api.hip: validation, size helpers, descriptor marshalling), compiled with the
   same sanitizers on the host pass only, is driven with the kernel launchers replaced by stubs
-  (tests/sanitize/api_driver.cpp); this build found two signed overflows at the top of the int range (workspace sizing
-  of the pivot score, the KV-split partition), now computed in 64 bits.
+  (tests/sanitize/api_driver.cpp); this build found four signed overflows at the top of the int range (workspace sizing
+  of the pivot score, twice; the KV-split partition and its default), now computed in 64 bits.
 Any report aborts the driver (-fno-sanitize-recover=all), which fails the test.
 """
 import os
