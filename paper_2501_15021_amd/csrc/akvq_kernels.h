@@ -36,16 +36,23 @@ constexpr long kAppendCus = 256;
 // to unit.  Units whose last group is short leave wavefronts without a block, and with an even number of groups the
 // short ones all fall on the same XCDs: from two workgroups a CU on, and a twelfth of the wavefronts idle, the groups run on
 // from unit to unit instead (up to 33 blocks).  29 prompts of 397 tokens, 32 heads, 61.5 -> 52.3 us; 64 of 150, 75 -> 54.
-// With fewer idle it gains nothing (16 of 8200, 4 heads, takes 1.1).  Up to five rounds of workgroups there has to be a round less:
-// a CU whose last workgroup was a short one has four full wavefronts instead (3 of 275, 40 heads, rotary, 720 workgroups to 540, three
-// rounds both: 8.9 -> 9.6; 13 of 350, 8 heads, 8.8 -> 9.5; but 5 of 144, 40 heads, 800 to 500, 11.0 -> 8.1).  Beyond, equal rounds gain
-// as well (4 of 919, 32 heads, eight both: 17.9 -> 16.6).  Of 72 shapes of 512 to 3072 workgroups 54 pass: 0.91 of the time, at most 1.023.
+// With fewer idle it gains nothing (16 of 8200, 4 heads, takes 1.1).
+// Up to ten rounds of workgroups, one per CU each, there has to be a round less: a CU whose last workgroup was a short one has four
+// full wavefronts instead (3 of 275, 40 heads, rotary, 720 workgroups to 540, three rounds both: 8.9 -> 9.6; 3 of 668, 40 heads, 1440
+// to 1320, six both: 10.7 -> 11.7; but 5 of 144, 40 heads, 800 to 500, 11.0 -> 8.1).  From five to ten rounds more than an eighth of
+// the wavefronts, and two of a unit, have to be idle as well (52 of 1051, 2 heads, a twelfth, eight rounds to seven, 13.4 -> 14.5; 3 of 659,
+// 40 heads, an eighth, six to five, 11.6 -> 12.3; 110 of 91, 8 heads, rotary, one of four, seven to six, 12.8 -> 13.8).  Units of three blocks
+// gain from three rounds to two (264 units 6.4 -> 5.2) and not beyond (118 of 91, 4 heads, four to three, 7.7 -> 8.1).
+// 400 shapes that pass, 512 to 8000 workgroups, plain, rotary and with tiers: 0.90 of the time, three above 1.01, at most 1.036 (74 of
+// 314, 4 heads, seven rounds to six, 13.2 -> 13.7).
 inline bool append_runs_on(long units, int n_blk, bool window) {
   const int groups = (n_blk + 3) / 4, idle = 4 * groups - n_blk;
   const long blocks = units * n_blk, in_units = 2 * units * groups, in_row = 2 * ((blocks + 3) / 4);  // workgroups
   const auto rounds = [](long workgroups) { return (workgroups + kAppendCus - 1) / kAppendCus; };
-  return !window && n_blk > 1 && 3 * idle >= groups && in_units > 2 * kAppendCus && (in_units > 5 * kAppendCus || rounds(in_row) < rounds(in_units)) &&
-         blocks * n_blk < (1l << 32);
+  if (window || n_blk <= 1 || 3 * idle < groups || in_units <= 2 * kAppendCus || blocks * n_blk >= (1l << 32)) return false;
+  if (in_units > 10 * kAppendCus) return true;
+  if (rounds(in_row) >= rounds(in_units)) return false;
+  return in_units > 5 * kAppendCus ? idle >= 2 && 2 * idle > groups : n_blk != 3 || in_row <= 2 * kAppendCus;
 }
 // Block `at` of such an append is one of unit (at * reciprocal_of_blocks(n_blk)) >> 32: with blocks * n_blk below 2^32 the rounding up
 // does not reach the next unit.

@@ -27,10 +27,10 @@ def _append(d, b, G, clip, before, rope, tiers):
 
 
 # two to 33 blocks, the number of units no multiple of four (a group that ends behind the last block), rows that leave the first
-# block partly old, just above two and just above five workgroups per CU.  The last two keep their own groups: two workgroups per CU, and
+# block partly old, just above two, five and ten workgroups per CU.  The last two keep their own groups: two workgroups per CU, and
 # no round of workgroups saved (test_append_runs.py says which kernel each takes)
 FLAT = [(257, 1, 33, 128, 0), (67, 4, 70, 64, 0), (67, 2, 140, 128, 17), (43, 3, 200, 64, 5), (33, 2, 400, 128, 0), (23, 2, 640, 128, 31), (15, 2, 1040, 64, 0),
-        (131, 1, 150, 128, 0), (259, 1, 33, 128, 0), (27, 3, 919, 128, 0)]
+        (131, 1, 150, 128, 0), (259, 1, 33, 128, 0), (81, 2, 400, 128, 5), (161, 1, 919, 128, 0)]
 OWN_GROUPS = [(128, 2, 30, 128, 9), (60, 2, 270, 128, 0)]
 
 
