@@ -285,21 +285,23 @@ inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
 // (psa_once_kernel: a launch more, which clears the words they exchange).
 // One head per KV head: in one pass up to kOnceKeys * kOnceMaxChunks keys (beyond, the words a workgroup collects are a
 // quarter of its keys and more).  110 shapes of 513 to 768 keys: 0.76 of the time of two passes; the small kernel up to
-// 512 workgroups, two rounds of them on the CUs: 16 x 640 keys, 32 heads, 33.3 us in small, 33.9 in once, 32 x 640 63.9 and 57.8.
+// 512 workgroups, two rounds of them on the CUs: 16 x 640 keys, 32 heads, 33.3 us in small, 33.9 in once, 32 x 640 63.9 and 57.8.  Up
+// to 64 workgroups of the once kernel and four chunks, two passes of shorter chunks are as fast: 77 such shapes 0.99 of their time, 12 of them
+// 1.02 to 1.07 (16 x 971 keys 14.8 -> 15.8); 143 others of 513 to 2600 keys, up to 200 heads, 0.86, one above 1.01 (1.026).
 // Several heads per KV head: each head reads and converts the keys for itself, which costs what the second pass did (64 x 768
 // keys, 32/8 heads, 101 us in two passes, 112 in one; 16 x 8192, 28/4 heads, 150 and 209), so one pass pays where everything is
 // resident at once: it is a launch less, or the same three with shorter ones (2 x 1000, 12/2 heads, 26.2 -> 18.2).  In the small
 // kernel up to 512 keys that is 512 workgroups, two per CU, beyond one per CU; up to 256 keys with four per CU it is faster at any
 // number (73 x 256, 28/4 heads, 64 -> 38), but not with eight heads, whose two passes have no feeders to wait for (32 x 256,
-// 64/8 heads, 1.05 of the time).  671 shapes of 256 to 4096 keys, 2 to 8 heads: 0.87 of the time of two passes, none slower
-// by more than 1 %.
+// 64/8 heads, 1.05 of the time).  671 shapes of 256 to 4096 keys, 2 to 8 heads: 0.87 of the time of two passes; of 240 in one pass,
+// 513 to 20000 keys, 0.82, ten 1.02 to 1.046 (100 x 1202 keys, 4 heads, 20.6 -> 21.3), all with 2 to 4 heads and among others that gain as much.
 enum ScorePath { kScoreTwoPasses, kScoreSmall, kScoreOnce };
 inline int score_path(int B, int Hq, int Hkv, int T, int W, float sm_scale, bool shared) {
   const long heads = (long)B * Hq, chunks = ((long)T + kOnceKeys - 1) / kOnceKeys;
   if (W != 64 || Hq > 8 * Hkv || !(sm_scale > 0.0f) || chunks > kOnceMaxChunks) return kScoreTwoPasses;
   if (Hq == Hkv) {
     if (T <= 512 || (T <= kSmallKeys && heads <= 2 * kScoreCus)) return shared ? kScoreTwoPasses : kScoreSmall;
-    return kScoreOnce;
+    return T <= 4 * kOnceKeys && heads * chunks <= 64 ? kScoreTwoPasses : kScoreOnce;
   }
   if (shared) return kScoreTwoPasses;  // (each KV head's mass is needed before they are added)
   const long small = T <= 256 ? (Hq < 8 * Hkv ? heads : 2 * kScoreCus) : T <= 512 ? 2 * kScoreCus : T <= kSmallKeys ? kScoreCus : 0;

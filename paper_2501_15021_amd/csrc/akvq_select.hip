@@ -1250,7 +1250,7 @@ __global__ __launch_bounds__(NT) void psa_small_kernel(SelectArgs a) {
 // dealt to the wavefronts four at a time, so that all wavefronts' loads are 8 KB in a row (64 keys each, 16 KB in a row: 251
 // -> 239).
 // Us per selection, two passes and this: 32 heads, 8 x 16384 keys 357 -> 234, 16 x 4096 184 -> 127, 33 x 2170 314 -> 147,
-// 2 x 32768 187 -> 137, 1 x 1024 16.9 -> 16.5.  Not kept: 256 registers and 128 keys a wavefront (252 when this took 250; a
+// 2 x 32768 187 -> 137.  Not kept: 256 registers and 128 keys a wavefront (252 when this took 250; a
 // lone wavefront per SIMD and workgroup waits for its own chains), four wavefronts a workgroup, three workgroups a CU and
 // all keys requested ahead (143 at 16 x 4096), six wavefronts (they do not spread evenly over four SIMDs: one workgroup a CU),
 // the other half of the keys requested between the halves of the column sums (237).

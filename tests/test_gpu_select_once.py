@@ -47,8 +47,10 @@ def _check(w, d, c, mass, top_k=8):
 
 
 # one head per KV head: 512 workgroups of the small kernel and one more head, two chunks and two tokens more, a last chunk of one
-# key, heads in one round and in several, 32 and 33 chunks (one and two batches of words), 64 and the first prompt beyond
-@pytest.mark.parametrize("B,H,T", [(16, 32, 513), (19, 27, 513), (19, 27, 768), (1, 3, 769), (1, 2, 1024), (2, 2, 1025), (1, 2, 1537), (5, 40, 1500),
+# key, 64 workgroups of up to four chunks (two passes) and more, heads in one round and in several, 32 and 33 chunks (one and two
+# batches of words), 64 and the first prompt beyond
+@pytest.mark.parametrize("B,H,T", [(16, 32, 513), (19, 27, 513), (19, 27, 768), (11, 3, 769), (17, 2, 1024), (11, 2, 1025), (9, 2, 1537), (5, 40, 1500),
+                                   (1, 32, 1024), (1, 33, 1024), (1, 2, 2048), (1, 2, 2049),
                                    (2, 16, 8193), (1, 2, 16384), (1, 2, 16385), (1, 9, 32768), (1, 2, 32769)])
 def test_one_head(B, H, T):
     w, d = _inputs(B, H, H, T)
@@ -83,7 +85,7 @@ def test_smaller_workspaces_take_two_passes(B, Hq, Hkv, T):
 
 
 # a last chunk of one key, two batches of words, several rounds of heads, several heads per KV head
-@pytest.mark.parametrize("B,Hq,Hkv,T", [(1, 2, 2, 1025), (1, 2, 2, 16800), (20, 32, 32, 900), (2, 12, 2, 1300)])
+@pytest.mark.parametrize("B,Hq,Hkv,T", [(11, 2, 2, 1025), (1, 2, 2, 16800), (20, 32, 32, 900), (2, 12, 2, 1300)])
 def test_missing_chunks_are_scored_by_who_waits(B, Hq, Hkv, T):
     """The same kernels built to look for a missing word once: a workgroup that does not find its siblings' statistics scores
     their chunks itself, to the same bits."""

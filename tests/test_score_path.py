@@ -64,4 +64,8 @@ def test_what_takes_two_passes(rule):
     cases = [(1, 32, 32, 300, 48, 0.1, 0), (1, 32, 32, 300, 64, 0.0, 0), (1, 32, 32, 300, 64, -0.1, 0), (1, 32, 32, 300, 64, 0.1, 1),
              (1, 28, 4, 300, 64, 0.1, 1), (1, 32, 32, 32769, 64, 0.1, 0), (64, 32, 8, 768, 64, 0.1, 0)]
     assert [r[0] for r in rule(cases)] == [TWO] * len(cases)
+    # one head per KV head: up to 64 workgroups and four chunks
+    few = [(1, 32, 32, 1024, 64, 0.1, 0), (33, 1, 1, 1024, 64, 0.1, 0), (1, 2, 2, 2048, 64, 0.1, 0), (1, 2, 2, 2049, 64, 0.1, 0), (1, 16, 16, 2048, 64, 0.1, 1),
+           (17, 1, 1, 2048, 64, 0.1, 1)]
+    assert [r[0] for r in rule(few)] == [TWO, ONCE, TWO, ONCE, TWO, ONCE]
     assert [r[0] for r in rule([(1, 32, 32, 640, 64, 0.1, 0), (17, 32, 32, 640, 64, 0.1, 0), (8, 32, 32, 16384, 64, 0.1, 1)])] == [SMALL, ONCE, ONCE]
