@@ -340,6 +340,12 @@ inline size_t score_max_head_masses(int B, int Hq, int Hkv, int T, int W) {
   const size_t most = resident > few_keys ? resident : few_keys;
   return all < most ? all : most;
 }
+// Threads of a workgroup that lists the text positions of one row of T (rows: batch elements x KV heads): with 256 a round covers
+// 4096 positions, with 1024 it covers 16384, but its barriers and scan are longer.  1024 for rows of more than two rounds where one
+// workgroup per CU holds them all (us: 28 rows of 15167 positions 8.4 -> 6.3, 32 of 32768 9.7 -> 5.8; 99 such shapes 0.83 of the time, at most
+// 0.99).  Not for shorter ones (160 of 6808, 6.1 and 6.4; 80 of 8020, 5.9 and 6.1), nor for more rows (352 of 20425, 11.0 and 12.7; 288 of
+// 4708, 4.2 and 5.0; 2048 of 8192, 8.3 and 15.9).
+inline int text_threads(long rows, int T) { return T > 8192 && rows <= kScoreCus ? 1024 : 256; }
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_psa(const SelectArgs &a, hipStream_t stream);
 hipError_t launch_select_massive(const SelectArgs &a, hipStream_t stream);

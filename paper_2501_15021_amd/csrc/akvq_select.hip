@@ -16,8 +16,7 @@ namespace {
 // Text positions of one batch element, listed for all of its kv-heads by one workgroup per (batch, kv-head).  Latency is
 // all there is to it: a row of a few KB, scanned once.  Each thread takes kTsaBytes consecutive positions at a time, so a
 // round of loads, one workgroup scan and two barriers cover 4096 positions (256 before: 4001 positions of 256 heads took
-// 11.2 us, now 5.9 us), or 16384 with 1024 threads, which longer rows get where two workgroups per CU hold
-// them all (us per call: 28 heads of 15167 positions 8.4 -> 6.3, 32 of 32768 9.7 -> 5.8; but 2048 of 8192 8.3 and 15.9).
+// 11.2 us, now 5.9 us), or 16384 with 1024 threads (text_threads).
 constexpr int kTsaBytes = 16;
 template <int NT>
 __global__ __launch_bounds__(NT) void select_tsa_kernel(SelectArgs a) {
@@ -1515,7 +1514,7 @@ hipError_t launch_select_massive(const SelectArgs &a, hipStream_t stream) {
 
 hipError_t launch_select_tsa(const SelectArgs &a, hipStream_t stream) {
   const dim3 grid(a.B * a.Hkv);
-  if (a.T <= 256 * kTsaBytes || a.B * a.Hkv > 2 * kScoreCus) hipLaunchKernelGGL(select_tsa_kernel<256>, grid, dim3(256), 0, stream, a);
+  if (text_threads((long)a.B * a.Hkv, a.T) == 256) hipLaunchKernelGGL(select_tsa_kernel<256>, grid, dim3(256), 0, stream, a);
   else hipLaunchKernelGGL(select_tsa_kernel<1024>, grid, dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
