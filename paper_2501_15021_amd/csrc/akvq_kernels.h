@@ -43,7 +43,7 @@ constexpr long kAppendCus = 256;
 // the wavefronts, and two of a unit, have to be idle as well (52 of 1051, 2 heads, a twelfth, eight rounds to seven, 13.4 -> 14.5; 3 of 659,
 // 40 heads, an eighth, six to five, 11.6 -> 12.3; 110 of 91, 8 heads, rotary, one of four, seven to six, 12.8 -> 13.8).  Units of three blocks
 // gain from three rounds to two (264 units 6.4 -> 5.2) and not beyond (118 of 91, 4 heads, four to three, 7.7 -> 8.1).
-// 400 shapes that pass, 512 to 8000 workgroups, plain, rotary and with tiers: 0.90 of the time, three above 1.01, at most 1.036 (74 of
+// 400 shapes that pass, 512 to 8000 workgroups, plain, rotary and with tiers: 0.90 of the time, three above 1.01, at most 1.04 (74 of
 // 314, 4 heads, seven rounds to six, 13.2 -> 13.7).
 inline bool append_runs_on(long units, int n_blk, bool window) {
   const int groups = (n_blk + 3) / 4, idle = 4 * groups - n_blk;

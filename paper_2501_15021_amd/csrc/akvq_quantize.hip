@@ -330,9 +330,11 @@ __device__ __forceinline__ void quantize_append_body(const QuantArgs &a, int gro
 
   if (lane < kTokBlock) slot_of[lane] = -1;
   wave_lds_sync();
-  if (stride <= 1) {
+  // (long lists out of the way of the others' code: between it, they cost launches of few workgroups up to 5 %, 12 prompts of 368 tokens,
+  // 4 heads, G = 64, 5.5 -> 5.8 us, one list entry a head)
+  if (__builtin_expect(stride <= 1, 1)) {
     if (e1 >= t0 && e1 < t0 + kTokBlock) slot_of[e1 - t0] = lane;
-  } else if (stride <= 32) {
+  } else if (__builtin_expect(stride <= 32, 1)) {
     const int below = __popcll(__ballot(e1 < t0));  // samples before the block: the run starts after the last of them
     const int idx = max(below - 1, 0) * stride + lane;
     const int e2 = idx < cnt ? sidx[idx] : 0x7FFFFFFF;
