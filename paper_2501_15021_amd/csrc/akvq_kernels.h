@@ -294,7 +294,8 @@ inline size_t score_max_triples(int B, int Hq, int Hkv, int T, int W) {
 // kernel up to 512 keys that is 512 workgroups, two per CU, beyond one per CU; up to 256 keys with four per CU it is faster at any
 // number (73 x 256, 28/4 heads, 64 -> 38), but not with eight heads, whose two passes have no feeders to wait for (32 x 256,
 // 64/8 heads, 1.05 of the time).  671 shapes of 256 to 4096 keys, 2 to 8 heads: 0.87 of the time of two passes; of 240 in one pass,
-// 513 to 20000 keys, 0.82, ten 1.02 to 1.046 (100 x 1202 keys, 4 heads, 20.6 -> 21.3), all with 2 to 4 heads and among others that gain as much.
+// 513 to 20000 keys, 0.82, ten 1.02 to 1.046 (100 heads, four to a KV head, of 1202 keys 20.6 -> 21.3; of other shapes 18, three to one, of 7349 28.8
+// -> 30.9), all with 2 to 4 heads per KV head and among others that gain as much.
 enum ScorePath { kScoreTwoPasses, kScoreSmall, kScoreOnce };
 inline int score_path(int B, int Hq, int Hkv, int T, int W, float sm_scale, bool shared) {
   const long heads = (long)B * Hq, chunks = ((long)T + kOnceKeys - 1) / kOnceKeys;
